@@ -17,7 +17,9 @@ SOURCES = ["planner.cpp", "dual_balance.cpp", "cost_model.cpp", "api.hip", "attn
 # handling the max chains of the softmax compile to v_max3_f32.  (Host-side argument checks in
 # api.hip do test for NaN, so the flag is not global.)  The ILP-driven machine scheduler
 # interleaves the softmax's vector work with the MFMAs better than the default one (measured).
-EXTRA_FLAGS = {"attn_fwd.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]}
+# VGPR-form MFMAs: the 512-register instances would otherwise form every product in accumulation
+# registers and copy the scores out of them one by one.
+EXTRA_FLAGS = {"attn_fwd.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 # Packed-FP32 VALU ops are switched off for all device code (-packed-fp32-ops removes the feature).
 HIP_FLAGS = [

@@ -134,9 +134,22 @@ int get_kv_staging(dbsp_plan* plan) {
 int upload(dbsp_plan* plan) {
   dbsp_host_plan& hp = plan->host;
   dbsp_device_plan& dv = plan->dev;
-  const std::vector<int32_t>* arrays[] = {&hp.row_ptr,    &hp.items,      &hp.item_slot, &hp.split_rows,
-                                          &hp.empty_rows, &hp.part_ptr,   &hp.part_items, &hp.tail_items};
-  constexpr int NA = 8;
+  // what a workgroup needs to know of an item, in the order the partitions' lists (then the shared
+  // queue) hold them: one load instead of a chain through list, item, slot and row offset
+  const int64_t n_placed = (int64_t)hp.part_items.size(), n_sched = n_placed + (int64_t)hp.tail_items.size();
+  std::vector<int32_t> sched(8 * (size_t)n_sched);
+  for (int64_t k = 0; k < n_sched; ++k) {
+    const int64_t i = k < n_placed ? hp.part_items[k] : hp.tail_items[k - n_placed];
+    const int32_t* it = hp.items.data() + 4 * i;
+    int32_t* s = sched.data() + 8 * k;
+    s[0] = it[0];                                                                                  // head
+    s[1] = it[1];                                                                                  // row of the plan (query block, or pair of them)
+    s[2] = (hp.row_ptr[(int64_t)it[0] * hp.nQ + it[1]] + it[2]) * (hp.pair ? 2 : 1);               // first word of its KV list
+    s[3] = it[3] - it[2];                                                                          // blocks (super blocks)
+    s[4] = hp.item_slot[i];
+  }
+  const std::vector<int32_t>* arrays[] = {&hp.split_rows, &hp.empty_rows, &hp.part_ptr, &sched};
+  constexpr int NA = 4;
   size_t off[NA + 1];   // in int32 units, each array 16-byte aligned
   off[0] = 0;
   for (int i = 0; i < NA; ++i) off[i + 1] = off[i] + ((arrays[i]->size() + 3) & ~size_t(3));
@@ -178,14 +191,10 @@ int upload(dbsp_plan* plan) {
   DBSP_HIP(hipEventRecord(ev_up, us));
 
   const int32_t* ints = reinterpret_cast<const int32_t*>(dv.blob);
-  dv.row_ptr = ints + off[0];
-  dv.items = ints + off[1];
-  dv.item_slot = ints + off[2];
-  dv.split_rows = ints + off[3];
-  dv.empty_rows = ints + off[4];
-  dv.part_ptr = ints + off[5];
-  dv.part_items = ints + off[6];
-  dv.tail_items = ints + off[7];
+  dv.split_rows = ints + off[0];
+  dv.empty_rows = ints + off[1];
+  dv.part_ptr = ints + off[2];
+  dv.sched = ints + off[3];
   dv.queue = reinterpret_cast<uint32_t*>(dv.blob + queue_off);
   dv.kv_idx = reinterpret_cast<const int32_t*>(dv.blob + kv_off);
   dv.busy = reinterpret_cast<uint64_t*>(dv.blob + busy_off);
@@ -435,15 +444,12 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   p.v = static_cast<const uint16_t*>(v);
   p.o = static_cast<uint16_t*>(o);
   p.lse = lse;
-  p.row_ptr = dv.row_ptr;
   p.kv_idx = dv.kv_idx;
-  p.items = dv.items;
-  p.item_slot = dv.item_slot;
   p.split_rows = dv.split_rows;
   p.empty_rows = dv.empty_rows;
   p.part_ptr = dv.part_ptr;
-  p.part_items = dv.part_items;
-  p.tail_items = dv.tail_items;
+  p.sched = dv.sched;
+  p.n_placed = (int32_t)hp.part_items.size();
   p.queue = dv.queue;
   p.n_tail = (int32_t)hp.tail_items.size();
   p.part_o = part_o;

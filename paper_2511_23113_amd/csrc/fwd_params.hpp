@@ -11,15 +11,11 @@ struct dbsp_fwd_params {
   const uint16_t* v;   // bf16 [B,H,nK*BLK,D]
   uint16_t* o;         // bf16 [B,H,nQ*BLK,D]
   float* lse;          // f32  [B,H,nQ*BLK] or null
-  const int32_t* row_ptr;
   const int32_t* kv_idx;
-  const int32_t* items;       // 4 x int32 per item
-  const int32_t* item_slot;
   const int32_t* split_rows;  // 4 x int32 per split row
   const int32_t* empty_rows;
   const int32_t* part_ptr;
-  const int32_t* part_items;
-  const int32_t* tail_items;  // items no partition owns, in queue order
+  const int32_t* sched;       // 8 x int32 per item: the partitions' lists, then the shared queue: head, row, first KV word, blocks, slot
   uint32_t* queue;            // [0] next queue position, [1] workgroups that have left, [2 + t] times tail item t was taken
   float* part_o;       // f32 [B][n_slots][BLK][D]
   float* part_lse;     // f32 [B][n_slots][BLK]
@@ -28,6 +24,7 @@ struct dbsp_fwd_params {
   int32_t B, H, nQ, nK;     // nQ: rows per head of the plan (pair mode: pairs of query blocks); nK: KV blocks
   int32_t Nq, Nk;           // tokens per head
   int32_t n_slots, n_split, n_empty, n_tail;
+  int32_t n_placed;         // items the partitions' lists hold (all of them but the shared queue's)
   float scale;         // softmax scale
   float scale_log2;    // softmax scale * log2(e)
 };

@@ -56,15 +56,11 @@ struct dbsp_device_plan {
   void* uploaded = nullptr;       // hipEvent_t: the upload has finished
   void* last_use = nullptr;       // hipEvent_t: recorded after every forward launch
   bool used = false;
-  const int32_t* row_ptr = nullptr;
   const int32_t* kv_idx = nullptr;
-  const int32_t* items = nullptr;
-  const int32_t* item_slot = nullptr;
   const int32_t* split_rows = nullptr;
   const int32_t* empty_rows = nullptr;
   const int32_t* part_ptr = nullptr;
-  const int32_t* part_items = nullptr;
-  const int32_t* tail_items = nullptr;
+  const int32_t* sched = nullptr;  // 8 x int32 per item, see upload()
   uint32_t* queue = nullptr;      // [2 + n_tail]: next queue position, workgroups that have left, take count per tail item
   uint64_t* busy = nullptr;       // [P]
   uint32_t* hw_id = nullptr;      // [P]
