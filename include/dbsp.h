@@ -141,7 +141,8 @@ typedef struct dbsp_plan_opts {
  * asynchronous (a stream of the library's own, pinned staging, buffers recycled from a
  * process-wide pool): the call returns without waiting for it, and sparse_attn_fwd makes its
  * stream wait for the copy, so planning the next call overlaps with the device's work on the
- * current one.  Masks over 1 MB are counted on up to 8 host threads; the index lists are written
+ * current one.  A plan of up to 64 KiB is instead fetched by a kernel that the first
+ * sparse_attn_fwd enqueues in front of its own.  Masks over 1 MB are counted on up to 8 host threads; the index lists are written
  * straight into pinned memory by helper threads while the calling thread builds items and
  * placement (the helpers belong to a process-wide pool and sleep between plans; all of them are
  * done before the call returns).
@@ -190,8 +191,7 @@ int plan_sparse_attn_reuse(const dbsp_plan* previous, const uint8_t* mask_host, 
  * the mask has no batch axis: every batch entry uses the same per-head mask.
  * softmax_scale <= 0 selects 1 / sqrt(d).  A query row with no active block gets O = 0, LSE = -inf.
  * stream: a hipStream_t (NULL = default stream).  The call only enqueues work: one persistent
- * kernel with one workgroup per partition, plus a small fix-up kernel when rows were split or
- * are empty.  It neither allocates nor synchronises with the host.  bf16 inputs, f32 accumulation.
+ * kernel with one workgroup per partition (fewer where a plan has fewer items than partitions).  It neither allocates nor synchronises with the host.  bf16 inputs, f32 accumulation.
  * Errors: DBSP_EINVAL (also: B above the plan's max_batch when rows are split), DBSP_ESHAPE, DBSP_EHIP.
  */
 int sparse_attn_fwd(const dbsp_plan* plan, const void* q, const void* k, const void* v, void* o,
@@ -347,8 +347,9 @@ int dbsp_plan_tail_takes(const dbsp_plan* plan, uint32_t* takes, void* stream);
  * either may be NULL.  Synchronises `stream` before reading. */
 int dbsp_plan_busy(const dbsp_plan* plan, uint64_t* busy_ticks, uint32_t* hw_id, void* stream);
 
-/* dbsp_plan_destroy: waits (on the host) until the last sparse_attn_fwd enqueued with this plan
- * and the plan's upload have finished, then recycles its buffers.  NULL is ignored. */
+/* dbsp_plan_destroy: the plan is gone for the caller; its device and pinned buffers are recycled once the
+ * last sparse_attn_fwd enqueued with it and its upload have finished, which the call does not wait for
+ * (unless more than 16 destroyed plans are still in use by the GPU: then for the oldest).  NULL is ignored. */
 void dbsp_plan_destroy(dbsp_plan* plan);
 
 const char* dbsp_last_error(void);

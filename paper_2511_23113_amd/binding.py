@@ -44,6 +44,7 @@ class PlanOpts(C.Structure):
 
 
 _lib = None
+_torch = None      # torch, once a forward call has needed it
 
 
 def load_library(path: str | None = None):
@@ -198,11 +199,15 @@ def plan_sparse_attn(mask, block: int, num_partitions: int = 0, mode: int = MODE
     opts = PlanOpts(num_partitions, mode, max_item_len, item_overhead, flags, locality_groups,
                     cost.ctypes.data_as(C.c_void_p) if cost is not None else None, max_batch, dynamic_tail, float(reward),
                     head_dim)
-    out = C.c_void_p()
-    _check(load_library().plan_sparse_attn(mask.ctypes.data_as(C.c_void_p), H, nQ, nK, block, C.byref(opts), C.byref(out)))
-    chosen = C.c_int32()
-    _check(load_library().dbsp_plan_pair_rows(out, C.byref(chosen)))
-    return Plan(out.value, H, nQ, nK, block, bool(chosen.value))
+    lib, out = load_library(), C.c_void_p()
+    rc = lib.plan_sparse_attn(_addr(mask), H, nQ, nK, block, C.byref(opts), C.byref(out))
+    if rc:
+        _check(rc)
+    if pair_rows == "auto":
+        chosen = C.c_int32()
+        _check(lib.dbsp_plan_pair_rows(out, C.byref(chosen)))
+        pair_rows = bool(chosen.value)
+    return Plan(out.value, H, nQ, nK, block, bool(pair_rows))
 
 
 def plan_sparse_attn_reuse(previous: Plan, mask, reuse_threshold: float, num_partitions: int = 0, mode: int = MODE_BALANCED,
@@ -223,10 +228,15 @@ def plan_sparse_attn_reuse(previous: Plan, mask, reuse_threshold: float, num_par
     opts = PlanOpts(num_partitions, mode, max_item_len, item_overhead, flags, locality_groups,
                     cost.ctypes.data_as(C.c_void_p) if cost is not None else None, max_batch, dynamic_tail, 0.0)
     out, reused, rho = C.c_void_p(), C.c_int32(), C.c_double()
-    _check(load_library().plan_sparse_attn_reuse(previous.handle, mask.ctypes.data_as(C.c_void_p), C.byref(opts),
+    _check(load_library().plan_sparse_attn_reuse(previous.handle, _addr(mask), C.byref(opts),
                                                  float(reuse_threshold), C.byref(out), C.byref(reused), C.byref(rho)))
     return (Plan(out.value, previous.H, previous.nQ, previous.nK, previous.block, previous.pair_rows),
             bool(reused.value), rho.value)
+
+
+def _addr(array) -> int:
+    """Address of a numpy array's data (ndarray.ctypes builds an object per call)."""
+    return array.__array_interface__["data"][0]
 
 
 def _stream_ptr(stream):
@@ -246,23 +256,37 @@ def sparse_attn_fwd(plan: Plan, q, k, v, o=None, lse=None, softmax_scale: float 
     `stream` (default: torch's current stream) and returns (o, lse) without synchronising.
     static_scratch=True calls sparse_attn_fwd_static (pass o and lse then: this wrapper allocates
     the ones it is not given)."""
-    import torch
-    for name, x in (("q", q), ("k", k), ("v", v)):
-        if x.dtype != torch.bfloat16 or not x.is_cuda or not x.is_contiguous() or x.dim() != 4:
-            raise ValueError(f"{name} must be a contiguous 4-d bf16 tensor on the GPU")
+    global _torch
+    if _torch is None:
+        import torch as _torch_module
+        _torch = _torch_module
+    torch = _torch
+    bf16 = torch.bfloat16
+    if not (q.dtype == k.dtype == v.dtype == bf16 and q.is_cuda and k.is_cuda and v.is_cuda
+            and q.is_contiguous() and k.is_contiguous() and v.is_contiguous() and q.dim() == k.dim() == v.dim() == 4):
+        for name, x in (("q", q), ("k", k), ("v", v)):
+            if x.dtype != bf16 or not x.is_cuda or not x.is_contiguous() or x.dim() != 4:
+                raise ValueError(f"{name} must be a contiguous 4-d bf16 tensor on the GPU")
     B, H, Nq, d = q.shape
-    Nk = k.shape[2]
-    if k.shape != (B, H, Nk, d) or v.shape != k.shape or H != plan.H:
+    kshape = k.shape
+    Nk = kshape[2]
+    if kshape != (B, H, Nk, d) or v.shape != kshape or H != plan.H:
         raise ValueError("q/k/v shapes disagree with each other or with the plan")
     if o is None:
         o = torch.empty_like(q)
     if lse is None and want_lse:
-        lse = torch.empty((B, H, Nq), dtype=torch.float32, device=q.device)
-    lse_ptr = C.c_void_p(lse.data_ptr()) if lse is not None else C.c_void_p(0)
-    entry = load_library().sparse_attn_fwd_static if static_scratch else load_library().sparse_attn_fwd
-    _check(entry(plan.handle, C.c_void_p(q.data_ptr()), C.c_void_p(k.data_ptr()),
-                 C.c_void_p(v.data_ptr()), C.c_void_p(o.data_ptr()), lse_ptr,
-                 B, Nq, Nk, d, float(softmax_scale), _stream_ptr(stream)))
+        lse = q.new_empty((B, H, Nq), dtype=torch.float32)
+    if stream is None:
+        # the raw handle of torch's current stream, as a kernel launch needs it
+        stream = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    elif not isinstance(stream, int):
+        stream = stream.cuda_stream
+    lib = load_library()
+    entry = lib.sparse_attn_fwd_static if static_scratch else lib.sparse_attn_fwd
+    rc = entry(plan.handle, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None if lse is None else lse.data_ptr(),
+               B, Nq, Nk, d, softmax_scale, stream)
+    if rc:
+        _check(rc)
     return o, lse
 
 

@@ -1,6 +1,7 @@
 // C ABI of libdbsp: argument checks, plan life cycle, device upload, kernel launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -39,24 +40,77 @@ int fail_hip(hipError_t e, const char* what) {
     if (e_ != hipSuccess) return fail_hip(e_, #call);   \
   } while (0)
 
+constexpr int kMaxWaves = 8;     // waves of the largest workgroup: a split row has a counter for each
+
 // ---- process-wide resources: upload stream, device and pinned-host buffer pools -------------
 // Plans are created and destroyed per attention call when masks are dynamic, so their buffers are
 // recycled instead of going through hipMalloc / hipFree (which synchronises the device) each time.
 // Entries remember the device that was current when they were allocated and only go back to it.
+// The buffers of a destroyed plan that the GPU still uses are retired together with the plan's events
+// and join the pools once those have passed: destroying a plan does not wait (up to kMaxRetired plans).
 struct BufferPool {
   struct Entry { void* ptr; size_t bytes; int device; };
   std::vector<Entry> free_list;
   static constexpr size_t kMaxCached = 8;
 };
+struct Retired {
+  hipEvent_t events[2];            // last use, upload; null = nothing to wait for
+  BufferPool::Entry dev, pin[2];
+};
 
 constexpr int kMaxDevices = 64;
+constexpr size_t kMaxRetired = 16;
 std::mutex g_mu;
 hipStream_t g_upload_stream[kMaxDevices] = {};
 BufferPool g_dev_pool, g_pin_pool;
+std::vector<Retired> g_retired;
+
+// g_mu is held.  Surplus buffers go to `surplus` (to be freed without the lock: freeing synchronises).
+struct Surplus { std::vector<void*> dev, pin; };
+void pool_put(BufferPool& pool, const BufferPool::Entry& e, std::vector<void*>& surplus) {
+  if (!e.ptr) return;
+  pool.free_list.push_back(e);
+  if (pool.free_list.size() > BufferPool::kMaxCached) {
+    size_t smallest = 0;
+    for (size_t i = 1; i < pool.free_list.size(); ++i)
+      if (pool.free_list[i].bytes < pool.free_list[smallest].bytes) smallest = i;
+    surplus.push_back(pool.free_list[smallest].ptr);
+    pool.free_list.erase(pool.free_list.begin() + smallest);
+  }
+}
+
+// g_mu is held.  Recycles what the GPU is done with; with `wait_oldest` the oldest retired plan is waited for.
+void reap(Surplus& surplus, bool wait_oldest) {
+  for (size_t i = 0; i < g_retired.size();) {
+    Retired& r = g_retired[i];
+    bool done = true;
+    for (hipEvent_t ev : r.events) {
+      if (!ev) continue;
+      if (wait_oldest && i == 0) (void)hipEventSynchronize(ev);
+      else done = done && hipEventQuery(ev) != hipErrorNotReady;
+    }
+    if (!done) { ++i; continue; }
+    for (hipEvent_t ev : r.events)
+      if (ev) (void)hipEventDestroy(ev);
+    pool_put(g_dev_pool, r.dev, surplus.dev);
+    for (const BufferPool::Entry& e : r.pin) pool_put(g_pin_pool, e, surplus.pin);
+    g_retired.erase(g_retired.begin() + i);
+    wait_oldest = false;
+  }
+  (void)hipGetLastError();         // a query's "not ready" is no error
+}
+
+void release(const Surplus& surplus) {
+  for (void* p : surplus.dev) (void)hipFree(p);
+  for (void* p : surplus.pin) (void)hipHostFree(p);
+}
 
 hipError_t pool_get(BufferPool& pool, bool pinned, int device, size_t bytes, void** out, size_t* cap) {
+  Surplus surplus;
+  bool found = false;
   {
     std::lock_guard<std::mutex> lk(g_mu);
+    if (!g_retired.empty()) reap(surplus, false);
     int best = -1;
     for (size_t i = 0; i < pool.free_list.size(); ++i)
       if (pool.free_list[i].device == device && pool.free_list[i].bytes >= bytes &&
@@ -66,30 +120,15 @@ hipError_t pool_get(BufferPool& pool, bool pinned, int device, size_t bytes, voi
       *out = pool.free_list[best].ptr;
       *cap = pool.free_list[best].bytes;
       pool.free_list.erase(pool.free_list.begin() + best);
-      return hipSuccess;
+      found = true;
     }
   }
+  release(surplus);
+  if (found) return hipSuccess;
   const size_t rounded = (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);   // 1 MiB granules
   hipError_t e = pinned ? hipHostMalloc(out, rounded, hipHostMallocDefault) : hipMalloc(out, rounded);
   *cap = rounded;
   return e;
-}
-
-void pool_put(BufferPool& pool, bool pinned, int device, void* ptr, size_t bytes) {
-  if (!ptr) return;
-  void* victim = nullptr;
-  {
-    std::lock_guard<std::mutex> lk(g_mu);
-    pool.free_list.push_back({ptr, bytes, device});
-    if (pool.free_list.size() > BufferPool::kMaxCached) {
-      size_t smallest = 0;
-      for (size_t i = 1; i < pool.free_list.size(); ++i)
-        if (pool.free_list[i].bytes < pool.free_list[smallest].bytes) smallest = i;
-      victim = pool.free_list[smallest].ptr;
-      pool.free_list.erase(pool.free_list.begin() + smallest);
-    }
-  }
-  if (victim) (void)(pinned ? hipHostFree(victim) : hipFree(victim));
 }
 
 // One upload stream per device (created on first use, with that device current).
@@ -104,15 +143,24 @@ hipError_t upload_stream(int device, hipStream_t* out) {
   return hipSuccess;
 }
 
-// Waits until nothing on the device still uses the plan's buffers, then recycles them.
+// Hands the plan's buffers back, at once or, if the GPU may still use them, once its events have passed.
 void free_device(dbsp_device_plan& d) {
-  if (d.last_use && d.used) (void)hipEventSynchronize(static_cast<hipEvent_t>(d.last_use));
-  if (d.uploaded) (void)hipEventSynchronize(static_cast<hipEvent_t>(d.uploaded));
-  if (d.last_use) (void)hipEventDestroy(static_cast<hipEvent_t>(d.last_use));
-  if (d.uploaded) (void)hipEventDestroy(static_cast<hipEvent_t>(d.uploaded));
-  pool_put(g_dev_pool, false, d.device, d.blob, d.blob_bytes);
-  pool_put(g_pin_pool, true, d.device, d.staging, d.staging_bytes);
-  pool_put(g_pin_pool, true, d.device, d.staging_kv, d.staging_kv_bytes);
+  Retired r = {{nullptr, nullptr}, {d.blob, d.blob_bytes, d.device}, {{d.staging, d.staging_bytes, d.device}, {d.staging_kv, d.staging_kv_bytes, d.device}}};
+  if (d.last_use) {
+    if (d.used) r.events[0] = static_cast<hipEvent_t>(d.last_use);
+    else (void)hipEventDestroy(static_cast<hipEvent_t>(d.last_use));
+  }
+  if (d.uploaded) {
+    if (d.sent == dbsp_device_plan::kByCopy) r.events[1] = static_cast<hipEvent_t>(d.uploaded);
+    else (void)hipEventDestroy(static_cast<hipEvent_t>(d.uploaded));
+  }
+  Surplus surplus;
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_retired.push_back(r);
+    reap(surplus, g_retired.size() > kMaxRetired);
+  }
+  release(surplus);
   (void)hipGetLastError();
   d = dbsp_device_plan();
 }
@@ -128,16 +176,48 @@ int get_kv_staging(dbsp_plan* plan) {
   return DBSP_OK;
 }
 
-// Copies the plan to the device: the index lists from their pinned buffer, the small arrays through
-// a second pinned staging buffer, both asynchronously on the library's upload stream, and one event
-// that forward launches wait for.  The host does not wait.
+// Sends the plan to the device on the library's upload stream, asynchronously, with one event that forward
+// launches wait for: the small arrays from their staging buffer, the index lists from theirs.
+int send_upload(dbsp_device_plan& dv) {
+  hipStream_t us;
+  DBSP_HIP(upload_stream(dv.device, &us));
+  DBSP_HIP(hipMemcpyAsync(dv.blob, dv.staging, dv.up_bytes, hipMemcpyHostToDevice, us));
+  if (dv.kv_bytes) DBSP_HIP(hipMemcpyAsync(dv.blob + dv.up_bytes, dv.staging_kv, dv.kv_bytes, hipMemcpyHostToDevice, us));
+  DBSP_HIP(hipEventRecord(static_cast<hipEvent_t>(dv.uploaded), us));
+  dv.sent = dbsp_device_plan::kByCopy;
+  return DBSP_OK;
+}
+
+// Lays the plan out for the device and sends it; the host does not wait.  A plan of up to kInStreamBytes is
+// not sent here: its first forward launch is preceded, on its own stream, by a kernel that fetches the
+// plan from the pinned buffers (64 KiB take it about 3 us).  Two streams and the wait between them cost the
+// host 12 us and more; for larger plans they let the copy run beside the kernels before it.
+constexpr size_t kInStreamBytes = size_t(64) << 10;
+
+__global__ __launch_bounds__(256) void dbsp_fetch_kernel(uint4* __restrict__ dst, const uint4* __restrict__ a, uint32_t na, const uint4* __restrict__ b, uint32_t n) {
+  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = i < na ? a[i] : b[i - na];
+}
+
+int fetch_in_stream(dbsp_device_plan& dv, hipStream_t st) {
+  // the index lists' last 16 bytes may reach into the slack both buffers have behind them
+  const uint32_t na = (uint32_t)(dv.up_bytes / 16), n = na + (uint32_t)((dv.kv_bytes + 15) / 16);
+  hipLaunchKernelGGL(dbsp_fetch_kernel, dim3((n + 255) / 256), dim3(256), 0, st, reinterpret_cast<uint4*>(dv.blob),
+                     static_cast<const uint4*>(dv.staging), na, static_cast<const uint4*>(dv.staging_kv), n);
+  DBSP_HIP(hipGetLastError());
+  dv.sent = dbsp_device_plan::kInStream;
+  dv.upload_stream = st;
+  return DBSP_OK;
+}
 int upload(dbsp_plan* plan) {
   dbsp_host_plan& hp = plan->host;
   dbsp_device_plan& dv = plan->dev;
   // what a workgroup needs to know of an item, in the order the partitions' lists (then the shared
   // queue) hold them: one load instead of a chain through list, item, slot and row offset
   const int64_t n_placed = (int64_t)hp.part_items.size(), n_sched = n_placed + (int64_t)hp.tail_items.size();
-  std::vector<int32_t> sched(8 * (size_t)n_sched);
+  std::vector<int32_t> sched(8 * (size_t)n_sched), slot_row(hp.n_slots);
+  const size_t n_split = hp.split_rows.size() / 4;
+  for (size_t r = 0; r < n_split; ++r)
+    for (int32_t k = 0; k < hp.split_rows[4 * r + 2]; ++k) slot_row[hp.split_rows[4 * r + 1] + k] = (int32_t)r;
   for (int64_t k = 0; k < n_sched; ++k) {
     const int64_t i = k < n_placed ? hp.part_items[k] : hp.tail_items[k - n_placed];
     const int32_t* it = hp.items.data() + 4 * i;
@@ -147,20 +227,28 @@ int upload(dbsp_plan* plan) {
     s[2] = (hp.row_ptr[(int64_t)it[0] * hp.nQ + it[1]] + it[2]) * (hp.pair ? 2 : 1);               // first word of its KV list
     s[3] = it[3] - it[2];                                                                          // blocks (super blocks)
     s[4] = hp.item_slot[i];
+    if (s[4] >= 0) {
+      const int32_t r = slot_row[s[4]];
+      s[5] = r; s[6] = hp.split_rows[4 * (size_t)r + 2]; s[7] = hp.split_rows[4 * (size_t)r + 1];  // index of the split row, its chunks, its first slot
+    }
   }
-  const std::vector<int32_t>* arrays[] = {&hp.split_rows, &hp.empty_rows, &hp.part_ptr, &sched};
-  constexpr int NA = 4;
+  dv.used_parts = 0;
+  for (int32_t g = 0; g < hp.P; ++g)
+    if (hp.part_ptr[g + 1] > hp.part_ptr[g]) dv.used_parts = g + 1;
+  const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &hp.part_ptr, &sched};
+  constexpr int NA = 3;
   size_t off[NA + 1];   // in int32 units, each array 16-byte aligned
   off[0] = 0;
   for (int i = 0; i < NA; ++i) off[i + 1] = off[i] + ((arrays[i]->size() + 3) & ~size_t(3));
   const size_t ints_bytes = off[NA] * sizeof(int32_t);
   const size_t busy_off = (ints_bytes + 255) & ~size_t(255);
   const size_t hw_off = busy_off + (((size_t)hp.P * sizeof(uint64_t) + 255) & ~size_t(255));
-  // shared queue of the dynamic tail: [0] next position, [1] workgroups that have left, then one take count per tail item
+  // shared queue of the dynamic tail: [0] next position, then one take count per tail item; then the split rows' counters
   const size_t queue_off = hw_off + (((size_t)hp.P * sizeof(uint32_t) + 255) & ~size_t(255));
-  const size_t up_bytes = queue_off + (((2 + hp.tail_items.size()) * sizeof(uint32_t) + 255) & ~size_t(255));   // staged part ends here
-  const size_t kv_off = up_bytes;
-  const size_t kv_bytes = (size_t)hp.kv_ints() * sizeof(int32_t);
+  const size_t cnt_off = queue_off + (((1 + hp.tail_items.size()) * sizeof(uint32_t) + 255) & ~size_t(255));
+  dv.up_bytes = cnt_off + (((size_t)dv.max_batch * n_split * kMaxWaves * sizeof(uint32_t) + 255) & ~size_t(255));   // staged part ends here
+  const size_t up_bytes = dv.up_bytes, kv_off = up_bytes;
+  const size_t kv_bytes = dv.kv_bytes = (size_t)hp.kv_ints() * sizeof(int32_t);
   // split-row scratch for max_batch batch entries at d = 128
   const int64_t rows = (int64_t)dv.max_batch * hp.n_slots * hp.tile_rows();
   const size_t lse_off = (kv_off + kv_bytes + 255) & ~size_t(255);
@@ -184,18 +272,17 @@ int upload(dbsp_plan* plan) {
   dv.uploaded = ev_up;
   DBSP_HIP(hipEventCreateWithFlags(&ev_use, hipEventDisableTiming));
   dv.last_use = ev_use;
-  hipStream_t us;
-  DBSP_HIP(upload_stream(dv.device, &us));
-  DBSP_HIP(hipMemcpyAsync(dv.blob, st, up_bytes, hipMemcpyHostToDevice, us));
-  if (kv_bytes) DBSP_HIP(hipMemcpyAsync(dv.blob + kv_off, dv.staging_kv, kv_bytes, hipMemcpyHostToDevice, us));
-  DBSP_HIP(hipEventRecord(ev_up, us));
+  if (up_bytes + kv_bytes > kInStreamBytes) {
+    const int rc = send_upload(dv);
+    if (rc != DBSP_OK) return rc;
+  }
 
   const int32_t* ints = reinterpret_cast<const int32_t*>(dv.blob);
-  dv.split_rows = ints + off[0];
-  dv.empty_rows = ints + off[1];
-  dv.part_ptr = ints + off[2];
-  dv.sched = ints + off[3];
+  dv.empty_rows = ints + off[0];
+  dv.part_ptr = ints + off[1];
+  dv.sched = ints + off[2];
   dv.queue = reinterpret_cast<uint32_t*>(dv.blob + queue_off);
+  dv.split_cnt = reinterpret_cast<uint32_t*>(dv.blob + cnt_off);
   dv.kv_idx = reinterpret_cast<const int32_t*>(dv.blob + kv_off);
   dv.busy = reinterpret_cast<uint64_t*>(dv.blob + busy_off);
   dv.hw_id = reinterpret_cast<uint32_t*>(dv.blob + hw_off);
@@ -211,7 +298,11 @@ int upload(dbsp_plan* plan) {
 // call on a GPU shares it.  In host code the array's name is only a handle for
 // hipGetSymbolAddress: the device address is looked up once per device and used from then on.
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;   // 32 MiB
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// Behind it the counters of the split rows, zero when the library is loaded and between launches.  A split
+// row has at least two chunks of at least 64 x 65 floats, so 32 MiB hold the chunks of at most 1008 rows.
+constexpr size_t kStaticCounters = 1024 * kMaxWaves;
+static_assert(kStaticScratchBytes / (2 * 64 * 65 * sizeof(float)) * kMaxWaves <= kStaticCounters, "counters for every split row that fits");
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticCounters * sizeof(uint32_t)];
 
 unsigned char* g_scratch_ptr[kMaxDevices] = {};
 
@@ -401,41 +492,43 @@ void dbsp_plan_destroy(dbsp_plan* plan) {
 static int forward(const dbsp_plan* plan, const void* q, const void* k, const void* v, void* o,
                    float* lse, int32_t B, int32_t Nq, int32_t Nk, int32_t d, float softmax_scale,
                    void* stream, bool static_scratch_wanted, const char* who) {
-  const std::string w(who);
-  if (!plan || !q || !k || !v || !o) return fail(DBSP_EINVAL, w + ": null pointer");
+  auto bad = [&](int code, const std::string& what) { return fail(code, std::string(who) + what); };
+  if (!plan || !q || !k || !v || !o) return bad(DBSP_EINVAL, ": null pointer");
   const dbsp_host_plan& hp = plan->host;
-  if (B <= 0) return fail(DBSP_EINVAL, w + ": B must be positive");
-  if (d != 64 && d != 128) return fail(DBSP_EINVAL, w + ": head dim must be 64 or 128");
-  if (hp.block != 64 && hp.block != 128) return fail(DBSP_EINVAL, w + ": the plan's block size must be 64 or 128");
+  if (B <= 0) return bad(DBSP_EINVAL, ": B must be positive");
+  if (d != 64 && d != 128) return bad(DBSP_EINVAL, ": head dim must be 64 or 128");
+  if (hp.block != 64 && hp.block != 128) return bad(DBSP_EINVAL, ": the plan's block size must be 64 or 128");
   if (Nq <= 0 || Nk <= 0 || Nq % hp.block != 0 || Nk % hp.block != 0)
-    return fail(DBSP_ESHAPE, w + ": sequence lengths must be positive multiples of the block size");
+    return bad(DBSP_ESHAPE, ": sequence lengths must be positive multiples of the block size");
   if (Nq / hp.block != hp.nQ_blocks || Nk / hp.block != hp.nK)
-    return fail(DBSP_ESHAPE, w + ": Nq/Nk do not match the plan's block grid");
-  if (hp.pair && d != 128) return fail(DBSP_EINVAL, w + ": a plan made with DBSP_PLAN_PAIR_ROWS needs head dim 128");
-  if (!plan->dev.resident) return fail(DBSP_EINVAL, w + ": the plan was built host-only");
-  if (!(softmax_scale == softmax_scale)) return fail(DBSP_EINVAL, w + ": softmax_scale is NaN");
+    return bad(DBSP_ESHAPE, ": Nq/Nk do not match the plan's block grid");
+  if (hp.pair && d != 128) return bad(DBSP_EINVAL, ": a plan made with DBSP_PLAN_PAIR_ROWS needs head dim 128");
+  if (!plan->dev.resident) return bad(DBSP_EINVAL, ": the plan was built host-only");
+  if (!(softmax_scale == softmax_scale)) return bad(DBSP_EINVAL, ": softmax_scale is NaN");
   int cur = -1;
   DBSP_HIP(hipGetDevice(&cur));
-  if (cur != plan->dev.device) return fail(DBSP_EINVAL, w + ": the plan lives on another device than the current one");
+  if (cur != plan->dev.device) return bad(DBSP_EINVAL, ": the plan lives on another device than the current one");
 
   const dbsp_device_plan& dv = plan->dev;
   float* part_o = dv.part_o;
   float* part_lse = dv.part_lse;
+  uint32_t* split_cnt = dv.split_cnt;
   if (static_scratch_wanted) {
     // partial outputs f32 [B][n_slots][block][d], then their LSE f32 [B][n_slots][block]
     const size_t rows = (size_t)B * hp.n_slots * hp.tile_rows();
     const size_t lse_off = (rows * d * sizeof(float) + 255) & ~size_t(255);
     const size_t need = lse_off + rows * sizeof(float);
     if (need > kStaticScratchBytes)
-      return fail(DBSP_EINVAL, w + ": the split rows of this plan need " + std::to_string(need) + " bytes of scratch for B = " +
+      return bad(DBSP_EINVAL, ": the split rows of this plan need " + std::to_string(need) + " bytes of scratch for B = " +
                                    std::to_string(B) + ", the static buffer holds " + std::to_string(kStaticScratchBytes));
     unsigned char* base = nullptr;
     const int rc = static_scratch(cur, &base);
     if (rc != DBSP_OK) return rc;
     part_o = reinterpret_cast<float*>(base);
+    split_cnt = reinterpret_cast<uint32_t*>(base + kStaticScratchBytes);
     part_lse = reinterpret_cast<float*>(base + lse_off);
   } else if (B > dv.max_batch && hp.n_slots > 0) {
-    return fail(DBSP_EINVAL, w + ": B exceeds the max_batch the plan's split-row scratch was sized for");
+    return bad(DBSP_EINVAL, ": B exceeds the max_batch the plan's split-row scratch was sized for");
   }
 
   dbsp_fwd_params p;
@@ -445,7 +538,6 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   p.o = static_cast<uint16_t*>(o);
   p.lse = lse;
   p.kv_idx = dv.kv_idx;
-  p.split_rows = dv.split_rows;
   p.empty_rows = dv.empty_rows;
   p.part_ptr = dv.part_ptr;
   p.sched = dv.sched;
@@ -454,6 +546,7 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   p.n_tail = (int32_t)hp.tail_items.size();
   p.part_o = part_o;
   p.part_lse = part_lse;
+  p.split_cnt = split_cnt;
   p.busy = dv.busy;
   p.hw_id = dv.hw_id;
   p.B = B; p.H = hp.H; p.nQ = hp.nQ; p.nK = hp.nK;
@@ -464,10 +557,35 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   p.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)d);
   p.scale_log2 = p.scale * 1.4426950408889634f;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  DBSP_HIP(hipStreamWaitEvent(st, static_cast<hipEvent_t>(dv.uploaded), 0));   // the plan's upload is asynchronous
-  hipError_t e = dbsp_launch_fwd(p, hp.block, d, hp.pair, hp.P, st);
-  if (e != hipSuccess) return fail_hip(e, (w + " launch").c_str());
-  DBSP_HIP(hipEventRecord(static_cast<hipEvent_t>(dv.last_use), st));
+  // every partition with items gets its workgroup; what is left to deal (queue items, empty rows) may ask for more, up to P
+  const int64_t deal = std::max<int64_t>((int64_t)B * p.n_tail, (int64_t)B * p.n_empty);
+  const int grid = (int)std::max<int64_t>(std::max<int64_t>(dv.used_parts, 1), std::min<int64_t>(deal, hp.P));
+  dbsp_device_plan& dm = plan->dev;
+  // inside a stream capture everything goes through commands that a graph can hold
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();
+  const bool capture = capturing != hipStreamCaptureStatusNone;
+  if (!dm.upload_done) {
+    if (dm.sent == dbsp_device_plan::kNotSent) {
+      const int rc = capture ? send_upload(dm) : fetch_in_stream(dm, st);
+      if (rc != DBSP_OK) return rc;
+    }
+    // fetched in stream order: the stream itself waits, another one for the launch behind the fetch
+    hipEvent_t arrived = static_cast<hipEvent_t>(dm.sent == dbsp_device_plan::kByCopy ? dm.uploaded : dm.last_use);
+    if (dm.sent == dbsp_device_plan::kByCopy || (dm.upload_stream != stream && dm.used)) {
+      if (!capture && hipEventQuery(arrived) == hipSuccess) {
+        dm.upload_done = true;
+      } else {
+        (void)hipGetLastError();
+        DBSP_HIP(hipStreamWaitEvent(st, arrived, 0));
+      }
+    }
+  }
+  const hipError_t e = dbsp_launch_fwd(p, hp.block, d, hp.pair, grid, st, capture ? nullptr : static_cast<hipEvent_t>(dm.last_use));
+  if (e != hipSuccess && dm.sent == dbsp_device_plan::kInStream) (void)hipStreamSynchronize(st);      // no event vouches for the fetch
+  if (e != hipSuccess) return fail_hip(e, (std::string(who) + " launch").c_str());
+  if (capture) DBSP_HIP(hipEventRecord(static_cast<hipEvent_t>(dm.last_use), st));
+  dm.last_grid = grid;
   plan->dev.used = true;
   return DBSP_OK;
 }
@@ -548,8 +666,16 @@ int dbsp_plan_busy(const dbsp_plan* plan, uint64_t* busy_ticks, uint32_t* hw_id,
   if (!plan) return fail(DBSP_EINVAL, "dbsp_plan_busy: null plan");
   if (!plan->dev.resident) return fail(DBSP_EINVAL, "dbsp_plan_busy: the plan was built host-only");
   DBSP_HIP(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
-  if (busy_ticks) DBSP_HIP(hipMemcpy(busy_ticks, plan->dev.busy, plan->host.P * sizeof(uint64_t), hipMemcpyDeviceToHost));
-  if (hw_id) DBSP_HIP(hipMemcpy(hw_id, plan->dev.hw_id, plan->host.P * sizeof(uint32_t), hipMemcpyDeviceToHost));
+  // partitions the last launch had no workgroup for (no items) were idle
+  const int32_t ran = plan->dev.last_grid;
+  if (busy_ticks) {
+    if (ran) DBSP_HIP(hipMemcpy(busy_ticks, plan->dev.busy, ran * sizeof(uint64_t), hipMemcpyDeviceToHost));
+    std::fill(busy_ticks + ran, busy_ticks + plan->host.P, 0);
+  }
+  if (hw_id) {
+    if (ran) DBSP_HIP(hipMemcpy(hw_id, plan->dev.hw_id, ran * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    std::fill(hw_id + ran, hw_id + plan->host.P, 0);
+  }
   return DBSP_OK;
 }
 
@@ -558,7 +684,8 @@ int dbsp_plan_tail_takes(const dbsp_plan* plan, uint32_t* takes, void* stream) {
   if (!plan->dev.resident) return fail(DBSP_EINVAL, "dbsp_plan_tail_takes: the plan was built host-only");
   DBSP_HIP(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
   const size_t n = plan->host.tail_items.size();
-  if (n) DBSP_HIP(hipMemcpy(takes, plan->dev.queue + 2, n * sizeof(uint32_t), hipMemcpyDeviceToHost));
+  if (plan->dev.sent == dbsp_device_plan::kNotSent) std::fill(takes, takes + n, 0);      // no launch yet
+  else if (n) DBSP_HIP(hipMemcpy(takes, plan->dev.queue + 1, n * sizeof(uint32_t), hipMemcpyDeviceToHost));
   return DBSP_OK;
 }
 
@@ -567,8 +694,8 @@ int dbsp_plan_calibrate(const dbsp_plan* plan, int32_t* cost, void* stream) {
   if (!plan->dev.resident) return fail(DBSP_EINVAL, "dbsp_plan_calibrate: the plan was built host-only");
   const int32_t P = plan->host.P;
   std::vector<uint64_t> busy(P);
-  DBSP_HIP(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
-  DBSP_HIP(hipMemcpy(busy.data(), plan->dev.busy, P * sizeof(uint64_t), hipMemcpyDeviceToHost));
+  const int rc = dbsp_plan_busy(plan, busy.data(), nullptr, stream);
+  if (rc != DBSP_OK) return rc;
   // cost[g] = round(1024 * (busy[g] / load[g]) / (sum busy / sum load)), exact, round half up
   unsigned __int128 sb = 0, sl = 0;
   for (int32_t g = 0; g < P; ++g)

@@ -54,6 +54,11 @@ __device__ __forceinline__ float sum_xor32(float x) {
   return sw.lo + sw.hi;
 }
 
+// The swap itself: the upper half (lanes 32..63) of a and the lower half of b change places.
+__device__ __forceinline__ void swap_upper_lower(uint32_t& a, uint32_t& b) {
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+
 // Direct global -> LDS copies.  One global_load_lds_dwordx4 moves 64 x 16 bytes: lane i reads
 // 16 bytes at base + voff(i) + OFF and they land at LDS byte address M0 + OFF + 16*i; the
 // instruction offset applies to both sides, so the copies of one group share a base and an M0.

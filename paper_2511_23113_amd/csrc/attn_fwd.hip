@@ -59,6 +59,7 @@
 //     is linear): K by the row index so that the 16-byte operand reads of 16 lanes (16
 //     consecutive keys) hit distinct banks; V by (row & 3) so that the 4 keys of a
 //     transposing read hit distinct bank quarters.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -89,12 +90,12 @@ struct Cfg {
   static constexpr int RPC = 64 / NCH;      // rows per copy
   static constexpr int KVAR = (NCH * RPL) / RPC;   // copies per period (16 rows) of K's swizzle
   static constexpr int RING = 2 * NB * SL;  // a key group's ring: NB slices of K, then NB of V
-  // end-of-item exchange: of the 2 DT accumulator tiles (32 d x 32 queries) a wave finalises TPW and
-  // hands the others to the waves of the other key groups
+  // End-of-item exchange: of the 2 DT accumulator tiles (32 d x 32 queries) a wave finalises TPW and hands
+  // the others to the waves of the other key groups.  Its outbox lies at the end of its group's ring, clear
+  // of the first two K slices, which already belong to the next item by then.
   static constexpr int TPW = 2 * DT / NC, XCH = (NC - 1) * TPW * 4096;
-  static constexpr int XSTRIDE = NQ == 1 ? RING : XCH;   // one query group: a wave's outbox lies in its own ring
-  static constexpr int LDS_BYTES = (NW * XSTRIDE > NC * RING) ? NW * XSTRIDE : NC * RING;
-  static_assert(NQ > 1 || XCH <= RING, "a wave's outbox must fit its own ring");
+  static constexpr int LDS_BYTES = NC * RING;
+  static_assert(NQ * XCH <= RING - 2 * SL, "the outboxes must leave the first two K slices alone");
   static_assert(U == 1 || (U == 2 && NQ > 1), "what the step sequence assumes");
   static_assert(NC == 2 || (NC == 4 && TPW == 1), "tile ownership at the end of an item");
 };
@@ -102,6 +103,19 @@ struct Cfg {
 template <int N>
 __device__ __forceinline__ void wait_copies() {      // all but the N youngest copies of this wave have landed
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Partial results of split rows cross from one compute die's L2 to another's inside a launch: they are
+// written and read with the chip as their scope (past the L2s), two floats per lane at a time and the
+// lanes of a wave side by side: single rows' 8-byte pieces, which the L2 cannot gather on that way, took
+// ten times as long.
+__device__ __forceinline__ void store_shared(float* to, float a, float b) {
+  const uint64_t v = ((uint64_t)__builtin_bit_cast(uint32_t, b) << 32) | __builtin_bit_cast(uint32_t, a);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(to), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x2 load_shared(const float* from) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(from), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return f32x2{__builtin_bit_cast(float, (uint32_t)v), __builtin_bit_cast(float, (uint32_t)(v >> 32))};
 }
 
 template <int D, int NQ, int NC, int U, bool PAIR>
@@ -160,86 +174,40 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   const uint32_t src_off = (PAIR ? 0 : wc * U * C::SL) + share;
   constexpr uint32_t BLOCK_BYTES = PAIR ? U * C::SL : NC * U * C::SL;
 
+  // Rows with no active block: O = 0, LSE = -inf, dealt to the workgroups in turn.
+  for (int64_t x = part; x < (int64_t)p.B * p.n_empty; x += gridDim.x) {
+    const int row = p.empty_rows[x % p.n_empty];
+    const int64_t head = (x / p.n_empty) * p.H + row / p.nQ;
+    const int first = (row % p.nQ) * C::QROWS, rows = PAIR ? min(C::QROWS, p.Nq - first) : C::QROWS;
+    u32x4* to = reinterpret_cast<u32x4*>(p.o + (head * p.Nq + first) * D);
+    for (int y = t; y < rows * (D / 8); y += C::NT) to[y] = u32x4{0u, 0u, 0u, 0u};
+    if (p.lse != nullptr)
+      for (int y = t; y < rows; y += C::NT) p.lse[head * p.Nq + first + y] = -INFINITY;
+  }
+
   uint64_t busy = 0;
+  // Work of this workgroup: its own list (once per batch entry), then items from the queue all
+  // workgroups share, taken one by one with an atomic counter -- the greedy rule "each unit to the
+  // least-loaded partition" (Methodology, "Head-level Partitioning") applied at run time, where
+  // "least loaded" is "first to run out of work".  Where nothing is placed (fewer items than
+  // partitions) every workgroup starts at the queue: the first takes are then known beforehand,
+  // one each in workgroup order, and need no counter.  A take costs about 11 ns of everybody's time
+  // (one address for the whole chip): with 1024 workgroups, a first take and a failing one each,
+  // that used to be half of a short launch.
   const int it_begin = g_part_ptr[part], n_own = g_part_ptr[part + 1] - it_begin;
-  const int64_t total_own = (int64_t)p.B * n_own;
   const uint32_t total_tail = (uint32_t)p.B * (uint32_t)p.n_tail;
-  for (int64_t step_no = 0;; ++step_no) {
-    int pos, bb;
-    if (step_no < total_own) {
-      bb = (int)(step_no / n_own);
-      pos = it_begin + (int)(step_no % n_own);
-    } else {
-      if (total_tail == 0) break;
-      if (t == 0) tail_pos = atomicAdd(&p.queue[0], 1u);
-      __syncthreads();
-      const uint32_t tp = __builtin_amdgcn_readfirstlane(tail_pos);
-      __syncthreads();
-      if (tp >= total_tail) break;
-      bb = (int)(tp / (uint32_t)p.n_tail);
-      const int tq = (int)(tp % (uint32_t)p.n_tail);
-      pos = p.n_placed + tq;
-      if (t == 0) atomicAdd(&p.queue[2 + tq], 1u);
-    }
-    const uint64_t t0 = wall_clock64();
-    const int4 da = g_sched[2 * pos], db = g_sched[2 * pos + 1];
-    const int h = da.x, I = da.y, n = __builtin_amdgcn_readfirstlane(da.w), slot = db.x;
-    const int32_t* __restrict__ kv = g_kv_idx + da.z;
-    const int64_t bh = (int64_t)bb * p.H + h;
-    const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k + bh * p.Nk * D) + src_off;
-    const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v + bh * p.Nk * D) + src_off;
-    const int nS = n * U;                     // slices
+  const uint32_t n_first = p.n_placed == 0 ? gridDim.x : 0u;       // takes without the counter
 
-    // Block ids, 64 at a time, one per lane (a scalar load per block would make every LDS wait a full
-    // wait, since the two share a counter).  Past the end the last id repeats.  Pair rows: id of this
-    // wave's KV block of the super block, and a mask of the super blocks in which the wave's
-    // (query block, KV block) combination is active.
-    int ids, ids_next;
-    uint64_t act = ~0ull, act_next = ~0ull;
-    auto load_ids = [&](int from, int& id, uint64_t& am) {
-      const int x = min(from + l, n - 1);
-      if constexpr (PAIR) {
-        const int w1 = kv[2 * x + 1];
-        id = wc ? (w1 & 0xffffff) : kv[2 * x];
-        am = __builtin_amdgcn_ballot_w64(((w1 >> (24 + wa + 2 * wc)) & 1) != 0);
-      } else {
-        id = kv[x];
-      }
-    };
-    load_ids(0, ids, act);
-    load_ids(64, ids_next, act_next);
-    auto id_of = [&](int T) { return __builtin_amdgcn_readlane(ids, T & 63); };
-    auto act_of = [&](int T) { return ((act >> (T & 63)) & 1) != 0; };
-
-    // Copies of this wave's share of a slice: K or V of slice u of block J into position b of its ring,
-    // KiB by KiB: begin() once (destination and base), then one() for x = 0 .. LOADS - 1.  Past the end of
-    // the list the last block is copied again, into positions nobody reads: that costs less than a branch
-    // in the step sequence.
-    const unsigned char* from = kbase;
-    auto copy_begin = [&](const unsigned char* base, int J, int u, uint32_t b, int x) {
-      from = base + (int64_t)J * BLOCK_BYTES + u * C::SL + x * 1024;
-      set_copy_dst(ring + b * C::SL + share + x * 1024);
-    };
-    auto copy_one = [&](bool is_k, int x) { copy16_nth(x % 4, from, is_k ? k_src[x % C::KVAR] : v_src); };
-    auto copy_k = [&](int J, int u, uint32_t b) {
-#pragma unroll
-      for (int x = 0; x < C::LOADS; ++x) {
-        if (x % 4 == 0) copy_begin(kbase, J, u, b, x);
-        copy_one(true, x);
-      }
-    };
-    auto copy_v = [&](int J, int u, uint32_t b) {
-#pragma unroll
-      for (int x = 0; x < C::LOADS; ++x) {
-        if (x % 4 == 0) copy_begin(vbase, J, u, NB + b, x);
-        copy_one(false, x);
-      }
-    };
-    copy_k(id_of(0), 0, 0);
-    copy_k(id_of(1 / U), 1 % U, 1);
-    copy_v(id_of(0), 0, 0);
-
-    bf16x8 q[2][C::KS];
+  // An item overlaps with the end of the one before it in the workgroup's own list: its description, the
+  // ids of its first KV blocks, its Q and its first two K slices are fetched while that one drains its
+  // pipeline and stores its result (what an item costs besides its blocks: 13 thousand clocks without,
+  // about 5 thousand with).
+  int4 da = {}, db = {};         // what the item is, see upload() in api.hip
+  int pos = 0, bb = 0;           // its place in the schedule, its batch entry
+  int ids = 0;                   // ids of its first 64 KV blocks, one per lane
+  uint64_t act = ~0ull;
+  bf16x8 q[2][C::KS];
+  auto load_q = [&](int64_t bh, int I) {
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
       // pair rows: the last pair of a head may lack its second query block; its waves load some valid
@@ -249,7 +217,8 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 #pragma unroll
       for (int ks = 0; ks < C::KS; ++ks) q[qt][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(qrow + 16 * ks + 8 * g));
     }
-    // the wait for the Q loads belongs here, not at their first use behind later copies
+  };
+  auto pin_q = [&]() {
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
@@ -258,11 +227,232 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
         if constexpr (D == 64) asm volatile("" : "+v"(q[qt][ks]));
         else asm volatile("" : "+a"(q[qt][ks]));
       }
-    wait_copies<0>();
+  };
+  // Block ids, 64 at a time, one per lane (a scalar load per block would make every LDS wait a full
+  // wait, since the two share a counter).  Past the end the last id repeats.  Pair rows: id of this
+  // wave's KV block of the super block, and a mask of the super blocks in which the wave's
+  // (query block, KV block) combination is active.
+  struct id_words { int w0, w1; };
+  auto load_ids = [&](const int4& d, int from) -> id_words {
+    const int x = min(from + l, d.w - 1);
+    const int32_t* kv = g_kv_idx + d.z;
+    if constexpr (PAIR) return {kv[2 * x], kv[2 * x + 1]};
+    else return {kv[x], 0};
+  };
+  auto set_ids = [&](const id_words& v, int& id, uint64_t& am) {
+    if constexpr (PAIR) {
+      id = wc ? (v.w1 & 0xffffff) : v.w0;
+      am = __builtin_amdgcn_ballot_w64(((v.w1 >> (24 + wa + 2 * wc)) & 1) != 0);
+    } else {
+      id = v.w0;
+    }
+  };
+  auto head_of = [&](const int4& d, int batch) { return (int64_t)batch * p.H + d.x; };
+  // Copies of this wave's share of a slice: K or V of slice u of block J into position b of its ring,
+  // KiB by KiB: begin() once (destination and base), then one() for x = 0 .. LOADS - 1.  Past the end of
+  // the list the last block is copied again, into positions nobody reads: that costs less than a branch
+  // in the step sequence.
+  const unsigned char* from = nullptr;
+  auto copy_begin = [&](const unsigned char* base, int J, int u, uint32_t b, int x) {
+    from = base + (int64_t)J * BLOCK_BYTES + u * C::SL + x * 1024;
+    set_copy_dst(ring + b * C::SL + share + x * 1024);
+  };
+  auto copy_one = [&](bool is_k, int x) { copy16_nth(x % 4, from, is_k ? k_src[x % C::KVAR] : v_src); };
+  auto copy_k = [&](const unsigned char* base, int J, int u, uint32_t b) {
+#pragma unroll
+    for (int x = 0; x < C::LOADS; ++x) {
+      if (x % 4 == 0) copy_begin(base, J, u, b, x);
+      copy_one(true, x);
+    }
+  };
+  auto copy_v = [&](const unsigned char* base, int J, int u, uint32_t b) {
+#pragma unroll
+    for (int x = 0; x < C::LOADS; ++x) {
+      if (x % 4 == 0) copy_begin(base, J, u, NB + b, x);
+      copy_one(false, x);
+    }
+  };
+  auto k_of = [&](int64_t bh) { return reinterpret_cast<const unsigned char*>(p.k + bh * p.Nk * D) + src_off; };
+  auto v_of = [&](int64_t bh) { return reinterpret_cast<const unsigned char*>(p.v + bh * p.Nk * D) + src_off; };
+
+  // tile k of key group cc: d-tile and query tile
+  auto tile_dt = [](int cc, int k) { return C::NC == 2 ? cc * (C::DT / 2) + k % (C::DT / 2) : cc % C::DT; };
+  auto tile_qt = [](int cc, int k) { return C::NC == 2 ? k / (C::DT / 2) : cc / C::DT; };
+  // does key group cc store the LSE of the query tiles it finalises?
+  auto has_lse = [](int cc) { return C::NC == 2 ? cc == 0 : cc % C::DT == 0; };
+  auto by_key_group = [&](auto&& f) {
+    if constexpr (C::NC == 4) {
+      if (wc == 2) return f(std::integral_constant<int, 2>{});
+      if (wc == 3) return f(std::integral_constant<int, 3>{});
+    }
+    if (wc == 0) f(std::integral_constant<int, 0>{});
+    else f(std::integral_constant<int, 1>{});
+  };
+  // Stores one accumulator tile: lane (r, g) holds, of query r, d-values 8 e4 + 4 g .. + 3 in res[e4].  The
+  // lane pair swaps halves so that each lane stores 16 bytes side by side.
+  auto store_tile = [&](const f32x4 (&res)[4], int64_t tok, int dt) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      uint32_t a0 = pack_bf16x2(res[2 * i].x, res[2 * i].y), a1 = pack_bf16x2(res[2 * i].z, res[2 * i].w);
+      uint32_t b0 = pack_bf16x2(res[2 * i + 1].x, res[2 * i + 1].y), b1 = pack_bf16x2(res[2 * i + 1].z, res[2 * i + 1].w);
+      swap_upper_lower(a0, b0);
+      swap_upper_lower(a1, b1);
+      *reinterpret_cast<u32x4*>(p.o + tok * D + 32 * dt + 16 * i + 8 * g) = u32x4{a0, a1, b0, b1};
+    }
+  };
+
+  // Split rows.  A chunk's partial result (f32, the accumulator tiles as the lanes hold them) goes to memory,
+  // and the wave that stores the last chunk's share of a row merges that share (log-sum-exp identity, the
+  // same one that combines per-chunk partial attention in Ring Attention):
+  //   LSE = log sum_k exp(LSE_k),  O = sum_k exp(LSE_k - LSE) O_k.
+  // Waves count for themselves (they finalise the same tiles in every chunk), so no barrier is needed, and
+  // the count is taken during the next item, when the stores have long reached memory: a second launch
+  // that merges cost 8 - 14 us, waiting for stores and count at the end of each item 5 us per item.
+  // Pair rows: a query block may have no active block in some or all chunks (LSE_k = -inf).
+  auto partial = [&](int64_t slot_no, int k, int e4) {
+    return p.part_o + (slot_no * C::NW + w) * (C::TPW * 1024) + (k * 4 + e4) * 256 + l * 2;
+  };
+  bool pend_chunk = false;
+  int4 pa = {}, pb = {};         // the item whose count is due
+  int pbb = 0;
+  auto count_chunk = [&]() -> uint32_t {       // chunks of the row this wave's share is complete of (lane 0 of the result)
+    uint32_t before = 0;
+    if (l == 0) before = __hip_atomic_fetch_add(p.split_cnt + ((int64_t)pbb * p.n_split + pb.y) * C::NW + w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return before;
+  };
+  auto merge_if_last = [&](uint32_t before_lane0) {
+    pend_chunk = false;
+    const int n_chunks = pb.z;
+    if (__builtin_amdgcn_readfirstlane(before_lane0) != (uint32_t)n_chunks - 1) return;
+    if (l == 0)        // ready for the next launch
+      __hip_atomic_store(p.split_cnt + ((int64_t)pbb * p.n_split + pb.y) * C::NW + w, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int64_t first = (int64_t)pbb * p.n_slots + pb.w;
+    const int64_t tok0 = head_of(pa, pbb) * p.Nq + (int64_t)pa.y * C::QROWS + 64 * wa + r;
+    const bool q_there = !PAIR || pa.y * C::QROWS + 64 * wa < p.Nq;
+    by_key_group([&](auto c_tag) {
+      constexpr int WC = decltype(c_tag)::value;
+      constexpr int G = 2;                       // chunks fetched at once
+#pragma unroll
+      for (int k = 0; k < C::TPW; ++k) {
+        const int qt = tile_qt(WC, k), qloc = 64 * wa + 32 * qt + r;
+        float m = -INFINITY, tot = 0.f;
+        f32x4 acc[4];
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) acc[e4] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int x0 = 0; x0 < n_chunks; x0 += G) {
+          float ls[G];
+          f32x2 lo[G][4], hi[G][4];
+#pragma unroll
+          for (int y = 0; y < G; ++y) {
+            const int64_t sl = first + min(x0 + y, n_chunks - 1);
+            ls[y] = __hip_atomic_load(p.part_lse + sl * C::QROWS + qloc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+              lo[y][e4] = load_shared(partial(sl, k, e4));
+              hi[y][e4] = load_shared(partial(sl, k, e4) + 128);
+            }
+          }
+          float mn = m;
+#pragma unroll
+          for (int y = 0; y < G; ++y) mn = fmaxf(mn, ls[y]);
+          const float mref = (mn == -INFINITY) ? 0.f : mn;       // nothing for this query yet: weights of 0, not inf - inf
+          const float old = __expf(m - mref);
+          m = mn;
+          tot *= old;
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4) acc[e4] *= old;
+#pragma unroll
+          for (int y = 0; y < G; ++y) {
+            const float wgt = (x0 + y < n_chunks) ? __expf(ls[y] - mref) : 0.f;
+            tot += wgt;
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+              acc[e4].x += wgt * lo[y][e4].x;  acc[e4].y += wgt * lo[y][e4].y;
+              acc[e4].z += wgt * hi[y][e4].x;  acc[e4].w += wgt * hi[y][e4].y;
+            }
+          }
+        }
+        const bool none = !(tot > 0.f);          // no chunk has anything for this query: O = 0, LSE = -inf
+        const float inv = none ? 0.f : 1.0f / tot;
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) acc[e4] *= inv;
+        if (!q_there) continue;
+        store_tile(acc, tok0 + 32 * qt, tile_dt(WC, k));
+        if (has_lse(WC) && k % (C::TPW > 1 ? C::TPW / 2 : 1) == 0 && g == 0 && p.lse != nullptr)
+          p.lse[tok0 + 32 * qt] = none ? -INFINITY : m + __logf(tot);
+      }
+    });
+  };
+
+  int own_i = 0, own_b = n_own > 0 ? 0 : p.B;      // own list: position and batch entry of the current item (p.B: done)
+  bool first_take = true;
+  bool ready = false;            // the item's ids are there, its Q and first K slices on their way
+  int stores = 0;                // what the item before stored: 1 = TPW tiles of O, 2 = a chunk's partial result, 0 = maybe nothing
+  for (;;) {
+    if (!ready) {
+      if (own_b < p.B) {                          // the first item
+        bb = 0;
+        pos = it_begin;
+      } else {
+        uint32_t tp = blockIdx.x;
+        if (n_first == 0 || !first_take) {
+          if (total_tail <= n_first) break;
+          if (t == 0) {
+            const uint32_t raw = atomicAdd(&p.queue[0], 1u);
+            // every workgroup fails once: the last to do so rewinds the queue for the next launch
+            if (raw == total_tail - n_first + gridDim.x - 1) p.queue[0] = 0;
+            tail_pos = n_first + raw;
+          }
+          __syncthreads();
+          tp = __builtin_amdgcn_readfirstlane(tail_pos);
+          __syncthreads();                        // everybody has read it before the next take overwrites it
+        }
+        first_take = false;
+        if (tp >= total_tail) break;
+        bb = (int)(tp / (uint32_t)p.n_tail);
+        const int tq = (int)(tp % (uint32_t)p.n_tail);
+        pos = p.n_placed + tq;
+        if (t == 0) atomicAdd(&p.queue[1 + tq], 1u);     // take count, read back by dbsp_plan_tail_takes
+      }
+      da = g_sched[2 * pos];
+      db = g_sched[2 * pos + 1];
+      set_ids(load_ids(da, 0), ids, act);
+      asm volatile("" : "+v"(ids));      // waited for here, so that nobody waits where the two ways meet
+    }
+    const uint64_t t0 = wall_clock64();
+    const int I = da.y, n = __builtin_amdgcn_readfirstlane(da.w), slot = db.x;
+    const int64_t bh = head_of(da, bb);
+    const unsigned char *kbase = k_of(bh), *vbase = v_of(bh);
+    const int nS = n * U;                     // slices
+    auto id_of = [&](int T) { return __builtin_amdgcn_readlane(ids, T & 63); };
+    auto act_of = [&](int T) { return ((act >> (T & 63)) & 1) != 0; };
+    if (!ready) {
+      copy_k(kbase, id_of(0), 0, 0);
+      copy_k(kbase, id_of(1 / U), 1 % U, 1);
+      load_q(bh, I);
+      pin_q();      // (waited for where nothing else is under way, see the ids)
+    }
+    id_words ids_next = {0, 0};
+    if (n > 64) ids_next = load_ids(da, 64);
+    // the next item of this workgroup's own list
+    if (own_b < p.B && ++own_i == n_own) { own_i = 0; ++own_b; }
+    const bool more = own_b < p.B;
+    // (or this one again: loads in a branch would be waited for behind it, whatever else is under way)
+    const int npos = more ? it_begin + own_i : pos, nbb = more ? own_b : bb;
+    const int4 na = g_sched[2 * npos], nb = g_sched[2 * npos + 1];
+    int ids_n = 0;
+    uint64_t act_n = ~0ull;
+    copy_v(vbase, id_of(0), 0, 0);
+
+    pin_q();      // the wait for the Q loads belongs here, not at their first use behind later copies
+    // the first K slices have landed; the first V slice and the stores of the item before may be under way
+    if (stores == 1) wait_copies<C::LOADS + 2 * C::TPW>();
+    else if (stores == 2) wait_copies<C::LOADS + 8 * C::TPW>();
+    else wait_copies<C::LOADS>();
     if constexpr (SHARED) {
       __syncthreads();
-      copy_k(id_of(2 / U), 0, 2);
-      copy_v(id_of(1 / U), 1 % U, 1);
+      copy_k(kbase, id_of(2 / U), 0, 2);
+      copy_v(vbase, id_of(1 / U), 1 % U, 1);
     }
 
     f32x16 o[C::DT][2];
@@ -487,12 +677,12 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     for (int x = 0; x < C::KS; ++x) read_k(0, x);
     auto next_ids = [&](int T) {       // before block ids T (and T + 1) are asked for: they may start a new group of 64
       if ((T & 63) == 0) {
-        ids = ids_next;
-        act = act_next;
-        load_ids(T + 64, ids_next, act_next);
+        set_ids(ids_next, ids, act);
+        if (T + 64 < n) ids_next = load_ids(da, T + 64);
       }
     };
     step(0, T0{}, T0{}, Yes{}, No{}, No{});
+    const id_words words_n = load_ids(na, 0);
     step(0, T1{}, T0{}, Yes{}, Yes{}, No{});
     int s = 1;
     if constexpr (U == 2) {
@@ -519,7 +709,12 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
         step(s, T1{}, T1{}, Yes{}, Yes{}, Yes{});
       }
     }
+    set_ids(words_n, ids_n, act_n);
+    const int jn0 = __builtin_amdgcn_readlane(ids_n, 0), jn1 = __builtin_amdgcn_readlane(ids_n, 1 / U);
+    uint32_t counted = 0;
+    if (pend_chunk) counted = count_chunk();
     step(nS, T0{}, T0{}, No{}, Yes{}, Yes{});
+    if (more) load_q(head_of(na, nbb), na.y);
     step(nS, T1{}, T0{}, No{}, No{}, Yes{});
     // back to the first half of the rings for the next item
     if constexpr (SHARED) {
@@ -529,8 +724,14 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 
     // ---- end of item: combine the slices' shares of the keys and store.  Wave c finalises TPW of the
     //      accumulator tiles and hands the others to the waves of their slices.
-    wait_copies<0>();
-    if constexpr (NQ > 1) __syncthreads();    // everybody is done with the slices: the buffers become the exchange area
+    if (more) wait_copies<2 * C::KS>();       // all copies; the loads of the next item's Q may be under way
+    else wait_copies<0>();
+    if constexpr (SHARED) __syncthreads();    // everybody is done with the slices: the rings become the exchange area
+    if (more) {
+      const unsigned char* kb = k_of(head_of(na, nbb));
+      copy_k(kb, jn0, 0, 0);
+      copy_k(kb, jn1, 1 % U, 1);
+    }
     const int64_t tok0 = bh * p.Nq + (int64_t)I * C::QROWS + 64 * wa + r;
     // pair rows: false for the waves of a query block past the end of the head (they still fill their
     // rows of a split row's partial result: zeros and -inf)
@@ -538,13 +739,10 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     const int64_t ps = (int64_t)bb * p.n_slots + slot;
     auto finish = [&](auto c_tag) {
       constexpr int WC = decltype(c_tag)::value;
-      // tile k of wave c: d-tile and query tile
-      auto tile_dt = [](int cc, int k) { return C::NC == 2 ? cc * (C::DT / 2) + k % (C::DT / 2) : cc % C::DT; };
-      auto tile_qt = [](int cc, int k) { return C::NC == 2 ? k / (C::DT / 2) : cc / C::DT; };
       // this wave's outbox: TPW tiles for each of the other slices, in ascending order of their slice
       auto box = [&](int from_c, int to_c, int k) {
         const int idx = (to_c < from_c ? to_c : to_c - 1) * C::TPW + k;
-        return reinterpret_cast<float*>(lds + (wa * C::NC + from_c) * C::XSTRIDE) + idx * 1024;
+        return reinterpret_cast<float*>(lds + from_c * C::RING + (C::RING - NQ * C::XCH) + wa * C::XCH) + idx * 1024;
       };
       float lf[2];
 #pragma unroll
@@ -594,55 +792,64 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 #pragma unroll
         for (int k = 0; k < C::TPW; ++k) {
           if (tile_qt(WC, k) != qt) continue;
-          const int dt = tile_dt(WC, k);
+          const f32x16& ov = o[tile_dt(WC, k)][qt];
+          f32x4 res[4];
 #pragma unroll
           for (int e4 = 0; e4 < 4; ++e4) {
-            const f32x16& ov = o[dt][qt];
-            f32x4 res = {ov[4 * e4] * f[WC], ov[4 * e4 + 1] * f[WC], ov[4 * e4 + 2] * f[WC], ov[4 * e4 + 3] * f[WC]};
+            res[e4] = f32x4{ov[4 * e4] * f[WC], ov[4 * e4 + 1] * f[WC], ov[4 * e4 + 2] * f[WC], ov[4 * e4 + 3] * f[WC]};
 #pragma unroll
             for (int cc = 0; cc < C::NC; ++cc) {
               if (cc == WC) continue;
               const f32x4 y = *reinterpret_cast<const f32x4*>(box(cc, WC, k) + (e4 * 64 + l) * 4);
-              res.x += y.x * f[cc];  res.y += y.y * f[cc];  res.z += y.z * f[cc];  res.w += y.w * f[cc];
-            }
-            const int dcol = 32 * dt + 8 * e4 + 4 * g;
-            if (slot < 0) {
-              if (!q_there) continue;
-              u32x2 pk;
-              pk.x = pack_bf16x2(res.x, res.y);
-              pk.y = pack_bf16x2(res.z, res.w);
-              *reinterpret_cast<u32x2*>(p.o + tok * D + dcol) = pk;
-            } else {
-              *reinterpret_cast<f32x4*>(p.part_o + (ps * C::QROWS + qloc) * D + dcol) = res;
+              res[e4].x += y.x * f[cc];  res[e4].y += y.y * f[cc];  res[e4].z += y.z * f[cc];  res[e4].w += y.w * f[cc];
             }
           }
+          if (slot >= 0) {
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+              store_shared(partial(ps, k, e4), res[e4].x, res[e4].y);
+              store_shared(partial(ps, k, e4) + 128, res[e4].z, res[e4].w);
+            }
+          } else if (q_there) {
+            store_tile(res, tok, tile_dt(WC, k));
+          }
         }
-        if ((C::NC == 2 ? WC == 0 : WC % C::DT == 0) && g == 0) {
+        if (g == 0) {
+          // every wave that finalises a tile of these queries stores the LSE of a chunk (the same bits), so
+          // that its own count vouches for it
           const float lse = mt * p.scale + __logf(lt);
-          if (slot >= 0) p.part_lse[ps * C::QROWS + qloc] = lse;
-          else if (p.lse != nullptr && q_there) p.lse[tok] = lse;
+          if (slot >= 0) __hip_atomic_store(p.part_lse + ps * C::QROWS + qloc, lse, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          else if (has_lse(WC) && p.lse != nullptr && q_there) p.lse[tok] = lse;
         }
       }
     };
-    if (wc == 0) finish(std::integral_constant<int, 0>{});
-    else if (wc == 1) finish(std::integral_constant<int, 1>{});
-    if constexpr (C::NC == 4) {
-      if (wc == 2) finish(std::integral_constant<int, 2>{});
-      else if (wc == 3) finish(std::integral_constant<int, 3>{});
-    }
+    by_key_group(finish);
     __syncthreads();      // the exchange has been read before the next item's copies overwrite it
+    if (pend_chunk) merge_if_last(counted);
+    if (slot >= 0) {
+      pend_chunk = true;
+      pa = da;
+      pb = db;
+      pbb = bb;
+    }
+    stores = slot >= 0 ? 2 : q_there ? 1 : 0;
+    ready = more;
+    if (more) {
+      pos = npos;
+      da = na;
+      db = nb;
+      bb = nbb;
+      ids = ids_n;
+      act = act_n;
+    }
     busy += wall_clock64() - t0;
+  }
+  if (pend_chunk) {
+    wait_copies<0>();
+    merge_if_last(count_chunk());
   }
 
   if (t == 0) {
-    if (total_tail != 0) {
-      __threadfence();
-      if (atomicAdd(&p.queue[1], 1u) == gridDim.x - 1) {
-        p.queue[0] = 0;
-        p.queue[1] = 0;
-        __threadfence();
-      }
-    }
     p.busy[part] = busy;
     const uint32_t hw = __builtin_amdgcn_s_getreg((31 << 11) | (0 << 6) | 4);    // HW_ID
     const uint32_t xcc = __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20);   // XCC_ID[3:0]
@@ -651,59 +858,8 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   }
 }
 
-// Fix-up pass: merges the chunks of split rows (log-sum-exp identity, the same one that
-// combines per-chunk partial attention in Ring Attention) and fills rows with no active block.
-//   LSE = log sum_k exp(LSE_k),  O = sum_k exp(LSE_k - LSE) O_k;   empty row: O = 0, LSE = -inf.
-// Grid: (B * (n_split + n_empty), blk * D / 4 / 256) workgroups of 256 threads; a thread produces four
-// consecutive d-values of one query (all its loads are independent of each other: the pass is
-// bandwidth-bound, not latency-bound).
-// blk = query rows of a plan row (pair mode: 128, where the last row of a head may reach past Nq
-// by one 64-token block and a query block may have no active block in some or all chunks).
-template <int D>
-__global__ __launch_bounds__(256) void dbsp_fixup_kernel(const dbsp_fwd_params p, int blk) {
-  const int per_b = p.n_split + p.n_empty;
-  const int bb = blockIdx.x / per_b, e = blockIdx.x % per_b;
-  const int x = blockIdx.y * 256 + threadIdx.x;          // < blk * D / 4
-  const int qloc = x / (D / 4), d4 = x % (D / 4);
-  if (e < p.n_split) {
-    const int4 sr = reinterpret_cast<const int4*>(p.split_rows)[e];
-    const int row = sr.x, first = sr.y, nch = sr.z;
-    const int h = row / p.nQ, I = row % p.nQ;
-    const int64_t bh = (int64_t)bb * p.H + h;
-    const int64_t ps0 = (int64_t)bb * p.n_slots + first;
-    if (I * blk + qloc >= p.Nq) return;
-    float mx = -INFINITY;
-    for (int kx = 0; kx < nch; ++kx) mx = fmaxf(mx, p.part_lse[(ps0 + kx) * blk + qloc]);
-    const bool none = (mx == -INFINITY);      // no chunk has anything for this query: O = 0, LSE = -inf
-    const float mref = none ? 0.f : mx;
-    float tot = 0.f;
-    for (int kx = 0; kx < nch; ++kx) tot += __expf(p.part_lse[(ps0 + kx) * blk + qloc] - mref);
-    const float lse = none ? -INFINITY : mx + __logf(tot);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int kx = 0; kx < nch; ++kx) {
-      const float wgt = none ? 0.f : __expf(p.part_lse[(ps0 + kx) * blk + qloc] - lse);
-      const f32x4 f = *reinterpret_cast<const f32x4*>(p.part_o + ((ps0 + kx) * blk + qloc) * D + 4 * d4);
-      acc.x += wgt * f.x;  acc.y += wgt * f.y;  acc.z += wgt * f.z;  acc.w += wgt * f.w;
-    }
-    const int64_t tok = bh * p.Nq + (int64_t)I * blk + qloc;
-    u32x2 pk;
-    pk.x = pack_bf16x2(acc.x, acc.y);
-    pk.y = pack_bf16x2(acc.z, acc.w);
-    *reinterpret_cast<u32x2*>(p.o + tok * D + 4 * d4) = pk;
-    if (p.lse != nullptr && d4 == 0) p.lse[tok] = lse;
-  } else {
-    const int row = p.empty_rows[e - p.n_split];
-    const int h = row / p.nQ, I = row % p.nQ;
-    const int64_t bh = (int64_t)bb * p.H + h;
-    if (I * blk + qloc >= p.Nq) return;
-    const int64_t tok = bh * p.Nq + (int64_t)I * blk + qloc;
-    *reinterpret_cast<u32x2*>(p.o + tok * D + 4 * d4) = u32x2{0u, 0u};
-    if (p.lse != nullptr && d4 == 0) p.lse[tok] = -INFINITY;
-  }
-}
-
 template <int D, int NQ, int NC, int U, bool PAIR = false>
-hipError_t launch_fwd(const dbsp_fwd_params& p, int P, hipStream_t stream) {
+hipError_t launch_fwd(const dbsp_fwd_params& p, int grid, hipStream_t stream, hipEvent_t done) {
   using C = Cfg<D, NQ, NC, U>;
   // the dynamic-LDS limit is a per-device function attribute: set it once per device
   static std::atomic<uint32_t> attr_set_mask{0};
@@ -717,27 +873,19 @@ hipError_t launch_fwd(const dbsp_fwd_params& p, int P, hipStream_t stream) {
     if (e != hipSuccess) return e;
     attr_set_mask.fetch_or(bit, std::memory_order_release);
   }
-  hipLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(P), dim3(C::NT), C::LDS_BYTES, stream, p, p.kv_idx,
-                     reinterpret_cast<const int4*>(p.sched), p.part_ptr);
+  const int4* sched = reinterpret_cast<const int4*>(p.sched);
+  if (done)
+    hipExtLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, nullptr, done, 0, p, p.kv_idx, sched, p.part_ptr);
+  else
+    hipLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, p, p.kv_idx, sched, p.part_ptr);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int P, hipStream_t stream) {
+hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int grid, hipStream_t stream, hipEvent_t done) {
   if ((block != 64 && block != 128) || (d != 64 && d != 128) || (pair && (block != 64 || d != 128))) return hipErrorInvalidValue;
-  const hipError_t e = pair              ? launch_fwd<128, 2, 2, 2, true>(p, P, stream)
-                       : block == 64     ? (d == 128 ? launch_fwd<128, 1, 2, 1>(p, P, stream) : launch_fwd<64, 1, 2, 1>(p, P, stream))
-                       : d == 128        ? launch_fwd<128, 2, 2, 2>(p, P, stream)
-                                         : launch_fwd<64, 2, 4, 1>(p, P, stream);
-  if (e != hipSuccess) return e;
-  const int fix = p.B * (p.n_split + p.n_empty);
-  if (fix > 0) {
-    const int rows = pair ? 128 : block;
-    const dim3 grid(fix, rows * d / 4 / 256);      // rows >= 64 and d >= 64: a whole number of workgroups per row
-    if (d == 128) hipLaunchKernelGGL((dbsp_fixup_kernel<128>), grid, dim3(256), 0, stream, p, rows);
-    else hipLaunchKernelGGL((dbsp_fixup_kernel<64>), grid, dim3(256), 0, stream, p, rows);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  if (pair) return launch_fwd<128, 2, 2, 2, true>(p, grid, stream, done);
+  if (block == 64) return d == 128 ? launch_fwd<128, 1, 2, 1>(p, grid, stream, done) : launch_fwd<64, 1, 2, 1>(p, grid, stream, done);
+  return d == 128 ? launch_fwd<128, 2, 2, 2>(p, grid, stream, done) : launch_fwd<64, 2, 4, 1>(p, grid, stream, done);
 }

@@ -12,13 +12,13 @@ struct dbsp_fwd_params {
   uint16_t* o;         // bf16 [B,H,nQ*BLK,D]
   float* lse;          // f32  [B,H,nQ*BLK] or null
   const int32_t* kv_idx;
-  const int32_t* split_rows;  // 4 x int32 per split row
   const int32_t* empty_rows;
   const int32_t* part_ptr;
-  const int32_t* sched;       // 8 x int32 per item: the partitions' lists, then the shared queue: head, row, first KV word, blocks, slot
-  uint32_t* queue;            // [0] next queue position, [1] workgroups that have left, [2 + t] times tail item t was taken
+  const int32_t* sched;       // 8 x int32 per item: the partitions' lists, then the shared queue: head, row, first KV word, blocks, slot; of split rows also index of the row, its chunks, its first slot
+  uint32_t* queue;            // [0] next queue position, [1 + t] times tail item t was taken
   float* part_o;       // f32 [B][n_slots][BLK][D]
   float* part_lse;     // f32 [B][n_slots][BLK]
+  uint32_t* split_cnt; // [B][n_split][waves of a workgroup] chunks of a split row that are done; zero between launches
   uint64_t* busy;      // [P]
   uint32_t* hw_id;     // [P]
   int32_t B, H, nQ, nK;     // nQ: rows per head of the plan (pair mode: pairs of query blocks); nK: KV blocks
@@ -29,6 +29,9 @@ struct dbsp_fwd_params {
   float scale_log2;    // softmax scale * log2(e)
 };
 
-// Enqueues the persistent kernel (grid = P workgroups) and, if needed, the fix-up kernel.
+// Enqueues the persistent kernel: `grid` workgroups, enough to reach every partition that has items (all of
+// them unless the plan has fewer items than partitions).
 // pair: the plan's rows are pairs of 64-token query blocks and its units pairs of 64-token KV blocks (d = 128 only).
-hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int P, hipStream_t stream);
+// done: event that the end of the kernel completes (null inside a stream capture): the launch's own completion
+// signal, where a record behind the launch would put another packet between this kernel and the next (4 us).
+hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int grid, hipStream_t stream, hipEvent_t done);

@@ -53,15 +53,23 @@ struct dbsp_device_plan {
   size_t staging_bytes = 0;
   void* staging_kv = nullptr;     // pinned host memory the index lists are compacted into (the plan's kv_idx)
   size_t staging_kv_bytes = 0;
-  void* uploaded = nullptr;       // hipEvent_t: the upload has finished
-  void* last_use = nullptr;       // hipEvent_t: recorded after every forward launch
+  size_t up_bytes = 0, kv_bytes = 0;   // what is sent: the small arrays and zeroed counters, then the index lists, to the front of blob
+  // How the plan gets to the device: not yet; by copies on the library's upload stream (`uploaded` tells when);
+  // or by a kernel in front of the first forward launch, on that launch's stream
+  enum { kNotSent, kByCopy, kInStream } sent = kNotSent;
+  bool upload_done = false;       // known to have arrived
+  void* upload_stream = nullptr;  // hipStream_t of kInStream
+  void* uploaded = nullptr;       // hipEvent_t: the copies of kByCopy have finished
+  void* last_use = nullptr;       // hipEvent_t: the last forward launch has finished
   bool used = false;
+  int32_t last_grid = 0;          // workgroups of the last forward launch
   const int32_t* kv_idx = nullptr;
-  const int32_t* split_rows = nullptr;
   const int32_t* empty_rows = nullptr;
   const int32_t* part_ptr = nullptr;
   const int32_t* sched = nullptr;  // 8 x int32 per item, see upload()
-  uint32_t* queue = nullptr;      // [2 + n_tail]: next queue position, workgroups that have left, take count per tail item
+  uint32_t* queue = nullptr;      // [1 + n_tail]: next queue position, take count per tail item
+  uint32_t* split_cnt = nullptr;  // [max_batch][n_split][8]: finished chunks of a split row, per wave, zero between launches
+  int32_t used_parts = 0;         // partitions up to the last one that has items
   uint64_t* busy = nullptr;       // [P]
   uint32_t* hw_id = nullptr;      // [P]
   float* part_o = nullptr;        // split-row partial outputs, f32 [batches][n_slots][block][d]
