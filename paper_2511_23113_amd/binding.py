@@ -301,7 +301,7 @@ def imbalance_ratio(work) -> float:
 
 
 def _ptr(a):
-    return a.ctypes.data_as(C.c_void_p) if a is not None else None
+    return _addr(a) if a is not None else None
 
 
 def _split(flat, ptr):

@@ -119,6 +119,11 @@ int dbsp_build_host_plan(const uint8_t* mask, int32_t H, int32_t nQ, int32_t nK,
 // rho_s of the naive and / or the greedy longest-first placement of the plan's items (each costs a placement pass).
 void dbsp_host_plan_lazy_rhos(const dbsp_host_plan& hp, bool want_naive, bool want_balanced, double* rho_naive, double* rho_balanced);
 
+// Passes over a mask's rows: body(0) .. body(n - 1), n <= dbsp_row_threads(), on the calling thread and the pooled helper
+// threads (all on the calling thread if another planner has those).  Throws std::bad_alloc if a body did.
+int dbsp_row_threads();
+void dbsp_run_rows(int n, const std::function<void(int)>& body);
+
 double dbsp_rho(const int64_t* work, int32_t periods, int32_t partitions);
 
 // Records the calling thread's error text (returned by dbsp_last_error) and hands `code` back.

@@ -401,11 +401,20 @@ double dbsp_rho(const int64_t* work, int32_t periods, int32_t partitions) {
   return (double)num / ((double)total / (double)partitions);
 }
 
+int dbsp_row_threads() {
+  static const unsigned hw = std::thread::hardware_concurrency();
+  return (int)std::min<unsigned>(hw ? hw : 1, RowPool::kMaxThreads);
+}
+
+void dbsp_run_rows(int n, const std::function<void(int)>& body) {
+  if (n <= 1) body(0);
+  else if (!RowPool::instance().run(n, body)) throw std::bad_alloc();
+}
+
 namespace {
 int row_threads(int64_t mask_bytes) {
   if (mask_bytes < (int64_t)1 << 20) return 1;
-  const unsigned hw = std::thread::hardware_concurrency();
-  return (int)std::min<int64_t>(std::min<unsigned>(hw ? hw : 1, RowPool::kMaxThreads), mask_bytes >> 19);
+  return (int)std::min<int64_t>(dbsp_row_threads(), mask_bytes >> 19);
 }
 }  // namespace
 

@@ -74,6 +74,22 @@ def test_blocks_on_configs(cfg, y):
         _same(B.partition_blocks(mask, y, reward), db.partition_blocks(mask, y, reward), BLOCK_KEYS)
 
 
+@pytest.mark.parametrize("H,nQ,nK,y", [
+    (1, 1, 1, 1), (254, 3, 5, 2), (255, 3, 5, 2), (256, 3, 5, 2), (300, 40, 33, 3),     # bytes hold 255 heads
+    (255, 257, 2, 4), (256, 256, 2, 4),                                                 # 16 bits hold 65535 blocks of a column
+    (9, 171, 171, 8), (65, 64, 128, 5),                                                 # just over 256 and 512 KiB: 1 and 2 threads
+    (40, 256, 256, 8),                                                                  # every thread
+    (65535, 1, 2, 1), (65536, 2, 3, 2),                                                 # 32-bit sums
+])
+def test_blocks_at_the_edges_of_the_sums(H, nQ, nK, y):
+    rng = np.random.default_rng(H + nQ)
+    for mask in (np.ones((H, nQ, nK), dtype=np.uint8), rng.integers(0, 3, (H, nQ, nK), dtype=np.uint8)):
+        ref = db.partition_blocks(mask, y, 0.5)
+        _same(B.partition_blocks(mask, y, 0.5), ref, BLOCK_KEYS)
+        work, rho = B.ring_work(mask, y, ref["gpu_of_q"], ref["chunk_of_kv"])
+        assert work == ref["work"] and rho == ref["rho"]
+
+
 def test_argument_errors():
     lib = B.load_library()
     cnt = np.array([3, 2, 1], dtype=np.int64)
