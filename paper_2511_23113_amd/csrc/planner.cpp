@@ -24,27 +24,55 @@
 
 namespace {
 
-// Bit 7 of every byte of the result is set exactly where the byte of w is nonzero.
-inline uint64_t nonzero_bytes(uint64_t w) {
-  const uint64_t low7 = 0x7f7f7f7f7f7f7f7fULL;
-  return (((w & low7) + low7) | w) & ~low7;
-}
+// The row passes read 16 mask bytes at a time, and a row's last n % 16 bytes without leaving the row.
+inline __m128i load16(const uint8_t* p) { return _mm_loadu_si128(reinterpret_cast<const __m128i*>(p)); }
+inline uint32_t nonzero16(__m128i v) { return 0xFFFFu & ~(uint32_t)_mm_movemask_epi8(_mm_cmpeq_epi8(v, _mm_setzero_si128())); }
 
-// Number of nonzero bytes of row[0..n).
-inline int32_t count_row(const uint8_t* row, int32_t n) {
-  int32_t c = 0, j = 0;
-  for (; j + 8 <= n; j += 8) {
-    uint64_t w;
-    std::memcpy(&w, row + j, 8);
-    c += __builtin_popcountll(nonzero_bytes(w));
+// row[j .. n), 1 to 15 bytes, as the highest bytes of the vector, zeros below
+struct RestMask {
+  uint8_t b[32];
+  RestMask() { for (int k = 0; k < 32; ++k) b[k] = k < 16 ? 0 : 0xFF; }
+};
+const RestMask g_rest;
+inline __m128i load_rest(const uint8_t* row, int32_t j, int32_t n) {
+  const int32_t rest = n - j;
+  if (n >= 16) return _mm_and_si128(load16(row + n - 16), load16(g_rest.b + rest));
+  uint64_t lo = 0, hi = 0;
+  if (rest >= 8) {
+    std::memcpy(&hi, row + n - 8, 8);
+    for (int32_t k = 0; k < rest - 8; ++k) lo |= (uint64_t)row[j + k] << (8 * (16 - rest + k));
+  } else {
+    for (int32_t k = 0; k < rest; ++k) hi |= (uint64_t)row[j + k] << (8 * (8 - rest + k));
   }
-  for (; j < n; ++j) c += row[j] != 0;
-  return c;
+  return _mm_set_epi64x((long long)hi, (long long)lo);
 }
 
-// Table for the compaction below: byte t of entry m is the position of the t-th set bit of m.
+// Number of nonzero bytes of row[0..n), or of row0 | row1.
+template <class Load, class Rest>
+inline int32_t count_bytes(int32_t n, Load load, Rest rest) {
+  const __m128i zero = _mm_setzero_si128();
+  __m128i total = zero;           // zero bytes, as two 64-bit sums
+  int32_t j = 0, seen = n;
+  while (j + 16 <= n) {
+    const int32_t end = std::min(n - 15, j + 16 * 255);      // a byte counts up to 255
+    __m128i z = zero;
+    for (; j < end; j += 16) z = _mm_sub_epi8(z, _mm_cmpeq_epi8(load(j), zero));
+    total = _mm_add_epi64(total, _mm_sad_epu8(z, zero));
+  }
+  if (j < n) {
+    total = _mm_add_epi64(total, _mm_sad_epu8(_mm_sub_epi8(zero, _mm_cmpeq_epi8(rest(j), zero)), zero));
+    seen = j + 16;
+  }
+  return seen - (int32_t)(_mm_cvtsi128_si64(total) + _mm_cvtsi128_si64(_mm_unpackhi_epi64(total, total)));
+}
+inline int32_t count_row(const uint8_t* row, int32_t n) {
+  return count_bytes(n, [&](int32_t j) { return load16(row + j); }, [&](int32_t j) { return load_rest(row, j, n); });
+}
+
+// Tables for the compaction below: byte t of e[m] is the position of the t-th set bit of m, bits[m] their number.
 struct CompactTable {
   uint64_t e[256];
+  uint8_t bits[256];
   CompactTable() {
     for (int m = 0; m < 256; ++m) {
       uint64_t v = 0;
@@ -52,35 +80,38 @@ struct CompactTable {
       for (int k = 0; k < 8; ++k)
         if (m & (1 << k)) v |= (uint64_t)k << (8 * t++);
       e[m] = v;
+      bits[m] = (uint8_t)t;
     }
   }
 };
 const CompactTable g_compact;
 
-// Writes the ascending indices of the nonzero bytes of row[0..n) to out; returns one past the last.
-// Branch-free per 8-byte word (a test per byte mispredicts all the time at 30 % density): the
-// word's nonzero-byte mask selects a table entry holding the positions of its set bits, which are
-// widened to 32 bits, offset and stored as 8 values; the cursor advances by the mask's popcount.
-// The destination therefore needs 8 elements of slack past the last valid one.
-inline int32_t* compact_row(const uint8_t* row, int32_t n, int32_t* out) {
+// Appends the positions of the set bits of the 8-bit m, plus j, to out: branch-free (a test per byte
+// mispredicts all the time at 30 % density), 8 values stored and the cursor moved by the number of bits.
+inline int32_t* append_bits(uint32_t m, int32_t j, int32_t* out) {
   const __m128i zero = _mm_setzero_si128();
+  const __m128i b = _mm_cvtsi64_si128((long long)g_compact.e[m]);
+  const __m128i h = _mm_unpacklo_epi8(b, zero);
+  const __m128i base = _mm_set1_epi32(j);
+  _mm_storeu_si128(reinterpret_cast<__m128i*>(out), _mm_add_epi32(_mm_unpacklo_epi16(h, zero), base));
+  _mm_storeu_si128(reinterpret_cast<__m128i*>(out + 4), _mm_add_epi32(_mm_unpackhi_epi16(h, zero), base));
+  return out + g_compact.bits[m];
+}
+
+// Writes the ascending indices of the nonzero bytes of row[0..n) to out; returns one past the last.
+// The destination needs 8 elements of slack past the last valid one.
+inline int32_t* compact_row(const uint8_t* row, int32_t n, int32_t* out) {
   int32_t j = 0;
-  for (; j + 8 <= n; j += 8) {
-    uint64_t w;
-    std::memcpy(&w, row + j, 8);
-    if (w == 0) continue;
-    // bit 7 of byte k -> bit k of the top byte (the multiplier's terms never collide, so no carries)
-    const uint32_t m = (uint32_t)(((nonzero_bytes(w) >> 7) * 0x0102040810204080ULL) >> 56);
-    const __m128i b = _mm_cvtsi64_si128((long long)g_compact.e[m]);
-    const __m128i h = _mm_unpacklo_epi8(b, zero);
-    const __m128i base = _mm_set1_epi32(j);
-    _mm_storeu_si128(reinterpret_cast<__m128i*>(out), _mm_add_epi32(_mm_unpacklo_epi16(h, zero), base));
-    _mm_storeu_si128(reinterpret_cast<__m128i*>(out + 4), _mm_add_epi32(_mm_unpackhi_epi16(h, zero), base));
-    out += __builtin_popcount(m);
+  for (; j + 16 <= n; j += 16) {
+    const uint32_t m = nonzero16(load16(row + j));
+    if (!m) continue;
+    out = append_bits(m & 255, j, out);
+    out = append_bits(m >> 8, j + 8, out);
   }
-  for (; j < n; ++j) {
-    *out = j;
-    out += (row[j] != 0);
+  if (j < n) {
+    const uint32_t m = nonzero16(load_rest(row, j, n)) >> (16 - (n - j));
+    if (m & 255) out = append_bits(m & 255, j, out);
+    if (m >> 8) out = append_bits(m >> 8, j + 8, out);
   }
   return out;
 }
@@ -88,33 +119,34 @@ inline int32_t* compact_row(const uint8_t* row, int32_t n, int32_t* out) {
 // Pair mode (two query blocks per row): number of KV blocks either of the two mask rows needs.
 inline int32_t count_union(const uint8_t* row0, const uint8_t* row1, int32_t n) {
   if (!row1) return count_row(row0, n);
-  int32_t c = 0, j = 0;
-  for (; j + 8 <= n; j += 8) {
-    uint64_t a, b;
-    std::memcpy(&a, row0 + j, 8);
-    std::memcpy(&b, row1 + j, 8);
-    c += __builtin_popcountll(nonzero_bytes(a) | nonzero_bytes(b));
-  }
-  for (; j < n; ++j) c += (row0[j] | row1[j]) != 0;
-  return c;
+  return count_bytes(n, [&](int32_t j) { return _mm_or_si128(load16(row0 + j), load16(row1 + j)); },
+                     [&](int32_t j) { return _mm_or_si128(load_rest(row0, j, n), load_rest(row1, j, n)); });
 }
 
 // Pair mode: the super blocks of one super-row: consecutive pairs (j0, j1) of the ascending union of
 // the two rows' KV blocks, stored as j0 and j1 | flags << 24, flags bit (q + 2k) = "query block q
 // needs KV block j_k".  A union of odd length ends with j1 = j0 and no flag for the second slot.
-inline void compact_pair(const uint8_t* row0, const uint8_t* row1, int32_t n, int32_t* out) {
-  int32_t have = -1, have_f = 0;
-  for (int32_t j = 0; j < n; ++j) {
-    const int32_t f = (row0[j] != 0 ? 1 : 0) | ((row1 && row1[j] != 0) ? 2 : 0);
-    if (!f) continue;
-    if (have < 0) { have = j; have_f = f; continue; }
-    *out++ = have;
-    *out++ = j | ((have_f | (f << 2)) << 24);
-    have = -1;
+// `list` has room for n elements.
+inline void compact_pair(const uint8_t* row0, const uint8_t* row1, int32_t n, int32_t* list, int32_t* out) {
+  int32_t* end = list;
+  for (int32_t j = 0; j < n; j += 16) {
+    const bool whole = j + 16 <= n;
+    const int32_t down = whole ? 0 : 16 - (n - j);
+    const uint32_t m0 = nonzero16(whole ? load16(row0 + j) : load_rest(row0, j, n)) >> down;
+    const uint32_t m1 = !row1 ? 0 : nonzero16(whole ? load16(row1 + j) : load_rest(row1, j, n)) >> down;
+    for (uint32_t u = m0 | m1; u; u &= u - 1) {
+      const int32_t b = __builtin_ctz(u);
+      *end++ = (j + b) | (int32_t)(((m0 >> b) & 1) | ((m1 >> b) & 1) << 1) << 24;
+    }
   }
-  if (have >= 0) {
-    *out++ = have;
-    *out++ = have | (have_f << 24);
+  constexpr int32_t kId = 0xFFFFFF;
+  for (; list + 1 < end; list += 2) {
+    *out++ = list[0] & kId;
+    *out++ = (list[1] & kId) | (list[0] & ~kId) | (list[1] & ~kId) << 2;
+  }
+  if (list < end) {
+    *out++ = list[0] & kId;
+    *out++ = list[0];
   }
 }
 
@@ -128,6 +160,10 @@ struct LoadHeap {
   const int32_t* cost;        // may be null (unit cost)
   LoadHeap(int32_t P, const int32_t* cost_) : load(P, 0), heap(P), cost(cost_) {
     for (int32_t g = 0; g < P; ++g) heap[g] = g;  // all loads equal: ascending ids form a valid heap
+  }
+  explicit LoadHeap(std::vector<int64_t> load_) : load(std::move(load_)), heap(load.size()), cost(nullptr) {
+    for (size_t g = 0; g < heap.size(); ++g) heap[g] = (int32_t)g;
+    std::make_heap(heap.begin(), heap.end(), [&](int32_t a, int32_t b) { return less(b, a); });
   }
   bool less(int32_t a, int32_t b) const { return load[a] < load[b] || (load[a] == load[b] && a < b); }
   int32_t place(int64_t w) {
@@ -298,6 +334,40 @@ void order_by_weight_desc(int64_t n_items, int64_t wmax, Weight weight, std::vec
   for (int64_t i = 0; i < n_items; ++i) order[bucket_start[wmax - weight(i)]++] = (int32_t)i;
 }
 
+// order[r] = position of the r-th smallest of val[0..n), ties by position: a counting sort where the values
+// span little more than their number; ranks by comparing every pair, which the compiler vectorises, for a few
+// dozen; else a sort of (value, position) packed into one word; else one by comparison.
+struct SmallOrder {
+  std::vector<int32_t> count, key32;
+  std::vector<uint64_t> key64;
+  void operator()(const int64_t* val, int32_t n, int32_t* order) {
+    const auto [lo_at, hi_at] = std::minmax_element(val, val + n);
+    const int64_t lo = *lo_at, span = *hi_at - lo + 1;
+    if (span <= 2 * (int64_t)n) {
+      count.assign((size_t)span + 1, 0);
+      for (int32_t t = 0; t < n; ++t) ++count[val[t] - lo + 1];
+      for (int64_t v = 0; v < span; ++v) count[v + 1] += count[v];
+      for (int32_t t = 0; t < n; ++t) order[count[val[t] - lo]++] = t;
+    } else if (n <= 64 && span * n <= INT32_MAX) {
+      key32.resize(n);
+      for (int32_t t = 0; t < n; ++t) key32[t] = (int32_t)(val[t] - lo) * n + t;
+      for (int32_t t = 0; t < n; ++t) {
+        int32_t rank = 0;
+        for (int32_t u = 0; u < n; ++u) rank += key32[u] < key32[t];
+        order[rank] = t;
+      }
+    } else if (n < (1 << 20) && span < ((int64_t)1 << 43)) {
+      key64.resize(n);
+      for (int32_t t = 0; t < n; ++t) key64[t] = ((uint64_t)(val[t] - lo) << 20) | (uint64_t)t;
+      std::sort(key64.begin(), key64.end());
+      for (int32_t t = 0; t < n; ++t) order[t] = (int32_t)(key64[t] & 0xFFFFF);
+    } else {
+      for (int32_t t = 0; t < n; ++t) order[t] = t;
+      std::stable_sort(order, order + n, [&](int32_t a, int32_t b) { return val[a] < val[b]; });
+    }
+  }
+};
+
 std::vector<int64_t> loads_of(const dbsp_host_plan& hp, const std::vector<int32_t>& assign) {
   std::vector<int64_t> ld(hp.P, 0);
   const int64_t n_items = hp.n_items();
@@ -315,6 +385,8 @@ std::vector<int32_t> place_naive(const dbsp_host_plan& hp) {
   return assign;
 }
 
+constexpr int64_t kRingWords = int64_t(1) << 16;     // 512 KiB: 4096 loads of 1024 partitions
+
 // greedy longest-first placement (Alg. 1, first loop)
 std::vector<int32_t> place_greedy(const dbsp_host_plan& hp) {
   const int64_t n_items = hp.n_items();
@@ -322,6 +394,34 @@ std::vector<int32_t> place_greedy(const dbsp_host_plan& hp) {
   const int64_t ov = hp.item_overhead;
   auto weight = [&](int64_t i) { return (int64_t)(hp.items[4 * i + 3] - hp.items[4 * i + 2]) + ov; };
   order_by_weight_desc(n_items, (int64_t)hp.nK + ov, weight, order);
+  // At unit cost the loads are small integers and the least load never falls: the partitions wait in a
+  // ring of buckets, one per load from the least to the least plus the largest weight, each a bitmap of
+  // partition ids (so the lowest index comes first).  An item never returns its partition to the bucket
+  // being emptied, as every weight is positive.  8 ns an item where a heap of 1024 takes 22.
+  const int64_t wm = n_items ? weight(order[0]) : 0, words = (hp.P + 63) / 64;
+  if (hp.partition_cost.empty() && (wm + 1) * words <= kRingWords) {
+    std::vector<uint64_t> ring((size_t)((wm + 1) * words), 0);
+    std::vector<int32_t> held(wm + 1, 0);
+    for (int32_t g = 0; g < hp.P; ++g) ring[g >> 6] |= 1ull << (g & 63);
+    held[0] = hp.P;
+    int64_t slot = 0;                    // bucket of the least load
+    for (int64_t t = 0; t < n_items; slot = slot == wm ? 0 : slot + 1) {
+      if (!held[slot]) continue;
+      uint64_t* bucket = ring.data() + slot * words;
+      for (int64_t k = 0; k < words && t < n_items; ++k)
+        for (; bucket[k] && t < n_items; ++t) {
+          const int bit = __builtin_ctzll(bucket[k]);
+          bucket[k] &= bucket[k] - 1;
+          --held[slot];
+          int64_t to = slot + weight(order[t]);
+          if (to > wm) to -= wm + 1;
+          ring[to * words + k] |= 1ull << bit;
+          ++held[to];
+          assign[order[t]] = (int32_t)(64 * k + bit);
+        }
+    }
+    return assign;
+  }
   LoadHeap heap(hp.P, hp.partition_cost.empty() ? nullptr : hp.partition_cost.data());
   for (int64_t t = 0; t < n_items; ++t) assign[order[t]] = heap.place(weight(order[t]));
   return assign;
@@ -412,9 +512,11 @@ void dbsp_run_rows(int n, const std::function<void(int)>& body) {
 }
 
 namespace {
-int row_threads(int64_t mask_bytes) {
-  if (mask_bytes < (int64_t)1 << 20) return 1;
-  return (int)std::min<int64_t>(dbsp_row_threads(), mask_bytes >> 19);
+// Threads for a pass over the rows: one for every `share` mask bytes.  Waking helpers costs 5 to 10 us, in which
+// one thread counts 200 KB and compacts 80 KB.
+constexpr int64_t kCountShare = int64_t(1) << 19, kCompactShare = int64_t(1) << 17;
+int row_threads(int64_t mask_bytes, int64_t share) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(dbsp_row_threads(), mask_bytes / share));
 }
 }  // namespace
 
@@ -432,7 +534,7 @@ int dbsp_plan_count(const uint8_t* mask, int32_t H, int32_t nQ_blocks, int32_t n
     hp.row_cnt.resize(R);
     hp.row_ptr.resize(R + 1);
     hp.blocks_per_head.assign(H, 0);
-    const int n_thr = row_threads((int64_t)H * nQ_blocks * nK);
+    const int n_thr = row_threads((int64_t)H * nQ_blocks * nK, kCountShare);
     const std::function<void(int)> job = [&](int k) {
       for (int64_t r = R * k / n_thr; r < R * (k + 1) / n_thr; ++r) {
         if (!pair) { hp.row_cnt[r] = count_row(mask + r * nK, nK); continue; }
@@ -468,33 +570,32 @@ int dbsp_plan_count(const uint8_t* mask, int32_t H, int32_t nQ_blocks, int32_t n
 void dbsp_compact_begin(const uint8_t* mask, const dbsp_host_plan& hp, int32_t* dst, dbsp_compaction& job) {
   const int64_t R = (int64_t)hp.H * hp.nQ;
   const int32_t nK = hp.nK;
-  const int n_thr = row_threads((int64_t)hp.H * hp.nQ_blocks * nK);
+  const int n_thr = row_threads((int64_t)hp.H * hp.nQ_blocks * nK, kCompactShare);
   const dbsp_host_plan* php = &hp;
   job.body = [=](int k) {
     const dbsp_host_plan& h = *php;
     const int64_t r0 = R * k / n_thr, r1 = R * (k + 1) / n_thr;
+    std::vector<int32_t> bounce((size_t)nK + 8);
     if (h.pair) {     // two ints per super block, written exactly: no slack between rows needed
       for (int64_t r = r0; r < r1; ++r) {
         if (!h.row_cnt[r]) continue;
         const int64_t hd = r / h.nQ, q0 = 2 * (r % h.nQ);
         const uint8_t* row0 = mask + (hd * h.nQ_blocks + q0) * nK;
-        compact_pair(row0, q0 + 1 < h.nQ_blocks ? row0 + nK : nullptr, nK, dst + 2 * (int64_t)h.row_ptr[r]);
+        compact_pair(row0, q0 + 1 < h.nQ_blocks ? row0 + nK : nullptr, nK, bounce.data(), dst + 2 * (int64_t)h.row_ptr[r]);
       }
       return;
     }
-    std::vector<int32_t> bounce;
     for (int64_t r = r0; r < r1; ++r) {
       if (!h.row_cnt[r]) continue;
       if (r1 == R || (int64_t)h.row_ptr[r + 1] + 8 <= (int64_t)h.row_ptr[r1]) {
         compact_row(mask + r * nK, nK, dst + h.row_ptr[r]);
       } else {
-        bounce.resize((size_t)nK + 8);
         compact_row(mask + r * nK, nK, bounce.data());
         std::memcpy(dst + h.row_ptr[r], bounce.data(), sizeof(int32_t) * (size_t)h.row_cnt[r]);
       }
     }
   };
-  if (n_thr <= 1 && (int64_t)hp.H * hp.nQ_blocks * nK < ((int64_t)1 << 18)) {   // a small mask: done before a helper thread would have woken up
+  if ((int64_t)hp.H * hp.nQ_blocks * nK < kCompactShare) {   // a small mask: done before a helper thread would have woken up
     job.pool = nullptr;
     job.body(0);
     return;
@@ -596,14 +697,10 @@ int dbsp_plan_place(const dbsp_place_opts& opts, const dbsp_host_plan* prev, dou
           load[assign_reuse[i]] += hp.items[4 * i + 3] - hp.items[4 * i + 2];
         }
       }
-      for (int64_t i = 0; i < n_items; ++i) {
-        if (assign_reuse[i] >= 0) continue;
-        int32_t best = 0;
-        for (int32_t g = 1; g < P; ++g)
-          if (load[g] < load[best]) best = g;
-        assign_reuse[i] = best;
-        load[best] += hp.items[4 * i + 3] - hp.items[4 * i + 2];
-      }
+      LoadHeap heap(std::move(load));
+      for (int64_t i = 0; i < n_items; ++i)
+        if (assign_reuse[i] < 0) assign_reuse[i] = heap.place(hp.items[4 * i + 3] - hp.items[4 * i + 2]);
+      load = std::move(heap.load);
       hp.rho_reuse = dbsp_rho(load.data(), 1, P);
       hp.reused = hp.rho_reuse <= reuse_threshold;
     }
@@ -638,21 +735,13 @@ int dbsp_plan_place(const dbsp_place_opts& opts, const dbsp_host_plan* prev, dou
       // query blocks -- and the same greedy runs one level up: heaviest chunk first, each to the
       // least-loaded group that has no chunk yet in this round.
       const int32_t G = locality_groups > 1 ? locality_groups : 1, per = P / G;
-      const int64_t wmax = (int64_t)nK + item_overhead;
       std::vector<int64_t> load(P, 0), chunk_w(G), group_load(G);
       std::vector<int32_t> chunk_order(G);
       std::vector<char> taken(G);
       std::vector<int32_t> wseq(n_items);            // weights in sequence order
       for (int64_t t = 0; t < n_items; ++t) wseq[t] = (int32_t)weight(seq[t]);
-      // Both orders inside a chunk -- items by weight, descending and stable; a group's partitions
-      // by accumulated load, ascending and stable -- are orders of distinct integers
-      // (key << 20 | position) and come from plain integer sorts.  The keys hold a position in 20
-      // bits and a weight or a load above it; inputs too large for that take the comparison sorts.
-      int64_t cost_max = 1;
-      if (partition_cost) cost_max = *std::max_element(partition_cost, partition_cost + P);
-      const bool packed_keys = per < (1 << 20) && wmax < ((int64_t)1 << 40) &&
-                               (hp.nnz + (int64_t)item_overhead * n_items) < (((int64_t)1 << 43) / cost_max);
-      std::vector<uint64_t> item_key(per), part_key(per);
+      SmallOrder in_order;                           // both orders inside a chunk are stable
+      std::vector<int64_t> val(per);
       std::vector<int32_t> item_pos(per), part_rank(per);   // part_rank: positions k of a group's partitions (partition = g + k G), by load
       auto insertion_sort = [](auto* first, int64_t n, auto less) {
         for (int64_t a = 1; a < n; ++a) {
@@ -701,19 +790,10 @@ int dbsp_plan_place(const dbsp_place_opts& opts, const dbsp_host_plan* prev, dou
           // k-th heaviest item (stable) to the group's k-th least-loaded partition (stable)
           const int64_t n_c = c1 - c0;
           int32_t* rank = part_rank.data();
-          if (packed_keys) {
-            for (int64_t t = 0; t < n_c; ++t) item_key[t] = ((uint64_t)(wmax - wseq[c0 + t]) << 20) | (uint64_t)t;
-            std::sort(item_key.begin(), item_key.begin() + n_c);
-            for (int64_t t = 0; t < n_c; ++t) item_pos[t] = (int32_t)(item_key[t] & 0xFFFFF);
-            for (int32_t k = 0; k < per; ++k) part_key[k] = ((uint64_t)load[gamma + k * G] << 20) | (uint64_t)k;
-            std::sort(part_key.begin(), part_key.end());
-            for (int32_t k = 0; k < per; ++k) rank[k] = (int32_t)(part_key[k] & 0xFFFFF);
-          } else {
-            for (int64_t t = 0; t < n_c; ++t) item_pos[t] = (int32_t)t;
-            std::stable_sort(item_pos.begin(), item_pos.begin() + n_c, [&](int32_t a, int32_t b) { return wseq[c0 + a] > wseq[c0 + b]; });
-            for (int32_t k = 0; k < per; ++k) rank[k] = k;
-            std::stable_sort(rank, rank + per, [&](int32_t a, int32_t b) { return load[gamma + a * G] < load[gamma + b * G]; });
-          }
+          for (int64_t t = 0; t < n_c; ++t) val[t] = -(int64_t)wseq[c0 + t];
+          in_order(val.data(), (int32_t)n_c, item_pos.data());
+          for (int32_t k = 0; k < per; ++k) val[k] = load[gamma + k * G];
+          in_order(val.data(), per, rank);
           for (int64_t k = 0; k < n_c; ++k) {
             const int32_t it = seq[c0 + item_pos[k]];
             const int32_t pt = gamma + rank[k] * G;
