@@ -349,7 +349,7 @@ int dbsp_plan_busy(const dbsp_plan* plan, uint64_t* busy_ticks, uint32_t* hw_id,
 
 /* dbsp_plan_destroy: the plan is gone for the caller; its device and pinned buffers are recycled once the
  * last sparse_attn_fwd enqueued with it and its upload have finished, which the call does not wait for
- * (unless more than 16 destroyed plans are still in use by the GPU: then for the oldest).  NULL is ignored. */
+ * (unless the GPU still uses three others that the calling thread has destroyed: then for the oldest).  NULL is ignored. */
 void dbsp_plan_destroy(dbsp_plan* plan);
 
 const char* dbsp_last_error(void);

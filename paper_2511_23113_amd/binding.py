@@ -284,7 +284,7 @@ def sparse_attn_fwd(plan: Plan, q, k, v, o=None, lse=None, softmax_scale: float 
     lib = load_library()
     entry = lib.sparse_attn_fwd_static if static_scratch else lib.sparse_attn_fwd
     rc = entry(plan.handle, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None if lse is None else lse.data_ptr(),
-               B, Nq, Nk, d, softmax_scale, stream)
+               B, Nq, Nk, d, float(softmax_scale), stream)
     if rc:
         _check(rc)
     return o, lse

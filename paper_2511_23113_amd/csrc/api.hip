@@ -1,4 +1,5 @@
 // C ABI of libdbsp: argument checks, plan life cycle, device upload, kernel launches.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -9,6 +10,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "dbsp.h"
@@ -47,8 +49,8 @@ constexpr int kMaxWaves = 8;     // waves of the largest workgroup: a split row 
 // recycled instead of going through hipMalloc / hipFree (which synchronises the device) each time.
 // Entries remember the device that was current when they were allocated and only go back to it.
 // The buffers of a destroyed plan that the GPU still uses are retired together with the plan's events
-// and join the pools once those have passed: destroying a plan does not wait, unless kMaxRetired plans are
-// retired already.  So a caller that plans every step stays that many steps ahead of the GPU, which hides the
+// and join the pools once those have passed: destroying a plan does not wait, unless the calling thread has
+// kMaxRetired retired plans on the device already: then for the oldest of these.  So a caller that plans every step stays that many steps ahead of the GPU, which hides the
 // planning, and the pools can hold all the buffers in flight; a host further ahead would gain nothing and
 // allocate (40 heads, 256 x 256 blocks, 5 to 60 % of them active: 350 us more per step of 5840 with 16 let ahead and pools of 8).
 struct BufferPool {
@@ -57,6 +59,7 @@ struct BufferPool {
   std::vector<Entry> free_list;
 };
 struct Retired {
+  std::thread::id by;
   hipEvent_t events[2];            // last use, upload; null = nothing to wait for
   BufferPool::Entry dev, pin[2];
 };
@@ -82,23 +85,31 @@ void pool_put(BufferPool& pool, const BufferPool::Entry& e, std::vector<void*>& 
   }
 }
 
-// g_mu is held.  Recycles what the GPU is done with; with `wait_oldest` the oldest retired plan is waited for.
-void reap(Surplus& surplus, bool wait_oldest) {
+// Asking for an event's state is no part of any capture: it neither fails nor spoils one that is under way.
+struct OutsideCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// g_mu is held.
+void recycle(const Retired& r, Surplus& surplus) {
+  for (hipEvent_t ev : r.events)
+    if (ev) (void)hipEventDestroy(ev);
+  pool_put(g_dev_pool, r.dev, surplus.dev);
+  for (const BufferPool::Entry& e : r.pin) pool_put(g_pin_pool, e, surplus.pin);
+}
+
+// g_mu is held.  Recycles what the GPU is done with.
+void reap(Surplus& surplus) {
+  if (g_retired.empty()) return;
+  OutsideCapture relaxed;
   for (size_t i = 0; i < g_retired.size();) {
-    Retired& r = g_retired[i];
     bool done = true;
-    for (hipEvent_t ev : r.events) {
-      if (!ev) continue;
-      if (wait_oldest && i == 0) (void)hipEventSynchronize(ev);
-      else done = done && hipEventQuery(ev) != hipErrorNotReady;
-    }
+    for (hipEvent_t ev : g_retired[i].events) done = done && (!ev || hipEventQuery(ev) != hipErrorNotReady);
     if (!done) { ++i; continue; }
-    for (hipEvent_t ev : r.events)
-      if (ev) (void)hipEventDestroy(ev);
-    pool_put(g_dev_pool, r.dev, surplus.dev);
-    for (const BufferPool::Entry& e : r.pin) pool_put(g_pin_pool, e, surplus.pin);
+    recycle(g_retired[i], surplus);
     g_retired.erase(g_retired.begin() + i);
-    wait_oldest = false;
   }
   (void)hipGetLastError();         // a query's "not ready" is no error
 }
@@ -113,7 +124,7 @@ hipError_t pool_get(BufferPool& pool, bool pinned, int device, size_t bytes, voi
   bool found = false;
   {
     std::lock_guard<std::mutex> lk(g_mu);
-    if (!g_retired.empty()) reap(surplus, false);
+    reap(surplus);
     int best = -1;
     for (size_t i = 0; i < pool.free_list.size(); ++i)
       if (pool.free_list[i].device == device && pool.free_list[i].bytes >= bytes &&
@@ -148,20 +159,35 @@ hipError_t upload_stream(int device, hipStream_t* out) {
 
 // Hands the plan's buffers back, at once or, if the GPU may still use them, once its events have passed.
 void free_device(dbsp_device_plan& d) {
-  Retired r = {{nullptr, nullptr}, {d.blob, d.blob_bytes, d.device}, {{d.staging, d.staging_bytes, d.device}, {d.staging_kv, d.staging_kv_bytes, d.device}}};
+  Retired r = {std::this_thread::get_id(), {nullptr, nullptr}, {d.blob, d.blob_bytes, d.device}, {{d.staging, d.staging_bytes, d.device}, {d.staging_kv, d.staging_kv_bytes, d.device}}};
   if (d.last_use) {
     if (d.used) r.events[0] = static_cast<hipEvent_t>(d.last_use);
     else (void)hipEventDestroy(static_cast<hipEvent_t>(d.last_use));
   }
   if (d.uploaded) {
-    if (d.sent == dbsp_device_plan::kByCopy) r.events[1] = static_cast<hipEvent_t>(d.uploaded);
+    if (d.sent) r.events[1] = static_cast<hipEvent_t>(d.uploaded);
     else (void)hipEventDestroy(static_cast<hipEvent_t>(d.uploaded));
   }
   Surplus surplus;
+  bool wait = false;
   {
     std::lock_guard<std::mutex> lk(g_mu);
     g_retired.push_back(r);
-    reap(surplus, g_retired.size() > kMaxRetired);
+    reap(surplus);
+    size_t mine = 0, oldest = 0;
+    for (size_t i = g_retired.size(); i-- > 0;)
+      if (g_retired[i].by == r.by && g_retired[i].dev.device == d.device) { ++mine; oldest = i; }
+    if (mine > kMaxRetired) {
+      r = g_retired[oldest];       // waited for without the lock: others go on planning
+      g_retired.erase(g_retired.begin() + oldest);
+      wait = true;
+    }
+  }
+  if (wait) {
+    for (hipEvent_t ev : r.events)
+      if (ev) (void)hipEventSynchronize(ev);
+    std::lock_guard<std::mutex> lk(g_mu);
+    recycle(r, surplus);
   }
   release(surplus);
   (void)hipGetLastError();
@@ -187,7 +213,7 @@ int send_upload(dbsp_device_plan& dv) {
   DBSP_HIP(hipMemcpyAsync(dv.blob, dv.staging, dv.up_bytes, hipMemcpyHostToDevice, us));
   if (dv.kv_bytes) DBSP_HIP(hipMemcpyAsync(dv.blob + dv.up_bytes, dv.staging_kv, dv.kv_bytes, hipMemcpyHostToDevice, us));
   DBSP_HIP(hipEventRecord(static_cast<hipEvent_t>(dv.uploaded), us));
-  dv.sent = dbsp_device_plan::kByCopy;
+  dv.sent = true;
   return DBSP_OK;
 }
 
@@ -204,11 +230,10 @@ __global__ __launch_bounds__(256) void dbsp_fetch_kernel(uint4* __restrict__ dst
 int fetch_in_stream(dbsp_device_plan& dv, hipStream_t st) {
   // the index lists' last 16 bytes may reach into the slack both buffers have behind them
   const uint32_t na = (uint32_t)(dv.up_bytes / 16), n = na + (uint32_t)((dv.kv_bytes + 15) / 16);
-  hipLaunchKernelGGL(dbsp_fetch_kernel, dim3((n + 255) / 256), dim3(256), 0, st, reinterpret_cast<uint4*>(dv.blob),
-                     static_cast<const uint4*>(dv.staging), na, static_cast<const uint4*>(dv.staging_kv), n);
+  hipExtLaunchKernelGGL(dbsp_fetch_kernel, dim3((n + 255) / 256), dim3(256), 0, st, nullptr, static_cast<hipEvent_t>(dv.uploaded), 0,
+                        reinterpret_cast<uint4*>(dv.blob), static_cast<const uint4*>(dv.staging), na, static_cast<const uint4*>(dv.staging_kv), n);
   DBSP_HIP(hipGetLastError());
-  dv.sent = dbsp_device_plan::kInStream;
-  dv.upload_stream = st;
+  dv.sent = true;
   return DBSP_OK;
 }
 int upload(dbsp_plan* plan) {
@@ -569,23 +594,26 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();
   const bool capture = capturing != hipStreamCaptureStatusNone;
   if (!dm.upload_done) {
-    if (dm.sent == dbsp_device_plan::kNotSent) {
-      const int rc = capture ? send_upload(dm) : fetch_in_stream(dm, st);
+    bool in_order = false;         // the fetch is the command before this launch
+    if (!dm.sent) {
+      const bool fetch = !capture && dm.up_bytes + dm.kv_bytes <= kInStreamBytes;
+      const int rc = fetch ? fetch_in_stream(dm, st) : send_upload(dm);
       if (rc != DBSP_OK) return rc;
+      in_order = fetch;
     }
-    // fetched in stream order: the stream itself waits, another one for the launch behind the fetch
-    hipEvent_t arrived = static_cast<hipEvent_t>(dm.sent == dbsp_device_plan::kByCopy ? dm.uploaded : dm.last_use);
-    if (dm.sent == dbsp_device_plan::kByCopy || (dm.upload_stream != stream && dm.used)) {
-      if (!capture && hipEventQuery(arrived) == hipSuccess) {
-        dm.upload_done = true;
-      } else {
+    if (!in_order) {
+      hipEvent_t arrived = static_cast<hipEvent_t>(dm.uploaded);
+      if (!capture) {
+        OutsideCapture relaxed;    // another stream's
+        dm.upload_done = hipEventQuery(arrived) == hipSuccess;
+      }
+      if (!dm.upload_done) {
         (void)hipGetLastError();
         DBSP_HIP(hipStreamWaitEvent(st, arrived, 0));
       }
     }
   }
   const hipError_t e = dbsp_launch_fwd(p, hp.block, d, hp.pair, grid, st, capture ? nullptr : static_cast<hipEvent_t>(dm.last_use));
-  if (e != hipSuccess && dm.sent == dbsp_device_plan::kInStream) (void)hipStreamSynchronize(st);      // no event vouches for the fetch
   if (e != hipSuccess) return fail_hip(e, (std::string(who) + " launch").c_str());
   if (capture) DBSP_HIP(hipEventRecord(static_cast<hipEvent_t>(dm.last_use), st));
   dm.last_grid = grid;
@@ -687,7 +715,7 @@ int dbsp_plan_tail_takes(const dbsp_plan* plan, uint32_t* takes, void* stream) {
   if (!plan->dev.resident) return fail(DBSP_EINVAL, "dbsp_plan_tail_takes: the plan was built host-only");
   DBSP_HIP(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
   const size_t n = plan->host.tail_items.size();
-  if (plan->dev.sent == dbsp_device_plan::kNotSent) std::fill(takes, takes + n, 0);      // no launch yet
+  if (!plan->dev.sent) std::fill(takes, takes + n, 0);      // no launch yet
   else if (n) DBSP_HIP(hipMemcpy(takes, plan->dev.queue + 1, n * sizeof(uint32_t), hipMemcpyDeviceToHost));
   return DBSP_OK;
 }

@@ -54,12 +54,11 @@ struct dbsp_device_plan {
   void* staging_kv = nullptr;     // pinned host memory the index lists are compacted into (the plan's kv_idx)
   size_t staging_kv_bytes = 0;
   size_t up_bytes = 0, kv_bytes = 0;   // what is sent: the small arrays and zeroed counters, then the index lists, to the front of blob
-  // How the plan gets to the device: not yet; by copies on the library's upload stream (`uploaded` tells when);
-  // or by a kernel in front of the first forward launch, on that launch's stream
-  enum { kNotSent, kByCopy, kInStream } sent = kNotSent;
+  // A plan gets to the device by copies on the library's upload stream, or by a kernel in front of its first
+  // forward launch, on that launch's stream
+  bool sent = false;
   bool upload_done = false;       // known to have arrived
-  void* upload_stream = nullptr;  // hipStream_t of kInStream
-  void* uploaded = nullptr;       // hipEvent_t: the copies of kByCopy have finished
+  void* uploaded = nullptr;       // hipEvent_t: what was sent has arrived
   void* last_use = nullptr;       // hipEvent_t: the last forward launch has finished
   bool used = false;
   int32_t last_grid = 0;          // workgroups of the last forward launch

@@ -1,0 +1,127 @@
+"""Plans on their way to the device, on the GPU: several streams, graph captures, plans destroyed while in use.
+
+A plan of up to 64 KiB is fetched by a kernel in front of its first launch, a larger one copied on the
+library's own stream; H picks either.  Results of a plan are bitwise the same from launch to launch.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_23113_amd as dbsp
+
+pytestmark = pytest.mark.gpu
+
+SMALL, LARGE = 2, 96          # heads: about 12 KiB and 500 KiB of plan
+
+
+def _case(H, seed=0, n=16):
+    rng = np.random.default_rng(seed)
+    mask = (rng.random((H, n, n)) < 0.4).astype(np.uint8)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    qkv = [torch.randn((1, H, n * 64, 64), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3)]
+    return mask, qkv
+
+
+def _plan(mask):
+    return dbsp.plan_sparse_attn(mask, 64, num_partitions=64, mode=dbsp.MODE_ROUNDS, dynamic_tail=40)
+
+
+def _expected(mask, qkv):
+    plan = _plan(mask)
+    o, lse = dbsp.sparse_attn_fwd(plan, *qkv)
+    torch.cuda.synchronize()
+    plan.close()
+    return o, lse
+
+
+def _same(got, want):
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("H", [SMALL, LARGE])
+@pytest.mark.parametrize("eager_first", [True, False])
+def test_captures_of_one_plan(H, eager_first):
+    mask, qkv = _case(H)
+    want = _expected(mask, qkv)
+    plan = _plan(mask)
+    if eager_first:
+        _same(dbsp.sparse_attn_fwd(plan, *qkv), want)
+    graphs = []
+    for _ in range(2):                   # the second capture follows a launch that the first one recorded
+        out = torch.empty_like(want[0]), torch.empty_like(want[1])
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            dbsp.sparse_attn_fwd(plan, *qkv, o=out[0], lse=out[1])
+        graphs.append((g, out))
+    for _ in range(3):
+        for g, out in graphs:
+            out[0].zero_()
+            out[1].zero_()
+            g.replay()
+            _same(out, want)
+        _same(dbsp.sparse_attn_fwd(plan, *qkv), want)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        got = dbsp.sparse_attn_fwd(plan, *qkv)
+    _same(got, want)
+    plan.close()
+
+
+@pytest.mark.parametrize("H", [SMALL, LARGE])
+def test_second_stream_waits_for_the_plan(H):
+    mask, qkv = _case(H, 1)
+    want = _expected(mask, qkv)
+    for _ in range(4):
+        plan, side = _plan(mask), torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        first = dbsp.sparse_attn_fwd(plan, *qkv)
+        torch.cuda.current_stream().synchronize()      # one plan's launches must not overlap
+        with torch.cuda.stream(side):
+            second = dbsp.sparse_attn_fwd(plan, *qkv)
+        _same(first, want)
+        _same(second, want)
+        plan.close()
+
+
+@pytest.mark.parametrize("H", [SMALL, LARGE])
+def test_plans_destroyed_while_in_use(H):
+    """More plans than may wait for the GPU, each destroyed right behind its launch, on two streams in turn;
+    a buffer that went back too early would be overwritten by the next plan."""
+    cases = [_case(H, seed) for seed in range(2)]
+    wants = [_expected(*c) for c in cases]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    got = []
+    for i in range(24):
+        mask, qkv = cases[i % 2]
+        with torch.cuda.stream(side if i % 3 == 0 else torch.cuda.current_stream()):
+            plan = _plan(mask)
+            got.append(dbsp.sparse_attn_fwd(plan, *qkv))
+            plan.close()
+    torch.cuda.synchronize()
+    for i, g in enumerate(got):
+        _same(g, wants[i % 2])
+
+
+def test_planning_inside_a_capture_beside_retired_plans():
+    """Planning asks whether earlier plans' launches have ended: that must not spoil a capture."""
+    mask, qkv = _case(SMALL, 3)
+    want = _expected(mask, qkv)
+    for _ in range(6):                    # the pools hold buffers from here on, and plans wait for the GPU
+        plan = _plan(mask)
+        dbsp.sparse_attn_fwd(plan, *qkv)
+        plan.close()
+    out = torch.empty_like(want[0]), torch.empty_like(want[1])
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        kept = _plan(mask)
+        dbsp.sparse_attn_fwd(kept, *qkv, o=out[0], lse=out[1])
+    for _ in range(3):
+        out[0].zero_()
+        g.replay()
+        _same(out, want)
+        _same(dbsp.sparse_attn_fwd(kept, *qkv), want)
+    kept.close()
