@@ -191,7 +191,8 @@ int plan_sparse_attn_reuse(const dbsp_plan* previous, const uint8_t* mask_host, 
  * the mask has no batch axis: every batch entry uses the same per-head mask.
  * softmax_scale <= 0 selects 1 / sqrt(d).  A query row with no active block gets O = 0, LSE = -inf.
  * stream: a hipStream_t (NULL = default stream).  The call only enqueues work: one persistent
- * kernel with one workgroup per partition (fewer where a plan has fewer items than partitions).  It neither allocates nor synchronises with the host.  bf16 inputs, f32 accumulation.
+ * kernel with one workgroup per partition (fewer where a plan has fewer items than partitions), and where
+ * rows were split mostly a small one behind it that merges their chunks.  It neither allocates nor synchronises with the host.  bf16 inputs, f32 accumulation.
  * Errors: DBSP_EINVAL (also: B above the plan's max_batch when rows are split), DBSP_ESHAPE, DBSP_EHIP.
  */
 int sparse_attn_fwd(const dbsp_plan* plan, const void* q, const void* k, const void* v, void* o,

@@ -263,8 +263,9 @@ int upload(dbsp_plan* plan) {
   dv.used_parts = 0;
   for (int32_t g = 0; g < hp.P; ++g)
     if (hp.part_ptr[g + 1] > hp.part_ptr[g]) dv.used_parts = g + 1;
-  const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &hp.part_ptr, &sched};
-  constexpr int NA = 3;
+  for (size_t r = 0; r < n_split; ++r) dv.max_chunks = std::max(dv.max_chunks, hp.split_rows[4 * r + 2]);
+  const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &hp.part_ptr, &sched, &hp.split_rows};
+  constexpr int NA = 4;
   size_t off[NA + 1];   // in int32 units, each array 16-byte aligned
   off[0] = 0;
   for (int i = 0; i < NA; ++i) off[i + 1] = off[i] + ((arrays[i]->size() + 3) & ~size_t(3));
@@ -309,6 +310,7 @@ int upload(dbsp_plan* plan) {
   dv.empty_rows = ints + off[0];
   dv.part_ptr = ints + off[1];
   dv.sched = ints + off[2];
+  dv.split_rows = ints + off[3];
   dv.queue = reinterpret_cast<uint32_t*>(dv.blob + queue_off);
   dv.split_cnt = reinterpret_cast<uint32_t*>(dv.blob + cnt_off);
   dv.kv_idx = reinterpret_cast<const int32_t*>(dv.blob + kv_off);
@@ -575,6 +577,10 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   p.part_o = part_o;
   p.part_lse = part_lse;
   p.split_cnt = split_cnt;
+  p.split_rows = dv.split_rows;
+  p.max_chunks = dv.max_chunks;
+  p.one_each = (int64_t)B * hp.n_items() <= hp.P ? 1 : 0;
+  p.merge_later = 0;
   p.busy = dv.busy;
   p.hw_id = dv.hw_id;
   p.B = B; p.H = hp.H; p.nQ = hp.nQ; p.nK = hp.nK;

@@ -98,6 +98,12 @@ struct Cfg {
   static_assert(NQ * XCH <= RING - 2 * SL, "the outboxes must leave the first two K slices alone");
   static_assert(U == 1 || (U == 2 && NQ > 1), "what the step sequence assumes");
   static_assert(NC == 2 || (NC == 4 && TPW == 1), "tile ownership at the end of an item");
+  // tile k of key group cc: d-tile and query tile
+  static __device__ constexpr int tile_dt(int cc, int k) { return NC == 2 ? cc * (DT / 2) + k % (DT / 2) : cc % DT; }
+  static __device__ constexpr int tile_qt(int cc, int k) { return NC == 2 ? k / (DT / 2) : cc / DT; }
+  // does key group cc store the LSE of the query tiles it finalises, and with which of its tiles?
+  static __device__ constexpr bool has_lse(int cc) { return NC == 2 ? cc == 0 : cc % DT == 0; }
+  static __device__ constexpr bool lse_tile(int k) { return k % (TPW > 1 ? TPW / 2 : 1) == 0; }
 };
 
 template <int N>
@@ -116,6 +122,93 @@ __device__ __forceinline__ void store_shared(float* to, float a, float b) {
 __device__ __forceinline__ f32x2 load_shared(const float* from) {
   const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(from), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return f32x2{__builtin_bit_cast(float, (uint32_t)v), __builtin_bit_cast(float, (uint32_t)(v >> 32))};
+}
+
+// Stores one accumulator tile: lane (r, g) holds, of query r, d-values 8 e4 + 4 g .. + 3 in res[e4].  The
+// lane pair swaps halves so that each lane stores 16 bytes side by side.
+template <int D>
+__device__ __forceinline__ void store_tile(uint16_t* o, const f32x4 (&res)[4], int64_t tok, int dt, int g) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    uint32_t a0 = pack_bf16x2(res[2 * i].x, res[2 * i].y), a1 = pack_bf16x2(res[2 * i].z, res[2 * i].w);
+    uint32_t b0 = pack_bf16x2(res[2 * i + 1].x, res[2 * i + 1].y), b1 = pack_bf16x2(res[2 * i + 1].z, res[2 * i + 1].w);
+    swap_upper_lower(a0, b0);
+    swap_upper_lower(a1, b1);
+    *reinterpret_cast<u32x4*>(o + tok * D + 32 * dt + 16 * i + 8 * g) = u32x4{a0, a1, b0, b1};
+  }
+}
+
+// Where lane l of wave w keeps two floats (and two more 128 on) of tile k of a chunk.
+template <class C>
+__device__ __forceinline__ float* partial_of(float* part_o, int64_t slot_no, int w, int k, int e4, int l) {
+  return part_o + (slot_no * C::NW + w) * (C::TPW * 1024) + (k * 4 + e4) * 256 + l * 2;
+}
+
+// Merges tile k of wave w's share of a split row's chunks, G of them fetched at once, and stores it: token
+// tok, d-tile dt.  qloc: this lane's query inside the row.
+template <class C, int D, int G>
+__device__ __forceinline__ void merge_tile(const dbsp_fwd_params& p, int64_t first, int n_chunks, int w, int k, int l, int qloc,
+                                           int64_t tok, int dt, bool with_lse, bool q_there) {
+  float m = -INFINITY, tot = 0.f;
+  f32x4 acc[4];
+#pragma unroll
+  for (int e4 = 0; e4 < 4; ++e4) acc[e4] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int x0 = 0; x0 < n_chunks; x0 += G) {
+    float ls[G];
+    f32x2 lo[G][4], hi[G][4];
+#pragma unroll
+    for (int y = 0; y < G; ++y) {
+      const int64_t sl = first + min(x0 + y, n_chunks - 1);
+      ls[y] = __hip_atomic_load(p.part_lse + sl * C::QROWS + qloc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        lo[y][e4] = load_shared(partial_of<C>(p.part_o, sl, w, k, e4, l));
+        hi[y][e4] = load_shared(partial_of<C>(p.part_o, sl, w, k, e4, l) + 128);
+      }
+    }
+    float mn = m;
+#pragma unroll
+    for (int y = 0; y < G; ++y) mn = fmaxf(mn, ls[y]);
+    const float mref = (mn == -INFINITY) ? 0.f : mn;       // nothing for this query yet: weights of 0, not inf - inf
+    const float old = __expf(m - mref);
+    m = mn;
+    tot *= old;
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) acc[e4] *= old;
+#pragma unroll
+    for (int y = 0; y < G; ++y) {
+      const float wgt = (x0 + y < n_chunks) ? __expf(ls[y] - mref) : 0.f;
+      tot += wgt;
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        acc[e4].x += wgt * lo[y][e4].x;  acc[e4].y += wgt * lo[y][e4].y;
+        acc[e4].z += wgt * hi[y][e4].x;  acc[e4].w += wgt * hi[y][e4].y;
+      }
+    }
+  }
+  const bool none = !(tot > 0.f);          // no chunk has anything for this query: O = 0, LSE = -inf
+  const float inv = none ? 0.f : 1.0f / tot;
+#pragma unroll
+  for (int e4 = 0; e4 < 4; ++e4) acc[e4] *= inv;
+  if (!q_there) return;
+  store_tile<D>(p.o, acc, tok, dt, l >> 5);
+  if (with_lse && l < 32 && p.lse != nullptr) p.lse[tok] = none ? -INFINITY : m + __logf(tot);
+}
+
+// Merges all split rows behind the kernel that made their chunks: one wave for every tile (x: split row and
+// batch entry, y: tile of the wave's share).  Bound by reading the partial results once: 9925 chunks of 64 KiB
+// are 650 MB.  Four chunks in flight a wave, 20 thousand waves.
+template <int D, int NQ, int NC, int U, bool PAIR>
+__global__ __launch_bounds__(64 * NQ * NC) void dbsp_merge_kernel(const dbsp_fwd_params p) {
+  using C = Cfg<D, NQ, NC, U>;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = threadIdx.x & 63, r = l & 31;
+  const int wa = w / C::NC, wc = w % C::NC, k = blockIdx.y;
+  const int bb = blockIdx.x / p.n_split;
+  const int32_t* row = p.split_rows + 4 * (blockIdx.x % p.n_split);       // row, first slot, chunks
+  const int64_t bh = (int64_t)bb * p.H + row[0] / p.nQ;
+  const int first_q = (row[0] % p.nQ) * C::QROWS + 64 * wa, qt = C::tile_qt(wc, k);
+  merge_tile<C, D, 4>(p, (int64_t)bb * p.n_slots + row[1], row[2], w, k, l, 64 * wa + 32 * qt + r, bh * p.Nq + first_q + 32 * qt + r,
+                      C::tile_dt(wc, k), C::has_lse(wc) && C::lse_tile(k), !PAIR || first_q < p.Nq);
 }
 
 template <int D, int NQ, int NC, int U, bool PAIR>
@@ -275,11 +368,9 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   auto k_of = [&](int64_t bh) { return reinterpret_cast<const unsigned char*>(p.k + bh * p.Nk * D) + src_off; };
   auto v_of = [&](int64_t bh) { return reinterpret_cast<const unsigned char*>(p.v + bh * p.Nk * D) + src_off; };
 
-  // tile k of key group cc: d-tile and query tile
-  auto tile_dt = [](int cc, int k) { return C::NC == 2 ? cc * (C::DT / 2) + k % (C::DT / 2) : cc % C::DT; };
-  auto tile_qt = [](int cc, int k) { return C::NC == 2 ? k / (C::DT / 2) : cc / C::DT; };
-  // does key group cc store the LSE of the query tiles it finalises?
-  auto has_lse = [](int cc) { return C::NC == 2 ? cc == 0 : cc % C::DT == 0; };
+  auto tile_dt = [](int cc, int k) { return C::tile_dt(cc, k); };
+  auto tile_qt = [](int cc, int k) { return C::tile_qt(cc, k); };
+  auto has_lse = [](int cc) { return C::has_lse(cc); };
   auto by_key_group = [&](auto&& f) {
     if constexpr (C::NC == 4) {
       if (wc == 2) return f(std::integral_constant<int, 2>{});
@@ -288,30 +379,18 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     if (wc == 0) f(std::integral_constant<int, 0>{});
     else f(std::integral_constant<int, 1>{});
   };
-  // Stores one accumulator tile: lane (r, g) holds, of query r, d-values 8 e4 + 4 g .. + 3 in res[e4].  The
-  // lane pair swaps halves so that each lane stores 16 bytes side by side.
-  auto store_tile = [&](const f32x4 (&res)[4], int64_t tok, int dt) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      uint32_t a0 = pack_bf16x2(res[2 * i].x, res[2 * i].y), a1 = pack_bf16x2(res[2 * i].z, res[2 * i].w);
-      uint32_t b0 = pack_bf16x2(res[2 * i + 1].x, res[2 * i + 1].y), b1 = pack_bf16x2(res[2 * i + 1].z, res[2 * i + 1].w);
-      swap_upper_lower(a0, b0);
-      swap_upper_lower(a1, b1);
-      *reinterpret_cast<u32x4*>(p.o + tok * D + 32 * dt + 16 * i + 8 * g) = u32x4{a0, a1, b0, b1};
-    }
-  };
+  auto store_tile = [&](const f32x4 (&res)[4], int64_t tok, int dt) { ::store_tile<D>(p.o, res, tok, dt, g); };
 
   // Split rows.  A chunk's partial result (f32, the accumulator tiles as the lanes hold them) goes to memory,
-  // and the wave that stores the last chunk's share of a row merges that share (log-sum-exp identity, the
-  // same one that combines per-chunk partial attention in Ring Attention):
+  // and is merged (log-sum-exp identity, the same one that combines per-chunk partial attention in Ring
+  // Attention):
   //   LSE = log sum_k exp(LSE_k),  O = sum_k exp(LSE_k - LSE) O_k.
-  // Waves count for themselves (they finalise the same tiles in every chunk), so no barrier is needed, and
-  // the count is taken during the next item, when the stores have long reached memory: a second launch
-  // that merges cost 8 - 14 us, waiting for stores and count at the end of each item 5 us per item.
+  // by dbsp_merge_kernel, or in place (p.merge_later is 0, see launch_fwd) by the wave that stores the last
+  // chunk's share of a row.  Waves count for themselves (they finalise the same tiles in every chunk), so no
+  // barrier is needed, and the count is taken during the next item, or behind the last one, when the stores
+  // have reached memory.
   // Pair rows: a query block may have no active block in some or all chunks (LSE_k = -inf).
-  auto partial = [&](int64_t slot_no, int k, int e4) {
-    return p.part_o + (slot_no * C::NW + w) * (C::TPW * 1024) + (k * 4 + e4) * 256 + l * 2;
-  };
+  auto partial = [&](int64_t slot_no, int k, int e4) { return partial_of<C>(p.part_o, slot_no, w, k, e4, l); };
   bool pend_chunk = false;
   int4 pa = {}, pb = {};         // the item whose count is due
   int pbb = 0;
@@ -331,55 +410,10 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     const bool q_there = !PAIR || pa.y * C::QROWS + 64 * wa < p.Nq;
     by_key_group([&](auto c_tag) {
       constexpr int WC = decltype(c_tag)::value;
-      constexpr int G = 2;                       // chunks fetched at once
 #pragma unroll
       for (int k = 0; k < C::TPW; ++k) {
-        const int qt = tile_qt(WC, k), qloc = 64 * wa + 32 * qt + r;
-        float m = -INFINITY, tot = 0.f;
-        f32x4 acc[4];
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) acc[e4] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int x0 = 0; x0 < n_chunks; x0 += G) {
-          float ls[G];
-          f32x2 lo[G][4], hi[G][4];
-#pragma unroll
-          for (int y = 0; y < G; ++y) {
-            const int64_t sl = first + min(x0 + y, n_chunks - 1);
-            ls[y] = __hip_atomic_load(p.part_lse + sl * C::QROWS + qloc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-              lo[y][e4] = load_shared(partial(sl, k, e4));
-              hi[y][e4] = load_shared(partial(sl, k, e4) + 128);
-            }
-          }
-          float mn = m;
-#pragma unroll
-          for (int y = 0; y < G; ++y) mn = fmaxf(mn, ls[y]);
-          const float mref = (mn == -INFINITY) ? 0.f : mn;       // nothing for this query yet: weights of 0, not inf - inf
-          const float old = __expf(m - mref);
-          m = mn;
-          tot *= old;
-#pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) acc[e4] *= old;
-#pragma unroll
-          for (int y = 0; y < G; ++y) {
-            const float wgt = (x0 + y < n_chunks) ? __expf(ls[y] - mref) : 0.f;
-            tot += wgt;
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-              acc[e4].x += wgt * lo[y][e4].x;  acc[e4].y += wgt * lo[y][e4].y;
-              acc[e4].z += wgt * hi[y][e4].x;  acc[e4].w += wgt * hi[y][e4].y;
-            }
-          }
-        }
-        const bool none = !(tot > 0.f);          // no chunk has anything for this query: O = 0, LSE = -inf
-        const float inv = none ? 0.f : 1.0f / tot;
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) acc[e4] *= inv;
-        if (!q_there) continue;
-        store_tile(acc, tok0 + 32 * qt, tile_dt(WC, k));
-        if (has_lse(WC) && k % (C::TPW > 1 ? C::TPW / 2 : 1) == 0 && g == 0 && p.lse != nullptr)
-          p.lse[tok0 + 32 * qt] = none ? -INFINITY : m + __logf(tot);
+        const int qt = tile_qt(WC, k);
+        merge_tile<C, D, 2>(p, first, n_chunks, w, k, l, 64 * wa + 32 * qt + r, tok0 + 32 * qt, tile_dt(WC, k), has_lse(WC) && C::lse_tile(k), q_there);
       }
     });
   };
@@ -826,7 +860,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     by_key_group(finish);
     __syncthreads();      // the exchange has been read before the next item's copies overwrite it
     if (pend_chunk) merge_if_last(counted);
-    if (slot >= 0) {
+    if (slot >= 0 && !p.merge_later) {
       pend_chunk = true;
       pa = da;
       pb = db;
@@ -859,8 +893,16 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 }
 
 template <int D, int NQ, int NC, int U, bool PAIR = false>
-hipError_t launch_fwd(const dbsp_fwd_params& p, int grid, hipStream_t stream, hipEvent_t done) {
+hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream, hipEvent_t done) {
   using C = Cfg<D, NQ, NC, U>;
+  // Who merges split rows.  In place, the wave that ends a row merges its share, TPW tiles of every chunk one
+  // after the other, while its workgroup has no other item to get on with; a launch of its own has a wave
+  // for every tile and costs 2 us behind the kernel.  us in place / by a second launch, one item at most for
+  // a workgroup: 64-token blocks at d = 64, 3 chunks 24.7 / 27.0, 7 chunks 30.5 / 31.3, 14 chunks 38.0 / 29.8;
+  // 128 at d = 128, 3 chunks 226 / 227, 4 chunks 162 / 158.  Where items queue up, who merges falls behind,
+  // ends its next rows last and merges these as well: 12 heads, 21 x 23 blocks of 128, up to 4 chunks
+  // 72 / 65; 10 heads, 128 x 256, up to 8 chunks 1068 / 771.
+  p.merge_later = p.max_chunks > 0 && (p.max_chunks * C::TPW > 14 || !p.one_each);
   // the dynamic-LDS limit is a per-device function attribute: set it once per device
   static std::atomic<uint32_t> attr_set_mask{0};
   int dev = 0;
@@ -874,10 +916,15 @@ hipError_t launch_fwd(const dbsp_fwd_params& p, int grid, hipStream_t stream, hi
     attr_set_mask.fetch_or(bit, std::memory_order_release);
   }
   const int4* sched = reinterpret_cast<const int4*>(p.sched);
-  if (done)
+  if (done && !p.merge_later)
     hipExtLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, nullptr, done, 0, p, p.kv_idx, sched, p.part_ptr);
   else
     hipLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, p, p.kv_idx, sched, p.part_ptr);
+  e = hipGetLastError();
+  if (e != hipSuccess || !p.merge_later) return e;
+  const dim3 merge_grid((uint32_t)p.B * (uint32_t)p.n_split, C::TPW);
+  if (done) hipExtLaunchKernelGGL((dbsp_merge_kernel<D, NQ, NC, U, PAIR>), merge_grid, dim3(C::NT), 0, stream, nullptr, done, 0, p);
+  else hipLaunchKernelGGL((dbsp_merge_kernel<D, NQ, NC, U, PAIR>), merge_grid, dim3(C::NT), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -19,17 +19,21 @@ struct dbsp_fwd_params {
   float* part_o;       // f32 [B][n_slots][BLK][D]
   float* part_lse;     // f32 [B][n_slots][BLK]
   uint32_t* split_cnt; // [B][n_split][waves of a workgroup] chunks of a split row that are done; zero between launches
+  const int32_t* split_rows;  // 4 x int32 per split row: row, first slot, chunks, 0
   uint64_t* busy;      // [P]
   uint32_t* hw_id;     // [P]
   int32_t B, H, nQ, nK;     // nQ: rows per head of the plan (pair mode: pairs of query blocks); nK: KV blocks
   int32_t Nq, Nk;           // tokens per head
   int32_t n_slots, n_split, n_empty, n_tail;
   int32_t n_placed;         // items the partitions' lists hold (all of them but the shared queue's)
+  int32_t max_chunks;       // the most chunks a split row has; 0: no split rows
+  int32_t one_each;         // no more items than partitions, all batch entries counted
+  int32_t merge_later;      // set by dbsp_launch_fwd: split rows are merged by a kernel of their own behind this one
   float scale;         // softmax scale
   float scale_log2;    // softmax scale * log2(e)
 };
 
-// Enqueues the persistent kernel: `grid` workgroups, enough to reach every partition that has items (all of
+// Enqueues the persistent kernel, and behind it a merge kernel for split rows where that is faster: `grid` workgroups, enough to reach every partition that has items (all of
 // them unless the plan has fewer items than partitions).
 // pair: the plan's rows are pairs of 64-token query blocks and its units pairs of 64-token KV blocks (d = 128 only).
 // done: event that the end of the kernel completes (null inside a stream capture): the launch's own completion

@@ -63,6 +63,8 @@ struct dbsp_device_plan {
   bool used = false;
   int32_t last_grid = 0;          // workgroups of the last forward launch
   const int32_t* kv_idx = nullptr;
+  const int32_t* split_rows = nullptr;   // 4 x int32 per split row: row, first slot, chunks, 0
+  int32_t max_chunks = 0;         // the most chunks a split row has
   const int32_t* empty_rows = nullptr;
   const int32_t* part_ptr = nullptr;
   const int32_t* sched = nullptr;  // 8 x int32 per item, see upload()

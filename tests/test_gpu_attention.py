@@ -341,7 +341,10 @@ def test_calibrated_placement_matches_the_oracle_and_evens_out_busy_time():
     # rates move with the load and from launch to launch, so the measured spread is only kept sane)
     load1 = tuned.array(B.PART_LOAD)
     time0, time1 = load0 * cost.astype(np.int64), load1 * cost.astype(np.int64)
-    assert time1.max() / time1.mean() <= max(time0.max() / time0.mean(), 1.02)
+    # bound: an item weighs up to 87 blocks of the 221 a partition gets, so the rounds leave 1.038 at equal
+    # costs; over 1200 random sets of costs (dies apart by 1 - 3 %, units by 0.5 - 2 %) they left 1.056 at most,
+    # and up to 2.5 % of a kind left more than the first plan's measured spread
+    assert time1.max() / time1.mean() <= max(time0.max() / time0.mean(), 1.06)
     assert 1.0 <= float(t1.max() / t1.mean()) < 1.5
     rows = [(0, h, I) for h, I in ((0, 0), (3, 17), (9, 127), (5, 64))]
     q32, k32, v32 = (synth.bf16_bits_to_f32(x) for x in (qb, kb, vb))
