@@ -328,11 +328,7 @@ int upload(dbsp_plan* plan) {
 // call on a GPU shares it.  In host code the array's name is only a handle for
 // hipGetSymbolAddress: the device address is looked up once per device and used from then on.
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;   // 32 MiB
-// Behind it the counters of the split rows, zero when the library is loaded and between launches.  A split
-// row has at least two chunks of at least 64 x 65 floats, so 32 MiB hold the chunks of at most 1008 rows.
-constexpr size_t kStaticCounters = 1024 * kMaxWaves;
-static_assert(kStaticScratchBytes / (2 * 64 * 65 * sizeof(float)) * kMaxWaves <= kStaticCounters, "counters for every split row that fits");
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticCounters * sizeof(uint32_t)];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 unsigned char* g_scratch_ptr[kMaxDevices] = {};
 
@@ -542,7 +538,6 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   const dbsp_device_plan& dv = plan->dev;
   float* part_o = dv.part_o;
   float* part_lse = dv.part_lse;
-  uint32_t* split_cnt = dv.split_cnt;
   if (static_scratch_wanted) {
     // partial outputs f32 [B][n_slots][block][d], then their LSE f32 [B][n_slots][block]
     const size_t rows = (size_t)B * hp.n_slots * hp.tile_rows();
@@ -555,7 +550,6 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
     const int rc = static_scratch(cur, &base);
     if (rc != DBSP_OK) return rc;
     part_o = reinterpret_cast<float*>(base);
-    split_cnt = reinterpret_cast<uint32_t*>(base + kStaticScratchBytes);
     part_lse = reinterpret_cast<float*>(base + lse_off);
   } else if (B > dv.max_batch && hp.n_slots > 0) {
     return bad(DBSP_EINVAL, ": B exceeds the max_batch the plan's split-row scratch was sized for");
@@ -576,10 +570,12 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   p.n_tail = (int32_t)hp.tail_items.size();
   p.part_o = part_o;
   p.part_lse = part_lse;
-  p.split_cnt = split_cnt;
+  p.split_cnt = dv.split_cnt;
   p.split_rows = dv.split_rows;
   p.max_chunks = dv.max_chunks;
-  p.one_each = (int64_t)B * hp.n_items() <= hp.P ? 1 : 0;
+  // (the counters of in-place merges are sized for max_batch, and calls that share the static scratch leave
+  // nothing behind in it: its split rows are merged by the second launch)
+  p.in_place_ok = !static_scratch_wanted && (int64_t)B * hp.n_items() <= hp.P ? 1 : 0;
   p.merge_later = 0;
   p.busy = dv.busy;
   p.hw_id = dv.hw_id;

@@ -387,27 +387,20 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   //   LSE = log sum_k exp(LSE_k),  O = sum_k exp(LSE_k - LSE) O_k.
   // by dbsp_merge_kernel, or in place (p.merge_later is 0, see launch_fwd) by the wave that stores the last
   // chunk's share of a row.  Waves count for themselves (they finalise the same tiles in every chunk), so no
-  // barrier is needed, and the count is taken during the next item, or behind the last one, when the stores
-  // have reached memory.
+  // barrier is needed.
   // Pair rows: a query block may have no active block in some or all chunks (LSE_k = -inf).
   auto partial = [&](int64_t slot_no, int k, int e4) { return partial_of<C>(p.part_o, slot_no, w, k, e4, l); };
-  bool pend_chunk = false;
-  int4 pa = {}, pb = {};         // the item whose count is due
-  int pbb = 0;
-  auto count_chunk = [&]() -> uint32_t {       // chunks of the row this wave's share is complete of (lane 0 of the result)
+  auto merge_if_last = [&]() {                 // the current item's share is stored
+    wait_copies<0>();                          // and has reached memory
+    uint32_t* count = p.split_cnt + ((int64_t)bb * p.n_split + db.y) * C::NW + w;
+    const int n_chunks = db.z;
     uint32_t before = 0;
-    if (l == 0) before = __hip_atomic_fetch_add(p.split_cnt + ((int64_t)pbb * p.n_split + pb.y) * C::NW + w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return before;
-  };
-  auto merge_if_last = [&](uint32_t before_lane0) {
-    pend_chunk = false;
-    const int n_chunks = pb.z;
-    if (__builtin_amdgcn_readfirstlane(before_lane0) != (uint32_t)n_chunks - 1) return;
-    if (l == 0)        // ready for the next launch
-      __hip_atomic_store(p.split_cnt + ((int64_t)pbb * p.n_split + pb.y) * C::NW + w, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int64_t first = (int64_t)pbb * p.n_slots + pb.w;
-    const int64_t tok0 = head_of(pa, pbb) * p.Nq + (int64_t)pa.y * C::QROWS + 64 * wa + r;
-    const bool q_there = !PAIR || pa.y * C::QROWS + 64 * wa < p.Nq;
+    if (l == 0) before = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(before) != (uint32_t)n_chunks - 1) return;
+    if (l == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // ready for the next launch
+    const int64_t first = (int64_t)bb * p.n_slots + db.w;
+    const int64_t tok0 = head_of(da, bb) * p.Nq + (int64_t)da.y * C::QROWS + 64 * wa + r;
+    const bool q_there = !PAIR || da.y * C::QROWS + 64 * wa < p.Nq;
     by_key_group([&](auto c_tag) {
       constexpr int WC = decltype(c_tag)::value;
 #pragma unroll
@@ -417,7 +410,6 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
       }
     });
   };
-
   int own_i = 0, own_b = n_own > 0 ? 0 : p.B;      // own list: position and batch entry of the current item (p.B: done)
   bool first_take = true;
   bool ready = false;            // the item's ids are there, its Q and first K slices on their way
@@ -745,8 +737,6 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     }
     set_ids(words_n, ids_n, act_n);
     const int jn0 = __builtin_amdgcn_readlane(ids_n, 0), jn1 = __builtin_amdgcn_readlane(ids_n, 1 / U);
-    uint32_t counted = 0;
-    if (pend_chunk) counted = count_chunk();
     step(nS, T0{}, T0{}, No{}, Yes{}, Yes{});
     if (more) load_q(head_of(na, nbb), na.y);
     step(nS, T1{}, T0{}, No{}, No{}, Yes{});
@@ -859,13 +849,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     };
     by_key_group(finish);
     __syncthreads();      // the exchange has been read before the next item's copies overwrite it
-    if (pend_chunk) merge_if_last(counted);
-    if (slot >= 0 && !p.merge_later) {
-      pend_chunk = true;
-      pa = da;
-      pb = db;
-      pbb = bb;
-    }
+    if (slot >= 0 && !p.merge_later) merge_if_last();
     stores = slot >= 0 ? 2 : q_there ? 1 : 0;
     ready = more;
     if (more) {
@@ -878,11 +862,6 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     }
     busy += wall_clock64() - t0;
   }
-  if (pend_chunk) {
-    wait_copies<0>();
-    merge_if_last(count_chunk());
-  }
-
   if (t == 0) {
     p.busy[part] = busy;
     const uint32_t hw = __builtin_amdgcn_s_getreg((31 << 11) | (0 << 6) | 4);    // HW_ID
@@ -902,7 +881,7 @@ hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream, hipEvent_
   // 128 at d = 128, 3 chunks 226 / 227, 4 chunks 162 / 158.  Where items queue up, who merges falls behind,
   // ends its next rows last and merges these as well: 12 heads, 21 x 23 blocks of 128, up to 4 chunks
   // 72 / 65; 10 heads, 128 x 256, up to 8 chunks 1068 / 771.
-  p.merge_later = p.max_chunks > 0 && (p.max_chunks * C::TPW > 14 || !p.one_each);
+  p.merge_later = p.max_chunks > 0 && (p.max_chunks * C::TPW > 14 || !p.in_place_ok);
   // the dynamic-LDS limit is a per-device function attribute: set it once per device
   static std::atomic<uint32_t> attr_set_mask{0};
   int dev = 0;

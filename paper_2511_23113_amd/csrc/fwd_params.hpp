@@ -27,14 +27,15 @@ struct dbsp_fwd_params {
   int32_t n_slots, n_split, n_empty, n_tail;
   int32_t n_placed;         // items the partitions' lists hold (all of them but the shared queue's)
   int32_t max_chunks;       // the most chunks a split row has; 0: no split rows
-  int32_t one_each;         // no more items than partitions, all batch entries counted
+  int32_t in_place_ok;      // split_cnt may be used, and there are no more items than partitions, all batch entries counted
   int32_t merge_later;      // set by dbsp_launch_fwd: split rows are merged by a kernel of their own behind this one
   float scale;         // softmax scale
   float scale_log2;    // softmax scale * log2(e)
 };
 
-// Enqueues the persistent kernel, and behind it a merge kernel for split rows where that is faster: `grid` workgroups, enough to reach every partition that has items (all of
-// them unless the plan has fewer items than partitions).
+// Enqueues the persistent kernel, and behind it a merge kernel for split rows where that is faster: `grid`
+// workgroups, enough to reach every partition that has items (all of them unless the plan has fewer items
+// than partitions).
 // pair: the plan's rows are pairs of 64-token query blocks and its units pairs of 64-token KV blocks (d = 128 only).
 // done: event that the end of the kernel completes (null inside a stream capture): the launch's own completion
 // signal, where a record behind the launch would put another packet between this kernel and the next (4 us).
