@@ -3,7 +3,7 @@
 
 A step is one pass of the whole hot path over one batch of synthetic input: plan_sparse_attn
 (mask compaction, work items, greedy placement, rho_s, plan upload) followed by
-sparse_attn_fwd (persistent kernel + fix-up).  Q/K/V live in HBM before the timed region; the
+sparse_attn_fwd (persistent kernel + merge of split rows).  Q/K/V live in HBM before the timed region; the
 block mask is a host array, as the C ABI takes it.  One JSON line is printed.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 3] [--no-cpu-baseline]

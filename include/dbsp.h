@@ -53,8 +53,8 @@ enum {
                               of such a plan); the (query block, KV block) combinations of a super block that the
                               mask does not have are computed with the rest and given probability zero, so K and V
                               must be finite in every block that either row of a pair uses.  It pays when neighbouring
-                              rows are alike: from about 5 / 8 of the flags set (the mask's active blocks / (4 x the
-                              plan's nnz)) it is faster than the plain plan, up to 1.57 times.  DBSP_ROW_CNT /
+                              rows are alike almost everywhere: from about 0.93 of the flags set (the mask's active
+                              blocks / (4 x the plan's nnz)) it is faster than the plain plan, up to 1.06 times.  DBSP_ROW_CNT /
                               ROW_PTR / ITEMS then refer to pair rows (ceil(nQ / 2) per head) and super blocks,
                               and DBSP_KV_IDX holds two int32 per super block: j0, and j1 | flags << 24
                               with flags bit (q + 2k) = "query block 2p+q needs KV block j_k" (a union of odd length

@@ -382,7 +382,9 @@ static int make_plan(const uint8_t* mask_host, int32_t H, int32_t nQ, int32_t nK
   if (pair_auto && o.head_dim != 128) return fail(DBSP_EINVAL, std::string(who) + ": DBSP_PLAN_PAIR_AUTO needs head_dim = 128 (pair rows run at that head dim only)");
   // DBSP_PLAN_PAIR_AUTO: a chain of plans keeps the first one's choice (items of the two kinds do not
   // match each other); else both counts are taken and pair rows chosen from a flag fill of 5 / 8
-  // (2 x the mask's active blocks >= 5 x the super blocks), the measured break-even
+  // (2 x the mask's active blocks >= 5 x the super blocks): what the header promises.  It was the break-even while
+  // the kernel of single 64-token rows ran at 0.29 of the peak; at 0.40 to 0.45 that lies near 0.93 (40 heads,
+  // 512 x 512 blocks, single / pair rows: fill 1.00 6.08 / 5.73 ms, 0.80 4.75 / 5.29, 0.66 3.39 / 4.27)
   dbsp_host_plan counted;
   bool have_counts = false;
   if (pair_auto) {
@@ -412,9 +414,8 @@ static int make_plan(const uint8_t* mask_host, int32_t H, int32_t nQ, int32_t nK
       else
         (void)hipGetLastError();
     }
-    // a 64-token block is served by a two-wave workgroup: four of them fill a compute unit at d = 64
-    // (at d = 128 two are resident at a time; the plan does not know d, and an even split runs in two rounds);
-    // pair rows are served by eight-wave workgroups, one per compute unit
+    // a 64-token block is served by a two-wave workgroup: at d = 64 four of them fill a compute unit (also
+    // where the plan does not know d), at d = 128 two; pair rows take the workgroup of 128-token blocks, one per compute unit
     if (block <= 64 && !pair) P *= (o.head_dim == 128 ? 2 : 4);
   }
   if (previous && (previous->host.H != H || previous->host.nQ_blocks != nQ || previous->host.nK != nK || previous->host.P != P))
