@@ -63,6 +63,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cfloat>
 #include <cstdint>
 #include <type_traits>
 
@@ -146,7 +147,7 @@ __device__ __forceinline__ float* partial_of(float* part_o, int64_t slot_no, int
 
 // Merges tile k of wave w's share of a split row's chunks, G of them fetched at once, and stores it: token
 // tok, d-tile dt.  qloc: this lane's query inside the row.
-template <class C, int D, int G>
+template <class C, int D, int G, bool PAIR>
 __device__ __forceinline__ void merge_tile(const dbsp_fwd_params& p, int64_t first, int n_chunks, int w, int k, int l, int qloc,
                                            int64_t tok, int dt, bool with_lse, bool q_there) {
   float m = -INFINITY, tot = 0.f;
@@ -186,8 +187,10 @@ __device__ __forceinline__ void merge_tile(const dbsp_fwd_params& p, int64_t fir
       }
     }
   }
-  const bool none = !(tot > 0.f);          // no chunk has anything for this query: O = 0, LSE = -inf
-  const float inv = none ? 0.f : 1.0f / tot;
+  // no chunk has anything for this query: LSE = -inf, and O = 0 for a query block of pair rows that has no active
+  // block; scores that are all -inf give 0 / 0 as in a row that is not split
+  const bool none = !(tot > 0.f);
+  const float inv = (PAIR && none) ? 0.f : 1.0f / tot;
 #pragma unroll
   for (int e4 = 0; e4 < 4; ++e4) acc[e4] *= inv;
   if (!q_there) return;
@@ -207,7 +210,7 @@ __global__ __launch_bounds__(64 * NQ * NC) void dbsp_merge_kernel(const dbsp_fwd
   const int32_t* row = p.split_rows + 4 * (blockIdx.x % p.n_split);       // row, first slot, chunks
   const int64_t bh = (int64_t)bb * p.H + row[0] / p.nQ;
   const int first_q = (row[0] % p.nQ) * C::QROWS + 64 * wa, qt = C::tile_qt(wc, k);
-  merge_tile<C, D, 4>(p, (int64_t)bb * p.n_slots + row[1], row[2], w, k, l, 64 * wa + 32 * qt + r, bh * p.Nq + first_q + 32 * qt + r,
+  merge_tile<C, D, 4, PAIR>(p, (int64_t)bb * p.n_slots + row[1], row[2], w, k, l, 64 * wa + 32 * qt + r, bh * p.Nq + first_q + 32 * qt + r,
                       C::tile_dt(wc, k), C::has_lse(wc) && C::lse_tile(k), !PAIR || first_q < p.Nq);
 }
 
@@ -406,7 +409,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 #pragma unroll
       for (int k = 0; k < C::TPW; ++k) {
         const int qt = tile_qt(WC, k);
-        merge_tile<C, D, 2>(p, first, n_chunks, w, k, l, 64 * wa + 32 * qt + r, tok0 + 32 * qt, tile_dt(WC, k), has_lse(WC) && C::lse_tile(k), q_there);
+        merge_tile<C, D, 2, PAIR>(p, first, n_chunks, w, k, l, 64 * wa + 32 * qt + r, tok0 + 32 * qt, tile_dt(WC, k), has_lse(WC) && C::lse_tile(k), q_there);
       }
     });
   };
@@ -488,7 +491,9 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
       for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[dt][qt][e] = 0.f;
-    float m_run[2] = {-INFINITY, -INFINITY}, mc_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+    // the running max starts at the lowest finite value: scores of -inf (masked keys) then have probability 0
+    // from the first unit on, where -inf minus -inf would be a NaN
+    float m_run[2] = {-FLT_MAX, -FLT_MAX}, mc_run[2] = {-FLT_MAX, -FLT_MAX}, l_run[2] = {0.f, 0.f};
 
     f32x16 S[2];                  // scores of the last unit of each query tile
     bf16x8 P[2][2];               // [query tile][16-key step]: probabilities, packed as B operands
@@ -669,7 +674,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
           const float m_new = fmaxf(m_run[QS], max_xor32(fmaxf(mx0, mx1)));
           const float alpha = __builtin_amdgcn_exp2f((m_run[QS] - m_new) * c);
           m_run[QS] = m_new;
-          mc_run[QS] = m_new * c;
+          mc_run[QS] = fmaxf(m_new * c, -FLT_MAX);
           float a0 = 0.f, a1 = 0.f;
 #pragma unroll
           for (int hf = 0; hf < 2; ++hf) {
@@ -803,12 +808,12 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
         float lt = 0.f;
 #pragma unroll
         for (int cc = 0; cc < C::NC; ++cc) {
-          // pair rows: a query block may have nothing in this item (all maxima at -inf, sums 0): its
-          // rows come out as O = 0, LSE = -inf, without forming inf - inf or 0 / 0
-          f[cc] = __builtin_amdgcn_exp2f((ms[cc] - ((PAIR && mt == -INFINITY) ? 0.f : mt)) * c);
+          f[cc] = __builtin_amdgcn_exp2f((ms[cc] - mt) * c);
           lt += f[cc] * ((cc == WC) ? lf[qt] : xstat[wa * C::NC + cc][(2 * qt + 1) * 64 + l]);
         }
-        const float inv = (PAIR && !(lt > 0.f)) ? 0.f : 1.0f / lt;
+        // a query block of pair rows may have nothing in this item, and a query's scores in a chunk may all be
+        // -inf (all maxima at their start, sums 0): O = 0, LSE = -inf, which the merge leaves out
+        const float inv = ((PAIR || slot >= 0) && !(lt > 0.f)) ? 0.f : 1.0f / lt;
 #pragma unroll
         for (int cc = 0; cc < C::NC; ++cc) f[cc] *= inv;
         const int64_t tok = tok0 + 32 * qt;
