@@ -128,7 +128,7 @@ typedef struct dbsp_plan_opts {
  *            computed (a "dense block").  Read during the call only.
  * block:     block size b in tokens; the forward pass supports 64 and 128.
  * opts:      host, may be NULL (all zero = defaults).
- * out_plan:  receives the plan; free it with dbsp_plan_destroy.
+ * out_plan:  receives the plan; free it with dbsp_plan_destroy or dbsp_plan_release.
  *
  * Steps (all integer): per-row counts and per-head sums (Alg. 1, get_blocks_per_head); ascending
  * KV-block index list per row; work items (head, q_block, kv_begin, kv_end) in row-major order
@@ -348,10 +348,15 @@ int dbsp_plan_tail_takes(const dbsp_plan* plan, uint32_t* takes, void* stream);
  * either may be NULL.  Synchronises `stream` before reading. */
 int dbsp_plan_busy(const dbsp_plan* plan, uint64_t* busy_ticks, uint32_t* hw_id, void* stream);
 
-/* dbsp_plan_destroy: the plan is gone for the caller; its device and pinned buffers are recycled once the
- * last sparse_attn_fwd enqueued with it and its upload have finished, which the call does not wait for
- * (unless the GPU still uses three others that the calling thread has destroyed: then for the oldest).  NULL is ignored. */
+/* dbsp_plan_destroy: waits (on the host) until the last sparse_attn_fwd enqueued with this plan
+ * and the plan's upload have finished, then recycles its buffers.  NULL is ignored. */
 void dbsp_plan_destroy(dbsp_plan* plan);
+
+/* dbsp_plan_release: dbsp_plan_destroy for callers that plan every step: the plan is gone for the caller at once,
+ * and its buffers are recycled when the last sparse_attn_fwd enqueued with it and its upload have finished,
+ * which the call does not wait for (unless the GPU still uses three others that the calling thread has
+ * released: then for the oldest).  NULL is ignored. */
+void dbsp_plan_release(dbsp_plan* plan);
 
 const char* dbsp_last_error(void);
 

@@ -25,7 +25,7 @@ _INT64_ARRAYS = (PART_LOAD, BLOCKS_PER_HEAD)
 
 EXPORTS = (
     "plan_sparse_attn", "plan_sparse_attn_reuse", "sparse_attn_fwd", "sparse_attn_fwd_static", "imbalance_ratio", "dbsp_plan_get", "dbsp_plan_stats",
-    "dbsp_plan_busy", "dbsp_plan_tail_takes", "dbsp_plan_pair_rows", "dbsp_plan_calibrate", "dbsp_plan_destroy", "dbsp_last_error",
+    "dbsp_plan_busy", "dbsp_plan_tail_takes", "dbsp_plan_pair_rows", "dbsp_plan_calibrate", "dbsp_plan_destroy", "dbsp_plan_release", "dbsp_last_error",
     "dbsp_partition_heads", "dbsp_partition_blocks", "dbsp_ring_work", "dbsp_fit_cost_model", "dbsp_mfma_probe",
 )
 
@@ -94,6 +94,8 @@ def load_library(path: str | None = None):
     lib.dbsp_plan_pair_rows.restype = C.c_int
     lib.dbsp_plan_destroy.argtypes = [vp]
     lib.dbsp_plan_destroy.restype = None
+    lib.dbsp_plan_release.argtypes = [vp]
+    lib.dbsp_plan_release.restype = None
     lib.dbsp_last_error.argtypes = []
     lib.dbsp_last_error.restype = C.c_char_p
     _lib = lib
@@ -106,7 +108,8 @@ def _check(rc: int):
 
 
 class Plan:
-    """Owner of a dbsp_plan*; destroyed on close() or garbage collection."""
+    """Owner of a dbsp_plan*.  close() destroys it and waits for its last forward call; an object that is
+    dropped without it (a step's plan that the next one replaces) is released and waits for nothing."""
 
     def __init__(self, handle: int, H: int, nQ: int, nK: int, block: int, pair_rows: bool = False):
         self._h = C.c_void_p(handle)
@@ -173,7 +176,9 @@ class Plan:
 
     def __del__(self):
         try:
-            self.close()
+            if self._h:
+                load_library().dbsp_plan_release(self._h)
+                self._h = C.c_void_p()
         except Exception:
             pass
 

@@ -48,11 +48,11 @@ constexpr int kMaxWaves = 8;     // waves of the largest workgroup: a split row 
 // Plans are created and destroyed per attention call when masks are dynamic, so their buffers are
 // recycled instead of going through hipMalloc / hipFree (which synchronises the device) each time.
 // Entries remember the device that was current when they were allocated and only go back to it.
-// The buffers of a destroyed plan that the GPU still uses are retired together with the plan's events
-// and join the pools once those have passed: destroying a plan does not wait, unless the calling thread has
-// kMaxRetired retired plans on the device already: then for the oldest of these.  So a caller that plans every step stays that many steps ahead of the GPU, which hides the
-// planning, and the pools can hold all the buffers in flight; a host further ahead would gain nothing and
-// allocate (40 heads, 256 x 256 blocks, 5 to 60 % of them active: 350 us more per step of 5840 with 16 let ahead and pools of 8).
+// The buffers of a released plan that the GPU still uses are retired together with the plan's events
+// and join the pools once those have passed: releasing a plan does not wait, unless the calling thread has
+// kMaxRetired retired plans on the device already: then for the oldest of these.  So a caller that plans every
+// step stays that many steps ahead of the GPU, which hides the planning, and the pools can hold all the buffers
+// in flight; a host further ahead would gain nothing and allocate (40 heads, 256 x 256 blocks, 5 to 60 % of them active: 350 us more per step of 5840 with 16 let ahead and pools of 8).
 struct BufferPool {
   struct Entry { void* ptr; size_t bytes; int device; };
   size_t max_cached;
@@ -157,8 +157,8 @@ hipError_t upload_stream(int device, hipStream_t* out) {
   return hipSuccess;
 }
 
-// Hands the plan's buffers back, at once or, if the GPU may still use them, once its events have passed.
-void free_device(dbsp_device_plan& d) {
+// Hands the plan's buffers back once its events have passed: waits for them, or leaves them to later calls.
+void free_device(dbsp_device_plan& d, bool wait) {
   Retired r = {std::this_thread::get_id(), {nullptr, nullptr}, {d.blob, d.blob_bytes, d.device}, {{d.staging, d.staging_bytes, d.device}, {d.staging_kv, d.staging_kv_bytes, d.device}}};
   if (d.last_use) {
     if (d.used) r.events[0] = static_cast<hipEvent_t>(d.last_use);
@@ -169,8 +169,7 @@ void free_device(dbsp_device_plan& d) {
     else (void)hipEventDestroy(static_cast<hipEvent_t>(d.uploaded));
   }
   Surplus surplus;
-  bool wait = false;
-  {
+  if (!wait) {
     std::lock_guard<std::mutex> lk(g_mu);
     g_retired.push_back(r);
     reap(surplus);
@@ -456,7 +455,7 @@ static int make_plan(const uint8_t* mask_host, int32_t H, int32_t nQ, int32_t nK
     }
     rc = get_kv_staging(plan);
     if (rc != DBSP_OK) {
-      free_device(plan->dev);
+      free_device(plan->dev, true);
       delete plan;
       return rc;
     }
@@ -467,13 +466,13 @@ static int make_plan(const uint8_t* mask_host, int32_t H, int32_t nQ, int32_t nK
     const bool compacted = dbsp_compact_end(job);
     if (rc == DBSP_OK && !compacted) { rc = DBSP_ENOMEM; err = "out of host memory while planning"; }
     if (rc != DBSP_OK) {
-      free_device(plan->dev);
+      free_device(plan->dev, true);
       delete plan;
       return fail(rc, std::string(who) + ": " + err);
     }
     rc = upload(plan);
     if (rc != DBSP_OK) {
-      free_device(plan->dev);
+      free_device(plan->dev, true);
       delete plan;
       return rc;
     }
@@ -514,11 +513,15 @@ int plan_sparse_attn_reuse(const dbsp_plan* previous, const uint8_t* mask_host, 
   return DBSP_OK;
 }
 
-void dbsp_plan_destroy(dbsp_plan* plan) {
+static void give_up(dbsp_plan* plan, bool wait) {
   if (!plan) return;
-  if (plan->dev.resident || plan->dev.blob) free_device(plan->dev);
+  if (plan->dev.resident || plan->dev.blob) free_device(plan->dev, wait);
   delete plan;
 }
+
+void dbsp_plan_destroy(dbsp_plan* plan) { give_up(plan, true); }
+
+void dbsp_plan_release(dbsp_plan* plan) { give_up(plan, false); }
 
 static int forward(const dbsp_plan* plan, const void* q, const void* k, const void* v, void* o,
                    float* lse, int32_t B, int32_t Nq, int32_t Nk, int32_t d, float softmax_scale,

@@ -68,6 +68,7 @@ def test_argument_errors():
     assert lib.dbsp_plan_get(plan, B.ROW_PTR, None, C.byref(cnt)) == B.DBSP_EINVAL
     lib.dbsp_plan_destroy(plan)
     lib.dbsp_plan_destroy(None)
+    lib.dbsp_plan_release(None)
     # unsupported block size is a forward-pass error, not a planning error
     rc, plan = _plan_raw(mp, 1, 2, 2, 32, host)
     assert rc == B.DBSP_OK

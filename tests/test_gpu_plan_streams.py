@@ -1,4 +1,4 @@
-"""Plans on their way to the device, on the GPU: several streams, graph captures, plans destroyed while in use.
+"""Plans on their way to the device, on the GPU: several streams, graph captures, plans given up while in use.
 
 A plan of up to 64 KiB is fetched by a kernel in front of its first launch, a larger one copied on the
 library's own stream; H picks either.  Results of a plan are bitwise the same from launch to launch.
@@ -87,8 +87,27 @@ def test_second_stream_waits_for_the_plan(H):
 
 
 @pytest.mark.parametrize("H", [SMALL, LARGE])
-def test_plans_destroyed_while_in_use(H):
-    """More plans than may wait for the GPU, each destroyed right behind its launch, on two streams in turn;
+def test_close_waits_for_the_last_launch(H):
+    """Results may be read behind close() without any other synchronisation, here on a stream that waits for nothing."""
+    mask, qkv = _case(H, 2, n=64)
+    want = _expected(mask, qkv)
+    plan, side = _plan(mask), torch.cuda.Stream()
+    out = torch.full_like(want[0], float("nan")), torch.full_like(want[1], float("nan"))
+    torch.cuda.synchronize()
+    for _ in range(50):                  # the last launch ends milliseconds after the calls
+        dbsp.sparse_attn_fwd(plan, *qkv, o=out[0], lse=out[1])
+        out[0].fill_(float("nan"))
+    dbsp.sparse_attn_fwd(plan, *qkv, o=out[0], lse=out[1])
+    plan.close()
+    with torch.cuda.stream(side):
+        got = out[0].clone(), out[1].clone()
+    side.synchronize()
+    _same(got, want)
+
+
+@pytest.mark.parametrize("H", [SMALL, LARGE])
+def test_plans_dropped_while_in_use(H):
+    """More plans than may wait for the GPU, each dropped right behind its launch, on two streams in turn;
     a buffer that went back too early would be overwritten by the next plan."""
     cases = [_case(H, seed) for seed in range(2)]
     wants = [_expected(*c) for c in cases]
@@ -100,7 +119,7 @@ def test_plans_destroyed_while_in_use(H):
         with torch.cuda.stream(side if i % 3 == 0 else torch.cuda.current_stream()):
             plan = _plan(mask)
             got.append(dbsp.sparse_attn_fwd(plan, *qkv))
-            plan.close()
+            del plan
     torch.cuda.synchronize()
     for i, g in enumerate(got):
         _same(g, wants[i % 2])
@@ -113,7 +132,7 @@ def test_planning_inside_a_capture_beside_retired_plans():
     for _ in range(6):                    # the pools hold buffers from here on, and plans wait for the GPU
         plan = _plan(mask)
         dbsp.sparse_attn_fwd(plan, *qkv)
-        plan.close()
+        del plan
     out = torch.empty_like(want[0]), torch.empty_like(want[1])
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
