@@ -192,7 +192,9 @@ int plan_sparse_attn_reuse(const dbsp_plan* previous, const uint8_t* mask_host, 
  * softmax_scale <= 0 selects 1 / sqrt(d).  A query row with no active block gets O = 0, LSE = -inf.
  * stream: a hipStream_t (NULL = default stream).  The call only enqueues work: one persistent
  * kernel with one workgroup per partition (fewer where a plan has fewer items than partitions), and where
- * rows were split mostly a small one behind it that merges their chunks.  It neither allocates nor synchronises with the host.  bf16 inputs, f32 accumulation.
+ * rows were split mostly a small one behind it that merges their chunks.  It neither allocates nor synchronises with
+ * the host.  bf16 inputs, f32 accumulation.  Under stream capture the plan must outlive the graph's replays: these are
+ * not known to the library, and dbsp_plan_destroy waits for enqueued launches only.
  * Errors: DBSP_EINVAL (also: B above the plan's max_batch when rows are split), DBSP_ESHAPE, DBSP_EHIP.
  */
 int sparse_attn_fwd(const dbsp_plan* plan, const void* q, const void* k, const void* v, void* o,

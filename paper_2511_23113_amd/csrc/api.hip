@@ -85,7 +85,8 @@ void pool_put(BufferPool& pool, const BufferPool::Entry& e, std::vector<void*>& 
   }
 }
 
-// Asking for an event's state is no part of any capture: it neither fails nor spoils one that is under way.
+// Asking for an event's state, waiting for it and freeing buffers are no part of any capture: they neither fail in
+// nor spoil one that is under way.
 struct OutsideCapture {
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
@@ -100,13 +101,13 @@ void recycle(const Retired& r, Surplus& surplus) {
   for (const BufferPool::Entry& e : r.pin) pool_put(g_pin_pool, e, surplus.pin);
 }
 
-// g_mu is held.  Recycles what the GPU is done with.
+// g_mu is held.  Recycles what the GPU is known to be done with: any answer but success leaves a plan retired.
 void reap(Surplus& surplus) {
   if (g_retired.empty()) return;
   OutsideCapture relaxed;
   for (size_t i = 0; i < g_retired.size();) {
     bool done = true;
-    for (hipEvent_t ev : g_retired[i].events) done = done && (!ev || hipEventQuery(ev) != hipErrorNotReady);
+    for (hipEvent_t ev : g_retired[i].events) done = done && (!ev || hipEventQuery(ev) == hipSuccess);
     if (!done) { ++i; continue; }
     recycle(g_retired[i], surplus);
     g_retired.erase(g_retired.begin() + i);
@@ -115,6 +116,8 @@ void reap(Surplus& surplus) {
 }
 
 void release(const Surplus& surplus) {
+  if (surplus.dev.empty() && surplus.pin.empty()) return;
+  OutsideCapture relaxed;
   for (void* p : surplus.dev) (void)hipFree(p);
   for (void* p : surplus.pin) (void)hipHostFree(p);
 }
@@ -183,10 +186,12 @@ void free_device(dbsp_device_plan& d, bool wait) {
     }
   }
   if (wait) {
-    for (hipEvent_t ev : r.events)
-      if (ev) (void)hipEventSynchronize(ev);
+    OutsideCapture relaxed;
+    bool done = true;
+    for (hipEvent_t ev : r.events) done = done && (!ev || hipEventSynchronize(ev) == hipSuccess);
     std::lock_guard<std::mutex> lk(g_mu);
-    recycle(r, surplus);
+    if (done) recycle(r, surplus);
+    else g_retired.push_back(r);   // the GPU may still use its buffers
   }
   release(surplus);
   (void)hipGetLastError();
@@ -625,9 +630,9 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   }
   const hipError_t e = dbsp_launch_fwd(p, hp.block, d, hp.pair, grid, st, capture ? nullptr : static_cast<hipEvent_t>(dm.last_use));
   if (e != hipSuccess) return fail_hip(e, (std::string(who) + " launch").c_str());
-  if (capture) DBSP_HIP(hipEventRecord(static_cast<hipEvent_t>(dm.last_use), st));
+  // (a captured launch leaves the event to the last one that was enqueued: a graph's replays are the caller's to wait for)
+  if (!capture) dm.used = true;
   dm.last_grid = grid;
-  plan->dev.used = true;
   return DBSP_OK;
 }
 

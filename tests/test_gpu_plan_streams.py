@@ -144,3 +144,38 @@ def test_planning_inside_a_capture_beside_retired_plans():
         _same(out, want)
         _same(dbsp.sparse_attn_fwd(kept, *qkv), want)
     kept.close()
+
+
+@pytest.mark.parametrize("H", [SMALL, LARGE])
+@pytest.mark.parametrize("close", [True, False])
+def test_plans_given_up_inside_a_capture(H, close):
+    """More plans than may wait for the GPU, launched just before a capture on another stream (some captured as well)
+    and given up inside it: the capture stays whole, and no buffer goes back while its launch runs."""
+    cases = [_case(H, seed, n=32) for seed in range(2)]
+    wants = [_expected(*c) for c in cases]
+    plans = [_plan(cases[i % 2][0]) for i in range(8)]
+    spare = torch.empty_like(wants[0][0])
+    torch.cuda.synchronize()
+    got = []
+    for i, plan in enumerate(plans):
+        for _ in range(10):              # still running when the capture begins
+            dbsp.sparse_attn_fwd(plan, *cases[i % 2][1], o=spare, want_lse=False)
+        got.append(dbsp.sparse_attn_fwd(plan, *cases[i % 2][1]))
+    out = torch.zeros_like(wants[0][0]), torch.zeros_like(wants[0][1])
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        dbsp.sparse_attn_fwd(plans[0], *cases[0][1], o=spare, want_lse=False)
+        out[0].add_(1.0)
+        while plans:
+            plan = plans.pop(0)
+            if close:
+                plan.close()
+            del plan
+        graph.capture_end()
+    for i in range(8):                   # into the buffers that went back
+        plan = _plan(cases[i % 2][0])
+        got.append(dbsp.sparse_attn_fwd(plan, *cases[i % 2][1]))
+    for i, g in enumerate(got):
+        _same(g, wants[i % 2])
+    assert not out[0].any()              # captured, not run
