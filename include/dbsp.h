@@ -193,8 +193,10 @@ int plan_sparse_attn_reuse(const dbsp_plan* previous, const uint8_t* mask_host, 
  * stream: a hipStream_t (NULL = default stream).  The call only enqueues work: one persistent
  * kernel with one workgroup per partition (fewer where a plan has fewer items than partitions), and where
  * rows were split mostly a small one behind it that merges their chunks.  It neither allocates nor synchronises with
- * the host.  bf16 inputs, f32 accumulation.  Under stream capture the plan must outlive the graph's replays: these are
- * not known to the library, and dbsp_plan_destroy waits for enqueued launches only.
+ * the host (but see captures).  bf16 inputs, f32 accumulation.
+ * Captures: a call on a stream under capture waits on the host until the plan has arrived on the device, if that is
+ * not known yet (the first such call at most), so that the graph may be replayed at any time on any stream.  The plan
+ * must outlive the replays: these are not known to the library, and dbsp_plan_destroy waits for enqueued launches only.
  * Errors: DBSP_EINVAL (also: B above the plan's max_batch when rows are split), DBSP_ESHAPE, DBSP_EHIP.
  */
 int sparse_attn_fwd(const dbsp_plan* plan, const void* q, const void* k, const void* v, void* o,

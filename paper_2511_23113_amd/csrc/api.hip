@@ -612,19 +612,25 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
     bool in_order = false;         // the fetch is the command before this launch
     if (!dm.sent) {
       const bool fetch = !capture && dm.up_bytes + dm.kv_bytes <= kInStreamBytes;
+      OutsideCapture relaxed;      // the copies go to a stream that is not captured
       const int rc = fetch ? fetch_in_stream(dm, st) : send_upload(dm);
       if (rc != DBSP_OK) return rc;
       in_order = fetch;
     }
     if (!in_order) {
       hipEvent_t arrived = static_cast<hipEvent_t>(dm.uploaded);
-      if (!capture) {
-        OutsideCapture relaxed;    // another stream's
+      OutsideCapture relaxed;      // the event is another stream's
+      if (capture) {
+        // what a graph holds cannot wait for a command outside of it, and its replays, on any stream, are not
+        // known here: the plan has arrived before its launch is recorded
+        DBSP_HIP(hipEventSynchronize(arrived));
+        dm.upload_done = true;
+      } else {
         dm.upload_done = hipEventQuery(arrived) == hipSuccess;
-      }
-      if (!dm.upload_done) {
-        (void)hipGetLastError();
-        DBSP_HIP(hipStreamWaitEvent(st, arrived, 0));
+        if (!dm.upload_done) {
+          (void)hipGetLastError();
+          DBSP_HIP(hipStreamWaitEvent(st, arrived, 0));
+        }
       }
     }
   }

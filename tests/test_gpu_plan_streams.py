@@ -179,3 +179,30 @@ def test_plans_given_up_inside_a_capture(H, close):
     for i, g in enumerate(got):
         _same(g, wants[i % 2])
     assert not out[0].any()              # captured, not run
+
+
+@pytest.mark.parametrize("H", [SMALL, LARGE])
+def test_a_graph_replayed_at_once_on_another_stream(H):
+    """A graph holds nothing that waits for the plan's upload, so the plan has to be there when the capture ends, here
+    with the copies to the device kept busy beside it."""
+    mask, qkv = _case(H, 4)
+    want = _expected(mask, qkv)
+    out = torch.full_like(want[0], float("nan")), torch.full_like(want[1], float("nan"))
+    host = torch.empty(1 << 28, dtype=torch.uint8, pin_memory=True)
+    there = [torch.empty(1 << 28, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    side, others = torch.cuda.Stream(), [torch.cuda.Stream() for _ in there]
+    torch.cuda.synchronize()
+    for x, st in zip(there, others):
+        with torch.cuda.stream(st):
+            x.copy_(host, non_blocking=True)
+    plan, graph = _plan(mask), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        dbsp.sparse_attn_fwd(plan, *qkv, o=out[0], lse=out[1])
+        graph.capture_end()
+    for _ in range(2):
+        graph.replay()                   # on the current stream
+        _same(out, want)
+        out[0].zero_()
+        _same(dbsp.sparse_attn_fwd(plan, *qkv), want)
+    plan.close()
