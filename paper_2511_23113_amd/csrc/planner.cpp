@@ -348,7 +348,7 @@ struct SmallOrder {
       for (int32_t t = 0; t < n; ++t) ++count[val[t] - lo + 1];
       for (int64_t v = 0; v < span; ++v) count[v + 1] += count[v];
       for (int32_t t = 0; t < n; ++t) order[count[val[t] - lo]++] = t;
-    } else if (n <= 64 && span * n <= INT32_MAX) {
+    } else if (n <= 64 && span <= INT32_MAX / n) {      // (the product may pass 63 bits)
       key32.resize(n);
       for (int32_t t = 0; t < n; ++t) key32[t] = (int32_t)(val[t] - lo) * n + t;
       for (int32_t t = 0; t < n; ++t) {

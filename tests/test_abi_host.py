@@ -315,6 +315,19 @@ def test_partition_cost_bit_exact_and_errors():
     pl.close()
 
 
+@pytest.mark.parametrize("P", [3, 16, 64, 65])
+def test_rounds_at_loads_up_to_60_bits(P):
+    """Loads (weight x cost) whose span times P passes 63 bits: the order of a group's partitions by load stays right."""
+    rng = np.random.default_rng(P)
+    mask = (rng.random((2, 2 * P + 1, 9)) < 0.6).astype(np.uint8)
+    for overhead, low, high in ((1 << 20, 1 << 28, 1 << 29), (1 << 28, 1 << 27, 1 << 30), (300_000_000, 1 << 23, 1 << 29)):
+        cost = rng.integers(low, high, P).tolist()
+        pl = B.plan_sparse_attn(mask, 64, num_partitions=P, mode=B.MODE_ROUNDS, item_overhead=overhead, host_only=True, partition_cost=cost)
+        ref = op.plan(mask, P, mode=op.MODE_ROUNDS, item_overhead=overhead, partition_cost=cost)
+        assert pl.array(B.PART_PTR).tolist() == ref["part_ptr"] and pl.array(B.PART_ITEMS).tolist() == ref["part_items"]
+        pl.close()
+
+
 def test_concurrent_planners_share_the_helper_threads_and_agree():
     # several host threads plan a mask large enough for the threaded passes at the same time: one of
     # them gets the library's helper threads, the others run their passes themselves; every plan
