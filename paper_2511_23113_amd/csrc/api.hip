@@ -475,7 +475,11 @@ static int make_plan(const uint8_t* mask_host, int32_t H, int32_t nQ, int32_t nK
       delete plan;
       return fail(rc, std::string(who) + ": " + err);
     }
-    rc = upload(plan);
+    try {
+      rc = upload(plan);
+    } catch (const std::bad_alloc&) {
+      rc = fail(DBSP_ENOMEM, std::string(who) + ": out of host memory while planning");
+    }
     if (rc != DBSP_OK) {
       free_device(plan->dev, true);
       delete plan;

@@ -107,6 +107,7 @@ struct dbsp_compaction {
   std::function<void(int)> body;
   void* pool = nullptr;    // set between begin and end
   void* state = nullptr;
+  bool failed = false;     // out of memory before any helper ran
 };
 int dbsp_plan_count(const uint8_t* mask, int32_t H, int32_t nQ_blocks, int32_t nK, int32_t block, bool pair, dbsp_host_plan& out, std::string& err);
 void dbsp_compact_begin(const uint8_t* mask, const dbsp_host_plan& hp, int32_t* dst, dbsp_compaction& job);

@@ -291,8 +291,8 @@ class RowPool {
     while ((int)workers_ < want) {
       try {
         std::thread(&RowPool::worker, this, (int)workers_).detach();
-      } catch (const std::system_error&) {
-        return;   // no more threads to be had: the caller takes the remaining ranges
+      } catch (const std::exception&) {
+        return;   // no more threads, or memory for them, to be had: the caller takes the remaining ranges
       }
       ++workers_;
     }
@@ -572,42 +572,49 @@ void dbsp_compact_begin(const uint8_t* mask, const dbsp_host_plan& hp, int32_t* 
   const int32_t nK = hp.nK;
   const int n_thr = row_threads((int64_t)hp.H * hp.nQ_blocks * nK, kCompactShare);
   const dbsp_host_plan* php = &hp;
-  job.body = [=](int k) {
-    const dbsp_host_plan& h = *php;
-    const int64_t r0 = R * k / n_thr, r1 = R * (k + 1) / n_thr;
-    std::vector<int32_t> bounce((size_t)nK + 8);
-    if (h.pair) {     // two ints per super block, written exactly: no slack between rows needed
+  job.pool = job.state = nullptr;
+  job.failed = false;
+  try {
+    job.body = [=](int k) {
+      const dbsp_host_plan& h = *php;
+      const int64_t r0 = R * k / n_thr, r1 = R * (k + 1) / n_thr;
+      std::vector<int32_t> bounce((size_t)nK + 8);
+      if (h.pair) {     // two ints per super block, written exactly: no slack between rows needed
+        for (int64_t r = r0; r < r1; ++r) {
+          if (!h.row_cnt[r]) continue;
+          const int64_t hd = r / h.nQ, q0 = 2 * (r % h.nQ);
+          const uint8_t* row0 = mask + (hd * h.nQ_blocks + q0) * nK;
+          compact_pair(row0, q0 + 1 < h.nQ_blocks ? row0 + nK : nullptr, nK, bounce.data(), dst + 2 * (int64_t)h.row_ptr[r]);
+        }
+        return;
+      }
       for (int64_t r = r0; r < r1; ++r) {
         if (!h.row_cnt[r]) continue;
-        const int64_t hd = r / h.nQ, q0 = 2 * (r % h.nQ);
-        const uint8_t* row0 = mask + (hd * h.nQ_blocks + q0) * nK;
-        compact_pair(row0, q0 + 1 < h.nQ_blocks ? row0 + nK : nullptr, nK, bounce.data(), dst + 2 * (int64_t)h.row_ptr[r]);
+        if (r1 == R || (int64_t)h.row_ptr[r + 1] + 8 <= (int64_t)h.row_ptr[r1]) {
+          compact_row(mask + r * nK, nK, dst + h.row_ptr[r]);
+        } else {
+          compact_row(mask + r * nK, nK, bounce.data());
+          std::memcpy(dst + h.row_ptr[r], bounce.data(), sizeof(int32_t) * (size_t)h.row_cnt[r]);
+        }
       }
+    };
+    if ((int64_t)hp.H * hp.nQ_blocks * nK < kCompactShare) {   // a small mask: done before a helper thread would have woken up
+      job.body(0);
       return;
     }
-    for (int64_t r = r0; r < r1; ++r) {
-      if (!h.row_cnt[r]) continue;
-      if (r1 == R || (int64_t)h.row_ptr[r + 1] + 8 <= (int64_t)h.row_ptr[r1]) {
-        compact_row(mask + r * nK, nK, dst + h.row_ptr[r]);
-      } else {
-        compact_row(mask + r * nK, nK, bounce.data());
-        std::memcpy(dst + h.row_ptr[r], bounce.data(), sizeof(int32_t) * (size_t)h.row_cnt[r]);
-      }
-    }
-  };
-  if ((int64_t)hp.H * hp.nQ_blocks * nK < kCompactShare) {   // a small mask: done before a helper thread would have woken up
-    job.pool = nullptr;
-    job.body(0);
-    return;
+    auto* async = new RowPool::Async();
+    job.state = async;
+    job.pool = &RowPool::instance();
+    static_cast<RowPool*>(job.pool)->begin(n_thr, job.body, *async);
+  } catch (const std::bad_alloc&) {      // (none is thrown once a helper may run: dbsp_compact_end reports theirs)
+    delete static_cast<RowPool::Async*>(job.state);
+    job.pool = job.state = nullptr;
+    job.failed = true;
   }
-  job.pool = &RowPool::instance();
-  auto* async = new RowPool::Async();
-  job.state = async;
-  static_cast<RowPool*>(job.pool)->begin(n_thr, job.body, *async);
 }
 
 bool dbsp_compact_end(dbsp_compaction& job) {
-  if (!job.pool) return true;
+  if (!job.pool) return !job.failed;
   auto* async = static_cast<RowPool::Async*>(job.state);
   const bool ok = static_cast<RowPool*>(job.pool)->finish(*async);
   delete async;

@@ -5,6 +5,8 @@ planner's integer arrays and rho_s equal the oracle's bit for bit."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -326,6 +328,29 @@ def test_rounds_at_loads_up_to_60_bits(P):
         ref = op.plan(mask, P, mode=op.MODE_ROUNDS, item_overhead=overhead, partition_cost=cost)
         assert pl.array(B.PART_PTR).tolist() == ref["part_ptr"] and pl.array(B.PART_ITEMS).tolist() == ref["part_items"]
         pl.close()
+
+
+OUT_OF_MEMORY = """
+import resource
+import numpy as np
+from paper_2511_23113_amd import binding as B
+B.plan_sparse_attn(np.ones((1, 1, 3), np.uint8), 64, num_partitions=1, host_only=True).close()
+mask = np.zeros((1, 1, 131000), np.uint8)          # one block of a row whose compaction needs half a megabyte
+mask[0, 0, 5] = 1
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used, resource.getrlimit(resource.RLIMIT_AS)[1]))
+try:
+    B.plan_sparse_attn(mask, 64, num_partitions=1, host_only=True)
+except B.DbspError as e:
+    print("refused", e)
+"""
+
+
+def test_planning_out_of_memory_is_an_error_and_no_abort():
+    env = dict(os.environ, MALLOC_MMAP_THRESHOLD_="65536", MALLOC_TOP_PAD_="0")
+    res = subprocess.run([sys.executable, "-c", OUT_OF_MEMORY], cwd=ROOT, env=env, capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stderr
+    assert res.stdout.startswith("refused") and "out of host memory" in res.stdout
 
 
 def test_concurrent_planners_share_the_helper_threads_and_agree():
