@@ -1,5 +1,4 @@
 // C ABI of libdbsp: argument checks, plan life cycle, device upload, kernel launches.
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -231,19 +230,17 @@ __global__ __launch_bounds__(256) void dbsp_fetch_kernel(uint4* __restrict__ dst
   for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = i < na ? a[i] : b[i - na];
 }
 
+// The record behind the launch that follows vouches for the fetch as well (see forward).
 int fetch_in_stream(dbsp_device_plan& dv, hipStream_t st) {
   // the index lists' last 16 bytes may reach into the slack both buffers have behind them
   const uint32_t na = (uint32_t)(dv.up_bytes / 16), n = na + (uint32_t)((dv.kv_bytes + 15) / 16);
   hipLaunchKernelGGL(dbsp_fetch_kernel, dim3((n + 255) / 256), dim3(256), 0, st,
                         reinterpret_cast<uint4*>(dv.blob), static_cast<const uint4*>(dv.staging), na, static_cast<const uint4*>(dv.staging_kv), n);
   DBSP_HIP(hipGetLastError());
-  // a record, not the launch's own completion event: after 2000 plans and launches in a row that left the runtime
-  // work that made the next dozens of calls of the program slower (67 -> 118 us for the next plan and launch of
-  // 512 tokens, 400 -> 580 for 60 small kernels of other libraries), for at most 0.3 us of 20 a pass
-  DBSP_HIP(hipEventRecord(static_cast<hipEvent_t>(dv.uploaded), st));
   dv.sent = true;
   return DBSP_OK;
 }
+
 int upload(dbsp_plan* plan) {
   dbsp_host_plan& hp = plan->host;
   dbsp_device_plan& dv = plan->dev;
@@ -612,8 +609,8 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();
   const bool capture = capturing != hipStreamCaptureStatusNone;
+  bool in_order = false;           // the fetch is the command before this launch
   if (!dm.upload_done) {
-    bool in_order = false;         // the fetch is the command before this launch
     if (!dm.sent) {
       const bool fetch = !capture && dm.up_bytes + dm.kv_bytes <= kInStreamBytes;
       OutsideCapture relaxed;      // the copies go to a stream that is not captured
@@ -638,10 +635,22 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
       }
     }
   }
-  const hipError_t e = dbsp_launch_fwd(p, hp.block, d, hp.pair, grid, st, capture ? nullptr : static_cast<hipEvent_t>(dm.last_use));
-  if (e != hipSuccess) return fail_hip(e, (std::string(who) + " launch").c_str());
+  const hipError_t e = dbsp_launch_fwd(p, hp.block, d, hp.pair, grid, st);
+  // A record behind the launch, not the kernel's own completion event.  That is 1.5 us cheaper between launches of one
+  // plan (12 heads, 21 x 23 blocks of 128: 56.8 to 58.3 us in a row), but leaves the runtime work for the calls after
+  // them: a first pass on a new mask of that size took 114 us with it and takes 98, of 512 tokens 75 and 60, and 60
+  // small kernels of another library behind 2000 launches 715 or 1130 us, varying from process to process, and 740
+  // to 800 (with neither 735).  A plan's calls do not overlap, so a fetched plan's first launch needs one record only,
+  // for the launch and the fetch before it (512 tokens, planned on every call: 25.8 to 19.7 us a pass).
   // (a captured launch leaves the event to the last one that was enqueued: a graph's replays are the caller's to wait for)
-  if (!capture) dm.used = true;
+  hipError_t recorded = hipSuccess;
+  if (!capture) {                  // (also where a launch has failed: an earlier one of the call may be under way)
+    recorded = hipEventRecord(static_cast<hipEvent_t>(in_order ? dm.uploaded : dm.last_use), st);
+    if (recorded != hipSuccess) (void)hipStreamSynchronize(st);      // nothing else could vouch for the plan's buffers
+    else if (!in_order) dm.used = true;
+  }
+  if (e != hipSuccess) return fail_hip(e, (std::string(who) + " launch").c_str());
+  if (recorded != hipSuccess) return fail_hip(recorded, (std::string(who) + ": record").c_str());
   dm.last_grid = grid;
   return DBSP_OK;
 }

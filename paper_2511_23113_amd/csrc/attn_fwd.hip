@@ -59,7 +59,6 @@
 //     is linear): K by the row index so that the 16-byte operand reads of 16 lanes (16
 //     consecutive keys) hit distinct banks; V by (row & 3) so that the 4 keys of a
 //     transposing read hit distinct bank quarters.
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -877,7 +876,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 }
 
 template <int D, int NQ, int NC, int U, bool PAIR = false>
-hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream, hipEvent_t done) {
+hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream) {
   using C = Cfg<D, NQ, NC, U>;
   // Who merges split rows.  In place, the wave that ends a row merges its share, TPW tiles of every chunk one
   // after the other, while its workgroup has no other item to get on with; a launch of its own has a wave
@@ -900,23 +899,19 @@ hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream, hipEvent_
     attr_set_mask.fetch_or(bit, std::memory_order_release);
   }
   const int4* sched = reinterpret_cast<const int4*>(p.sched);
-  if (done && !p.merge_later)
-    hipExtLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, nullptr, done, 0, p, p.kv_idx, sched, p.part_ptr);
-  else
-    hipLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, p, p.kv_idx, sched, p.part_ptr);
+  hipLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, p, p.kv_idx, sched, p.part_ptr);
   e = hipGetLastError();
   if (e != hipSuccess || !p.merge_later) return e;
   const dim3 merge_grid((uint32_t)p.B * (uint32_t)p.n_split, C::TPW);
-  if (done) hipExtLaunchKernelGGL((dbsp_merge_kernel<D, NQ, NC, U, PAIR>), merge_grid, dim3(C::NT), 0, stream, nullptr, done, 0, p);
-  else hipLaunchKernelGGL((dbsp_merge_kernel<D, NQ, NC, U, PAIR>), merge_grid, dim3(C::NT), 0, stream, p);
+  hipLaunchKernelGGL((dbsp_merge_kernel<D, NQ, NC, U, PAIR>), merge_grid, dim3(C::NT), 0, stream, p);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int grid, hipStream_t stream, hipEvent_t done) {
+hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int grid, hipStream_t stream) {
   if ((block != 64 && block != 128) || (d != 64 && d != 128) || (pair && (block != 64 || d != 128))) return hipErrorInvalidValue;
-  if (pair) return launch_fwd<128, 2, 2, 2, true>(p, grid, stream, done);
-  if (block == 64) return d == 128 ? launch_fwd<128, 1, 2, 1>(p, grid, stream, done) : launch_fwd<64, 1, 2, 1>(p, grid, stream, done);
-  return d == 128 ? launch_fwd<128, 2, 2, 2>(p, grid, stream, done) : launch_fwd<64, 2, 4, 1>(p, grid, stream, done);
+  if (pair) return launch_fwd<128, 2, 2, 2, true>(p, grid, stream);
+  if (block == 64) return d == 128 ? launch_fwd<128, 1, 2, 1>(p, grid, stream) : launch_fwd<64, 1, 2, 1>(p, grid, stream);
+  return d == 128 ? launch_fwd<128, 2, 2, 2>(p, grid, stream) : launch_fwd<64, 2, 4, 1>(p, grid, stream);
 }

@@ -37,6 +37,4 @@ struct dbsp_fwd_params {
 // workgroups, enough to reach every partition that has items (all of them unless the plan has fewer items
 // than partitions).
 // pair: the plan's rows are pairs of 64-token query blocks and its units pairs of 64-token KV blocks (d = 128 only).
-// done: event that the end of the kernel completes (null inside a stream capture): the launch's own completion
-// signal, where a record behind the launch would put another packet between this kernel and the next (4 us).
-hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int grid, hipStream_t stream, hipEvent_t done);
+hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int grid, hipStream_t stream);

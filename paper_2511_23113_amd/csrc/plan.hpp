@@ -58,9 +58,9 @@ struct dbsp_device_plan {
   // forward launch, on that launch's stream
   bool sent = false;
   bool upload_done = false;       // known to have arrived
-  void* uploaded = nullptr;       // hipEvent_t: what was sent has arrived
+  void* uploaded = nullptr;       // hipEvent_t: what was sent has arrived (if a kernel fetched it: and the launch behind that has finished)
   void* last_use = nullptr;       // hipEvent_t: the last forward launch has finished
-  bool used = false;
+  bool used = false;              // last_use has been recorded
   int32_t last_grid = 0;          // workgroups of the last forward launch
   const int32_t* kv_idx = nullptr;
   const int32_t* split_rows = nullptr;   // 4 x int32 per split row: row, first slot, chunks, 0
