@@ -144,6 +144,10 @@ __device__ __forceinline__ float* partial_of(float* part_o, int64_t slot_no, int
   return part_o + (slot_no * C::NW + w) * (C::TPW * 1024) + (k * 4 + e4) * 256 + l * 2;
 }
 
+// Is a sum of weights +0?  By its bits: this file is compiled without regard to NaNs, where a comparison of floats
+// may come out either way for one.
+__device__ __forceinline__ bool is_zero(float x) { return __builtin_bit_cast(uint32_t, x) == 0u; }
+
 // Merges tile k of wave w's share of a split row's chunks, G of them fetched at once, and stores it: token
 // tok, d-tile dt.  qloc: this lane's query inside the row.
 template <class C, int D, int G, bool PAIR>
@@ -187,8 +191,9 @@ __device__ __forceinline__ void merge_tile(const dbsp_fwd_params& p, int64_t fir
     }
   }
   // no chunk has anything for this query: LSE = -inf, and O = 0 for a query block of pair rows that has no active
-  // block; scores that are all -inf give 0 / 0 as in a row that is not split
-  const bool none = !(tot > 0.f);
+  // block; scores that are all -inf give 0 / 0 as in a row that is not split.  (A sum of NaN is not
+  // nothing: some score is undefined, and O and LSE say so.)
+  const bool none = is_zero(tot);
   const float inv = (PAIR && none) ? 0.f : 1.0f / tot;
 #pragma unroll
   for (int e4 = 0; e4 < 4; ++e4) acc[e4] *= inv;
@@ -812,7 +817,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
         }
         // a query block of pair rows may have nothing in this item, and a query's scores in a chunk may all be
         // -inf (all maxima at their start, sums 0): O = 0, LSE = -inf, which the merge leaves out
-        const float inv = ((PAIR || slot >= 0) && !(lt > 0.f)) ? 0.f : 1.0f / lt;
+        const float inv = ((PAIR || slot >= 0) && is_zero(lt)) ? 0.f : 1.0f / lt;
 #pragma unroll
         for (int cc = 0; cc < C::NC; ++cc) f[cc] *= inv;
         const int64_t tok = tok0 + 32 * qt;

@@ -1,4 +1,5 @@
-"""Keys masked by scores of -inf, on the GPU against the oracle: they have probability 0, wherever they lie in a block."""
+"""Scores that are not finite, on the GPU.  Keys masked by scores of -inf have probability 0, wherever they lie in a
+block (against the oracle); a query with an undefined score has NaN as its O and LSE, and no other query has."""
 
 import numpy as np
 import pytest
@@ -40,3 +41,42 @@ def test_masked_keys(block, d, which, scale, length):
         return
     assert np.abs(got_o - ref_o).max() <= O_TOL
     assert np.abs(got_l - ref_l).max() <= LSE_TOL
+
+
+@pytest.mark.parametrize("block,d,pair", [(64, 64, False), (64, 128, False), (128, 64, False), (128, 128, False), (64, 128, True)])
+@pytest.mark.parametrize("length", [-1, 2, 1])          # rows whole, cut, cut into single blocks
+@pytest.mark.parametrize("which", ["a key", "a query", "an infinite score"])
+def test_undefined_scores_show(block, d, pair, length, which):
+    H, n, key, query = 2, 6, 37, 5
+    rng = np.random.default_rng(block + d)
+    mask = (rng.random((H, n, n)) < 0.6).astype(np.uint8)
+    mask[:, range(n), range(n)] = 1
+    mask[1, 4:] = 0                      # rows that are empty
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(block)
+    q, k, v = (torch.randn((1, H, n * block, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    nan = torch.zeros((H, n * block), dtype=torch.bool)
+    rows = torch.from_numpy(mask).bool().repeat_interleave(block, 1)          # [H, queries, KV blocks]
+    if which == "a query":
+        q[0, :, query] = float("nan")
+        nan[:, query] = True
+    else:                                # in KV block 2
+        if which == "a key":
+            k[0, :, 2 * block + key] = float("nan")
+        else:                            # inf - inf where the running max reaches it
+            q[..., 0] = 1
+            k[0, :, 2 * block + key, 0] = float("inf")
+        nan |= rows[:, :, 2]
+        if pair:                         # computed for both query blocks of a pair, and documented as undefined there
+            nan |= rows[:, :, 2].reshape(H, n // 2, 2, block).any(2, keepdim=True).expand(-1, -1, 2, -1).reshape(H, -1)
+    plan = dbsp.plan_sparse_attn(mask, block, max_item_len=length, num_partitions=16, pair_rows=pair)
+    o, lse = dbsp.sparse_attn_fwd(plan, q, k, v)
+    torch.cuda.synchronize()
+    o, lse = o[0].float().cpu(), lse[0].cpu()
+    if pair and which != "a query":      # (undefined where only the neighbour needs the block)
+        sure = rows[:, :, 2]
+        assert lse[sure].isnan().all() and o[sure].isnan().all()
+        assert not lse[~nan].isnan().any() and not o[~nan].isnan().any()
+        return
+    assert torch.equal(lse.isnan(), nan)
+    assert torch.equal(o.isnan(), nan[..., None].expand_as(o))
