@@ -317,6 +317,30 @@ def test_partition_cost_bit_exact_and_errors():
     pl.close()
 
 
+@pytest.mark.parametrize("kind", ["halves", "dies", "units"])
+def test_clearly_unequal_costs_even_out_the_weighted_load(kind):
+    mask, P = synth.mask_for_config(5), 256
+    g = np.arange(P)
+    cost = {"halves": np.where(g % 2, 1024, 1536), "dies": 1024 + 96 * (g % 8), "units": 1024 + 16 * (g // 8)}[kind].astype(np.int64)
+    for mode, groups in ((B.MODE_BALANCED, 0), (B.MODE_ROUNDS, 8)):
+        times, plans = [], []
+        for c in (None, cost.tolist()):
+            plans.append(B.plan_sparse_attn(mask, 128, num_partitions=P, mode=mode, locality_groups=groups, partition_cost=c, host_only=True))
+            times.append(plans[-1].array(B.PART_LOAD) * cost)
+        even, tuned = times
+        assert tuned.max() / tuned.mean() < even.max() / even.mean()
+        if mode == B.MODE_BALANCED:
+            # each item went to the partition of least time, heaviest items first: the slowest was at or below the final
+            # mean before its last and lightest item, which ignoring the costs exceeds many times over
+            slow = int(tuned.argmax())
+            items, ptr = plans[1].array(B.ITEMS).reshape(-1, 4), plans[1].array(B.PART_PTR)
+            mine = items[plans[1].array(B.PART_ITEMS)[ptr[slow]:ptr[slow + 1]]]
+            bound = tuned.mean() + cost[slow] * (mine[:, 3] - mine[:, 2]).min()
+            assert tuned.max() <= bound < even.max()
+        for pl in plans:
+            pl.close()
+
+
 @pytest.mark.parametrize("P", [3, 16, 64, 65])
 def test_rounds_at_loads_up_to_60_bits(P):
     """Loads (weight x cost) whose span times P passes 63 bits: the order of a group's partitions by load stays right."""

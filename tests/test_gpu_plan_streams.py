@@ -71,18 +71,33 @@ def test_captures_of_one_plan(H, eager_first):
 
 
 @pytest.mark.parametrize("H", [SMALL, LARGE])
-def test_second_stream_waits_for_the_plan(H):
-    mask, qkv = _case(H, 1)
-    want = _expected(mask, qkv)
-    for _ in range(4):
-        plan, side = _plan(mask), torch.cuda.Stream()
-        side.wait_stream(torch.cuda.current_stream())
-        first = dbsp.sparse_attn_fwd(plan, *qkv)
-        torch.cuda.current_stream().synchronize()      # one plan's launches must not overlap
+def test_first_launch_waits_for_the_plan(H):
+    """First launches while the copies to the device are kept busy, and second ones on another stream that is ordered
+    behind the first on the device only, with a long kernel in front.  The plans' buffers held another mask's plan of
+    the same shape before, so a launch that did not wait would work through that one."""
+    cases = [_case(H, seed) for seed in (1, 2)]
+    wants = [_expected(*c) for c in cases]
+    host = torch.empty(1 << 27, dtype=torch.uint8, pin_memory=True)
+    there = [torch.empty(1 << 27, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    long = torch.ones(1 << 28, device="cuda")
+    side, others = torch.cuda.Stream(), [torch.cuda.Stream() for _ in there]
+    torch.cuda.synchronize()
+    for i in range(6):
+        (mask, qkv), want = cases[i % 2], wants[i % 2]
+        outs = [[torch.full_like(x, float("nan")) for x in want] for _ in range(2)]
+        torch.cuda.synchronize()
+        for x, st in zip(there, others):
+            with torch.cuda.stream(st):
+                x.copy_(host, non_blocking=True)
+        plan = _plan(mask)
+        if i >= 2:                       # (or nothing in front)
+            long.mul_(1.0)
+        dbsp.sparse_attn_fwd(plan, *qkv, o=outs[0][0], lse=outs[0][1])
+        side.wait_stream(torch.cuda.current_stream())              # one plan's launches must not overlap
         with torch.cuda.stream(side):
-            second = dbsp.sparse_attn_fwd(plan, *qkv)
-        _same(first, want)
-        _same(second, want)
+            dbsp.sparse_attn_fwd(plan, *qkv, o=outs[1][0], lse=outs[1][1])
+        for got in outs:
+            _same(got, want)
         plan.close()
 
 
