@@ -62,7 +62,9 @@ enum {
   DBSP_PLAN_PAIR_AUTO = 4  /* flags bit, block == 64 and head_dim == 128 only, not together with DBSP_PLAN_PAIR_ROWS:
                               the library counts the mask both ways and plans with pair rows if at least 5 / 8 of the
                               flags would be set (2 x active blocks >= 5 x super blocks), else plainly;
-                              dbsp_plan_pair_rows tells which.  plan_sparse_attn_reuse keeps the previous plan's kind */
+                              dbsp_plan_pair_rows tells which.  With the present kernels the plain plan is the
+                              faster one up to about 0.93 of the flags: between 5 / 8 and there this choice costs
+                              up to a quarter (11 % at 0.80, 26 % at 0.66), which a program avoids by choosing itself.  plan_sparse_attn_reuse keeps the previous plan's kind */
 };
 
 typedef struct dbsp_plan_opts {
@@ -212,7 +214,8 @@ int sparse_attn_fwd(const dbsp_plan* plan, const void* q, const void* k, const v
  * instead of the scratch the plan allocated.  It therefore works for any B whatever the plan's
  * max_batch, as long as  B * n_split_chunks * block * (d + 1) * 4 bytes (plus alignment; with pair
  * rows 2 * block in place of block) fit in the 32 MiB; beyond that it returns DBSP_EINVAL and the message names both sizes.  The call makes
- * no allocation of any kind (its first use on a device looks up the array's device address).
+ * no allocation of any kind (its first use on a device looks up the array's device address); what it waits for under
+ * capture is what sparse_attn_fwd does.
  * Nothing in the array needs clearing: every slot a launch reads was written by that launch.
  * All calls on one GPU share the array: two such calls must not overlap on the device (different
  * streams without ordering, or concurrent host threads), or they race on it.
@@ -299,7 +302,7 @@ int dbsp_partition_blocks(const uint8_t* mask_host, int32_t H, int32_t nQ, int32
 int dbsp_ring_work(const uint8_t* mask_host, int32_t H, int32_t nQ, int32_t nK, int32_t y, const int32_t* gpu_of_q,
                    const int32_t* chunk_of_kv, int64_t* work, double* rho);
 
-/* Plan arrays (host copies, owned by the plan, valid until dbsp_plan_destroy). */
+/* Plan arrays (host copies, owned by the plan, valid until dbsp_plan_destroy or dbsp_plan_release). */
 enum dbsp_plan_array {
   DBSP_ROW_PTR = 0,         /* int32 [H*nQ + 1]  CSR offsets over rows r = h*nQ + I                  */
   DBSP_KV_IDX = 1,          /* int32 [nnz]       ascending active KV block ids of each row (pair rows: [2 nnz]) */

@@ -11,7 +11,9 @@
 // Work split inside a workgroup (wave = 64 lanes, lane = 32*g + r):
 //   * waves form a (query group) x (key group) grid.  Wave (a, c) owns 64 queries (two tiles of 32)
 //     and, of every KV block, the 32-key slices of key group c; it keeps its own running softmax
-//     statistics over its keys, and the key groups are combined once per item.  Two query tiles per
+//     statistics over its keys (so its probabilities are rounded to bf16 against its own running max:
+//     O is 2.3e-3 from 64 bits in the 2-norm, most of it the rounding of O itself, and no further
+//     with two or four key groups than with one), and the key groups are combined once per item.  Two query tiles per
 //     wave mean that every K and V^T operand read from the LDS feeds two MFMAs.
 //       64-token blocks              1 query group,  2 key groups of 1 slice:  2 waves
 //       128-token blocks, d = 64     2 query groups, 4 key groups of 1 slice:  8 waves
@@ -52,7 +54,7 @@
 //     its own copies only; no barrier couples the two waves until the end of an item.  128-token
 //     blocks: the two waves of a key group share its ring of four slices and copy half of each; one
 //     barrier every second slice publishes the next two slices and retires the last two, whose
-//     positions are refilled during the two steps that follow it (four steps to land).
+//     positions are refilled in that step and the next (three and two whole steps to land before the next barrier).
 //   * A copy instruction occupies its wave for about 18 clocks, so copies are spread over sub-slots.
 //   * LDS tiles are unpadded; 16-byte chunks are XOR-swizzled inside each row instead (the
 //     permutation is applied to the per-lane global source address, the LDS side of the copy
@@ -580,7 +582,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
       //   slice s and V of slice s-1, whose operands are in registers by the second half of the step.
       //   Shared slices: behind the barrier of an even slice s, K of slices s+3, s+4 and V of slices s+2,
       //   s+3 into the positions that barrier has retired: one pair of groups in its own step (A), the
-      //   other in the step after (B); four steps to land.
+      //   other in the step after (B): three and two whole steps to land before the next barrier.
       constexpr bool COPY = QK && (!SHARED ? QT == 0 : (QT == 1 && ODD == 0) || (QT == 0 && ODD == 1));
       auto copies = [&](int y) {                  // sub-slot y
         constexpr int GAP = SHARED ? SUB / (2 * C::LOADS) : 1;
@@ -884,7 +886,8 @@ template <int D, int NQ, int NC, int U, bool PAIR = false>
 hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream) {
   using C = Cfg<D, NQ, NC, U>;
   // Who merges split rows.  In place, the wave that ends a row merges its share, TPW tiles of every chunk one
-  // after the other, while its workgroup has no other item to get on with; a launch of its own has a wave
+  // after the other, where there are no more items than partitions, all batch entries counted (a workgroup mostly
+  // has one then, but a placed item runs there once for every batch entry); a launch of its own has a wave
   // for every tile and costs 2 us behind the kernel.  us in place / by a second launch, one item at most for
   // a workgroup: 64-token blocks at d = 64, 3 chunks 24.7 / 27.0, 7 chunks 30.5 / 31.3, 14 chunks 38.0 / 29.8;
   // 128 at d = 128, 3 chunks 226 / 227, 4 chunks 162 / 158.  Where items queue up, who merges falls behind,
