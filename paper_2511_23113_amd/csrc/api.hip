@@ -615,7 +615,11 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
       const bool fetch = !capture && dm.up_bytes + dm.kv_bytes <= kInStreamBytes;
       OutsideCapture relaxed;      // the copies go to a stream that is not captured
       const int rc = fetch ? fetch_in_stream(dm, st) : send_upload(dm);
-      if (rc != DBSP_OK) return rc;
+      if (rc != DBSP_OK) {
+        // (the error may be an earlier call's, the fetch under way, and nothing vouches for the buffers yet)
+        if (fetch) (void)hipStreamSynchronize(st);
+        return rc;
+      }
       in_order = fetch;
     }
     if (!in_order) {

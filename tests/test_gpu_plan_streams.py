@@ -196,6 +196,28 @@ def test_plans_given_up_inside_a_capture(H, close):
     assert not out[0].any()              # captured, not run
 
 
+def test_an_earlier_error_leaves_no_buffers_in_use():
+    """An error that the program left behind is reported by the call that fetches a plan; the plan can be used again, or
+    dropped, and what follows in its buffers is right."""
+    cases = [_case(SMALL, seed) for seed in range(2)]
+    wants = [_expected(*c) for c in cases]
+    hip = dbsp.load_library()                      # looks up the runtime it is linked to as well
+    for i in range(4):
+        (mask, qkv), want = cases[i % 2], wants[i % 2]
+        out = torch.empty_like(want[0]), torch.empty_like(want[1])
+        plan = _plan(mask)
+        hip.hipSetDevice(1 << 20)                  # refused
+        with pytest.raises(dbsp.DbspError):
+            dbsp.sparse_attn_fwd(plan, *qkv, o=out[0], lse=out[1])
+        if i < 2:
+            dbsp.sparse_attn_fwd(plan, *qkv, o=out[0], lse=out[1])
+            _same(out, want)
+        del plan
+        mask, qkv = cases[1 - i % 2]
+        plan = _plan(mask)
+        _same(dbsp.sparse_attn_fwd(plan, *qkv), wants[1 - i % 2])
+
+
 @pytest.mark.parametrize("H", [SMALL, LARGE])
 def test_a_graph_replayed_at_once_on_another_stream(H):
     """A graph holds nothing that waits for the plan's upload, so the plan has to be there when the capture ends, here
