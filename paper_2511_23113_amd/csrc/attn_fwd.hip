@@ -41,7 +41,19 @@
 //   the matrix pipe busy for 32 clocks and blocks the wave's next MFMA, but not its vector work, for
 //   that long.  Measured on the sequence of a step of 16 MFMAs and 56 vector instructions, one wave:
 //   530 clocks with single MFMAs, 672 with pairs of them, 840 with no interleaving.
-//   LDS operands are read a whole step ahead of their MFMAs.
+//   LDS operands are read a whole step ahead of their MFMAs.  At d = 128 a wave has its SIMD to itself, and
+//   what it issues per 32 clocks beside the MFMA bounds the sequence: six instructions are free, a copy counts as
+//   three to four, a wait for anything is the matrix pipe's wait.  So
+//     * the other work of a slice's two steps is dealt to their sub-slots by table (Cfg): operand reads, copies, their
+//       addresses one sub-slot ahead of them, the barrier;
+//     * the first half of a slice's operands has a second set of registers (24 more at d = 128), so that its
+//       reads need not wait for the last use of the operands before them;
+//     * K Q^T comes before V^T P^T in every pair of sub-slots: a step's softmax then begins two MFMAs behind the
+//       last of the scores' products (with V^T P^T first the compiler has to put 32 clocks of nothing in between);
+//     * the vote on the running max ends a sub-slot before its branch, which otherwise costs 24 clocks a step.
+//   A block of 128 x 128 at d = 128, item ends included: 3065 clocks with the operand reads, the copies and the
+//   barrier in one step of the two, 2700 so (2048 of them MFMA; in isolation the loop takes 2430, its MFMAs and softmax
+//   alone 2072).  40 heads of 256 x 256 blocks: 5838 -> 5538 us; 24 of 928 x 928: 35.1 -> 32.8 ms.
 //   The softmax is speculative: probabilities are formed against the running max as it stands; only
 //   when a unit's per-lane sum of probabilities exceeds SPEC_SUM_LIMIT (some score is far above the
 //   running max) is the unit redone with a raised max and the accumulator rescaled.  That path is kept
@@ -52,9 +64,12 @@
 //   * K and V slices go L2 -> LDS directly (global_load_lds_dwordx4, 16 bytes per lane, no VGPR
 //     staging).  64-token blocks: a wave copies its own slices into its own ring of two and waits for
 //     its own copies only; no barrier couples the two waves until the end of an item.  128-token
-//     blocks: the two waves of a key group share its ring of four slices and copy half of each; one
-//     barrier every second slice publishes the next two slices and retires the last two, whose
-//     positions are refilled in that step and the next (three and two whole steps to land before the next barrier).
+//     blocks: the two waves of a key group share its ring of four slices and copy half of each; a
+//     barrier in the first step of a slice publishes the next one and retires the last, whose
+//     positions are refilled behind it and have the two slices after this one to land (a barrier every second
+//     slice with a wait for all copies gave them two to three steps instead of four).  An item's first slice has its
+//     barrier in its second step, and three slices of copies in front of it, where no softmax runs yet.  The loop goes
+//     once round the ring, so that no address depends on the position.
 //   * A copy instruction occupies its wave for about 18 clocks, so copies are spread over sub-slots.
 //   * LDS tiles are unpadded; 16-byte chunks are XOR-swizzled inside each row instead (the
 //     permutation is applied to the per-lane global source address, the LDS side of the copy
@@ -67,6 +82,7 @@
 #include <cfloat>
 #include <cstdint>
 #include <type_traits>
+#include <utility>
 
 #include "attn_common.hpp"
 #include "fwd_params.hpp"
@@ -100,6 +116,26 @@ struct Cfg {
   static_assert(NQ * XCH <= RING - 2 * SL, "the outboxes must leave the first two K slices alone");
   static_assert(U == 1 || (U == 2 && NQ > 1), "what the step sequence assumes");
   static_assert(NC == 2 || (NC == 4 && TPW == 1), "tile ownership at the end of an item");
+  // The sub-slots of a step (SUB, one MFMA each) and of a slice (two steps) at which its other work is done.
+  // d = 128: eight dealings of reads and copies took 2420 to 2580 clocks a block in isolation, this one 2430; the
+  // barrier stands where the operand reads of the step before have all returned.
+  static constexpr int SUB = 2 * KS;
+  static_assert(NQ == 1 || (4 * LOADS == SUB && LOADS <= 4), "the first step of an item copies four slices");
+  static constexpr int H = NQ > 1 && D == 128 ? KS / 2 : 0;        // operands with two sets of registers
+  static constexpr int BARRIER_AT = 3 * KS / 4;
+  static constexpr int SOFTMAX_END = D == 128 ? 14 : SUB - 1;
+  // exponential of score j
+  static __device__ constexpr int exp_at(int j) { return D == 64 ? j / 2 : j == 0 ? 0 : j < 5 ? (j + 1) / 2 : j - 2; }
+  // operand read k of the first H operands (K, V^T, V^T of each)
+  static __device__ constexpr int read_at(int k) {
+    constexpr int at[12] = {7, 8, 9, 11, 12, 14, 15, 16, 19, 20, 22, 23};
+    return at[k];
+  }
+  static __device__ constexpr int copy_at(int k) {
+    constexpr int at[8] = {10, 13, 17, 18, 21, 24, 26, 28}, at64[4] = {4, 6, 9, 11};
+    if (NQ == 1) return SUB / 2 + k / (4 * LOADS / SUB);
+    return D == 128 ? at[k % 8] : at64[k % 4];
+  }
   // tile k of key group cc: d-tile and query tile
   static __device__ constexpr int tile_dt(int cc, int k) { return NC == 2 ? cc * (DT / 2) + k % (DT / 2) : cc % DT; }
   static __device__ constexpr int tile_qt(int cc, int k) { return NC == 2 ? k / (DT / 2) : cc / DT; }
@@ -107,6 +143,12 @@ struct Cfg {
   static __device__ constexpr bool has_lse(int cc) { return NC == 2 ? cc == 0 : cc % DT == 0; }
   static __device__ constexpr bool lse_tile(int k) { return k % (TPW > 1 ? TPW / 2 : 1) == 0; }
 };
+
+// f(0), ..., f(N - 1), as constants
+template <class F, int... I>
+__device__ __forceinline__ void for_each_of(F& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void for_each(F&& f) { for_each_of(f, std::make_integer_sequence<int, N>{}); }
 
 template <int N>
 __device__ __forceinline__ void wait_copies() {      // all but the N youngest copies of this wave have landed
@@ -225,7 +267,7 @@ __global__ __launch_bounds__(64 * NQ * NC) __attribute__((amdgpu_waves_per_eu(D 
 void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_idx, const int4* __restrict__ g_sched,
                        const int32_t* __restrict__ g_part_ptr) {
   using C = Cfg<D, NQ, NC, U>;
-  constexpr int NB = C::NB;
+  constexpr int NB = C::NB, H = C::H;
   constexpr bool SHARED = NQ > 1;      // the waves of the query groups share the slices' copies
   static_assert(!PAIR || (D == 128 && NQ == 2 && NC == 2 && U == 2), "pair rows: two query blocks, two KV blocks of 64 tokens, d = 128");
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -271,7 +313,6 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     for (int dt = 0; dt < C::DT; ++dt)
       v_rd[dt] = ring + NB * C::SL + key * C::ROW_BYTES + ((((4 * dt) ^ sw) + 2 * hh + (a4 >> 1)) << 4) + (a4 & 1) * 8;
   }
-  [[maybe_unused]] uint32_t k_half = 2 * C::SL, v_half = 2 * C::SL;
   // where this wave's copies come from inside a KV block (pair rows: inside its key group's own block)
   const uint32_t src_off = (PAIR ? 0 : wc * U * C::SL) + share;
   constexpr uint32_t BLOCK_BYTES = PAIR ? U * C::SL : NC * U * C::SL;
@@ -356,7 +397,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   // in the step sequence.
   const unsigned char* from = nullptr;
   auto copy_begin = [&](const unsigned char* base, int J, int u, uint32_t b, int x) {
-    from = base + (int64_t)J * BLOCK_BYTES + u * C::SL + x * 1024;
+    from = base + (int64_t)(SHARED && U == 1 ? __builtin_amdgcn_readfirstlane(J) : J) * BLOCK_BYTES + u * C::SL + x * 1024;
     set_copy_dst(ring + b * C::SL + share + x * 1024);
   };
   auto copy_one = [&](bool is_k, int x) { copy16_nth(x % 4, from, is_k ? k_src[x % C::KVAR] : v_src); };
@@ -484,11 +525,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     if (stores == 1) wait_copies<C::LOADS + 2 * C::TPW>();
     else if (stores == 2) wait_copies<C::LOADS + 8 * C::TPW>();
     else wait_copies<C::LOADS>();
-    if constexpr (SHARED) {
-      __syncthreads();
-      copy_k(kbase, id_of(2 / U), 0, 2);
-      copy_v(vbase, id_of(1 / U), 1 % U, 1);
-    }
+    if constexpr (SHARED) __syncthreads();
 
     f32x16 o[C::DT][2];
 #pragma unroll
@@ -503,45 +540,36 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 
     f32x16 S[2];                  // scores of the last unit of each query tile
     bf16x8 P[2][2];               // [query tile][16-key step]: probabilities, packed as B operands
-    bf16x8 kop[C::KS];            // K operands of the current slice
-    s16x4 vop[C::KS][2];          // V^T operands of the slice before, [16-key step * DT + d-tile]
-
-    auto read_k = [&](int odd, int ks) {      // odd: parity of the slice
-      kop[ks] = as_bf16x8(*(LDS_PTR(u32x4))(uintptr_t)(k_rd[ks] + odd * C::SL));
+    // K operands of the current slice, V^T operands of the slice before ([16-key step * DT + d-tile]).  The first H
+    // of them have two sets of registers, by the parity of their slice.
+    bf16x8 kop[C::KS - H], kop2[2][H > 0 ? H : 1];
+    s16x4 vop[C::KS - H][2], vop2[2][H > 0 ? H : 1][2];
+    auto kop_of = [&](int par, int x) -> bf16x8& { return x < H ? kop2[par][x] : kop[x - H]; };
+    auto vop_of = [&](int par, int x, int hf) -> s16x4& { return x < H ? vop2[par][x][hf] : vop[x - H][hf]; };
+    auto read_k = [&](int at, int ks) {       // at: place of the slice in its ring
+      kop_of(at & 1, ks) = as_bf16x8(*(LDS_PTR(u32x4))(uintptr_t)(k_rd[ks] + at * C::SL));
     };
-    auto read_v = [&](int odd, int x) {       // x = 16-key step * DT + d-tile
-      const uint32_t a = v_rd[x % C::DT] + odd * C::SL + (x / C::DT) * 16 * C::ROW_BYTES;
-      vop[x][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(uintptr_t)(a));
-      vop[x][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(uintptr_t)(a + 8 * C::ROW_BYTES));
-    };
-    // rings of four: reading moves between their halves
-    auto toggle_k = [&]() {
-#pragma unroll
-      for (int ks = 0; ks < C::KS; ++ks) k_rd[ks] += k_half;
-      k_half = 0u - k_half;
-    };
-    auto toggle_v = [&]() {
-#pragma unroll
-      for (int dt = 0; dt < C::DT; ++dt) v_rd[dt] += v_half;
-      v_half = 0u - v_half;
+    auto read_v = [&](int at, int x, int hf) {      // x = 16-key step * DT + d-tile; hf: keys 0 .. 7 or 8 .. 15 of the step
+      const uint32_t a = v_rd[x % C::DT] + at * C::SL + ((x / C::DT) * 16 + hf * 8) * C::ROW_BYTES;
+      vop_of(at & 1, x, hf) = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(uintptr_t)(a));
     };
 
-    // blocks whose copies come next (SHARED: of slices s + 2 .. s + 5 at an even slice s; else of slices s + 1, s + 2)
-    int j2 = id_of(SHARED ? 2 / U : 1), j3 = id_of(3 / U), j4 = j2, j5 = j2;
+    // blocks whose copies come next (SHARED: K of slice s + 4, V of slice s + 3; else of slices s + 2, s + 1)
+    int jk = id_of(SHARED ? 3 / U : 1), jv = jk;
     [[maybe_unused]] bool a_prev = false, a_cur = act_of(0), a_next = act_of(1), a_next2 = false;
 
     // One step: K Q^T of (slice s, tile QT), softmax of the step before, V^T P^T of the step before
-    // that = (slice s-1, tile QT).  Steps with QT = 1 read the operands of K of slice s+1 and V of slice
-    // s.  ODD = s & 1.
-    auto step = [&](int s, auto qt_tag, auto odd_tag, auto qk_tag, auto sm_tag, auto pv_tag) {
-      constexpr int QT = decltype(qt_tag)::value, ODD = decltype(odd_tag)::value;
+    // that = (slice s-1, tile QT).  AT = place of slice s in its ring.  What else the two steps of a slice do is
+    // placed by sub-slot z = 0 .. 2 SUB - 1 of the two.
+    auto step = [&](int s, auto qt_tag, auto at_tag, auto qk_tag, auto sm_tag, auto pv_tag) __attribute__((always_inline)) {
+      constexpr int QT = decltype(qt_tag)::value, AT = decltype(at_tag)::value, ODD = AT & 1;
       constexpr bool QK = decltype(qk_tag)::value, SM = decltype(sm_tag)::value, PV = decltype(pv_tag)::value;
+      constexpr bool FIRST = SHARED && !PV;       // shared slices: the item's first slice
       constexpr int QS = 1 - QT;                  // the softmax stage's tile
       constexpr int UU = U == 2 ? ODD : 0;        // slice s inside its block
-      constexpr bool READ = QK && QT == 1;
+      constexpr int SUB = C::SUB;
       // Softmax of the 16 scores in three stages one sub-slot apart (scaled difference, exponential,
       // sum and packing), so that no instruction waits for the one right before it.
-      constexpr int SUB = 2 * C::KS, PER = 16 / SUB;     // sub-slots (one MFMA each); scores per sub-slot: 2 or 1
       float xs[16], pr[16];
       float ls0 = 0.f, ls1 = 0.f, l_spec = 0.f;
       bool pend = false;
@@ -560,111 +588,98 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
           P[QS][j / 8] = as_bf16x8(pb);
         }
       };
-      auto softmax_sub = [&](int y) {             // y = 0 .. SUB - 1
+      auto softmax_sub = [&](int y) __attribute__((always_inline)) {             // y = 0 .. SUB - 1
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-          const int j = y * PER + k;
-          if (y == 0) stage_x(j);
-          if (y + 1 < SUB) stage_x(j + PER);
-          stage_e(j);
-          if (y > 0) stage_s(j - PER);
+        for (int j = 0; j < 16; ++j) {
+          const int e = C::exp_at(j);
+          if (y == (e > 0 ? e - 1 : 0)) stage_x(j);
+          if (y == e) stage_e(j);
+          if (y == e + 1) stage_s(j);
         }
-        if (y == SUB - 1) {
-#pragma unroll
-          for (int k = 0; k < PER; ++k) stage_s(y * PER + k);
+        if (y == C::SOFTMAX_END) {
+          if (C::exp_at(15) == y) { stage_s(14); stage_s(15); }
           const float ls = ls0 + ls1;
           pend = __builtin_amdgcn_ballot_w64(ls > SPEC_SUM_LIMIT) != 0;
           l_spec = l_run[QS] + ls;
         }
       };
-      // Copies, spread over the step's sub-slots.
-      //   Own slices: in steps with QT = 0, K of slice s+2 and V of slice s+1 into the positions of K of
-      //   slice s and V of slice s-1, whose operands are in registers by the second half of the step.
-      //   Shared slices: behind the barrier of an even slice s, K of slices s+3, s+4 and V of slices s+2,
-      //   s+3 into the positions that barrier has retired: one pair of groups in its own step (A), the
-      //   other in the step after (B): three and two whole steps to land before the next barrier.
-      constexpr bool COPY = QK && (!SHARED ? QT == 0 : (QT == 1 && ODD == 0) || (QT == 0 && ODD == 1));
-      auto copies = [&](int y) {                  // sub-slot y
-        constexpr int GAP = SHARED ? SUB / (2 * C::LOADS) : 1;
-        constexpr int Y0 = SHARED ? 0 : SUB / 2;
-        constexpr int PERY = SHARED ? 1 : 2 * C::LOADS / (SUB - Y0);     // copies per sub-slot that has any
-        static_assert(SHARED ? GAP >= 1 : PERY * (SUB - Y0) == 2 * C::LOADS, "copies spread over whole sub-slots");
-        if (y < Y0 || (y - Y0) % GAP != 0 || (y - Y0) / GAP * PERY >= 2 * C::LOADS) return;
-        if (y == Y0) {
-          if constexpr (!SHARED) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the operand reads of the step before are done
-            j3 = id_of(s + 2);
-          } else if constexpr (QT == 1) {
-            j4 = id_of((s + 4) / U);
-            if constexpr (U == 1) j5 = id_of(s + 5);
-            if constexpr (PAIR) a_next2 = act_of((s + 4) / U);
-          }
-        }
+      // LDS operands: K of slice s + 1 and V of slice s, each into registers whose last use is behind it.
+      auto reads = [&](int y) __attribute__((always_inline)) {
+        const int z = QT * SUB + y;
+        if constexpr (SHARED) {
 #pragma unroll
-        for (int k = 0; k < PERY; ++k) {
-          const int z = (y - Y0) / GAP * PERY + k, x = z % C::LOADS;
-          const bool first = z < C::LOADS;
-          if constexpr (!SHARED) {
-            if (x % 4 == 0) {
-              if (first) copy_begin(kbase, j3, 0, ODD, x);
-              else copy_begin(vbase, j2, 0, NB + 1 - ODD, x);
+          for (int k = 0; k < 3 * H; ++k)
+            if (z == (FIRST ? SUB + k : C::read_at(k))) {
+              if (k % 3 == 0) read_k((AT + 1) % NB, k / 3);
+              else read_v(AT, k / 3, k % 3 - 1);
             }
-            copy_one(first, x);
-          } else if constexpr (QT == 1) {         // group A of even slice s: V of s+2, K of s+3
-            if (x == 0) {
-              if (first) copy_begin(vbase, j2, 0, NB + ((s + 2) & 3), x);
-              else copy_begin(kbase, U == 2 ? j2 : j3, U - 1, (s + 3) & 3, x);
-            }
-            copy_one(!first, x);
-          } else {                                // group B of even slice s-1: K of (s-1)+4, V of (s-1)+3
-            if (x == 0) {
-              if (first) copy_begin(kbase, j4, 0, (s + 3) & 3, x);
-              else copy_begin(vbase, U == 2 ? j2 : j3, U - 1, NB + ((s + 2) & 3), x);
-            }
-            copy_one(first, x);
-          }
         }
-        if ((y - Y0) / GAP * PERY + PERY == 2 * C::LOADS) {      // the last ones of this step
-          if constexpr (!SHARED) j2 = j3;
-          else if constexpr (QT == 0) { j2 = j4; j3 = j5; }
+        if (QT == 1 && y / 2 >= H) {
+          if (y % 2 == 0) read_k((AT + 1) % NB, y / 2);
+          else { read_v(AT, y / 2, 0); read_v(AT, y / 2, 1); }
         }
       };
-      if constexpr (READ) {
-        if constexpr (!SHARED) {
-          wait_copies<2 * C::LOADS>();      // K of slice s+1 and V of slice s have landed; the copies of the step before may be under way
-        } else {
-          // every second slice: K of slices s+1, s+2 and V of slices s, s+1 have landed for everybody, and
-          // everybody has read all before them
-          if constexpr (ODD == 0) {
-            wait_copies<0>();
-            __syncthreads();
-          }
-          if constexpr (ODD == 1) toggle_k();
-          if constexpr (ODD == 0 && PV) toggle_v();
+      // Copies, spread over the steps' sub-slots.
+      //   Own slices: in steps with QT = 0, K of slice s+2 and V of slice s+1 into the positions of K of
+      //   slice s and V of slice s-1, whose operands are in registers by the second half of the step.
+      //   Shared slices: behind the barrier of slice s, K of slice s+4 and V of slice s+3 into the positions of K of
+      //   slice s and V of slice s-1, which that barrier has retired; they have the two slices after this one to land.
+      //   Address and destination of a group are made a sub-slot ahead.
+      auto copies = [&](int y) __attribute__((always_inline)) {                  // sub-slot y
+        const int z = QT * SUB + y;
+        if (FIRST && QT == 0) {                   // K of slices 2 and 3, V of 1 and 2, one copy a sub-slot
+          const int grp = y / C::LOADS, x = y % C::LOADS, sl = grp == 0 ? 2 : grp == 1 ? 1 : grp == 2 ? 3 : 2;
+          const bool is_k = grp % 2 == 0;
+          if (x == 0) copy_begin(is_k ? kbase : vbase, id_of(sl / U), sl % U, is_k ? sl : NB + sl, 0);
+          copy_one(is_k, x);
+          return;
         }
-      }
 #pragma unroll
-      for (int x = 0; x < C::KS; ++x) {
-        if constexpr (PV) {
-          const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vop[x][0], vop[x][1], 0, 1, 2, 3, 4, 5, 6, 7));
+        for (int k = 0; k < 2 * C::LOADS; ++k) {
+          const int x = k % C::LOADS, at = FIRST ? SUB + 2 + k : C::copy_at(k);
+          const bool is_k = k < C::LOADS;
+          if (z == at) copy_one(is_k, x);
+          if (x % 4 == 0 && z == at - 1) {
+            if (k == 0) {
+              if constexpr (!SHARED) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the operand reads of the step before are done
+              jv = jk;
+              if constexpr (U == 1 || ODD == 0) jk = id_of((s + (SHARED ? 4 : 2)) / U);
+              if constexpr (PAIR && ODD == 0) a_next2 = act_of((s + 4) / U);
+            }
+            if (is_k) copy_begin(kbase, jk, UU, SHARED ? AT : ODD, x);
+            else copy_begin(vbase, jv, U == 2 ? 1 - UU : 0, NB + (SHARED ? (AT + 3) % NB : 1 - ODD), x);
+          }
+        }
+      };
+      if constexpr (!SHARED && QK && QT == 1) wait_copies<2 * C::LOADS>();      // K of slice s+1 and V of slice s have landed; the copies of the step before may be under way
+      // K of slice s+1 and V of slice s have landed for everybody (what is younger: the copies of the last two slices),
+      // and everybody has read all before them
+      auto publish = [&](int y) __attribute__((always_inline)) {
+        if (!SHARED || QT != FIRST || y != (FIRST ? 0 : C::BARRIER_AT)) return;
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(4 * C::LOADS) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      };
+      // (by constants, not an unrolled loop: with the tables the loop would be past what the compiler unrolls)
+      for_each<SUB>([&](auto y_tag) __attribute__((always_inline)) {
+        constexpr int y = decltype(y_tag)::value, x = y / 2;
+        if constexpr (y % 2 == 0) {
+          if constexpr (QK) {
+            if constexpr (x == 0) {
+#pragma unroll
+              for (int e = 0; e < 16; ++e) S[QT][e] = 0.f;
+            }
+            S[QT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop_of(ODD, x), q[QT][x], S[QT], 0, 0, 0);
+          }
+        } else if constexpr (PV) {
+          const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vop_of(1 - ODD, x, 0), vop_of(1 - ODD, x, 1), 0, 1, 2, 3, 4, 5, 6, 7));
           o[x % C::DT][QT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, P[QT][x / C::DT], o[x % C::DT][QT], 0, 0, 0);
         }
-        if constexpr (READ) read_v(ODD, x);
-        if constexpr (SM) softmax_sub(2 * x);
-        if constexpr (COPY) copies(2 * x);
+        if constexpr (QK) { publish(y); reads(y); }
+        if constexpr (SM) softmax_sub(y);
+        if constexpr (QK) copies(y);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (QK) {
-          if (x == 0) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) S[QT][e] = 0.f;
-          }
-          S[QT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[x], q[QT][x], S[QT], 0, 0, 0);
-        }
-        if constexpr (READ) read_k(1 - ODD, x);
-        if constexpr (SM) softmax_sub(2 * x + 1);
-        if constexpr (COPY) copies(2 * x + 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      });
       if constexpr (PAIR && QK && QT == 1 && UU == U - 1) { a_prev = a_cur; a_cur = a_next; a_next = a_next2; }   // on to the next block
       if constexpr (SM) {
         asm volatile("" ::"v"(P[QS][0]), "v"(P[QS][1]), "v"(l_spec));
@@ -712,50 +727,57 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     using No = std::false_type;
 #pragma unroll
     for (int x = 0; x < C::KS; ++x) read_k(0, x);
-    auto next_ids = [&](int T) {       // before block ids T (and T + 1) are asked for: they may start a new group of 64
+    auto next_ids = [&](int T) {       // before block id T is asked for: it may start a new group of 64
       if ((T & 63) == 0) {
         set_ids(ids_next, ids, act);
         if (T + 64 < n) ids_next = load_ids(da, T + 64);
       }
     };
+    auto slice = [&](int s, auto at_tag) {       // both steps of a slice
+      step(s, T0{}, at_tag, Yes{}, Yes{}, Yes{});
+      step(s, T1{}, at_tag, Yes{}, Yes{}, Yes{});
+    };
     step(0, T0{}, T0{}, Yes{}, No{}, No{});
     const id_words words_n = load_ids(na, 0);
     step(0, T1{}, T0{}, Yes{}, Yes{}, No{});
+    // The loops go once round a ring, so that places in it are constants.
     int s = 1;
-    if constexpr (U == 2) {
-      step(1, T0{}, T1{}, Yes{}, Yes{}, Yes{});
-      step(1, T1{}, T1{}, Yes{}, Yes{}, Yes{});
-      for (s = 2; s < nS; s += 2) {
-        next_ids(s / 2 + 2);
-        step(s, T0{}, T0{}, Yes{}, Yes{}, Yes{});
-        step(s, T1{}, T0{}, Yes{}, Yes{}, Yes{});
-        step(s + 1, T0{}, T1{}, Yes{}, Yes{}, Yes{});
-        step(s + 1, T1{}, T1{}, Yes{}, Yes{}, Yes{});
+    if constexpr (SHARED) {
+      using T2 = std::integral_constant<int, 2>;
+      using T3 = std::integral_constant<int, 3>;
+      if constexpr (U == 2) slice(s++, T1{});
+      while (s < nS) {
+        if constexpr (U == 1) {
+          slice(s, T1{});
+          if (++s >= nS) break;
+        }
+        slice(s, T2{});
+        if (++s >= nS && U == 1) break;
+        slice(s, T3{});
+        if (++s >= nS) break;
+        next_ids((s + 4) / U);                   // (groups of 64 start at a multiple of four slices)
+        slice(s, T0{});
+        ++s;
+        if constexpr (U == 2) slice(s++, T1{});
       }
     } else {
       for (; s + 1 < nS; s += 2) {
-        if constexpr (!SHARED) next_ids(s + 2);
-        step(s, T0{}, T1{}, Yes{}, Yes{}, Yes{});
-        step(s, T1{}, T1{}, Yes{}, Yes{}, Yes{});
-        next_ids(SHARED ? s + 5 : s + 3);
-        step(s + 1, T0{}, T0{}, Yes{}, Yes{}, Yes{});
-        step(s + 1, T1{}, T0{}, Yes{}, Yes{}, Yes{});
+        next_ids(s + 2);
+        slice(s, T1{});
+        next_ids(s + 3);
+        slice(s + 1, T0{});
       }
-      if (s < nS) {
-        step(s, T0{}, T1{}, Yes{}, Yes{}, Yes{});
-        step(s, T1{}, T1{}, Yes{}, Yes{}, Yes{});
-      }
+      if (s < nS) slice(s, T1{});
     }
     set_ids(words_n, ids_n, act_n);
     const int jn0 = __builtin_amdgcn_readlane(ids_n, 0), jn1 = __builtin_amdgcn_readlane(ids_n, 1 / U);
-    step(nS, T0{}, T0{}, No{}, Yes{}, Yes{});
-    if (more) load_q(head_of(na, nbb), na.y);
-    step(nS, T1{}, T0{}, No{}, No{}, Yes{});
-    // back to the first half of the rings for the next item
-    if constexpr (SHARED) {
-      if ((nS >> 1) & 1) toggle_k();
-      if (((nS - 1) >> 1) & 1) toggle_v();
-    }
+    auto drain = [&](auto at_tag) {
+      step(nS, T0{}, at_tag, No{}, Yes{}, Yes{});
+      if (more) load_q(head_of(na, nbb), na.y);
+      step(nS, T1{}, at_tag, No{}, No{}, Yes{});
+    };
+    if (H > 0 && U == 1 && (nS & 1)) drain(T1{});
+    else drain(T0{});
 
     // ---- end of item: combine the slices' shares of the keys and store.  Wave c finalises TPW of the
     //      accumulator tiles and hands the others to the waves of their slices.
