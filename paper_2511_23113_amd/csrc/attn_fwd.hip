@@ -163,6 +163,13 @@ __device__ __forceinline__ void store_shared(float* to, float a, float b) {
   const uint64_t v = ((uint64_t)__builtin_bit_cast(uint32_t, b) << 32) | __builtin_bit_cast(uint32_t, a);
   __hip_atomic_store(reinterpret_cast<uint64_t*>(to), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Four floats a lane, what a launch behind this one reads: half the instructions (12 heads, 21 x 23 blocks of 128, all
+// rows split: 57.6 -> 56.9 us).  Past the L2s here too: left in them, the launch boundary has to write them back, 58.3
+// us by plain stores, 60.4 by streaming ones.  (The wait state belongs between a store of 16 bytes and the next write
+// to its data's registers, which the compiler cannot see.)
+__device__ __forceinline__ void store_shared(float* to, f32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(to), "v"(v) : "memory");
+}
 __device__ __forceinline__ f32x2 load_shared(const float* from) {
   const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(from), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return f32x2{__builtin_bit_cast(float, (uint32_t)v), __builtin_bit_cast(float, (uint32_t)(v >> 32))};
@@ -182,10 +189,16 @@ __device__ __forceinline__ void store_tile(uint16_t* o, const f32x4 (&res)[4], i
   }
 }
 
-// Where lane l of wave w keeps two floats (and two more 128 on) of tile k of a chunk.
+// Where lane l of wave w keeps two floats (and two more 128 on) of tile k of a chunk; where a launch of its own merges
+// them, there lie four floats a lane side by side instead.
 template <class C>
 __device__ __forceinline__ float* partial_of(float* part_o, int64_t slot_no, int w, int k, int e4, int l) {
   return part_o + (slot_no * C::NW + w) * (C::TPW * 1024) + (k * 4 + e4) * 256 + l * 2;
+}
+
+template <class C>
+__device__ __forceinline__ float* partial4_of(float* part_o, int64_t slot_no, int w, int k, int e4, int l) {
+  return part_o + (slot_no * C::NW + w) * (C::TPW * 1024) + (k * 4 + e4) * 256 + l * 4;
 }
 
 // Is a sum of weights +0?  By its bits: this file is compiled without regard to NaNs, where a comparison of floats
@@ -194,7 +207,7 @@ __device__ __forceinline__ bool is_zero(float x) { return __builtin_bit_cast(uin
 
 // Merges tile k of wave w's share of a split row's chunks, G of them fetched at once, and stores it: token
 // tok, d-tile dt.  qloc: this lane's query inside the row.
-template <class C, int D, int G, bool PAIR>
+template <class C, int D, int G, bool PAIR, bool LATER>
 __device__ __forceinline__ void merge_tile(const dbsp_fwd_params& p, int64_t first, int n_chunks, int w, int k, int l, int qloc,
                                            int64_t tok, int dt, bool with_lse, bool q_there) {
   float m = -INFINITY, tot = 0.f;
@@ -210,8 +223,14 @@ __device__ __forceinline__ void merge_tile(const dbsp_fwd_params& p, int64_t fir
       ls[y] = __hip_atomic_load(p.part_lse + sl * C::QROWS + qloc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
       for (int e4 = 0; e4 < 4; ++e4) {
-        lo[y][e4] = load_shared(partial_of<C>(p.part_o, sl, w, k, e4, l));
-        hi[y][e4] = load_shared(partial_of<C>(p.part_o, sl, w, k, e4, l) + 128);
+        if constexpr (LATER) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(partial4_of<C>(p.part_o, sl, w, k, e4, l));
+          lo[y][e4] = f32x2{v.x, v.y};
+          hi[y][e4] = f32x2{v.z, v.w};
+        } else {
+          lo[y][e4] = load_shared(partial_of<C>(p.part_o, sl, w, k, e4, l));
+          hi[y][e4] = load_shared(partial_of<C>(p.part_o, sl, w, k, e4, l) + 128);
+        }
       }
     }
     float mn = m;
@@ -258,7 +277,7 @@ __global__ __launch_bounds__(64 * NQ * NC) void dbsp_merge_kernel(const dbsp_fwd
   const int32_t* row = p.split_rows + 4 * (blockIdx.x % p.n_split);       // row, first slot, chunks
   const int64_t bh = (int64_t)bb * p.H + row[0] / p.nQ;
   const int first_q = (row[0] % p.nQ) * C::QROWS + 64 * wa, qt = C::tile_qt(wc, k);
-  merge_tile<C, D, 4, PAIR>(p, (int64_t)bb * p.n_slots + row[1], row[2], w, k, l, 64 * wa + 32 * qt + r, bh * p.Nq + first_q + 32 * qt + r,
+  merge_tile<C, D, 4, PAIR, true>(p, (int64_t)bb * p.n_slots + row[1], row[2], w, k, l, 64 * wa + 32 * qt + r, bh * p.Nq + first_q + 32 * qt + r,
                       C::tile_dt(wc, k), C::has_lse(wc) && C::lse_tile(k), !PAIR || first_q < p.Nq);
 }
 
@@ -456,7 +475,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 #pragma unroll
       for (int k = 0; k < C::TPW; ++k) {
         const int qt = tile_qt(WC, k);
-        merge_tile<C, D, 2, PAIR>(p, first, n_chunks, w, k, l, 64 * wa + 32 * qt + r, tok0 + 32 * qt, tile_dt(WC, k), has_lse(WC) && C::lse_tile(k), q_there);
+        merge_tile<C, D, 2, PAIR, false>(p, first, n_chunks, w, k, l, 64 * wa + 32 * qt + r, tok0 + 32 * qt, tile_dt(WC, k), has_lse(WC) && C::lse_tile(k), q_there);
       }
     });
   };
@@ -523,7 +542,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     pin_q();      // the wait for the Q loads belongs here, not at their first use behind later copies
     // the first K slices have landed; the first V slice and the stores of the item before may be under way
     if (stores == 1) wait_copies<C::LOADS + 2 * C::TPW>();
-    else if (stores == 2) wait_copies<C::LOADS + 8 * C::TPW>();
+    else if (stores == 2) wait_copies<C::LOADS + 4 * C::TPW>();      // (or twice as many)
     else wait_copies<C::LOADS>();
     if constexpr (SHARED) __syncthreads();
 
@@ -861,7 +880,10 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
               res[e4].x += y.x * f[cc];  res[e4].y += y.y * f[cc];  res[e4].z += y.z * f[cc];  res[e4].w += y.w * f[cc];
             }
           }
-          if (slot >= 0) {
+          if (slot >= 0 && p.merge_later) {
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) store_shared(partial4_of<C>(p.part_o, ps, w, k, e4, l), res[e4]);
+          } else if (slot >= 0) {
 #pragma unroll
             for (int e4 = 0; e4 < 4; ++e4) {
               store_shared(partial(ps, k, e4), res[e4].x, res[e4].y);

@@ -16,7 +16,7 @@ struct dbsp_fwd_params {
   const int32_t* part_ptr;
   const int32_t* sched;       // 8 x int32 per item: the partitions' lists, then the shared queue: head, row, first KV word, blocks, slot; of split rows also index of the row, its chunks, its first slot
   uint32_t* queue;            // [0] next queue position, [1 + t] times tail item t was taken
-  float* part_o;       // f32 [B][n_slots][BLK][D]
+  float* part_o;       // f32 [B][n_slots][BLK][D], every chunk as its waves' lanes hold it
   float* part_lse;     // f32 [B][n_slots][BLK]
   uint32_t* split_cnt; // [B][n_split][waves of a workgroup] chunks of a split row that are done; zero between launches
   const int32_t* split_rows;  // 4 x int32 per split row: row, first slot, chunks, 0
