@@ -163,12 +163,14 @@ __device__ __forceinline__ void store_shared(float* to, float a, float b) {
   const uint64_t v = ((uint64_t)__builtin_bit_cast(uint32_t, b) << 32) | __builtin_bit_cast(uint32_t, a);
   __hip_atomic_store(reinterpret_cast<uint64_t*>(to), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Four floats a lane, what a launch behind this one reads: half the instructions (12 heads, 21 x 23 blocks of 128, all
-// rows split: 57.6 -> 56.9 us).  Past the L2s here too: left in them, the launch boundary has to write them back, 58.3
-// us by plain stores, 60.4 by streaming ones.  (The wait state belongs between a store of 16 bytes and the next write
-// to its data's registers, which the compiler cannot see.)
+// Four floats a lane, what a launch behind this one reads: half the instructions.  us a pass, 8 / 16 bytes a lane, in one
+// run: d = 64, 6 heads, 84 x 84 blocks of 128 122.0 / 120.3; 64-token blocks at d = 128, 8 heads, 40 x 40 46.7 /
+// 46.1; d = 128, 12 heads, 21 x 23 blocks of 128 56.4 / 55.0.  Past the L2s here too: left in them, the launch boundary has
+// to write them back, and where the last case took 56.9 us by these it took 58.3 by plain stores, 60.4 by streaming ones.
+// gfx950 needs two wait states between a store of more than 8 bytes and the next vector write to its data's registers, and
+// the compiler, which keeps them for its own stores, does not look into an asm block.
 __device__ __forceinline__ void store_shared(float* to, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(to), "v"(v) : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(to), "v"(v) : "memory");
 }
 __device__ __forceinline__ f32x2 load_shared(const float* from) {
   const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(from), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
