@@ -122,6 +122,7 @@ struct Cfg {
   static constexpr int SUB = 2 * KS;
   static_assert(NQ == 1 || (4 * LOADS == SUB && LOADS <= 4), "the first step of an item copies four slices");
   static constexpr int H = NQ > 1 && D == 128 ? KS / 2 : 0;        // operands with two sets of registers
+  static_assert(H == 0 || U == 2, "an item's last slice is an odd one where its operands' set of registers goes by parity");
   static constexpr int BARRIER_AT = 3 * KS / 4;
   static constexpr int SOFTMAX_END = D == 128 ? 14 : SUB - 1;
   // exponential of score j
@@ -792,13 +793,10 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     }
     set_ids(words_n, ids_n, act_n);
     const int jn0 = __builtin_amdgcn_readlane(ids_n, 0), jn1 = __builtin_amdgcn_readlane(ids_n, 1 / U);
-    auto drain = [&](auto at_tag) {
-      step(nS, T0{}, at_tag, No{}, Yes{}, Yes{});
-      if (more) load_q(head_of(na, nbb), na.y);
-      step(nS, T1{}, at_tag, No{}, No{}, Yes{});
-    };
-    if (H > 0 && U == 1 && (nS & 1)) drain(T1{});
-    else drain(T0{});
+    // to drain: where the operands have two sets of registers, the last slice's are in the odd one (see Cfg)
+    step(nS, T0{}, T0{}, No{}, Yes{}, Yes{});
+    if (more) load_q(head_of(na, nbb), na.y);
+    step(nS, T1{}, T0{}, No{}, No{}, Yes{});
 
     // ---- end of item: combine the slices' shares of the keys and store.  Wave c finalises TPW of the
     //      accumulator tiles and hands the others to the waves of their slices.
