@@ -793,10 +793,12 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     }
     set_ids(words_n, ids_n, act_n);
     const int jn0 = __builtin_amdgcn_readlane(ids_n, 0), jn1 = __builtin_amdgcn_readlane(ids_n, 1 / U);
-    // to drain: where the operands have two sets of registers, the last slice's are in the odd one (see Cfg)
-    step(nS, T0{}, T0{}, No{}, Yes{}, Yes{});
-    if (more) load_q(head_of(na, nbb), na.y);
-    step(nS, T1{}, T0{}, No{}, No{}, Yes{});
+    auto drain = [&]() {       // where the operands have two sets of registers, the last slice's are in the odd one (see Cfg)
+      step(nS, T0{}, T0{}, No{}, Yes{}, Yes{});
+      if (more) load_q(head_of(na, nbb), na.y);
+      step(nS, T1{}, T0{}, No{}, No{}, Yes{});
+    };
+    drain();
 
     // ---- end of item: combine the slices' shares of the keys and store.  Wave c finalises TPW of the
     //      accumulator tiles and hands the others to the waves of their slices.
