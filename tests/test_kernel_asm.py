@@ -66,3 +66,10 @@ def test_wide_stores_keep_their_data_as_long_as_the_compiler_does(kernel_listing
     stores = [(blk, i) for blk in asm_blocks(kernel_listing) for i, line in enumerate(blk) if WIDE_STORE.match(line)]
     assert stores
     assert min(nop_states(blk[i:]) for blk, i in stores) >= needed
+
+
+def test_m0_is_the_copies_own(kernel_listing):
+    # a group of copies keeps its LDS destination in M0 across whole steps; its asm blocks set M0, nothing else does
+    set_here = sum("m0" in re.split(r"[ ,\[\]]+", line.split(";")[0]) for blk in asm_blocks(kernel_listing) for line in blk)
+    all_set = sum("m0" in re.split(r"[ ,\[\]]+", line.split(";")[0]) for line in kernel_listing)
+    assert set_here == all_set > 0
