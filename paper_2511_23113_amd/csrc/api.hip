@@ -590,6 +590,7 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   // (the counters of in-place merges are sized for max_batch, and calls that share the static scratch leave
   // nothing behind in it: its split rows are merged by the second launch)
   p.in_place_ok = !static_scratch_wanted && (int64_t)B * hp.n_items() <= hp.P ? 1 : 0;
+  p.by_rounds = hp.by_rounds ? 1 : 0;
   p.merge_later = 0;
   p.busy = dv.busy;
   p.hw_id = dv.hw_id;

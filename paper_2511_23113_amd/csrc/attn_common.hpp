@@ -64,9 +64,9 @@ __device__ __forceinline__ void swap_upper_lower(uint32_t& a, uint32_t& b) {
 // instruction offset applies to both sides, so the copies of one group share a base and an M0.
 // Inline assembly keeps the copies outside the compiler's wait-count bookkeeping: the kernel waits for them itself, by
 // count.  What a wait or a barrier publishes has to be older than the N youngest of the wave's vector memory operations
-// at its s_waitcnt vmcnt(N): where two query groups share their slices, N is 4 x LOADS in front of a slice's barrier, the
-// copies of the last two slices, so every slice has to issue its 2 x LOADS copies, also past the end of the list (other
-// operations among them only make it wait for more).  Between set_copy_dst and the last copy of its group M0 must not
+// at its s_waitcnt vmcnt(N): where two query groups share their slices, N is at most 4 x LOADS in front of a slice's
+// barrier, the copies of the last two slices, so every slice has to issue its 2 x LOADS copies, also past the end of the list
+// (other operations among them only make it wait for more).  Between set_copy_dst and the last copy of its group M0 must not
 // change.  A group goes on over other sub-slots, the end of a step and the redone softmax behind it, and the asm
 // says nothing of M0: the kernels use nothing else that sets it, which a test reads from their listing.
 // No "memory" clobber: LDS reads of the OTHER buffer may be scheduled across a copy.

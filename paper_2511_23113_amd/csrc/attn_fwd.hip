@@ -67,7 +67,8 @@
 //     blocks: the two waves of a key group share its ring of four slices and copy half of each; a
 //     barrier in the first step of a slice publishes the next one and retires the last, whose
 //     positions are refilled behind it and have the two slices after this one to land (a barrier every second
-//     slice with a wait for all copies gave them two to three steps instead of four).  An item's first slice has its
+//     slice with a wait for all copies gave them two to three steps instead of four); where K and V come from behind the
+//     L2s, K has until the next barrier and V until the one after it, see dbsp_launch_fwd.  An item's first slice has its
 //     barrier in its second step, and three slices of copies in front of it, where no softmax runs yet.  The loop goes
 //     once round the ring, so that no address depends on the position.
 //   * A copy instruction occupies its wave for about 18 clocks, so copies are spread over sub-slots.
@@ -124,6 +125,7 @@ struct Cfg {
   static constexpr int H = NQ > 1 && D == 128 ? KS / 2 : 0;        // operands with two sets of registers
   static_assert(H == 0 || U == 2, "an item's last slice is an odd one where its operands' set of registers goes by parity");
   static constexpr int BARRIER_AT = 3 * KS / 4;
+  static constexpr int UNDER_WAY = 4 * LOADS;       // copies that may be under way at a barrier: those of the last two slices
   static constexpr int SOFTMAX_END = D == 128 ? 14 : SUB - 1;
   // exponential of score j
   static __device__ constexpr int exp_at(int j) { return D == 64 ? j / 2 : j == 0 ? 0 : j < 5 ? (j + 1) / 2 : j - 2; }
@@ -284,13 +286,15 @@ __global__ __launch_bounds__(64 * NQ * NC) void dbsp_merge_kernel(const dbsp_fwd
                       C::tile_dt(wc, k), C::has_lse(wc) && C::lse_tile(k), !PAIR || first_q < p.Nq);
 }
 
-template <int D, int NQ, int NC, int U, bool PAIR>
+// SCATTERED: from an item's third slice on, a barrier leaves only the last slice's V under way, see dbsp_launch_fwd.
+template <int D, int NQ, int NC, int U, bool PAIR, bool SCATTERED>
 __global__ __launch_bounds__(64 * NQ * NC) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, D == 64 ? 2 : 1)))
 void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_idx, const int4* __restrict__ g_sched,
                        const int32_t* __restrict__ g_part_ptr) {
   using C = Cfg<D, NQ, NC, U>;
   constexpr int NB = C::NB, H = C::H;
   constexpr bool SHARED = NQ > 1;      // the waves of the query groups share the slices' copies
+  static_assert(!SCATTERED || (SHARED && D == 128), "a barrier's wait, at d = 128");
   static_assert(!PAIR || (D == 128 && NQ == 2 && NC == 2 && U == 2), "pair rows: two query blocks, two KV blocks of 64 tokens, d = 128");
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   __shared__ float xstat[C::NW][4 * 64];
@@ -581,10 +585,10 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     [[maybe_unused]] bool a_prev = false, a_cur = act_of(0), a_next = act_of(1), a_next2 = false;
 
     // One step: K Q^T of (slice s, tile QT), softmax of the step before, V^T P^T of the step before
-    // that = (slice s-1, tile QT).  AT = place of slice s in its ring.  What else the two steps of a slice do is
+    // that = (slice s-1, tile QT).  AT = place of slice s in its ring, WAIT: copies that its barrier leaves under way.  What else the two steps of a slice do is
     // placed by sub-slot z = 0 .. 2 SUB - 1 of the two.
-    auto step = [&](int s, auto qt_tag, auto at_tag, auto qk_tag, auto sm_tag, auto pv_tag) __attribute__((always_inline)) {
-      constexpr int QT = decltype(qt_tag)::value, AT = decltype(at_tag)::value, ODD = AT & 1;
+    auto step = [&](int s, auto qt_tag, auto at_tag, auto wait_tag, auto qk_tag, auto sm_tag, auto pv_tag) __attribute__((always_inline)) {
+      constexpr int QT = decltype(qt_tag)::value, AT = decltype(at_tag)::value, ODD = AT & 1, WAIT = decltype(wait_tag)::value;
       constexpr bool QK = decltype(qk_tag)::value, SM = decltype(sm_tag)::value, PV = decltype(pv_tag)::value;
       constexpr bool FIRST = SHARED && !PV;       // shared slices: the item's first slice
       constexpr int QS = 1 - QT;                  // the softmax stage's tile
@@ -674,11 +678,11 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
         }
       };
       if constexpr (!SHARED && QK && QT == 1) wait_copies<2 * C::LOADS>();      // K of slice s+1 and V of slice s have landed; the copies of the step before may be under way
-      // K of slice s+1 and V of slice s have landed for everybody (what is younger: the copies of the last two slices),
-      // and everybody has read all before them
+      // K of slice s+1 and V of slice s have landed for everybody (what is younger: the copies of the last two slices, of
+      // which the wait may leave fewer), and everybody has read all before them
       auto publish = [&](int y) __attribute__((always_inline)) {
         if (!SHARED || QT != FIRST || y != (FIRST ? 0 : C::BARRIER_AT)) return;
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(4 * C::LOADS) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(WAIT) : "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
       };
@@ -747,6 +751,8 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     using T1 = std::integral_constant<int, 1>;
     using Yes = std::true_type;
     using No = std::false_type;
+    using Early = std::integral_constant<int, C::UNDER_WAY>;
+    using Steady = std::integral_constant<int, SCATTERED ? C::LOADS : C::UNDER_WAY>;
 #pragma unroll
     for (int x = 0; x < C::KS; ++x) read_k(0, x);
     auto next_ids = [&](int T) {       // before block id T is asked for: it may start a new group of 64
@@ -755,19 +761,20 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
         if (T + 64 < n) ids_next = load_ids(da, T + 64);
       }
     };
-    auto slice = [&](int s, auto at_tag) {       // both steps of a slice
-      step(s, T0{}, at_tag, Yes{}, Yes{}, Yes{});
-      step(s, T1{}, at_tag, Yes{}, Yes{}, Yes{});
+    auto slice_of = [&](int s, auto at_tag, auto wait_tag) __attribute__((always_inline)) {       // both steps of a slice
+      step(s, T0{}, at_tag, wait_tag, Yes{}, Yes{}, Yes{});
+      step(s, T1{}, at_tag, wait_tag, Yes{}, Yes{}, Yes{});
     };
-    step(0, T0{}, T0{}, Yes{}, No{}, No{});
+    auto slice = [&](int s, auto at_tag) __attribute__((always_inline)) { slice_of(s, at_tag, Steady{}); };
+    step(0, T0{}, T0{}, Early{}, Yes{}, No{}, No{});
     const id_words words_n = load_ids(na, 0);
-    step(0, T1{}, T0{}, Yes{}, Yes{}, No{});
+    step(0, T1{}, T0{}, Early{}, Yes{}, Yes{}, No{});
     // The loops go once round a ring, so that places in it are constants.
     int s = 1;
     if constexpr (SHARED) {
       using T2 = std::integral_constant<int, 2>;
       using T3 = std::integral_constant<int, 3>;
-      if constexpr (U == 2) slice(s++, T1{});
+      if constexpr (U == 2) slice_of(s++, T1{}, Early{});
       while (s < nS) {
         if constexpr (U == 1) {
           slice(s, T1{});
@@ -794,9 +801,9 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     set_ids(words_n, ids_n, act_n);
     const int jn0 = __builtin_amdgcn_readlane(ids_n, 0), jn1 = __builtin_amdgcn_readlane(ids_n, 1 / U);
     auto drain = [&]() {       // where the operands have two sets of registers, the last slice's are in the odd one (see Cfg)
-      step(nS, T0{}, T0{}, No{}, Yes{}, Yes{});
+      step(nS, T0{}, T0{}, Steady{}, No{}, Yes{}, Yes{});
       if (more) load_q(head_of(na, nbb), na.y);
-      step(nS, T1{}, T0{}, No{}, No{}, Yes{});
+      step(nS, T1{}, T0{}, Steady{}, No{}, No{}, Yes{});
     };
     drain();
 
@@ -928,7 +935,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   }
 }
 
-template <int D, int NQ, int NC, int U, bool PAIR = false>
+template <int D, int NQ, int NC, int U, bool PAIR = false, bool SCATTERED = false>
 hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream) {
   using C = Cfg<D, NQ, NC, U>;
   // Who merges split rows.  In place, the wave that ends a row merges its share, TPW tiles of every chunk one
@@ -947,13 +954,13 @@ hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream) {
   if (e != hipSuccess) return e;
   const uint32_t bit = 1u << (dev & 31);
   if (!(attr_set_mask.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dbsp_fwd_kernel<D, NQ, NC, U, PAIR>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dbsp_fwd_kernel<D, NQ, NC, U, PAIR, SCATTERED>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (e != hipSuccess) return e;
     attr_set_mask.fetch_or(bit, std::memory_order_release);
   }
   const int4* sched = reinterpret_cast<const int4*>(p.sched);
-  hipLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, p, p.kv_idx, sched, p.part_ptr);
+  hipLaunchKernelGGL((dbsp_fwd_kernel<D, NQ, NC, U, PAIR, SCATTERED>), dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, p, p.kv_idx, sched, p.part_ptr);
   e = hipGetLastError();
   if (e != hipSuccess || !p.merge_later) return e;
   const dim3 merge_grid((uint32_t)p.B * (uint32_t)p.n_split, C::TPW);
@@ -965,7 +972,20 @@ hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream) {
 
 hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int grid, hipStream_t stream) {
   if ((block != 64 && block != 128) || (d != 64 && d != 128) || (pair && (block != 64 || d != 128))) return hipErrorInvalidValue;
-  if (pair) return launch_fwd<128, 2, 2, 2, true>(p, grid, stream);
+  // How many copies a slice's barrier leaves under way, at d = 128 and 128-token tiles.  Under a placement without the
+  // rounds' locality K and V come from behind the L2s, and long launches are bound by that: with two slices' copies under
+  // way every second die then gets more of the fabric than its neighbour (busy times 6.2 and 7.0 ms, with the shorter wait
+  // all at 6.6), nothing evens out the end, and the slower dies make the launch longer.  us under the greedy
+  // placement, two slices' copies / one V slice's: 40 heads, 256 x 256 blocks 7755 / 7175; 30 heads, 137 x 137 1450 / 1381;
+  // pair rows, 40 heads, 512 x 512 7460 / 6860 (boxes differ, the least seen was 2 %; 5, 6 or 8 copies in place of 4, or
+  // the short wait at every second slice, keep part of the loss, 2 copies cost 1 - 10 % of other cases).  Where it gains
+  // nothing it costs little: 16 heads, 513 x 513 blocks, 22 a row 1457 / 1475.  Under the rounds' placement two
+  // slices' copies are the better ones: 40 heads, 256 x 256 5646 / 5666, dense 97 x 97 up to 4 %.  An item's first two
+  // slices have their copies in front of them in either case (12 heads, 21 x 23 blocks, 5 an item: 59.3 / 58.9).  d = 64 takes
+  // half the bytes a clock and loses nothing by two slices' copies (40 heads, 256 x 256, greedy: 3932 / 3937).
+  const bool scattered = !p.by_rounds;
+  if (pair) return scattered ? launch_fwd<128, 2, 2, 2, true, true>(p, grid, stream) : launch_fwd<128, 2, 2, 2, true>(p, grid, stream);
   if (block == 64) return d == 128 ? launch_fwd<128, 1, 2, 1>(p, grid, stream) : launch_fwd<64, 1, 2, 1>(p, grid, stream);
-  return d == 128 ? launch_fwd<128, 2, 2, 2>(p, grid, stream) : launch_fwd<64, 2, 4, 1>(p, grid, stream);
+  if (d == 64) return launch_fwd<64, 2, 4, 1>(p, grid, stream);
+  return scattered ? launch_fwd<128, 2, 2, 2, false, true>(p, grid, stream) : launch_fwd<128, 2, 2, 2>(p, grid, stream);
 }

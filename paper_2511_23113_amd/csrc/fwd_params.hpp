@@ -28,6 +28,7 @@ struct dbsp_fwd_params {
   int32_t n_placed;         // items the partitions' lists hold (all of them but the shared queue's)
   int32_t max_chunks;       // the most chunks a split row has; 0: no split rows
   int32_t in_place_ok;      // split_cnt may be used, and there are no more items than partitions, all batch entries counted
+  int32_t by_rounds;        // the plan's placement is the round-based one: neighbouring rows run at a time behind one L2
   int32_t merge_later;      // set by dbsp_launch_fwd: split rows are merged by a kernel of their own behind this one
   float scale;         // softmax scale
   float scale_log2;    // softmax scale * log2(e)

@@ -36,6 +36,7 @@ struct dbsp_host_plan {
   mutable double rho_naive = 1.0, rho_balanced = 1.0;
   mutable bool have_rho_naive = false, have_rho_balanced = false;
   bool reused = false;       // the placement was carried over from a previous plan
+  bool by_rounds = false;    // DBSP_MODE_ROUNDS made the placement (a carried-over one: made the plan it comes from)
   double rho_reuse = 0.0;    // rho_s of this mask under the previous plan's placement (0 if none was tried)
   int64_t n_items() const { return (int64_t)item_slot.size(); }
   int64_t kv_ints() const { return pair ? 2 * nnz : nnz; }   // length of kv_idx

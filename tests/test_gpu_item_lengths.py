@@ -43,14 +43,15 @@ def rel_errors(got, ref, block):
 @pytest.mark.gpu
 @pytest.mark.parametrize("block,d,pair", KERNELS)
 @pytest.mark.parametrize("P", [1, 7])                # one workgroup walks all items one behind the other, or seven share them
-def test_item_lengths(block, d, pair, P):
+@pytest.mark.parametrize("mode", [dbsp.MODE_BALANCED, dbsp.MODE_ROUNDS])       # kernels differ in how long a barrier waits
+def test_item_lengths(block, d, pair, P, mode):
     _, mask = masks_by_length(block, d, pair, P)
     _, nQ, nK = mask.shape
     gen = torch.Generator(device="cuda")
     gen.manual_seed(P)
     q, k = (torch.randn((1, 1, n * block, d), generator=gen, device="cuda").to(torch.bfloat16) for n in (nQ, nK))
     v = (2 * torch.rand((1, 1, nK * block, d), generator=gen, device="cuda") - 1).to(torch.bfloat16)
-    plan = dbsp.plan_sparse_attn(mask, block, num_partitions=P, max_item_len=nK, pair_rows=pair)
+    plan = dbsp.plan_sparse_attn(mask, block, num_partitions=P, max_item_len=nK, pair_rows=pair, mode=mode)
     assert sorted(np.asarray(plan.array(ITEMS)).reshape(-1, 4)[:, 3].tolist()) == sorted(LENGTHS)
     ref_o, ref_l = oa.masked_attention(*(x.float().cpu().numpy() for x in (q, k, v)), mask, block, dtype=np.float32)
     for _ in range(2):
