@@ -53,8 +53,8 @@ enum {
                               of such a plan); the (query block, KV block) combinations of a super block that the
                               mask does not have are computed with the rest and given probability zero, so K and V
                               must be finite in every block that either row of a pair uses.  It pays when neighbouring
-                              rows are alike almost everywhere: from about 0.90 of the flags set (the mask's active
-                              blocks / (4 x the plan's nnz)) it is faster than the plain plan, up to 1.10 times.  DBSP_ROW_CNT /
+                              rows are alike almost everywhere: from about 0.87 of the flags set (the mask's active
+                              blocks / (4 x the plan's nnz)) it is faster than the plain plan, up to 1.11 times.  DBSP_ROW_CNT /
                               ROW_PTR / ITEMS then refer to pair rows (ceil(nQ / 2) per head) and super blocks,
                               and DBSP_KV_IDX holds two int32 per super block: j0, and j1 | flags << 24
                               with flags bit (q + 2k) = "query block 2p+q needs KV block j_k" (a union of odd length
@@ -63,8 +63,8 @@ enum {
                               the library counts the mask both ways and plans with pair rows if at least 5 / 8 of the
                               flags would be set (2 x active blocks >= 5 x super blocks), else plainly;
                               dbsp_plan_pair_rows tells which.  With the present kernels the plain plan is the
-                              faster one up to about 0.90 of the flags: between 5 / 8 and there this choice costs
-                              up to a fifth (8 % at 0.80, 21 % at 0.66), which a program avoids by choosing itself.  plan_sparse_attn_reuse keeps the previous plan's kind */
+                              faster one up to about 0.87 of the flags: between 5 / 8 and there this choice costs
+                              up to a fifth (7 % at 0.80, 20 % at 0.66), which a program avoids by choosing itself.  plan_sparse_attn_reuse keeps the previous plan's kind */
 };
 
 typedef struct dbsp_plan_opts {

@@ -97,7 +97,7 @@ def pair_rows(mask):
 def pair_rows_pay(mask) -> bool:
     """The library's rule for choosing pair rows by itself: at least 5 / 8 of the (query block, KV block)
     combinations of the super blocks are the mask's own, i.e. active blocks / (4 * super blocks) >= 5 / 8,
-    taken in integers.  (The rule the interface states; the break-even against the plain plan lies near 0.90.)"""
+    taken in integers.  (The rule the interface states; the break-even against the plain plan lies near 0.87.)"""
     cnt, _, _ = pair_rows(mask)
     return 2 * int((np.asarray(mask) != 0).sum()) >= 5 * sum(cnt)
 

@@ -388,8 +388,8 @@ static int make_plan(const uint8_t* mask_host, int32_t H, int32_t nQ, int32_t nK
   // DBSP_PLAN_PAIR_AUTO: a chain of plans keeps the first one's choice (items of the two kinds do not
   // match each other); else both counts are taken and pair rows chosen from a flag fill of 5 / 8
   // (2 x the mask's active blocks >= 5 x the super blocks): what the header promises.  It was the break-even while
-  // the kernel of single 64-token rows ran at 0.29 of the peak; at 0.40 to 0.45 that lies near 0.90 (40 heads,
-  // 512 x 512 blocks, single / pair rows: fill 1.00 5.95 / 5.41 ms, 0.80 4.66 / 5.01, 0.66 3.34 / 4.05)
+  // the kernel of single 64-token rows ran at 0.29 of the peak; at 0.40 to 0.45 that lies near 0.87 (40 heads,
+  // 512 x 512 blocks, single / pair rows: fill 1.00 5.98 / 5.38 ms, 0.80 4.69 / 5.00, 0.66 3.36 / 4.05)
   dbsp_host_plan counted;
   bool have_counts = false;
   if (pair_auto) {

@@ -118,8 +118,10 @@ struct Cfg {
   static_assert(U == 1 || (U == 2 && NQ > 1), "what the step sequence assumes");
   static_assert(NC == 2 || (NC == 4 && TPW == 1), "tile ownership at the end of an item");
   // The sub-slots of a step (SUB, one MFMA each) and of a slice (two steps) at which its other work is done.
-  // d = 128: eight dealings of reads and copies took 2420 to 2580 clocks a block in isolation, this one 2430; the
-  // barrier stands where the operand reads of the step before have all returned.
+  // d = 128: eight dealings of reads and copies took 2420 to 2580 clocks a block in isolation.  This one, 2430, ten
+  // off the best, is the one that was timed in the kernel with K Q^T first in every pair.  The barrier stands where the
+  // operand reads of the step before have all returned.  d = 64: the first dealing tried.  64-token blocks' copies in
+  // the second half of a step: four other places took up to 2 % longer.
   static constexpr int SUB = 2 * KS;
   static_assert(NQ == 1 || (4 * LOADS == SUB && LOADS <= 4), "the first step of an item copies four slices");
   static constexpr int H = NQ > 1 && D == 128 ? KS / 2 : 0;        // operands with two sets of registers
@@ -166,10 +168,11 @@ __device__ __forceinline__ void store_shared(float* to, float a, float b) {
   const uint64_t v = ((uint64_t)__builtin_bit_cast(uint32_t, b) << 32) | __builtin_bit_cast(uint32_t, a);
   __hip_atomic_store(reinterpret_cast<uint64_t*>(to), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Four floats a lane, what a launch behind this one reads: half the instructions.  us a pass, 8 / 16 bytes a lane, in one
-// run: d = 64, 6 heads, 84 x 84 blocks of 128 122.0 / 120.3; 64-token blocks at d = 128, 8 heads, 40 x 40 46.7 /
-// 46.1; d = 128, 12 heads, 21 x 23 blocks of 128 56.4 / 55.0.  Past the L2s here too: left in them, the launch boundary has
-// to write them back, and where the last case took 56.9 us by these it took 58.3 by plain stores, 60.4 by streaming ones.
+// Four floats a lane, what a launch behind this one reads: half the instructions.  us a pass, 8 / 16 bytes a lane, in
+// turn: d = 64, 6 heads, 84 x 84 blocks of 128 118.6 / 117.4; 64-token blocks at d = 128, 8 heads, 40 x 40 49.1 / 48.4;
+// d = 128, 2 heads, 97 x 97 blocks of 128 104.7 / 104.1; 12 heads, 21 x 23 no difference.  Past the L2s here too: left in
+// them, the launch boundary has to write them back, and where the last case took 56.9 us by these it took 58.3 by plain
+// stores, 60.4 by streaming ones.
 // gfx950 needs two wait states between a store of more than 8 bytes and the next vector write to its data's registers, and
 // the compiler, which keeps them for its own stores, does not look into an asm block.
 __device__ __forceinline__ void store_shared(float* to, f32x4 v) {
@@ -369,8 +372,9 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 
   // An item overlaps with the end of the one before it in the workgroup's own list: its description, the
   // ids of its first KV blocks, its Q and its first two K slices are fetched while that one drains its
-  // pipeline and stores its result (about 8 thousand clocks less an item; what is left of it, 12 thousand at d = 128 and
-  // 128-token blocks, is 4600 from the exchange to the last store, 2400 - 3900 to drain, 1800 for the first slices).
+  // pipeline and stores its result.  What an item costs besides its blocks, at d = 128 and 128-token blocks: 13 thousand
+  // clocks, of which 1400 - 1800 until its copies are on their way, 900 - 1000 waiting for its first slices, 1800 for the
+  // first slice's steps, 3700 - 3900 to drain and meet, 4500 from the exchange to the last store, 200 at the last barrier.
   int4 da = {}, db = {};         // what the item is, see upload() in api.hip
   int pos = 0, bb = 0;           // its place in the schedule, its batch entry
   int ids = 0;                   // ids of its first 64 KV blocks, one per lane
