@@ -336,8 +336,8 @@ int dbsp_plan_stats(const dbsp_plan* plan, double* rho_naive, double* rho_balanc
                     double* plan_usec);
 
 /* dbsp_plan_calibrate: relative time per block of every partition in the LAST sparse_attn_fwd on this plan,
- * for dbsp_plan_opts.partition_cost of later plans with the same partition count (compute units of one
- * chip differ by a few percent in speed, systematically).  cost: host, int32 [P], written:
+ * for dbsp_plan_opts.partition_cost of later plans with the same mode and partition count (compute units of one
+ * chip differ by a few percent in speed, systematically; a mode settles which of them runs a partition).  cost: host, int32 [P], written:
  * cost[g] = round(1024 * (busy[g] / load[g]) / (sum busy / sum load)) in exact integer arithmetic (round
  * half up), clamped to [512, 2048]; 1024 for a partition without work or measurement.  Synchronises
  * `stream` before reading.  Errors: DBSP_EINVAL (null pointer, host-only plan), DBSP_EHIP. */

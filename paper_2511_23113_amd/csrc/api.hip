@@ -10,6 +10,7 @@
 #include <new>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "dbsp.h"
@@ -241,18 +242,85 @@ int fetch_in_stream(dbsp_device_plan& dv, hipStream_t st) {
   return DBSP_OK;
 }
 
+// What the workgroups of a greedy placement run: where their lists begin, and the lists.  Workgroup b has partition
+// part_of(b)'s items, the longest first, equal ones by their id.  The greedy deals items in
+// that order, one to every partition before anybody gets a second one: run so, all partitions are at items of about the
+// same length at the same time, that is of the few heads whose rows are about that long, and find each other's KV
+// blocks in the L2.  In the lists' own order (head by head) they drift apart by as many heads as a partition has items
+// more or fewer of them than the mean.
+void order_lists(const dbsp_host_plan& hp, const dbsp_device_plan& dv, std::vector<int32_t>& ptr, std::vector<int32_t>& run) {
+  ptr.resize((size_t)hp.P + 1);
+  run.resize(hp.part_items.size());
+  std::vector<int32_t> next(hp.P);            // of every partition: where its next item goes
+  ptr[0] = 0;
+  for (int32_t b = 0; b < hp.P; ++b) {
+    const int32_t g = dv.part_of(b), n = hp.part_ptr[g + 1] - hp.part_ptr[g];
+    next[g] = ptr[b];
+    ptr[b + 1] = ptr[b] + n;
+  }
+  const int32_t n = (int32_t)hp.part_items.size();          // every item: a greedy placement has no queue
+  auto weight = [&](int32_t i) { return hp.items[4 * (size_t)i + 3] - hp.items[4 * (size_t)i + 2]; };
+  int32_t longest = 0;
+  for (int32_t i = 0; i < n; ++i) longest = std::max(longest, weight(i));
+  std::vector<int32_t> first((size_t)longest + 2, 0), part_of(n), sorted(n);
+  for (int32_t g = 0; g < hp.P; ++g)
+    for (int32_t k = hp.part_ptr[g]; k < hp.part_ptr[g + 1]; ++k) part_of[hp.part_items[k]] = g;
+  for (int32_t i = 0; i < n; ++i) ++first[longest - weight(i) + 1];
+  for (int32_t w = 0; w <= longest; ++w) first[w + 1] += first[w];
+  for (int32_t i = 0; i < n; ++i) sorted[first[longest - weight(i)]++] = i;
+  for (int32_t i : sorted) run[next[part_of[i]]++] = i;
+}
+
+// Which partitions share an L2 (see part_of).  Workgroup b runs on compute die b mod 8, and the greedy hands neighbouring items, of
+// one head mostly, to neighbouring partitions, as many in a row as have the same load so far: of its placements every
+// die runs 2^result partitions in a row, an eighth of all where it can.  Partitions differ in load where each has few
+// items (970 rows of 97 blocks on 256: four or three), and then the ones with more lie together: no run is so long that
+// some die gets 3 % more blocks than the mean (those rows, in runs of 1 / 16 / 32: 667 / 692 / 691 us).
+// Both together, us a pass before / the order alone / runs alone / both, in turn, defaults: 30 heads, 137 x 137 blocks of 128 at
+// d = 64, B = 2 1571 / 1552 / 1527 / 1511; 12 heads, 21 x 23 at d = 128 59.5 / 60.0 / 55.4 / 55.2; 40 heads, 256 x 256 6940 /
+// 6645 / 6531 / 6201; 16 heads, 513 x 513, 22 a row 1501 / 1546 / 1419 / 1420; 48 heads, 275 x 275 blocks of 64 at d = 64
+// 1926 / 1767 / 1713 / 1488, 24 heads, 301 x 301 at d = 128 2127 / 1827 / 1962 / 1774.
+// Runs of 2, 4, 8, 16 of the 256 partitions instead of 32, 40 heads, 256 x 256: 6668, 6518, 6506, 6495 / 6474.
+constexpr int kDies = 8;
+int die_run_log2(const dbsp_host_plan& hp, int32_t used_parts) {
+  if (!hp.by_greedy) return 0;
+  int lg = 0;            // (a handful of workgroups has an L2 almost to itself)
+  while (used_parts >= 64 && (int64_t)kDies << (lg + 1) <= used_parts) ++lg;
+  for (; lg > 0; --lg) {
+    int64_t load[kDies] = {}, total = 0;
+    const int32_t mapped = used_parts >> (lg + 3) << (lg + 3);
+    for (int32_t g = 0; g < used_parts; ++g) load[(g < mapped ? g >> lg : g) % kDies] += hp.part_load[g];
+    for (int64_t x : load) total += x;
+    if (100 * kDies * *std::max_element(load, load + kDies) <= 103 * total) break;
+  }
+  return lg;
+}
+
 int upload(dbsp_plan* plan) {
   dbsp_host_plan& hp = plan->host;
   dbsp_device_plan& dv = plan->dev;
-  // what a workgroup needs to know of an item, in the order the partitions' lists (then the shared
-  // queue) hold them: one load instead of a chain through list, item, slot and row offset
+  // what a workgroup needs to know of an item, in the order the workgroups run them (then the shared
+  // queue's): one load instead of a chain through list, item, slot and row offset
   const int64_t n_placed = (int64_t)hp.part_items.size(), n_sched = n_placed + (int64_t)hp.tail_items.size();
   std::vector<int32_t> sched(8 * (size_t)n_sched), slot_row(hp.n_slots);
   const size_t n_split = hp.split_rows.size() / 4;
   for (size_t r = 0; r < n_split; ++r)
     for (int32_t k = 0; k < hp.split_rows[4 * r + 2]; ++k) slot_row[hp.split_rows[4 * r + 1] + k] = (int32_t)r;
+  dv.used_parts = 0;
+  int32_t longest_list = 0;
+  for (int32_t g = 0; g < hp.P; ++g) {
+    const int32_t n = hp.part_ptr[g + 1] - hp.part_ptr[g];
+    longest_list = std::max(longest_list, n);
+    if (n) dv.used_parts = g + 1;
+  }
+  dv.die_run_log2 = die_run_log2(hp, dv.used_parts);
+  std::vector<int32_t> own_ptr, own_run;
+  const bool reorder = hp.by_greedy && (longest_list > 1 || dv.die_run_log2 > 0);
+  if (reorder) order_lists(hp, dv, own_ptr, own_run);
+  const std::vector<int32_t>& part_ptr = reorder ? own_ptr : hp.part_ptr;
+  const std::vector<int32_t>& run = reorder ? own_run : hp.part_items;
   for (int64_t k = 0; k < n_sched; ++k) {
-    const int64_t i = k < n_placed ? hp.part_items[k] : hp.tail_items[k - n_placed];
+    const int64_t i = k < n_placed ? run[k] : hp.tail_items[k - n_placed];
     const int32_t* it = hp.items.data() + 4 * i;
     int32_t* s = sched.data() + 8 * k;
     s[0] = it[0];                                                                                  // head
@@ -265,11 +333,8 @@ int upload(dbsp_plan* plan) {
       s[5] = r; s[6] = hp.split_rows[4 * (size_t)r + 2]; s[7] = hp.split_rows[4 * (size_t)r + 1];  // index of the split row, its chunks, its first slot
     }
   }
-  dv.used_parts = 0;
-  for (int32_t g = 0; g < hp.P; ++g)
-    if (hp.part_ptr[g + 1] > hp.part_ptr[g]) dv.used_parts = g + 1;
   for (size_t r = 0; r < n_split; ++r) dv.max_chunks = std::max(dv.max_chunks, hp.split_rows[4 * r + 2]);
-  const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &hp.part_ptr, &sched, &hp.split_rows};
+  const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &part_ptr, &sched, &hp.split_rows};
   constexpr int NA = 4;
   size_t off[NA + 1];   // in int32 units, each array 16-byte aligned
   off[0] = 0;
@@ -590,7 +655,7 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   // (the counters of in-place merges are sized for max_batch, and calls that share the static scratch leave
   // nothing behind in it: its split rows are merged by the second launch)
   p.in_place_ok = !static_scratch_wanted && (int64_t)B * hp.n_items() <= hp.P ? 1 : 0;
-  p.by_rounds = hp.by_rounds ? 1 : 0;
+  p.local = hp.by_rounds || hp.by_greedy ? 1 : 0;
   p.merge_later = 0;
   p.busy = dv.busy;
   p.hw_id = dv.hw_id;
@@ -737,14 +802,20 @@ int dbsp_plan_busy(const dbsp_plan* plan, uint64_t* busy_ticks, uint32_t* hw_id,
   if (!plan->dev.resident) return fail(DBSP_EINVAL, "dbsp_plan_busy: the plan was built host-only");
   DBSP_HIP(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
   // partitions the last launch had no workgroup for (no items) were idle
-  const int32_t ran = plan->dev.last_grid;
-  if (busy_ticks) {
-    if (ran) DBSP_HIP(hipMemcpy(busy_ticks, plan->dev.busy, ran * sizeof(uint64_t), hipMemcpyDeviceToHost));
-    std::fill(busy_ticks + ran, busy_ticks + plan->host.P, 0);
-  }
-  if (hw_id) {
-    if (ran) DBSP_HIP(hipMemcpy(hw_id, plan->dev.hw_id, ran * sizeof(uint32_t), hipMemcpyDeviceToHost));
-    std::fill(hw_id + ran, hw_id + plan->host.P, 0);
+  const dbsp_device_plan& dv = plan->dev;
+  const int32_t ran = dv.last_grid;
+  try {
+    auto fetch = [&](auto* out, const auto* from) {
+      std::fill(out, out + plan->host.P, 0);
+      std::vector<std::remove_reference_t<decltype(*out)>> by_group(ran);
+      const hipError_t e = ran ? hipMemcpy(by_group.data(), from, ran * sizeof(*out), hipMemcpyDeviceToHost) : hipSuccess;
+      for (int32_t b = 0; b < ran && e == hipSuccess; ++b) out[dv.part_of(b)] = by_group[b];
+      return e;
+    };
+    if (busy_ticks) DBSP_HIP(fetch(busy_ticks, dv.busy));
+    if (hw_id) DBSP_HIP(fetch(hw_id, dv.hw_id));
+  } catch (const std::bad_alloc&) {
+    return fail(DBSP_ENOMEM, "dbsp_plan_busy: out of host memory");
   }
   return DBSP_OK;
 }

@@ -976,18 +976,20 @@ hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream) {
 
 hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair, int grid, hipStream_t stream) {
   if ((block != 64 && block != 128) || (d != 64 && d != 128) || (pair && (block != 64 || d != 128))) return hipErrorInvalidValue;
-  // How many copies a slice's barrier leaves under way, at d = 128 and 128-token tiles.  Under a placement without the
-  // rounds' locality K and V come from behind the L2s, and long launches are bound by that: with two slices' copies under
+  // How many copies a slice's barrier leaves under way, at d = 128 and 128-token tiles.  Under a placement without
+  // locality K and V come from behind the L2s, and long launches are bound by that: with two slices' copies under
   // way every second die then gets more of the fabric than its neighbour (busy times 6.2 and 7.0 ms, with the shorter wait
-  // all at 6.6), nothing evens out the end, and the slower dies make the launch longer.  us under the greedy
-  // placement, two slices' copies / one V slice's: 40 heads, 256 x 256 blocks 7755 / 7175; 30 heads, 137 x 137 1450 / 1381;
-  // pair rows, 40 heads, 512 x 512 7460 / 6860 (boxes differ, the least seen was 2 %; 5, 6 or 8 copies in place of 4, or
-  // the short wait at every second slice, keep part of the loss, 2 copies cost 1 - 10 % of other cases).  Where it gains
-  // nothing it costs little: 16 heads, 513 x 513 blocks, 22 a row 1457 / 1475.  Under the rounds' placement two
-  // slices' copies are the better ones: 40 heads, 256 x 256 5646 / 5666, dense 97 x 97 up to 4 %.  An item's first two
-  // slices have their copies in front of them in either case (12 heads, 21 x 23 blocks, 5 an item: 59.3 / 58.9).  d = 64 takes
-  // half the bytes a clock and loses nothing by two slices' copies (40 heads, 256 x 256, greedy: 3932 / 3937).
-  const bool scattered = !p.by_rounds;
+  // all at 6.6), nothing evens out the end, and the slower dies make the launch longer.  us, two slices' copies / one V
+  // slice's, with the greedy's items in the order of their heads and its partitions dealt to the dies one by one: 40 heads,
+  // 256 x 256 blocks 7755 / 7175; pair rows, 40 heads, 512 x 512 7460 / 6860 (5, 6 or 8 copies in place of 4, or the short wait
+  // at every second slice, keep part of the loss, 2 copies cost 1 - 10 % of other cases).  That is how the naive
+  // and the reward-biased placement still run.  The rounds' and, longest items first and partitions in a row on a die
+  // (see run_order in api.hip), the greedy's run does better with two slices' copies: rounds, 40 heads, 256 x 256 5646 / 5666,
+  // dense 97 x 97 up to 4 %; greedy, 40 heads, 256 x 256 5969 / 6187, 24 heads, 928 x 928 36.9 / 38.0 ms, pair rows, 40 heads, 512 x 512
+  // 5816 / 5933, 16 heads, 513 x 513 1402 / 1410; 12 heads, 21 x 23, 5 blocks an item, 56.2 / 55.8.  An item's first two
+  // slices have their copies in front of them in either case.  d = 64 takes half the bytes a clock and loses nothing by
+  // two slices' copies.
+  const bool scattered = !p.local;
   if (pair) return scattered ? launch_fwd<128, 2, 2, 2, true, true>(p, grid, stream) : launch_fwd<128, 2, 2, 2, true>(p, grid, stream);
   if (block == 64) return d == 128 ? launch_fwd<128, 1, 2, 1>(p, grid, stream) : launch_fwd<64, 1, 2, 1>(p, grid, stream);
   if (d == 64) return launch_fwd<64, 2, 4, 1>(p, grid, stream);

@@ -13,7 +13,7 @@ struct dbsp_fwd_params {
   float* lse;          // f32  [B,H,nQ*BLK] or null
   const int32_t* kv_idx;
   const int32_t* empty_rows;
-  const int32_t* part_ptr;
+  const int32_t* part_ptr;    // [P + 1] where in sched the workgroups' lists begin
   const int32_t* sched;       // 8 x int32 per item: the partitions' lists, then the shared queue: head, row, first KV word, blocks, slot; of split rows also index of the row, its chunks, its first slot
   uint32_t* queue;            // [0] next queue position, [1 + t] times tail item t was taken
   float* part_o;       // f32 [B][n_slots][BLK][D], every chunk as its waves' lanes hold it
@@ -28,7 +28,7 @@ struct dbsp_fwd_params {
   int32_t n_placed;         // items the partitions' lists hold (all of them but the shared queue's)
   int32_t max_chunks;       // the most chunks a split row has; 0: no split rows
   int32_t in_place_ok;      // split_cnt may be used, and there are no more items than partitions, all batch entries counted
-  int32_t by_rounds;        // the plan's placement is the round-based one: neighbouring rows run at a time behind one L2
+  int32_t local;            // rows that share KV blocks run at a time behind one L2: the plan's placement is the round-based or the greedy one
   int32_t merge_later;      // set by dbsp_launch_fwd: split rows are merged by a kernel of their own behind this one
   float scale;         // softmax scale
   float scale_log2;    // softmax scale * log2(e)

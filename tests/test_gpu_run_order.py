@@ -1,0 +1,56 @@
+"""Greedy placements run their partitions' items longest first and give every compute die partitions in a row: which
+workgroup runs what, at partition counts with and without whole runs for every die, against the same items placed naively
+(an item's result does not depend on who computes it, and a split row's chunks are merged in their own order: the outputs
+are the same bits) and against the oracle."""
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import attention as oa
+
+pytestmark = pytest.mark.gpu
+
+O_TOL, LSE_TOL = 1e-2, 1e-3
+
+
+def _run(plan, q, k, v):
+    import torch
+    import paper_2511_23113_amd as dbsp
+    o, lse = dbsp.sparse_attn_fwd(plan, q, k, v)
+    torch.cuda.synchronize()
+    return o.float().cpu().numpy(), lse.cpu().numpy()
+
+
+# 60 rows of up to 13 blocks: equal rows (runs as long as they get, or cut short where the last partitions have an item
+# less), rows of all lengths, empty rows (workgroups behind the last partition that has items)
+@pytest.mark.parametrize("block, d", [(128, 128), (64, 64)])
+@pytest.mark.parametrize("kind", ["equal", "ragged", "empty_rows"])
+@pytest.mark.parametrize("P", [7, 8, 15, 16, 33, 60, 64, 130, 256])
+def test_every_partition_runs_once(block, d, kind, P):
+    import paper_2511_23113_amd as dbsp
+    from paper_2511_23113_amd import binding as B
+    from test_gpu_attention import _dev
+    H, nQ, nK = 3, 20, 13
+    rng = np.random.default_rng(P)
+    keep = {"equal": np.full((H, nQ), 6), "ragged": rng.integers(1, nK + 1, (H, nQ)), "empty_rows": rng.integers(0, 2, (H, nQ)) * 9}[kind]
+    mask = np.zeros((H, nQ, nK), np.uint8)
+    for h in range(H):
+        for i in range(nQ):
+            mask[h, i, rng.permutation(nK)[:keep[h, i]]] = 1
+    qb, kb, vb = (synth.normal_bf16((1, H, n * block, d), s) for n, s in ((nQ, 1), (nK, 2), (nK, 3)))
+    q, k, v = _dev(qb), _dev(kb), _dev(vb)
+    greedy = dbsp.plan_sparse_attn(mask, block, num_partitions=P, max_item_len=5)
+    o, lse = _run(greedy, q, k, v)
+    ticks, _ = greedy.busy()
+    assert np.array_equal(ticks > 0, greedy.array(B.PART_LOAD) > 0)          # a partition's time is its own
+    o0, lse0 = _run(dbsp.plan_sparse_attn(mask, block, num_partitions=P, max_item_len=5, mode=dbsp.MODE_NAIVE), q, k, v)
+    assert np.array_equal(o, o0) and np.array_equal(lse, lse0)
+    kept, _, _ = dbsp.plan_sparse_attn_reuse(greedy, mask, 8.0, max_item_len=5)
+    o1, lse1 = _run(kept, q, k, v)
+    assert np.array_equal(o, o1) and np.array_equal(lse, lse1)
+    if P in (8, 60):
+        Or, Lr = oa.masked_attention(*(synth.bf16_bits_to_f32(x) for x in (qb, kb, vb)), mask, block)
+        some = ~np.isneginf(Lr)
+        assert np.array_equal(~np.isneginf(lse), some)
+        assert np.abs(o - Or).max() <= O_TOL * max(1.0, np.abs(Or).max()) and np.abs(lse[some] - Lr[some]).max() <= LSE_TOL
