@@ -113,7 +113,12 @@ struct Cfg {
   // the others to the waves of the other key groups.  Its outbox lies at the end of its group's ring, clear
   // of the first two K slices, which already belong to the next item by then.
   static constexpr int TPW = 2 * DT / NC, XCH = (NC - 1) * TPW * 4096;
-  static constexpr int LDS_BYTES = NC * RING;
+  // Where the query groups share slices an item's Q comes by way of the LDS, tiles of 32 queries laid out like slices of K:
+  // each wave copies QCP KiB of it.  It lies in the third and fourth K slice of the ring of key group wa, which neither the
+  // next item's first slices nor the outboxes use, or behind the rings.
+  static constexpr int QCP = 2 * SL / 1024 / NC;
+  static constexpr bool Q_IN_RING = NQ * XCH + 4 * SL <= RING && NQ <= NC && NB == 4;
+  static constexpr int LDS_BYTES = NC * RING + (NQ > 1 && !Q_IN_RING ? NQ * 2 * SL : 0);
   static_assert(NQ * XCH <= RING - 2 * SL, "the outboxes must leave the first two K slices alone");
   static_assert(U == 1 || (U == 2 && NQ > 1), "what the step sequence assumes");
   static_assert(NC == 2 || (NC == 4 && TPW == 1), "tile ownership at the end of an item");
@@ -375,6 +380,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   // pipeline and stores its result.  What an item costs besides its blocks, at d = 128 and 128-token blocks: 13 thousand
   // clocks, of which 1400 - 1800 until its copies are on their way, 900 - 1000 waiting for its first slices, 1800 for the
   // first slice's steps, 3700 - 3900 to drain and meet, 4500 from the exchange to the last store, 200 at the last barrier.
+  const unsigned char* from = nullptr;      // of the copies, see copy_begin
   int4 da = {}, db = {};         // what the item is, see upload() in api.hip
   int pos = 0, bb = 0;           // its place in the schedule, its batch entry
   int ids = 0;                   // ids of its first 64 KV blocks, one per lane
@@ -390,6 +396,35 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 #pragma unroll
       for (int ks = 0; ks < C::KS; ++ks) q[qt][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(qrow + 16 * ks + 8 * g));
     }
+  };
+  // The same by way of the LDS: whole rows a KiB at a time, each of them once, where the loads above take 32 bytes of
+  // 32 rows at a time and both (d = 64: all four) waves of a query group take them all: 64 such loads kept the compute unit's
+  // one path to the cache busy for 2 - 3 thousand clocks, at the end of every item.  us with those loads / this way, in turn:
+  // 12 heads, 21 x 23 blocks 53.1 / 50.5, 16 heads, 513 x 513, 22 a row 1349 / 1330, 10 heads, 128 x 256 458 / 454, pair rows, 40
+  // heads, 512 x 512 5402 / 5372, d = 64, 30 heads, 137 x 137, B = 2 1513 / 1498, 40 heads, 256 x 256 5700 / 5686, dense 97 x 97 the same.
+  // 64-token blocks, whose one query group loads each row twice, have no room for it: two (d = 64: four) workgroups' rings
+  // and statistics leave 14 (6) KiB of a compute unit's LDS to each, Q is 16 (8).
+  const uint32_t q_at = SHARED ? lds_base + (C::Q_IN_RING ? wa * C::RING + 2 * C::SL : NC * C::RING + wa * 2 * C::SL) : 0u;
+  auto copy_q = [&](int64_t bh, int I) {
+    int first = I * C::QROWS + 64 * wa;
+    if (PAIR && first >= p.Nq) first = I * C::QROWS;
+    const unsigned char* rows = reinterpret_cast<const unsigned char*>(p.q + (bh * p.Nq + first) * D) + wc * C::QCP * 1024;
+#pragma unroll
+    for (int x = 0; x < C::QCP; ++x) {
+      if (x % 4 == 0) {
+        from = rows + x * 1024;
+        set_copy_dst(q_at + wc * C::QCP * 1024 + x * 1024);
+      }
+      copy16_nth(x % 4, from, k_src[x % C::KVAR]);
+    }
+  };
+  const bool q_by_lds = SHARED && (reinterpret_cast<uintptr_t>(p.q) & 15) == 0;     // (plain loads take any address)
+  auto read_q = [&]() {
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+      for (int ks = 0; ks < C::KS; ++ks)
+        q[qt][ks] = as_bf16x8(*(LDS_PTR(u32x4))(uintptr_t)(k_rd[ks] - ring + q_at + qt * C::SL));
   };
   auto pin_q = [&]() {
 #pragma unroll
@@ -425,7 +460,6 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   // KiB by KiB: begin() once (destination and base), then one() for x = 0 .. LOADS - 1.  Past the end of
   // the list the last block is copied again, into positions nobody reads: that costs less than a branch
   // in the step sequence.
-  const unsigned char* from = nullptr;
   auto copy_begin = [&](const unsigned char* base, int J, int u, uint32_t b, int x) {
     from = base + (int64_t)(SHARED && U == 1 ? __builtin_amdgcn_readfirstlane(J) : J) * BLOCK_BYTES + u * C::SL + x * 1024;
     set_copy_dst(ring + b * C::SL + share + x * 1024);
@@ -533,10 +567,25 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     auto id_of = [&](int T) { return __builtin_amdgcn_readlane(ids, T & 63); };
     auto act_of = [&](int T) { return ((act >> (T & 63)) & 1) != 0; };
     if (!ready) {
+      if (q_by_lds) copy_q(bh, I);
       copy_k(kbase, id_of(0), 0, 0);
       copy_k(kbase, id_of(1 / U), 1 % U, 1);
-      load_q(bh, I);
-      pin_q();      // (waited for where nothing else is under way, see the ids)
+      if constexpr (!SHARED) {
+        load_q(bh, I);
+        pin_q();      // (waited for where nothing else is under way, see the ids)
+      } else {
+        wait_copies<2 * C::LOADS>();
+        __syncthreads();
+        stores = 0;      // the first K slices are younger than any
+      }
+    }
+    if constexpr (SHARED) {
+      if (q_by_lds) {
+        read_q();
+      } else {
+        load_q(bh, I);
+        pin_q();
+      }
     }
     id_words ids_next = {0, 0};
     if (n > 64) ids_next = load_ids(da, 64);
@@ -806,17 +855,20 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     const int jn0 = __builtin_amdgcn_readlane(ids_n, 0), jn1 = __builtin_amdgcn_readlane(ids_n, 1 / U);
     auto drain = [&]() {       // where the operands have two sets of registers, the last slice's are in the odd one (see Cfg)
       step(nS, T0{}, T0{}, Steady{}, No{}, Yes{}, Yes{});
-      if (more) load_q(head_of(na, nbb), na.y);
+      if constexpr (!SHARED) {
+        if (more) load_q(head_of(na, nbb), na.y);
+      }
       step(nS, T1{}, T0{}, Steady{}, No{}, No{}, Yes{});
     };
     drain();
 
     // ---- end of item: combine the slices' shares of the keys and store.  Wave c finalises TPW of the
     //      accumulator tiles and hands the others to the waves of their slices.
-    if (more) wait_copies<2 * C::KS>();       // all copies; the loads of the next item's Q may be under way
+    if (!SHARED && more) wait_copies<2 * C::KS>();       // all copies; the loads of the next item's Q may be under way
     else wait_copies<0>();
     if constexpr (SHARED) __syncthreads();    // everybody is done with the slices: the rings become the exchange area
     if (more) {
+      if (q_by_lds) copy_q(head_of(na, nbb), na.y);
       const unsigned char* kb = k_of(head_of(na, nbb));
       copy_k(kb, jn0, 0, 0);
       copy_k(kb, jn1, 1 % U, 1);
@@ -916,6 +968,11 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
       }
     };
     by_key_group(finish);
+    if constexpr (SHARED) {     // the next item's Q has landed; its first K slices and the stores may be under way
+      if (slot >= 0) wait_copies<2 * C::LOADS + 4 * C::TPW>();
+      else if (q_there) wait_copies<2 * C::LOADS + 2 * C::TPW>();
+      else wait_copies<2 * C::LOADS>();
+    }
     __syncthreads();      // the exchange has been read before the next item's copies overwrite it
     if (slot >= 0 && !p.merge_later) merge_if_last();
     stores = slot >= 0 ? 2 : q_there ? 1 : 0;

@@ -85,3 +85,29 @@ def test_one_wrong_slice_of_v_is_seen_at_every_length(block, d, pair):
             wrong[0, 0, last * block + lo:last * block + hi] = v[0, 0, other * block + lo:other * block + hi]
             got, _ = oa.masked_attention_rows(q, k, wrong, mask, block, [(0, 0, per_item * i + y) for y in range(per_item)], dtype=np.float32)
             assert rel_errors(got, ref[i], block).max() > 2 * O_REL_TOL, (n, lo)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("block,d,pair", [(128, 128, False), (64, 128, True)])
+@pytest.mark.parametrize("P", [1, 7])
+def test_item_lengths_under_a_placement_without_locality(block, d, pair, P):         # the kernels of the shorter wait
+    test_item_lengths(block, d, pair, P, dbsp.MODE_NAIVE)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("block, d, pair", [(128, 128, False), (128, 64, False), (64, 128, True), (64, 64, False)])
+@pytest.mark.parametrize("offset", [1, 2, 4, 8])
+def test_queries_at_any_address(block, d, pair, offset):
+    # Q goes through the LDS where its address is a multiple of 16 bytes, else straight to registers: the same bits
+    H, nQ, nK = 2, 5, 7
+    rng = np.random.default_rng(offset)
+    mask = (rng.random((H, nQ, nK)) < 0.6).astype(np.uint8)
+    q = torch.randn((1, H, nQ * block, d), device="cuda").to(torch.bfloat16)
+    k, v = (torch.randn((1, H, nK * block, d), device="cuda").to(torch.bfloat16) for _ in range(2))
+    moved = torch.empty(q.numel() + offset, device="cuda", dtype=torch.bfloat16)[offset:].view(q.shape)
+    moved.copy_(q)
+    for kw in (dict(num_partitions=2), dict(num_partitions=3, mode=dbsp.MODE_ROUNDS, dynamic_tail=400), dict(num_partitions=64, max_item_len=2)):
+        plan = dbsp.plan_sparse_attn(mask, block, pair_rows=pair, **kw)
+        o, lse = dbsp.sparse_attn_fwd(plan, q, k, v)
+        om, lsem = dbsp.sparse_attn_fwd(plan, moved, k, v, o=torch.empty_like(q), lse=torch.empty_like(lse))
+        assert torch.equal(o, om) and torch.equal(lse, lsem)
