@@ -73,3 +73,13 @@ def test_m0_is_the_copies_own(kernel_listing):
     set_here = sum("m0" in re.split(r"[ ,\[\]]+", line.split(";")[0]) for blk in asm_blocks(kernel_listing) for line in blk)
     all_set = sum("m0" in re.split(r"[ ,\[\]]+", line.split(";")[0]) for line in kernel_listing)
     assert set_here == all_set > 0
+
+
+def test_a_slices_barrier_waits_for_reads_and_copies(kernel_listing):
+    # by a builtin, in front of the builtin barrier: nothing but the markers of empty asm blocks stands between the two
+    code = [line for line in kernel_listing if line and not line.startswith(";")]
+    waits = [line for line, after in zip(code, code[1:]) if after == "s_barrier" and re.match(r"s_waitcnt vmcnt\(\d+\) lgkmcnt\(0\)$", line)]
+    # an item's first two slices and a round of the ring: two kernels at d = 128 with the longer wait throughout, two with
+    # the shorter one (4) in the ring; at d = 64 one kernel, its first slice and a round
+    for n, at_least in ((16, 2 * 6 + 2 * 2), (4, 2 * 4), (8, 1 + 4)):
+        assert waits.count(f"s_waitcnt vmcnt({n}) lgkmcnt(0)") >= at_least
