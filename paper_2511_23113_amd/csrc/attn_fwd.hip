@@ -160,6 +160,13 @@ __device__ __forceinline__ void for_each_of(F& f, std::integer_sequence<int, I..
 template <int N, class F>
 __device__ __forceinline__ void for_each(F&& f) { for_each_of(f, std::make_integer_sequence<int, N>{}); }
 
+// a < b ? x : y, all of them the wave's own (the compiler makes a branch of it)
+__device__ __forceinline__ const unsigned char* if_less(int a, int b, const unsigned char* x, const unsigned char* y) {
+  const unsigned char* z;
+  asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b64 %0, %3, %4" : "=s"(z) : "s"(a), "s"(b), "s"(x), "s"(y) : "scc");
+  return z;
+}
+
 // The same, and all LDS reads have returned.  By the builtin, whose meaning the compiler knows: behind an asm block it waits for
 // these reads again, operand by operand, nine instructions of a slice's two hundred.  us by asm / by the builtin: pair rows, 40
 // heads, 512 x 512 blocks 5338 / 5285, 24 heads, 301 x 301 blocks of 64 at d = 128 992 / 987, 40 heads, 256 x 256 of 128 5579 / 5556,
@@ -416,10 +423,15 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   // 64-token blocks, whose one query group loads each row twice, have no room for it: two (d = 64: four) workgroups' rings
   // and statistics leave 14 (6) KiB of a compute unit's LDS to each, Q is 16 (8).
   const uint32_t q_at = SHARED ? lds_base + (C::Q_IN_RING ? wa * C::RING + 2 * C::SL : NC * C::RING + wa * 2 * C::SL) : 0u;
-  auto copy_q = [&](int64_t bh, int I) {
-    int first = I * C::QROWS + 64 * wa;
+  auto q_rows = [&](int64_t bh, int I, int group) {      // pair rows: some valid ones in the place of a block that is not there
+    int first = I * C::QROWS + 64 * group;
     if (PAIR && first >= p.Nq) first = I * C::QROWS;
-    const unsigned char* rows = reinterpret_cast<const unsigned char*>(p.q + (bh * p.Nq + first) * D) + wc * C::QCP * 1024;
+    return reinterpret_cast<const unsigned char*>(p.q + (bh * p.Nq + first) * D);
+  };
+  // this wave's share of Q as if it were K: key group wc takes query group wc's rows
+  auto q_of = [&](int64_t bh, int I) { return q_rows(bh, I, wc) + share; };
+  auto copy_q = [&](int64_t bh, int I) {
+    const unsigned char* rows = q_rows(bh, I, wa) + wc * C::QCP * 1024;
 #pragma unroll
     for (int x = 0; x < C::QCP; ++x) {
       if (x % 4 == 0) {
@@ -538,6 +550,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   int own_i = 0, own_b = n_own > 0 ? 0 : p.B;      // own list: position and batch entry of the current item (p.B: done)
   bool first_take = true;
   bool ready = false;            // the item's ids are there, its Q and first K slices on their way
+  bool landed = false;           // and these have arrived, Q in its registers
   int stores = 0;                // what the item before stored: 1 = TPW tiles of O, 2 = a chunk's partial result, 0 = maybe nothing
   for (;;) {
     if (!ready) {
@@ -590,7 +603,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
         stores = 0;      // the first K slices are younger than any
       }
     }
-    if constexpr (SHARED) {
+    if (SHARED && !landed) {
       if (q_by_lds) {
         read_q();
       } else {
@@ -609,13 +622,21 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     int ids_n = 0;
     uint64_t act_n = ~0ull;
     copy_v(vbase, id_of(0), 0, 0);
+    // 128-token tiles at d = 128: the next item's first block of K, and its Q as if it were the second, take the places of the
+    // copies past the end of this one's list, so that they land while it still runs and Q is read in front of the item's
+    // last barrier: 1 us of the 6 us an item took besides its steps.  us without / with it: 16 heads, 513 x 513 blocks, 22
+    // a row 1329 / 1312, 12 heads, 21 x 23 51.5 / 50.4, 40 heads, 256 x 256 5569 / 5566, dense 97 x 97 no difference.  Not for
+    // items of one or two blocks, whose first copies are past their end already.
+    const bool in_flow = U == 2 && more && n >= 3 && q_by_lds;
 
     pin_q();      // the wait for the Q loads belongs here, not at their first use behind later copies
     // the first K slices have landed; the first V slice and the stores of the item before may be under way
-    if (stores == 1) wait_copies<C::LOADS + 2 * C::TPW>();
-    else if (stores == 2) wait_copies<C::LOADS + 4 * C::TPW>();      // (or twice as many)
-    else wait_copies<C::LOADS>();
-    if constexpr (SHARED) __syncthreads();
+    if (!landed) {
+      if (stores == 1) wait_copies<C::LOADS + 2 * C::TPW>();
+      else if (stores == 2) wait_copies<C::LOADS + 4 * C::TPW>();      // (or twice as many)
+      else wait_copies<C::LOADS>();
+      if constexpr (SHARED) __syncthreads();
+    }
 
     f32x16 o[C::DT][2];
 #pragma unroll
@@ -646,6 +667,9 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 
     // blocks whose copies come next (SHARED: K of slice s + 4, V of slice s + 3; else of slices s + 2, s + 1)
     int jk = id_of(SHARED ? 3 / U : 1), jv = jk;
+    // (U == 2) the block whose two slices of K are copied next, and what comes in the places of the first two past the
+    // end of the list
+    [[maybe_unused]] const unsigned char *k_next = nullptr, *k_past = nullptr, *past[2] = {kbase + (int64_t)id_of(0) * BLOCK_BYTES, kbase + (int64_t)id_of(0) * BLOCK_BYTES};
     [[maybe_unused]] bool a_prev = false, a_cur = act_of(0), a_next = act_of(1), a_next2 = false;
 
     // One step: K Q^T of (slice s, tile QT), softmax of the step before, V^T P^T of the step before
@@ -724,6 +748,18 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
           copy_one(is_k, x);
           return;
         }
+        if constexpr (U == 2) {                   // the block of K of slice s + 4, a little at a time; V's is one behind
+          const int T = (s + 4) / 2;
+          if (z == (FIRST ? SUB : 1)) {
+            jv = jk;
+            if constexpr (ODD == 0) jk = id_of(T);
+          }
+          if constexpr (ODD == 0) {
+            if (z == (FIRST ? SUB : 2)) k_next = kbase + (int64_t)jk * BLOCK_BYTES;
+            if (!FIRST && z == 3) k_past = if_less(T, n + 1, past[0], past[1]);
+            if (!FIRST && z == 4) k_next = if_less(T, n, k_next, k_past);
+          }
+        }
 #pragma unroll
         for (int k = 0; k < 2 * C::LOADS; ++k) {
           const int x = k % C::LOADS, at = FIRST ? SUB + 2 + k : C::copy_at(k);
@@ -732,11 +768,14 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
           if (x % 4 == 0 && z == at - 1) {
             if (k == 0) {
               if constexpr (!SHARED) wait_reads<63>();    // the operand reads of the step before are done
-              jv = jk;
-              if constexpr (U == 1 || ODD == 0) jk = id_of((s + (SHARED ? 4 : 2)) / U);
+              if constexpr (U == 1) {
+                jv = jk;
+                jk = id_of(s + (SHARED ? 4 : 2));
+              }
               if constexpr (PAIR && ODD == 0) a_next2 = act_of((s + 4) / U);
             }
-            if (is_k) copy_begin(kbase, jk, UU, SHARED ? AT : ODD, x);
+            if (is_k && U == 2) copy_begin(k_next, 0, UU, AT, x);
+            else if (is_k) copy_begin(kbase, jk, UU, SHARED ? AT : ODD, x);
             else copy_begin(vbase, jv, U == 2 ? 1 - UU : 0, NB + (SHARED ? (AT + 3) % NB : 1 - ODD), x);
           }
         }
@@ -832,13 +871,20 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     auto slice = [&](int s, auto at_tag) __attribute__((always_inline)) { slice_of(s, at_tag, Steady{}); };
     step(0, T0{}, T0{}, Early{}, Yes{}, No{}, No{});
     const id_words words_n = load_ids(na, 0);
+    const id_words first_n = {g_kv_idx[na.z], PAIR ? g_kv_idx[na.z + 1] : 0};
     step(0, T1{}, T0{}, Early{}, Yes{}, Yes{}, No{});
     // The loops go once round a ring, so that places in it are constants.
     int s = 1;
     if constexpr (SHARED) {
       using T2 = std::integral_constant<int, 2>;
       using T3 = std::integral_constant<int, 3>;
-      if constexpr (U == 2) slice_of(s++, T1{}, Early{});
+      if constexpr (U == 2) {
+        slice_of(s++, T1{}, Early{});
+        if (in_flow) {       // an even number of blocks: the third and fourth slice's places come second
+          past[n & 1] = k_of(head_of(na, nbb)) + (int64_t)(PAIR && wc ? first_n.w1 & 0xffffff : first_n.w0) * BLOCK_BYTES;
+          past[1 - (n & 1)] = q_of(head_of(na, nbb), na.y);
+        }
+      }
       while (s < nS) {
         if constexpr (U == 1) {
           slice(s, T1{});
@@ -878,7 +924,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     if (!SHARED && more) wait_copies<2 * C::KS>();       // all copies; the loads of the next item's Q may be under way
     else wait_copies<0>();
     if constexpr (SHARED) __syncthreads();    // everybody is done with the slices: the rings become the exchange area
-    if (more) {
+    if (more && !in_flow) {
       if (q_by_lds) copy_q(head_of(na, nbb), na.y);
       const unsigned char* kb = k_of(head_of(na, nbb));
       copy_k(kb, jn0, 0, 0);
@@ -979,7 +1025,10 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
       }
     };
     by_key_group(finish);
-    if constexpr (SHARED) {     // the next item's Q has landed; its first K slices and the stores may be under way
+    if (in_flow) {
+      read_q();
+      pin_q();
+    } else if constexpr (SHARED) {     // the next item's Q has landed; its first K slices and the stores may be under way
       if (slot >= 0) wait_copies<2 * C::LOADS + 4 * C::TPW>();
       else if (q_there) wait_copies<2 * C::LOADS + 2 * C::TPW>();
       else wait_copies<2 * C::LOADS>();
@@ -988,6 +1037,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
     if (slot >= 0 && !p.merge_later) merge_if_last();
     stores = slot >= 0 ? 2 : q_there ? 1 : 0;
     ready = more;
+    landed = in_flow;
     if (more) {
       pos = npos;
       da = na;
