@@ -54,7 +54,12 @@ constexpr int kMaxWaves = 8;     // waves of the largest workgroup: a split row 
 // step stays that many steps ahead of the GPU, which hides the planning, and the pools can hold all the buffers
 // in flight; a host further ahead would gain nothing and allocate (40 heads, 256 x 256 blocks, 5 to 60 % of them active: 350 us more per step of 5840 with 16 let ahead and pools of 8).
 struct BufferPool {
-  struct Entry { void* ptr; size_t bytes; int device; };
+  struct Entry {
+    void* ptr;
+    size_t bytes;
+    int device;
+    bool front_zero;               // device buffers: the first kFrontBytes are zero, see forward()
+  };
   size_t max_cached;
   std::vector<Entry> free_list;
 };
@@ -122,7 +127,7 @@ void release(const Surplus& surplus) {
   for (void* p : surplus.pin) (void)hipHostFree(p);
 }
 
-hipError_t pool_get(BufferPool& pool, bool pinned, int device, size_t bytes, void** out, size_t* cap) {
+hipError_t pool_get(BufferPool& pool, bool pinned, int device, size_t bytes, void** out, size_t* cap, bool* front_zero = nullptr) {
   Surplus surplus;
   bool found = false;
   {
@@ -136,6 +141,7 @@ hipError_t pool_get(BufferPool& pool, bool pinned, int device, size_t bytes, voi
     if (best >= 0) {
       *out = pool.free_list[best].ptr;
       *cap = pool.free_list[best].bytes;
+      if (front_zero) *front_zero = pool.free_list[best].front_zero;
       pool.free_list.erase(pool.free_list.begin() + best);
       found = true;
     }
@@ -162,7 +168,8 @@ hipError_t upload_stream(int device, hipStream_t* out) {
 
 // Hands the plan's buffers back once its events have passed: waits for them, or leaves them to later calls.
 void free_device(dbsp_device_plan& d, bool wait) {
-  Retired r = {std::this_thread::get_id(), {nullptr, nullptr}, {d.blob, d.blob_bytes, d.device}, {{d.staging, d.staging_bytes, d.device}, {d.staging_kv, d.staging_kv_bytes, d.device}}};
+  Retired r = {std::this_thread::get_id(), {nullptr, nullptr}, {d.blob, d.blob_bytes, d.device, d.sent || d.front_zero},
+               {{d.staging, d.staging_bytes, d.device, false}, {d.staging_kv, d.staging_kv_bytes, d.device, false}}};
   if (d.last_use) {
     if (d.used) r.events[0] = static_cast<hipEvent_t>(d.last_use);
     else (void)hipEventDestroy(static_cast<hipEvent_t>(d.last_use));
@@ -225,7 +232,8 @@ int send_upload(dbsp_device_plan& dv) {
 // not sent here: its first forward launch is preceded, on its own stream, by a kernel that fetches the
 // plan from the pinned buffers (64 KiB take it about 3 us).  Two streams and the wait between them cost the
 // host 12 us and more; for larger plans they let the copy run beside the kernels before it.
-constexpr size_t kInStreamBytes = size_t(64) << 10;
+constexpr size_t kFrontBytes = size_t(4) << 10;      // of every plan's device buffer: counters, zero between launches
+constexpr size_t kInStreamBytes = (size_t(64) << 10) + kFrontBytes;
 
 __global__ __launch_bounds__(256) void dbsp_fetch_kernel(uint4* __restrict__ dst, const uint4* __restrict__ a, uint32_t na, const uint4* __restrict__ b, uint32_t n) {
   for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = i < na ? a[i] : b[i - na];
@@ -337,15 +345,18 @@ int upload(dbsp_plan* plan) {
   const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &part_ptr, &sched, &hp.split_rows};
   constexpr int NA = 4;
   size_t off[NA + 1];   // in int32 units, each array 16-byte aligned
-  off[0] = 0;
+  off[0] = kFrontBytes / sizeof(int32_t);
   for (int i = 0; i < NA; ++i) off[i + 1] = off[i] + ((arrays[i]->size() + 3) & ~size_t(3));
   const size_t ints_bytes = off[NA] * sizeof(int32_t);
   const size_t busy_off = (ints_bytes + 255) & ~size_t(255);
   const size_t hw_off = busy_off + (((size_t)hp.P * sizeof(uint64_t) + 255) & ~size_t(255));
   // shared queue of the dynamic tail: [0] next position, then one take count per tail item; then the split rows' counters
+  // where the front does not hold them
   const size_t queue_off = hw_off + (((size_t)hp.P * sizeof(uint32_t) + 255) & ~size_t(255));
   const size_t cnt_off = queue_off + (((1 + hp.tail_items.size()) * sizeof(uint32_t) + 255) & ~size_t(255));
-  dv.up_bytes = cnt_off + (((size_t)dv.max_batch * n_split * kMaxWaves * sizeof(uint32_t) + 255) & ~size_t(255));   // staged part ends here
+  const size_t cnt_bytes = (size_t)dv.max_batch * n_split * kMaxWaves * sizeof(uint32_t);
+  const bool cnt_in_front = cnt_bytes <= kFrontBytes;
+  dv.up_bytes = cnt_off + (cnt_in_front ? 0 : (cnt_bytes + 255) & ~size_t(255));   // staged part ends here
   const size_t up_bytes = dv.up_bytes, kv_off = up_bytes;
   const size_t kv_bytes = dv.kv_bytes = (size_t)hp.kv_ints() * sizeof(int32_t);
   // split-row scratch for max_batch batch entries at d = 128
@@ -355,7 +366,7 @@ int upload(dbsp_plan* plan) {
   const size_t total = po_off + (size_t)rows * 128 * sizeof(float);
 
   void* blob = nullptr;
-  hipError_t e = pool_get(g_dev_pool, false, dv.device, total, &blob, &dv.blob_bytes);
+  hipError_t e = pool_get(g_dev_pool, false, dv.device, total, &blob, &dv.blob_bytes, &dv.front_zero);
   if (e != hipSuccess) { (void)hipGetLastError(); return fail(DBSP_ENOMEM, std::string("plan device buffer: ") + hipGetErrorString(e)); }
   dv.blob = static_cast<unsigned char*>(blob);
   e = pool_get(g_pin_pool, true, dv.device, up_bytes, &dv.staging, &dv.staging_bytes);
@@ -364,6 +375,7 @@ int upload(dbsp_plan* plan) {
   unsigned char* st = static_cast<unsigned char*>(dv.staging);
   for (int i = 0; i < NA; ++i)
     if (!arrays[i]->empty()) std::memcpy(st + off[i] * sizeof(int32_t), arrays[i]->data(), arrays[i]->size() * sizeof(int32_t));
+  std::memset(st, 0, kFrontBytes);
   std::memset(st + busy_off, 0, up_bytes - busy_off);   // busy ticks, hardware ids, the queue's counters start at zero
 
   hipEvent_t ev_up, ev_use;
@@ -376,13 +388,17 @@ int upload(dbsp_plan* plan) {
     if (rc != DBSP_OK) return rc;
   }
 
+  // A launch of at most an item a workgroup, with nothing to count but what the front holds, see forward()
+  dv.direct = dv.front_zero && cnt_in_front && longest_list <= 1 && hp.tail_items.empty() && 4 * dv.max_chunks <= 14 &&
+              up_bytes + kv_bytes <= kInStreamBytes;
+  for (int i = 0; i < NA; ++i) dv.array_off[i] = off[i];
   const int32_t* ints = reinterpret_cast<const int32_t*>(dv.blob);
   dv.empty_rows = ints + off[0];
   dv.part_ptr = ints + off[1];
   dv.sched = ints + off[2];
   dv.split_rows = ints + off[3];
   dv.queue = reinterpret_cast<uint32_t*>(dv.blob + queue_off);
-  dv.split_cnt = reinterpret_cast<uint32_t*>(dv.blob + cnt_off);
+  dv.split_cnt = reinterpret_cast<uint32_t*>(dv.blob + (cnt_in_front ? 0 : cnt_off));
   dv.kv_idx = reinterpret_cast<const int32_t*>(dv.blob + kv_off);
   dv.busy = reinterpret_cast<uint64_t*>(dv.blob + busy_off);
   dv.hw_id = reinterpret_cast<uint32_t*>(dv.blob + hw_off);
@@ -675,8 +691,25 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();
   const bool capture = capturing != hipStreamCaptureStatusNone;
+  // The first launch of a small plan, no more than an item a workgroup, reads it where it lies in pinned memory: a launch
+  // less, which the host takes longer to make than the kernel runs.  What such a launch counts it counts in the device buffer's front,
+  // which has to be zero: the plan that had the buffer before has sent zeros there, and every launch leaves them.  The
+  // second launch of the plan fetches it like any other's first.  512 tokens, two heads, planned on every call: 24.5 us a
+  // pass with the fetch, 21.4 so (the host's 19.3 and 17.7 for planning and launching).  A workgroup's way to its first
+  // blocks is three or four reads across the bus, one behind the other, as long as the fetch took; with more items a
+  // workgroup they would come in between.
+  const bool direct = dm.direct && !dm.sent && !capture && B == 1 && p.in_place_ok;
+  if (direct) {
+    const int32_t* ints = static_cast<const int32_t*>(dm.staging);
+    p.empty_rows = ints + dm.array_off[0];
+    p.part_ptr = ints + dm.array_off[1];
+    p.sched = ints + dm.array_off[2];
+    p.split_rows = ints + dm.array_off[3];
+    p.kv_idx = static_cast<const int32_t*>(dm.staging_kv);
+    dm.direct = false;
+  }
   bool in_order = false;           // the fetch is the command before this launch
-  if (!dm.upload_done) {
+  if (!direct && !dm.upload_done) {
     if (!dm.sent) {
       const bool fetch = !capture && dm.up_bytes + dm.kv_bytes <= kInStreamBytes;
       OutsideCapture relaxed;      // the copies go to a stream that is not captured

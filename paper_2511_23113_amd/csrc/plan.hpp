@@ -56,6 +56,9 @@ struct dbsp_device_plan {
   void* staging_kv = nullptr;     // pinned host memory the index lists are compacted into (the plan's kv_idx)
   size_t staging_kv_bytes = 0;
   size_t up_bytes = 0, kv_bytes = 0;   // what is sent: the small arrays and zeroed counters, then the index lists, to the front of blob
+  bool front_zero = false;        // the first bytes of blob were zero when the plan got it
+  bool direct = false;            // the next launch may read the plan where it is staged
+  size_t array_off[4] = {};       // in int32, of the staged arrays
   // A plan gets to the device by copies on the library's upload stream, or by a kernel in front of its first
   // forward launch, on that launch's stream
   bool sent = false;

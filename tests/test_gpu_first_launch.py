@@ -1,0 +1,62 @@
+"""Small plans' first launches read the plan where it is staged once their device buffer has been a plan's before: new
+masks call after call, each plan launched once or several times, on one stream or another, against the same items' results
+from a plan that another buffer's first launch has fetched."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+# split rows (counters), rows that are not split, empty rows, an item for every workgroup and for few of them
+@pytest.mark.parametrize("block, d", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("length", [2, 4, -1])
+@pytest.mark.parametrize("mode", [0, 2])
+def test_first_launches_of_small_plans(block, d, length, mode):
+    import torch
+    import paper_2511_23113_amd as dbsp
+    H, nQ, nK = 2, 6, 7
+    rng = np.random.default_rng(block + d + length)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn((1, H, n * block, d), generator=gen, device="cuda").to(torch.bfloat16) for n in (nQ, nK, nK))
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for step in range(24):
+        mask = (rng.random((H, nQ, nK)) < rng.choice([0.1, 0.4, 0.8])).astype(np.uint8)
+        mask[0, 0, 0] = 1
+        kw = dict(max_item_len=length, mode=mode, num_partitions=int(rng.choice([64, 256])))
+        # one partition: more than an item a workgroup, which is fetched
+        want_o, want_lse = dbsp.sparse_attn_fwd(dbsp.plan_sparse_attn(mask, block, max_item_len=length, num_partitions=1), q, k, v)
+        torch.cuda.synchronize()
+        plan = dbsp.plan_sparse_attn(mask, block, **kw)
+        for launch in range(1 + step % 3):
+            with torch.cuda.stream(streams[(step + launch) % 2]):
+                o, lse = dbsp.sparse_attn_fwd(plan, q, k, v)
+            if launch % 2 == 0:
+                torch.cuda.synchronize()      # (a plan's calls do not overlap)
+            else:
+                streams[(step + launch) % 2].synchronize()
+            # merged two chunks at a time here, four there: a rounding of O apart, a few of LSE (at most 8)
+            torch.testing.assert_close(o, want_o, rtol=2.0 ** -7, atol=1e-4)
+            torch.testing.assert_close(lse, want_lse, rtol=0, atol=8 * 2.0 ** -21)
+        ticks, _ = plan.busy()
+        assert mode == 2 or np.array_equal(ticks > 0, plan.array(7) > 0)          # 7: blocks per partition
+        del plan
+
+
+def test_a_batch_or_the_static_scratch_fetches():
+    import torch
+    import paper_2511_23113_amd as dbsp
+    rng = np.random.default_rng(5)
+    q, k, v = (torch.randn((2, 2, 6 * 64, 64), device="cuda").to(torch.bfloat16) for _ in range(3))
+    for step in range(12):
+        mask = (rng.random((2, 6, 6)) < 0.6).astype(np.uint8)
+        plan = dbsp.plan_sparse_attn(mask, 64, max_item_len=2, max_batch=2)
+        outs = []
+        for call in ((0, 1), (1, 0), (0, 0))[step % 3]:
+            if call:
+                outs.append(dbsp.sparse_attn_fwd(plan, q, k, v)[0][:1])
+            else:
+                outs.append(dbsp.sparse_attn_fwd(plan, q[:1], k[:1], v[:1], static_scratch=step % 2 == 0)[0])
+        torch.cuda.synchronize()
+        torch.testing.assert_close(outs[0], outs[1], rtol=2.0 ** -7, atol=1e-4)        # (merged in place or behind the launch)
