@@ -256,18 +256,41 @@ int fetch_in_stream(dbsp_device_plan& dv, hipStream_t st) {
 // same length at the same time, that is of the few heads whose rows are about that long, and find each other's KV
 // blocks in the L2.  In the lists' own order (head by head) they drift apart by as many heads as a partition has items
 // more or fewer of them than the mean.
-void order_lists(const dbsp_host_plan& hp, const dbsp_device_plan& dv, std::vector<int32_t>& ptr, std::vector<int32_t>& run) {
-  ptr.resize((size_t)hp.P + 1);
-  run.resize(hp.part_items.size());
-  std::vector<int32_t> next(hp.P);            // of every partition: where its next item goes
-  ptr[0] = 0;
-  for (int32_t b = 0; b < hp.P; ++b) {
-    const int32_t g = dv.part_of(b), n = hp.part_ptr[g + 1] - hp.part_ptr[g];
-    next[g] = ptr[b];
-    ptr[b + 1] = ptr[b] + n;
-  }
+// (Lists are short where a partition gets few items, and sorted one by one then, else all at once by counting: 2406 items on
+// 1024 partitions, a step of 77 us, took 12 us more by counting.)
+constexpr int32_t kShortList = 8;
+void order_lists(const dbsp_host_plan& hp, const dbsp_device_plan& dv, int32_t longest_list, std::vector<int32_t>& ptr, std::vector<int32_t>& run) {
   const int32_t n = (int32_t)hp.part_items.size();          // every item: a greedy placement has no queue
+  ptr.resize((size_t)hp.P + 1);
+  run.resize(n);
+  ptr[0] = 0;
   auto weight = [&](int32_t i) { return hp.items[4 * (size_t)i + 3] - hp.items[4 * (size_t)i + 2]; };
+  if (longest_list <= kShortList) {
+    int32_t* to = run.data();
+    for (int32_t b = 0; b < hp.P; ++b) {
+      const int32_t g = dv.part_of(b);
+      int32_t w[kShortList], m = 0;
+      for (int32_t k = hp.part_ptr[g]; k < hp.part_ptr[g + 1]; ++k, ++m) {
+        const int32_t i = hp.part_items[k], wi = weight(i);
+        int32_t at = m;
+        for (; at > 0 && w[at - 1] < wi; --at) {
+          w[at] = w[at - 1];
+          to[at] = to[at - 1];
+        }
+        w[at] = wi;
+        to[at] = i;
+      }
+      to += m;
+      ptr[b + 1] = ptr[b] + m;
+    }
+    return;
+  }
+  std::vector<int32_t> next(hp.P);            // of every partition: where its next item goes
+  for (int32_t b = 0; b < hp.P; ++b) {
+    const int32_t g = dv.part_of(b);
+    next[g] = ptr[b];
+    ptr[b + 1] = ptr[b] + hp.part_ptr[g + 1] - hp.part_ptr[g];
+  }
   int32_t longest = 0;
   for (int32_t i = 0; i < n; ++i) longest = std::max(longest, weight(i));
   std::vector<int32_t> first((size_t)longest + 2, 0), part_of(n), sorted(n);
@@ -291,15 +314,17 @@ void order_lists(const dbsp_host_plan& hp, const dbsp_device_plan& dv, std::vect
 // Runs of 2, 4, 8, 16 of the 256 partitions instead of 32, 40 heads, 256 x 256: 6668, 6518, 6506, 6495 / 6474.
 constexpr int kDies = 8;
 int die_run_log2(const dbsp_host_plan& hp, int32_t used_parts) {
-  if (!hp.by_greedy) return 0;
-  int lg = 0;            // (a handful of workgroups has an L2 almost to itself)
-  while (used_parts >= 64 && (int64_t)kDies << (lg + 1) <= used_parts) ++lg;
+  if (used_parts < 64) return 0;             // a handful of workgroups has an L2 almost to itself
+  std::vector<int64_t> before((size_t)used_parts + 1, 0);      // blocks of the partitions in front of each
+  for (int32_t g = 0; g < used_parts; ++g) before[g + 1] = before[g] + hp.part_load[g];
+  int lg = 0;
+  while ((int64_t)kDies << (lg + 1) <= used_parts) ++lg;
   for (; lg > 0; --lg) {
-    int64_t load[kDies] = {}, total = 0;
-    const int32_t mapped = used_parts >> (lg + 3) << (lg + 3);
-    for (int32_t g = 0; g < used_parts; ++g) load[(g < mapped ? g >> lg : g) % kDies] += hp.part_load[g];
-    for (int64_t x : load) total += x;
-    if (100 * kDies * *std::max_element(load, load + kDies) <= 103 * total) break;
+    int64_t load[kDies] = {};
+    const int32_t runs = used_parts >> (lg + 3) << 3;      // (the others are dealt one by one)
+    for (int32_t k = 0; k < runs; ++k) load[k % kDies] += before[(size_t)(k + 1) << lg] - before[(size_t)k << lg];
+    for (int32_t g = runs << lg; g < used_parts; ++g) load[g % kDies] += hp.part_load[g];
+    if (100 * kDies * *std::max_element(load, load + kDies) <= 103 * before[used_parts]) break;
   }
   return lg;
 }
@@ -310,7 +335,7 @@ int upload(dbsp_plan* plan) {
   // what a workgroup needs to know of an item, in the order the workgroups run them (then the shared
   // queue's): one load instead of a chain through list, item, slot and row offset
   const int64_t n_placed = (int64_t)hp.part_items.size(), n_sched = n_placed + (int64_t)hp.tail_items.size();
-  std::vector<int32_t> sched(8 * (size_t)n_sched), slot_row(hp.n_slots);
+  std::vector<int32_t> slot_row(hp.n_slots);
   const size_t n_split = hp.split_rows.size() / 4;
   for (size_t r = 0; r < n_split; ++r)
     for (int32_t k = 0; k < hp.split_rows[4 * r + 2]; ++k) slot_row[hp.split_rows[4 * r + 1] + k] = (int32_t)r;
@@ -321,32 +346,23 @@ int upload(dbsp_plan* plan) {
     longest_list = std::max(longest_list, n);
     if (n) dv.used_parts = g + 1;
   }
-  dv.die_run_log2 = die_run_log2(hp, dv.used_parts);
+  // (Not for short items, of fewer than two blocks of 128 tokens or eight of 64 in the mean: it takes the host longer than it
+  // gains.  3 heads, 217 x 108 blocks of 64 at d = 64, 6.2 blocks an item: the kernel 44.0 us without, 43.4 with it, planned on
+  // every call 86 and 90 a pass; 12 heads, 21 x 23 of 128, 5 an item: the kernel 59.5 and 55.2.)
+  const bool worth = hp.by_greedy && hp.nnz * hp.tile_rows() * hp.tile_rows() >= 32768 * hp.n_items();
+  dv.die_run_log2 = worth ? die_run_log2(hp, dv.used_parts) : 0;
   std::vector<int32_t> own_ptr, own_run;
-  const bool reorder = hp.by_greedy && (longest_list > 1 || dv.die_run_log2 > 0);
-  if (reorder) order_lists(hp, dv, own_ptr, own_run);
+  const bool reorder = worth && (longest_list > 1 || dv.die_run_log2 > 0);
+  if (reorder) order_lists(hp, dv, longest_list, own_ptr, own_run);
   const std::vector<int32_t>& part_ptr = reorder ? own_ptr : hp.part_ptr;
   const std::vector<int32_t>& run = reorder ? own_run : hp.part_items;
-  for (int64_t k = 0; k < n_sched; ++k) {
-    const int64_t i = k < n_placed ? run[k] : hp.tail_items[k - n_placed];
-    const int32_t* it = hp.items.data() + 4 * i;
-    int32_t* s = sched.data() + 8 * k;
-    s[0] = it[0];                                                                                  // head
-    s[1] = it[1];                                                                                  // row of the plan (query block, or pair of them)
-    s[2] = (hp.row_ptr[(int64_t)it[0] * hp.nQ + it[1]] + it[2]) * (hp.pair ? 2 : 1);               // first word of its KV list
-    s[3] = it[3] - it[2];                                                                          // blocks (super blocks)
-    s[4] = hp.item_slot[i];
-    if (s[4] >= 0) {
-      const int32_t r = slot_row[s[4]];
-      s[5] = r; s[6] = hp.split_rows[4 * (size_t)r + 2]; s[7] = hp.split_rows[4 * (size_t)r + 1];  // index of the split row, its chunks, its first slot
-    }
-  }
   for (size_t r = 0; r < n_split; ++r) dv.max_chunks = std::max(dv.max_chunks, hp.split_rows[4 * r + 2]);
-  const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &part_ptr, &sched, &hp.split_rows};
+  const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &part_ptr, nullptr, &hp.split_rows};      // (the schedule is made in place)
   constexpr int NA = 4;
+  const auto ints_of = [&](int i) { return arrays[i] ? arrays[i]->size() : 8 * (size_t)n_sched; };
   size_t off[NA + 1];   // in int32 units, each array 16-byte aligned
   off[0] = kFrontBytes / sizeof(int32_t);
-  for (int i = 0; i < NA; ++i) off[i + 1] = off[i] + ((arrays[i]->size() + 3) & ~size_t(3));
+  for (int i = 0; i < NA; ++i) off[i + 1] = off[i] + ((ints_of(i) + 3) & ~size_t(3));
   const size_t ints_bytes = off[NA] * sizeof(int32_t);
   const size_t busy_off = (ints_bytes + 255) & ~size_t(255);
   const size_t hw_off = busy_off + (((size_t)hp.P * sizeof(uint64_t) + 255) & ~size_t(255));
@@ -374,7 +390,23 @@ int upload(dbsp_plan* plan) {
 
   unsigned char* st = static_cast<unsigned char*>(dv.staging);
   for (int i = 0; i < NA; ++i)
-    if (!arrays[i]->empty()) std::memcpy(st + off[i] * sizeof(int32_t), arrays[i]->data(), arrays[i]->size() * sizeof(int32_t));
+    if (arrays[i] && !arrays[i]->empty()) std::memcpy(st + off[i] * sizeof(int32_t), arrays[i]->data(), arrays[i]->size() * sizeof(int32_t));
+  int32_t* sched = reinterpret_cast<int32_t*>(st) + off[2];
+  for (int64_t k = 0; k < n_sched; ++k) {
+    const int64_t i = k < n_placed ? run[k] : hp.tail_items[k - n_placed];
+    const int32_t* it = hp.items.data() + 4 * i;
+    int32_t* s = sched + 8 * k;
+    s[0] = it[0];                                                                                  // head
+    s[1] = it[1];                                                                                  // row of the plan (query block, or pair of them)
+    s[2] = (hp.row_ptr[(int64_t)it[0] * hp.nQ + it[1]] + it[2]) * (hp.pair ? 2 : 1);               // first word of its KV list
+    s[3] = it[3] - it[2];                                                                          // blocks (super blocks)
+    s[4] = hp.item_slot[i];
+    s[5] = s[6] = s[7] = 0;
+    if (s[4] >= 0) {
+      const int32_t r = slot_row[s[4]];
+      s[5] = r; s[6] = hp.split_rows[4 * (size_t)r + 2]; s[7] = hp.split_rows[4 * (size_t)r + 1];  // index of the split row, its chunks, its first slot
+    }
+  }
   std::memset(st, 0, kFrontBytes);
   std::memset(st + busy_off, 0, up_bytes - busy_off);   // busy ticks, hardware ids, the queue's counters start at zero
 

@@ -167,15 +167,20 @@ __device__ __forceinline__ const unsigned char* if_less(int a, int b, const unsi
   return z;
 }
 
-// The same, and all LDS reads have returned.  By the builtin, whose meaning the compiler knows: behind an asm block it waits for
-// these reads again, operand by operand, nine instructions of a slice's two hundred.  us by asm / by the builtin: pair rows, 40
-// heads, 512 x 512 blocks 5338 / 5285, 24 heads, 301 x 301 blocks of 64 at d = 128 992 / 987, 40 heads, 256 x 256 of 128 5579 / 5556,
-// 12 heads, 21 x 23 49.8 / 49.3; at d = 64, where another wave takes the slots, no difference.
-template <int N>
+// The same, and all LDS reads have returned.  At d = 128 by the builtin, whose meaning the compiler knows: behind an asm
+// block it waits for these reads again, operand by operand, nine instructions of a slice's two hundred.  us by asm / by the
+// builtin: pair rows, 40 heads, 512 x 512 blocks 5338 / 5285, 24 heads, 301 x 301 blocks of 64 992 / 987, 40 heads,
+// 256 x 256 of 128 5579 / 5556, 12 heads, 21 x 23 49.8 / 49.3.  At d = 64 another wave takes the slots, and the asm is the
+// better one: 48 heads, 275 x 275 blocks of 64 1025 / 1027, 30 heads, 137 x 137 of 128 1477 / 1481.
+template <int D, int N>
 __device__ __forceinline__ void wait_reads() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt((N & 15) | 7 << 4 | 0 << 8 | (N >> 4) << 14);      // vmcnt, expcnt (not waited for), lgkmcnt
-  asm volatile("" ::: "memory");
+  if constexpr (D == 64) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+  } else {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | 7 << 4 | 0 << 8 | (N >> 4) << 14);      // vmcnt, expcnt (not waited for), lgkmcnt
+    asm volatile("" ::: "memory");
+  }
 }
 
 template <int N>
@@ -767,7 +772,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
           if (z == at) copy_one(is_k, x);
           if (x % 4 == 0 && z == at - 1) {
             if (k == 0) {
-              if constexpr (!SHARED) wait_reads<63>();    // the operand reads of the step before are done
+              if constexpr (!SHARED) wait_reads<D, 63>();    // the operand reads of the step before are done
               if constexpr (U == 1) {
                 jv = jk;
                 jk = id_of(s + (SHARED ? 4 : 2));
@@ -785,7 +790,7 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
       // which the wait may leave fewer), and everybody has read all before them
       auto publish = [&](int y) __attribute__((always_inline)) {
         if (!SHARED || QT != FIRST || y != (FIRST ? 0 : C::BARRIER_AT)) return;
-        wait_reads<WAIT>();
+        wait_reads<D, WAIT>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
       };
