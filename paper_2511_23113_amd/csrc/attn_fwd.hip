@@ -400,9 +400,9 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
 
   // An item overlaps with the end of the one before it in the workgroup's own list: its description, the
   // ids of its first KV blocks, its Q and its first two K slices are fetched while that one drains its
-  // pipeline and stores its result.  What an item costs besides its blocks, at d = 128 and 128-token blocks: 13 thousand
-  // clocks, of which 1400 - 1800 until its copies are on their way, 900 - 1000 waiting for its first slices, 1800 for the
-  // first slice's steps, 3700 - 3900 to drain and meet, 4500 from the exchange to the last store, 200 at the last barrier.
+  // pipeline and stores its result.  What an item costs besides its blocks, at d = 128 and 128-token blocks: 9 thousand
+  // clocks, of which 800 at its start, 1800 for the first slice's steps, 850 to drain, 200 to meet, 1300 for the exchange's
+  // writes and their barrier, 3400 to combine and store, 600 to read the next Q.
   const unsigned char* from = nullptr;      // of the copies, see copy_begin
   int4 da = {}, db = {};         // what the item is, see upload() in api.hip
   int pos = 0, bb = 0;           // its place in the schedule, its batch entry
