@@ -346,10 +346,10 @@ int upload(dbsp_plan* plan) {
     longest_list = std::max(longest_list, n);
     if (n) dv.used_parts = g + 1;
   }
-  // (Not for short items, of fewer than two blocks of 128 tokens or eight of 64 in the mean: it takes the host longer than it
-  // gains.  3 heads, 217 x 108 blocks of 64 at d = 64, 6.2 blocks an item: the kernel 44.0 us without, 43.4 with it, planned on
+  // (Not for short items, of fewer than four blocks of 128 tokens or sixteen of 64 in the mean: it takes the host longer than it
+  // gains.  11 heads, 212 x 212 blocks of 64 at d = 64, 13 blocks an item, planned on every call 87 us without and 94 with it; 3 heads, 217 x 108 blocks of 64 at d = 64, 6.2 blocks an item: the kernel 44.0 us without, 43.4 with it, planned on
   // every call 86 and 90 a pass; 12 heads, 21 x 23 of 128, 5 an item: the kernel 59.5 and 55.2.)
-  const bool worth = hp.by_greedy && hp.nnz * hp.tile_rows() * hp.tile_rows() >= 32768 * hp.n_items();
+  const bool worth = hp.by_greedy && hp.nnz * hp.tile_rows() * hp.tile_rows() >= 65536 * hp.n_items();
   dv.die_run_log2 = worth ? die_run_log2(hp, dv.used_parts) : 0;
   std::vector<int32_t> own_ptr, own_run;
   const bool reorder = worth && (longest_list > 1 || dv.die_run_log2 > 0);
