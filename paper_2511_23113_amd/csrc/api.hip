@@ -216,12 +216,17 @@ int get_kv_staging(dbsp_plan* plan) {
   return DBSP_OK;
 }
 
+constexpr size_t kFrontBytes = size_t(4) << 10;      // of every plan's device buffer: counters, zero between launches
+
 // Sends the plan to the device on the library's upload stream, asynchronously, with one event that forward
-// launches wait for: the small arrays from their staging buffer, the index lists from theirs.
+// launches wait for: the small arrays from their staging buffer, the index lists from theirs.  Behind a first launch
+// that reads them where they are staged, which may still run, the arrays only: what it counts and measures lies in
+// front of and behind them, and nothing would order the staged zeros with that.
 int send_upload(dbsp_device_plan& dv) {
   hipStream_t us;
   DBSP_HIP(upload_stream(dv.device, &us));
-  DBSP_HIP(hipMemcpyAsync(dv.blob, dv.staging, dv.up_bytes, hipMemcpyHostToDevice, us));
+  const size_t from = dv.used ? kFrontBytes : 0, to = dv.used ? dv.arrays_end : dv.up_bytes;
+  DBSP_HIP(hipMemcpyAsync(dv.blob + from, static_cast<const unsigned char*>(dv.staging) + from, to - from, hipMemcpyHostToDevice, us));
   if (dv.kv_bytes) DBSP_HIP(hipMemcpyAsync(dv.blob + dv.up_bytes, dv.staging_kv, dv.kv_bytes, hipMemcpyHostToDevice, us));
   DBSP_HIP(hipEventRecord(static_cast<hipEvent_t>(dv.uploaded), us));
   dv.sent = true;
@@ -232,7 +237,6 @@ int send_upload(dbsp_device_plan& dv) {
 // not sent here: its first forward launch is preceded, on its own stream, by a kernel that fetches the
 // plan from the pinned buffers (64 KiB take it about 3 us).  Two streams and the wait between them cost the
 // host 12 us and more; for larger plans they let the copy run beside the kernels before it.
-constexpr size_t kFrontBytes = size_t(4) << 10;      // of every plan's device buffer: counters, zero between launches
 constexpr size_t kInStreamBytes = (size_t(64) << 10) + kFrontBytes;
 
 __global__ __launch_bounds__(256) void dbsp_fetch_kernel(uint4* __restrict__ dst, const uint4* __restrict__ a, uint32_t na, const uint4* __restrict__ b, uint32_t n) {
@@ -364,7 +368,7 @@ int upload(dbsp_plan* plan) {
   off[0] = kFrontBytes / sizeof(int32_t);
   for (int i = 0; i < NA; ++i) off[i + 1] = off[i] + ((ints_of(i) + 3) & ~size_t(3));
   const size_t ints_bytes = off[NA] * sizeof(int32_t);
-  const size_t busy_off = (ints_bytes + 255) & ~size_t(255);
+  const size_t busy_off = dv.arrays_end = (ints_bytes + 255) & ~size_t(255);
   const size_t hw_off = busy_off + (((size_t)hp.P * sizeof(uint64_t) + 255) & ~size_t(255));
   // shared queue of the dynamic tail: [0] next position, then one take count per tail item; then the split rows' counters
   // where the front does not hold them

@@ -56,6 +56,7 @@ struct dbsp_device_plan {
   void* staging_kv = nullptr;     // pinned host memory the index lists are compacted into (the plan's kv_idx)
   size_t staging_kv_bytes = 0;
   size_t up_bytes = 0, kv_bytes = 0;   // what is sent: the small arrays and zeroed counters, then the index lists, to the front of blob
+  size_t arrays_end = 0;          // where in the former the arrays end that launches only read
   bool front_zero = false;        // the first bytes of blob were zero when the plan got it
   bool direct = false;            // the next launch may read the plan where it is staged
   size_t array_off[4] = {};       // in int32, of the staged arrays

@@ -60,3 +60,56 @@ def test_a_batch_or_the_static_scratch_fetches():
                 outs.append(dbsp.sparse_attn_fwd(plan, q[:1], k[:1], v[:1], static_scratch=step % 2 == 0)[0])
         torch.cuda.synchronize()
         torch.testing.assert_close(outs[0], outs[1], rtol=2.0 ** -7, atol=1e-4)        # (merged in place or behind the launch)
+
+
+def test_a_capture_right_behind_a_first_launch():
+    """The captured call sends the plan on the library's own stream while the first launch is yet to run (behind a long
+    kernel), runs or has just ended: its results and busy times, every replay and the buffer's next plans stay right."""
+    import torch
+    import paper_2511_23113_amd as dbsp
+    H, n, block, d = 2, 8, 64, 64
+    rng = np.random.default_rng(7)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v = (torch.randn((1, H, n * block, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    masks = [(rng.random((H, n, n)) < 0.7).astype(np.uint8) for _ in range(3)]
+    wants = []
+    for mask in masks:
+        plan = dbsp.plan_sparse_attn(mask, block)
+        assert len(plan.array(4)) > 0                              # 4: split rows
+        for _ in range(2):                                         # the second launch is of the fetched plan
+            wants.append(dbsp.sparse_attn_fwd(plan, q, k, v))
+            torch.cuda.synchronize()
+        wants.pop(-2)
+        plan.close()
+    long, side = torch.ones(1 << 28, device="cuda"), torch.cuda.Stream()
+
+    def same(got, want):
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+    for step in range(6):
+        mask, want = masks[step % 3], wants[step % 3]
+        first, out = ([torch.full_like(x, float("nan")) for x in want] for _ in range(2))
+        plan, graph = dbsp.plan_sparse_attn(mask, block), torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(4 * (step % 2)):
+                long.mul_(1.0)
+            dbsp.sparse_attn_fwd(plan, q, k, v, o=first[0], lse=first[1])
+            graph.capture_begin()
+            dbsp.sparse_attn_fwd(plan, q, k, v, o=out[0], lse=out[1])
+            graph.capture_end()
+        ticks, _ = plan.busy(side)
+        assert np.array_equal(ticks > 0, plan.array(7) > 0)        # 7: blocks per partition
+        same(first, want)
+        for _ in range(3):
+            out[0].zero_()
+            out[1].zero_()
+            graph.replay()
+            same(out, want)
+            same(dbsp.sparse_attn_fwd(plan, q, k, v), want)
+        del graph
+        plan.close()
+        follower = dbsp.plan_sparse_attn(masks[(step + 1) % 3], block)
+        same(dbsp.sparse_attn_fwd(follower, q, k, v), wants[(step + 1) % 3])
+        follower.close()
