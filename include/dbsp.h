@@ -335,12 +335,14 @@ int dbsp_plan_stats(const dbsp_plan* plan, double* rho_naive, double* rho_balanc
                     int64_t* nnz, int64_t* n_items, int32_t* num_partitions, int32_t* max_item_len,
                     double* plan_usec);
 
-/* dbsp_plan_calibrate: relative time per block of every partition in the LAST sparse_attn_fwd on this plan,
+/* dbsp_plan_calibrate: relative time per block of the compute units, measured by the LAST sparse_attn_fwd on this plan,
  * for dbsp_plan_opts.partition_cost of later plans with the same mode and partition count (compute units of one
- * chip differ by a few percent in speed, systematically; a mode settles which of them runs a partition).  cost: host, int32 [P], written:
- * cost[g] = round(1024 * (busy[g] / load[g]) / (sum busy / sum load)) in exact integer arithmetic (round
+ * chip differ by a few percent in speed, systematically).  cost: host, int32 [P], written: cost[g] belongs to the compute
+ * unit that runs partition g of such a plan.  The partition h that it ran in this one is g, but for DBSP_MODE_BALANCED
+ * plans made without partition_cost, whose masks may settle it otherwise:
+ * cost[g] = round(1024 * (busy[h] / load[h]) / (sum busy / sum load)) in exact integer arithmetic (round
  * half up), clamped to [512, 2048]; 1024 for a partition without work or measurement.  Synchronises
- * `stream` before reading.  Errors: DBSP_EINVAL (null pointer, host-only plan), DBSP_EHIP. */
+ * `stream` before reading.  Errors: DBSP_EINVAL (null pointer, host-only plan), DBSP_ENOMEM, DBSP_EHIP. */
 int dbsp_plan_calibrate(const dbsp_plan* plan, int32_t* cost, void* stream);
 
 /* dbsp_plan_tail_takes: how often each item of the shared queue (DBSP_TAIL_ITEMS) has been taken since the plan was

@@ -26,7 +26,7 @@ _INT64_ARRAYS = (PART_LOAD, BLOCKS_PER_HEAD)
 EXPORTS = (
     "plan_sparse_attn", "plan_sparse_attn_reuse", "sparse_attn_fwd", "sparse_attn_fwd_static", "imbalance_ratio", "dbsp_plan_get", "dbsp_plan_stats",
     "dbsp_plan_busy", "dbsp_plan_tail_takes", "dbsp_plan_pair_rows", "dbsp_plan_calibrate", "dbsp_plan_destroy", "dbsp_plan_release", "dbsp_last_error",
-    "dbsp_partition_heads", "dbsp_partition_blocks", "dbsp_ring_work", "dbsp_fit_cost_model", "dbsp_mfma_probe",
+    "dbsp_partition_heads", "dbsp_partition_blocks", "dbsp_ring_work", "dbsp_fit_cost_model", "dbsp_mfma_probe", "dbsp_plan_run_order",
 )
 
 
@@ -92,6 +92,8 @@ def load_library(path: str | None = None):
     lib.dbsp_plan_tail_takes.restype = C.c_int
     lib.dbsp_plan_pair_rows.argtypes = [vp, C.POINTER(C.c_int32)]
     lib.dbsp_plan_pair_rows.restype = C.c_int
+    lib.dbsp_plan_run_order.argtypes = [vp, vp, vp, C.POINTER(C.c_int32)]
+    lib.dbsp_plan_run_order.restype = C.c_int
     lib.dbsp_plan_destroy.argtypes = [vp]
     lib.dbsp_plan_destroy.restype = None
     lib.dbsp_plan_release.argtypes = [vp]
@@ -163,11 +165,20 @@ class Plan:
         return takes
 
     def calibrate(self, stream=None):
-        """Relative time per block of every partition in the last forward call (int32 [P], mean about 1024):
-        pass it as partition_cost to later plans with the same partition count.  Synchronises."""
+        """Relative time per block of the compute units in the last forward call (int32 [P], mean about 1024):
+        pass it as partition_cost to later plans with the same mode and partition count.  Synchronises."""
         cost = np.zeros(self.stats(with_rho=False)["num_partitions"], dtype=np.int32)
         _check(load_library().dbsp_plan_calibrate(self.handle, cost.ctypes.data_as(C.c_void_p), _stream_ptr(stream)))
         return cost
+
+    def run_order(self):
+        """(partition of every workgroup int32 [P], item ids workgroup by workgroup in the order they run, whether a launch
+        has read the plan where it was staged): see dbsp_diag.h, dbsp_plan_run_order."""
+        part = np.zeros(self.stats(with_rho=False)["num_partitions"], dtype=np.int32)
+        items = np.zeros(self.array(PART_ITEMS).shape[0], dtype=np.int32)
+        staged = C.c_int32()
+        _check(load_library().dbsp_plan_run_order(self.handle, _addr(part), _addr(items), C.byref(staged)))
+        return part, items, bool(staged.value)
 
     def close(self):
         if self._h:

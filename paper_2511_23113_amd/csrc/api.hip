@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "dbsp.h"
+#include "dbsp_diag.h"
 #include "fwd_params.hpp"
 #include "plan.hpp"
 
@@ -254,61 +255,71 @@ int fetch_in_stream(dbsp_device_plan& dv, hipStream_t st) {
   return DBSP_OK;
 }
 
-// What the workgroups of a greedy placement run: where their lists begin, and the lists.  Workgroup b has partition
-// part_of(b)'s items, the longest first, equal ones by their id.  The greedy deals items in
-// that order, one to every partition before anybody gets a second one: run so, all partitions are at items of about the
-// same length at the same time, that is of the few heads whose rows are about that long, and find each other's KV
-// blocks in the L2.  In the lists' own order (head by head) they drift apart by as many heads as a partition has items
-// more or fewer of them than the mean.
+// Whose items the workgroups of a launch run, and in what order.
+struct RunOrder {
+  int32_t parts = 0, run_log2 = 0;         // workgroup b has partition dbsp_part_of(b, parts, run_log2)
+  int32_t groups = 0, longest_list = 0;    // workgroups up to the last one that has items, items the longest list has
+  bool own = false;                        // by the lists below instead of the placement's own
+  std::vector<int32_t> ptr, run;           // [P + 1] where the workgroups' lists begin, and the lists
+};
+
+// The lists.  Of a greedy placement a workgroup has its partition's items, the longest first, equal ones by their id.  The
+// greedy deals items in that order, one to every partition before anybody gets a second one: run so, all partitions are at
+// items of about the same length at the same time, that is of the few heads whose rows are about that long, and find each
+// other's KV blocks in the L2.  In the lists' own order (head by head) they drift apart by as many heads as a partition has
+// items more or fewer of them than the mean.
 // (Lists are short where a partition gets few items, and sorted one by one then, else all at once by counting: 2406 items on
 // 1024 partitions, a step of 77 us, took 12 us more by counting.)
 constexpr int32_t kShortList = 8;
-void order_lists(const dbsp_host_plan& hp, const dbsp_device_plan& dv, int32_t longest_list, std::vector<int32_t>& ptr, std::vector<int32_t>& run) {
+void order_lists(const dbsp_host_plan& hp, bool sorted, RunOrder& o) {
   const int32_t n = (int32_t)hp.part_items.size();          // every item: a greedy placement has no queue
-  ptr.resize((size_t)hp.P + 1);
-  run.resize(n);
-  ptr[0] = 0;
+  o.ptr.resize((size_t)hp.P + 1);
+  o.run.resize(n);
+  o.ptr[0] = 0;
   auto weight = [&](int32_t i) { return hp.items[4 * (size_t)i + 3] - hp.items[4 * (size_t)i + 2]; };
-  if (longest_list <= kShortList) {
-    int32_t* to = run.data();
+  if (!sorted || o.longest_list <= kShortList) {
+    int32_t* to = o.run.data();
     for (int32_t b = 0; b < hp.P; ++b) {
-      const int32_t g = dv.part_of(b);
+      const int32_t g = dbsp_part_of(b, o.parts, o.run_log2);
       int32_t w[kShortList], m = 0;
       for (int32_t k = hp.part_ptr[g]; k < hp.part_ptr[g + 1]; ++k, ++m) {
-        const int32_t i = hp.part_items[k], wi = weight(i);
+        const int32_t i = hp.part_items[k];
         int32_t at = m;
-        for (; at > 0 && w[at - 1] < wi; --at) {
-          w[at] = w[at - 1];
-          to[at] = to[at - 1];
+        if (sorted) {
+          const int32_t wi = weight(i);
+          for (; at > 0 && w[at - 1] < wi; --at) {
+            w[at] = w[at - 1];
+            to[at] = to[at - 1];
+          }
+          w[at] = wi;
         }
-        w[at] = wi;
         to[at] = i;
       }
       to += m;
-      ptr[b + 1] = ptr[b] + m;
+      o.ptr[b + 1] = o.ptr[b] + m;
     }
     return;
   }
   std::vector<int32_t> next(hp.P);            // of every partition: where its next item goes
   for (int32_t b = 0; b < hp.P; ++b) {
-    const int32_t g = dv.part_of(b);
-    next[g] = ptr[b];
-    ptr[b + 1] = ptr[b] + hp.part_ptr[g + 1] - hp.part_ptr[g];
+    const int32_t g = dbsp_part_of(b, o.parts, o.run_log2);
+    next[g] = o.ptr[b];
+    o.ptr[b + 1] = o.ptr[b] + hp.part_ptr[g + 1] - hp.part_ptr[g];
   }
   int32_t longest = 0;
   for (int32_t i = 0; i < n; ++i) longest = std::max(longest, weight(i));
-  std::vector<int32_t> first((size_t)longest + 2, 0), part_of(n), sorted(n);
+  std::vector<int32_t> first((size_t)longest + 2, 0), part_of(n), by_weight(n);
   for (int32_t g = 0; g < hp.P; ++g)
     for (int32_t k = hp.part_ptr[g]; k < hp.part_ptr[g + 1]; ++k) part_of[hp.part_items[k]] = g;
   for (int32_t i = 0; i < n; ++i) ++first[longest - weight(i) + 1];
   for (int32_t w = 0; w <= longest; ++w) first[w + 1] += first[w];
-  for (int32_t i = 0; i < n; ++i) sorted[first[longest - weight(i)]++] = i;
-  for (int32_t i : sorted) run[next[part_of[i]]++] = i;
+  for (int32_t i = 0; i < n; ++i) by_weight[first[longest - weight(i)]++] = i;
+  for (int32_t i : by_weight) o.run[next[part_of[i]]++] = i;
 }
 
-// Which partitions share an L2 (see part_of).  Workgroup b runs on compute die b mod 8, and the greedy hands neighbouring items, of
-// one head mostly, to neighbouring partitions, as many in a row as have the same load so far: of its placements every
-// die runs 2^result partitions in a row, an eighth of all where it can.  Partitions differ in load where each has few
+// Which partitions share an L2 (see dbsp_part_of).  Workgroup b runs on compute die b mod 8, and the greedy hands neighbouring
+// items, of one head mostly, to neighbouring partitions, as many in a row as have the same load so far: of its placements
+// every die runs 2^result partitions in a row, an eighth of all where it can.  Partitions differ in load where each has few
 // items (970 rows of 97 blocks on 256: four or three), and then the ones with more lie together: no run is so long that
 // some die gets 3 % more blocks than the mean (those rows, in runs of 1 / 16 / 32: 667 / 692 / 691 us).
 // Both together, us a pass before / the order alone / runs alone / both, in turn, defaults: 30 heads, 137 x 137 blocks of 128 at
@@ -317,20 +328,56 @@ void order_lists(const dbsp_host_plan& hp, const dbsp_device_plan& dv, int32_t l
 // 1926 / 1767 / 1713 / 1488, 24 heads, 301 x 301 at d = 128 2127 / 1827 / 1962 / 1774.
 // Runs of 2, 4, 8, 16 of the 256 partitions instead of 32, 40 heads, 256 x 256: 6668, 6518, 6506, 6495 / 6474.
 constexpr int kDies = 8;
-int die_run_log2(const dbsp_host_plan& hp, int32_t used_parts) {
-  if (used_parts < 64) return 0;             // a handful of workgroups has an L2 almost to itself
-  std::vector<int64_t> before((size_t)used_parts + 1, 0);      // blocks of the partitions in front of each
-  for (int32_t g = 0; g < used_parts; ++g) before[g + 1] = before[g] + hp.part_load[g];
+int longest_runs_log2(int32_t parts) {
+  if (parts < 64) return 0;             // a handful of workgroups has an L2 almost to itself
   int lg = 0;
-  while ((int64_t)kDies << (lg + 1) <= used_parts) ++lg;
+  while ((int64_t)kDies << (lg + 1) <= parts) ++lg;
+  return lg;
+}
+int die_run_log2(const dbsp_host_plan& hp, int32_t parts) {
+  int lg = longest_runs_log2(parts);
+  if (lg == 0) return 0;
+  std::vector<int64_t> before((size_t)parts + 1, 0);      // blocks of the partitions in front of each
+  for (int32_t g = 0; g < parts; ++g) before[g + 1] = before[g] + hp.part_load[g];
   for (; lg > 0; --lg) {
     int64_t load[kDies] = {};
-    const int32_t runs = used_parts >> (lg + 3) << 3;      // (the others are dealt one by one)
+    const int32_t runs = parts >> (lg + 3) << 3;      // (the others are dealt one by one)
     for (int32_t k = 0; k < runs; ++k) load[k % kDies] += before[(size_t)(k + 1) << lg] - before[(size_t)k << lg];
-    for (int32_t g = runs << lg; g < used_parts; ++g) load[g % kDies] += hp.part_load[g];
-    if (100 * kDies * *std::max_element(load, load + kDies) <= 103 * before[used_parts]) break;
+    for (int32_t g = runs << lg; g < parts; ++g) load[g % kDies] += hp.part_load[g];
+    if (100 * kDies * *std::max_element(load, load + kDies) <= 103 * before[parts]) break;
   }
   return lg;
+}
+
+RunOrder run_order(const dbsp_host_plan& hp) {
+  RunOrder o;
+  for (int32_t g = 0; g < hp.P; ++g) {
+    const int32_t n = hp.part_ptr[g + 1] - hp.part_ptr[g];
+    o.longest_list = std::max(o.longest_list, n);
+    if (n) o.groups = g + 1;
+  }
+  // (Not for short items, of fewer than four blocks of 128 tokens or sixteen of 64 in the mean: it takes the host longer than it
+  // gains.  11 heads, 212 x 212 blocks of 64 at d = 64, 13 blocks an item, planned on every call 87 us without and 94 with it; 3 heads, 217 x 108 blocks of 64 at d = 64, 6.2 blocks an item: the kernel 44.0 us without, 43.4 with it, planned on
+  // every call 86 and 90 a pass; 12 heads, 21 x 23 of 128, 5 an item: the kernel 59.5 and 55.2.)
+  const bool worth = hp.by_greedy && hp.nnz * hp.tile_rows() * hp.tile_rows() >= 65536 * hp.n_items();
+  o.parts = o.groups;
+  if (hp.by_greedy && hp.by_cost) {
+    // costs are a compute unit's: which one runs a partition must not depend on the mask that they are used for (nor on the
+    // one they were measured with, see dbsp_plan_calibrate), so the runs are those of the number of partitions.  us a pass
+    // with a plan's own costs, by runs that go with the loads / these: 48 heads, 275 x 275 blocks of 64 at d = 64 1932 / 1640, 24 heads,
+    // 301 x 301 at d = 128 2050 / 1833, 40 heads, 256 x 256 of 128 6265 / 6216, 12 heads, 21 x 23 57.6 / 52.9; in short items 48
+    // heads, 256 x 256 512 / 508, 11 heads, 212 x 212 blocks of 64 61.5 / 58.9
+    o.parts = hp.P;
+    o.run_log2 = longest_runs_log2(hp.P);
+  } else if (worth) {
+    o.run_log2 = die_run_log2(hp, o.groups);
+  }
+  o.own = (worth && o.longest_list > 1) || o.run_log2 > 0;
+  if (o.own) {
+    order_lists(hp, worth, o);
+    while (o.groups < hp.P && o.ptr[o.groups] < o.ptr[hp.P]) ++o.groups;
+  }
+  return o;
 }
 
 int upload(dbsp_plan* plan) {
@@ -343,23 +390,12 @@ int upload(dbsp_plan* plan) {
   const size_t n_split = hp.split_rows.size() / 4;
   for (size_t r = 0; r < n_split; ++r)
     for (int32_t k = 0; k < hp.split_rows[4 * r + 2]; ++k) slot_row[hp.split_rows[4 * r + 1] + k] = (int32_t)r;
-  dv.used_parts = 0;
-  int32_t longest_list = 0;
-  for (int32_t g = 0; g < hp.P; ++g) {
-    const int32_t n = hp.part_ptr[g + 1] - hp.part_ptr[g];
-    longest_list = std::max(longest_list, n);
-    if (n) dv.used_parts = g + 1;
-  }
-  // (Not for short items, of fewer than four blocks of 128 tokens or sixteen of 64 in the mean: it takes the host longer than it
-  // gains.  11 heads, 212 x 212 blocks of 64 at d = 64, 13 blocks an item, planned on every call 87 us without and 94 with it; 3 heads, 217 x 108 blocks of 64 at d = 64, 6.2 blocks an item: the kernel 44.0 us without, 43.4 with it, planned on
-  // every call 86 and 90 a pass; 12 heads, 21 x 23 of 128, 5 an item: the kernel 59.5 and 55.2.)
-  const bool worth = hp.by_greedy && hp.nnz * hp.tile_rows() * hp.tile_rows() >= 65536 * hp.n_items();
-  dv.die_run_log2 = worth ? die_run_log2(hp, dv.used_parts) : 0;
-  std::vector<int32_t> own_ptr, own_run;
-  const bool reorder = worth && (longest_list > 1 || dv.die_run_log2 > 0);
-  if (reorder) order_lists(hp, dv, longest_list, own_ptr, own_run);
-  const std::vector<int32_t>& part_ptr = reorder ? own_ptr : hp.part_ptr;
-  const std::vector<int32_t>& run = reorder ? own_run : hp.part_items;
+  const RunOrder order = run_order(hp);
+  dv.groups = order.groups;
+  dv.run_parts = order.parts;
+  dv.run_log2 = order.run_log2;
+  const std::vector<int32_t>& part_ptr = order.own ? order.ptr : hp.part_ptr;
+  const std::vector<int32_t>& run = order.own ? order.run : hp.part_items;
   for (size_t r = 0; r < n_split; ++r) dv.max_chunks = std::max(dv.max_chunks, hp.split_rows[4 * r + 2]);
   const std::vector<int32_t>* arrays[] = {&hp.empty_rows, &part_ptr, nullptr, &hp.split_rows};      // (the schedule is made in place)
   constexpr int NA = 4;
@@ -425,7 +461,7 @@ int upload(dbsp_plan* plan) {
   }
 
   // A launch of at most an item a workgroup, with nothing to count but what the front holds, see forward()
-  dv.direct = dv.front_zero && cnt_in_front && longest_list <= 1 && hp.tail_items.empty() && 4 * dv.max_chunks <= 14 &&
+  dv.direct = dv.front_zero && cnt_in_front && order.longest_list <= 1 && hp.tail_items.empty() && 4 * dv.max_chunks <= 14 &&
               up_bytes + kv_bytes <= kInStreamBytes;
   for (int i = 0; i < NA; ++i) dv.array_off[i] = off[i];
   const int32_t* ints = reinterpret_cast<const int32_t*>(dv.blob);
@@ -719,9 +755,9 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   p.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)d);
   p.scale_log2 = p.scale * 1.4426950408889634f;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // every partition with items gets its workgroup; what is left to deal (queue items, empty rows) may ask for more, up to P
+  // every list with items gets its workgroup; what is left to deal (queue items, empty rows) may ask for more, up to P
   const int64_t deal = std::max<int64_t>((int64_t)B * p.n_tail, (int64_t)B * p.n_empty);
-  const int grid = (int)std::max<int64_t>(std::max<int64_t>(dv.used_parts, 1), std::min<int64_t>(deal, hp.P));
+  const int grid = (int)std::max<int64_t>(std::max<int64_t>(dv.groups, 1), std::min<int64_t>(deal, hp.P));
   dbsp_device_plan& dm = plan->dev;
   // inside a stream capture everything goes through commands that a graph can hold
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
@@ -790,6 +826,7 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   }
   if (e != hipSuccess) return fail_hip(e, (std::string(who) + " launch").c_str());
   if (recorded != hipSuccess) return fail_hip(recorded, (std::string(who) + ": record").c_str());
+  dm.ran_staged = dm.ran_staged || direct;
   dm.last_grid = grid;
   return DBSP_OK;
 }
@@ -902,24 +939,48 @@ int dbsp_plan_tail_takes(const dbsp_plan* plan, uint32_t* takes, void* stream) {
 int dbsp_plan_calibrate(const dbsp_plan* plan, int32_t* cost, void* stream) {
   if (!plan || !cost) return fail(DBSP_EINVAL, "dbsp_plan_calibrate: null pointer");
   if (!plan->dev.resident) return fail(DBSP_EINVAL, "dbsp_plan_calibrate: the plan was built host-only");
-  const int32_t P = plan->host.P;
-  std::vector<uint64_t> busy(P);
-  const int rc = dbsp_plan_busy(plan, busy.data(), nullptr, stream);
-  if (rc != DBSP_OK) return rc;
-  // cost[g] = round(1024 * (busy[g] / load[g]) / (sum busy / sum load)), exact, round half up
-  unsigned __int128 sb = 0, sl = 0;
-  for (int32_t g = 0; g < P; ++g)
-    if (busy[g] > 0 && plan->host.part_load[g] > 0) {
-      sb += busy[g];
-      sl += (uint64_t)plan->host.part_load[g];
+  const dbsp_host_plan& hp = plan->host;
+  const int32_t P = hp.P;
+  try {
+    std::vector<uint64_t> busy(P);
+    const int rc = dbsp_plan_busy(plan, busy.data(), nullptr, stream);
+    if (rc != DBSP_OK) return rc;
+    // round(1024 * (busy[g] / load[g]) / (sum busy / sum load)), exact, round half up
+    unsigned __int128 sb = 0, sl = 0;
+    for (int32_t g = 0; g < P; ++g)
+      if (busy[g] > 0 && hp.part_load[g] > 0) {
+        sb += busy[g];
+        sl += (uint64_t)hp.part_load[g];
+      }
+    // the workgroup that ran partition g here runs partition `to` of a plan with costs
+    const int32_t cost_log2 = hp.by_greedy ? longest_runs_log2(P) : 0;
+    for (int32_t b = 0; b < P; ++b) {
+      const int32_t g = plan->dev.part_of(b), to = dbsp_part_of(b, P, cost_log2);
+      const int64_t l = hp.part_load[g];
+      if (busy[g] == 0 || l <= 0 || sb == 0) { cost[to] = 1024; continue; }
+      const unsigned __int128 num = (unsigned __int128)busy[g] * 1024 * sl, den = (unsigned __int128)(uint64_t)l * sb;
+      const unsigned __int128 q = (2 * num + den) / (2 * den);
+      cost[to] = q < 512 ? 512 : q > 2048 ? 2048 : (int32_t)q;
     }
-  for (int32_t g = 0; g < P; ++g) {
-    const int64_t l = plan->host.part_load[g];
-    if (busy[g] == 0 || l <= 0 || sb == 0) { cost[g] = 1024; continue; }
-    const unsigned __int128 num = (unsigned __int128)busy[g] * 1024 * sl, den = (unsigned __int128)(uint64_t)l * sb;
-    const unsigned __int128 q = (2 * num + den) / (2 * den);
-    cost[g] = q < 512 ? 512 : q > 2048 ? 2048 : (int32_t)q;
+  } catch (const std::bad_alloc&) {
+    return fail(DBSP_ENOMEM, "dbsp_plan_calibrate: out of host memory");
   }
+  return DBSP_OK;
+}
+
+int dbsp_plan_run_order(const dbsp_plan* plan, int32_t* partition_of, int32_t* items, int32_t* staged) {
+  if (!plan) return fail(DBSP_EINVAL, "dbsp_plan_run_order: null plan");
+  const dbsp_host_plan& hp = plan->host;
+  try {
+    const RunOrder o = run_order(hp);
+    if (partition_of)
+      for (int32_t b = 0; b < hp.P; ++b) partition_of[b] = dbsp_part_of(b, o.parts, o.run_log2);
+    const std::vector<int32_t>& run = o.own ? o.run : hp.part_items;
+    if (items) std::copy(run.begin(), run.end(), items);
+  } catch (const std::bad_alloc&) {
+    return fail(DBSP_ENOMEM, "dbsp_plan_run_order: out of host memory");
+  }
+  if (staged) *staged = plan->dev.ran_staged ? 1 : 0;
   return DBSP_OK;
 }
 

@@ -38,6 +38,7 @@ struct dbsp_host_plan {
   bool reused = false;       // the placement was carried over from a previous plan
   bool by_rounds = false;    // DBSP_MODE_ROUNDS made the placement (a carried-over one: made the plan it comes from)
   bool by_greedy = false;    // the same of DBSP_MODE_BALANCED
+  bool by_cost = false;      // and with partition_cost
   double rho_reuse = 0.0;    // rho_s of this mask under the previous plan's placement (0 if none was tried)
   int64_t n_items() const { return (int64_t)item_slot.size(); }
   int64_t kv_ints() const { return pair ? 2 * nnz : nnz; }   // length of kv_idx
@@ -46,6 +47,14 @@ struct dbsp_host_plan {
 
 // Device mirror.  One pooled allocation (`blob`) holds the int32 arrays, the busy-time capture
 // buffers and the split-row scratch for max_batch batch entries at d = 128.
+// The partition that workgroup b runs.  Workgroups with b mod 8 alike run on one die: of the first n partitions it has
+// 2^lg in a row, then the next 8 of their runs on, as far as there are whole runs for every die; the others are dealt one by one.
+inline int32_t dbsp_part_of(int32_t b, int32_t n, int32_t lg) {
+  const int32_t j = b >> 3;
+  if (b >= n >> (lg + 3) << (lg + 3)) return b;
+  return ((j >> lg) << (lg + 3)) + ((b & 7) << lg) + (j & ((1 << lg) - 1));
+}
+
 struct dbsp_device_plan {
   bool resident = false;
   int device = -1;
@@ -76,23 +85,16 @@ struct dbsp_device_plan {
   const int32_t* sched = nullptr;  // 8 x int32 per item, see upload()
   uint32_t* queue = nullptr;      // [1 + n_tail]: next queue position, take count per tail item
   uint32_t* split_cnt = nullptr;  // [max_batch][n_split][8]: finished chunks of a split row, per wave, zero between launches
-  int32_t used_parts = 0;         // partitions up to the last one that has items
-  int32_t die_run_log2 = 0;       // log2 of the partitions in a row that one compute die runs, see die_run_log2() in api.hip
-  int32_t part_of(int32_t b) const;      // the partition workgroup b runs
+  int32_t groups = 0;             // workgroups up to the last one that has items
+  int32_t run_parts = 0, run_log2 = 0;                 // see dbsp_part_of
+  int32_t part_of(int32_t b) const { return dbsp_part_of(b, run_parts, run_log2); }
+  bool ran_staged = false;        // a launch has read the plan where it is staged
   uint64_t* busy = nullptr;       // [P]
   uint32_t* hw_id = nullptr;      // [P]
   float* part_o = nullptr;        // split-row partial outputs, f32 [batches][n_slots][block][d]
   float* part_lse = nullptr;      // f32 [batches][n_slots][block]
   int32_t max_batch = 1;          // batch entries the split-row scratch was sized for
 };
-
-// Workgroups b with b mod 8 alike run on one die: 2^die_run_log2 partitions in a row, then the next 8 of their runs on, as
-// far as there are whole runs for every die.
-inline int32_t dbsp_device_plan::part_of(int32_t b) const {
-  const int32_t lg = die_run_log2, j = b >> 3;
-  if (b >= used_parts >> (lg + 3) << (lg + 3)) return b;
-  return ((j >> lg) << (lg + 3)) + ((b & 7) << lg) + (j & ((1 << lg) - 1));
-}
 
 struct dbsp_plan {
   dbsp_host_plan host;

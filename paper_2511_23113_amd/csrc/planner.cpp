@@ -714,6 +714,7 @@ int dbsp_plan_place(const dbsp_place_opts& opts, const dbsp_host_plan* prev, dou
 
     hp.by_rounds = hp.reused ? prev->by_rounds : mode == DBSP_MODE_ROUNDS;
     hp.by_greedy = hp.reused ? prev->by_greedy : mode == DBSP_MODE_BALANCED;
+    hp.by_cost = hp.reused ? prev->by_cost : partition_cost != nullptr;
 
     // The placement asked for; rho_s of the other ones is worked out only when dbsp_plan_stats asks.
     hp.partition_cost.assign(partition_cost ? partition_cost : nullptr, partition_cost ? partition_cost + P : nullptr);

@@ -55,3 +55,40 @@ def test_every_partition_runs_once(block, d, kind, P):
         some = ~np.isneginf(Lr)
         assert np.array_equal(~np.isneginf(lse), some)
         assert np.abs(o - Or).max() <= O_TOL * max(1.0, np.abs(Or).max()) and np.abs(lse[some] - Lr[some]).max() <= LSE_TOL
+
+
+# 60 rows and a mask that leaves their partitions dealt one by one; 600 equal rows, dealt in runs as with costs; 600 of all lengths
+@pytest.mark.parametrize("block, d", [(128, 128), (64, 64)])
+@pytest.mark.parametrize("rows", [60, 600])
+@pytest.mark.parametrize("P", [64, 130, 256])
+@pytest.mark.parametrize("kind", ["equal", "ragged"])
+def test_costs_stay_with_the_compute_unit(block, d, rows, P, kind):
+    import paper_2511_23113_amd as dbsp
+    import torch
+    from oracle import planner as op
+    from paper_2511_23113_amd import binding as B
+    H, nQ, nK = 3, rows // 3, 40
+    rng = np.random.default_rng(P)
+    keep = np.full((H, nQ), 21) if kind == "equal" else rng.integers(17, nK + 1, (H, nQ))
+    mask = np.zeros((H, nQ, nK), np.uint8)
+    for h in range(H):
+        for i in range(nQ):
+            mask[h, i, rng.permutation(nK)[:keep[h, i]]] = 1
+    q, k, v = (torch.randn((1, H, n * block, d), device="cuda").to(torch.bfloat16) for n in (nQ, nK, nK))
+
+    def launched(**kw):
+        plan = dbsp.plan_sparse_attn(mask, block, num_partitions=P, max_item_len=-1, **kw)
+        dbsp.sparse_attn_fwd(plan, q, k, v)
+        return (plan, *plan.busy())
+
+    plain, ticks, hw = launched()
+    cost = plain.calibrate()
+    by_partition = np.asarray(op.calibrate_cost(ticks.tolist(), plain.array(B.PART_LOAD).tolist()))
+    tuned, ticks, hw_tuned = launched(partition_cost=cost)
+    here, there = plain.run_order()[0], tuned.run_order()[0]
+    assert np.array_equal(cost[there], by_partition[here])
+    # and that is where it runs: workgroup b on one die in every launch
+    both = (plain.array(B.PART_LOAD)[here] > 0) & (tuned.array(B.PART_LOAD)[there] > 0)
+    assert both.any() and np.array_equal(hw[here][both] >> 16, hw_tuned[there][both] >> 16)
+    # measured under the costs' own order, a partition's cost is its own
+    assert tuned.calibrate().tolist() == op.calibrate_cost(ticks.tolist(), tuned.array(B.PART_LOAD).tolist())
