@@ -28,10 +28,11 @@ int dbsp_mfma_probe(double* tflops, double* clock_ghz, void* stream);
  * dbsp_plan_run_order -- what the workgroups of a plan's launches run (also of a host-only plan's).  partition_of:
  * int32 [P] or NULL, the partition that workgroup b has (b, but where DBSP_MODE_BALANCED made the placement).  items: int32,
  * as many as DBSP_PART_ITEMS has, or NULL: the workgroups' items one workgroup behind the other, in the order in which
- * they run.  staged: int32 or NULL, 1 if one of the plan's launches has read it where it was staged, without a fetch, else 0.
+ * they run.  local: int32 or NULL, 1 if the launches' waits count on KV blocks being found in the L2 (at d = 128 with items of
+ * 128 queries; else 0 or 1 without effect).  staged: int32 or NULL, 1 if one of the plan's launches has read it where it was staged, without a fetch, else 0.
  * Errors: DBSP_EINVAL, DBSP_ENOMEM.
  */
-int dbsp_plan_run_order(const dbsp_plan* plan, int32_t* partition_of, int32_t* items, int32_t* staged);
+int dbsp_plan_run_order(const dbsp_plan* plan, int32_t* partition_of, int32_t* items, int32_t* local, int32_t* staged);
 
 #ifdef __cplusplus
 }

@@ -92,7 +92,7 @@ def load_library(path: str | None = None):
     lib.dbsp_plan_tail_takes.restype = C.c_int
     lib.dbsp_plan_pair_rows.argtypes = [vp, C.POINTER(C.c_int32)]
     lib.dbsp_plan_pair_rows.restype = C.c_int
-    lib.dbsp_plan_run_order.argtypes = [vp, vp, vp, C.POINTER(C.c_int32)]
+    lib.dbsp_plan_run_order.argtypes = [vp, vp, vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
     lib.dbsp_plan_run_order.restype = C.c_int
     lib.dbsp_plan_destroy.argtypes = [vp]
     lib.dbsp_plan_destroy.restype = None
@@ -171,14 +171,14 @@ class Plan:
         _check(load_library().dbsp_plan_calibrate(self.handle, cost.ctypes.data_as(C.c_void_p), _stream_ptr(stream)))
         return cost
 
-    def run_order(self):
-        """(partition of every workgroup int32 [P], item ids workgroup by workgroup in the order they run, whether a launch
-        has read the plan where it was staged): see dbsp_diag.h, dbsp_plan_run_order."""
+    def run_order(self) -> dict:
+        """dbsp_plan_run_order (see dbsp_diag.h): partition_of (int32, of every workgroup), items (int32, workgroup by
+        workgroup in the order they run), local, staged."""
         part = np.zeros(self.stats(with_rho=False)["num_partitions"], dtype=np.int32)
         items = np.zeros(self.array(PART_ITEMS).shape[0], dtype=np.int32)
-        staged = C.c_int32()
-        _check(load_library().dbsp_plan_run_order(self.handle, _addr(part), _addr(items), C.byref(staged)))
-        return part, items, bool(staged.value)
+        local, staged = C.c_int32(), C.c_int32()
+        _check(load_library().dbsp_plan_run_order(self.handle, _addr(part), _addr(items), C.byref(local), C.byref(staged)))
+        return dict(partition_of=part, items=items, local=bool(local.value), staged=bool(staged.value))
 
     def close(self):
         if self._h:

@@ -260,6 +260,7 @@ struct RunOrder {
   int32_t parts = 0, run_log2 = 0;         // workgroup b has partition dbsp_part_of(b, parts, run_log2)
   int32_t groups = 0, longest_list = 0;    // workgroups up to the last one that has items, items the longest list has
   bool own = false;                        // by the lists below instead of the placement's own
+  bool local = false;                      // see dbsp_fwd_params
   std::vector<int32_t> ptr, run;           // [P + 1] where the workgroups' lists begin, and the lists
 };
 
@@ -377,6 +378,7 @@ RunOrder run_order(const dbsp_host_plan& hp) {
     order_lists(hp, worth, o);
     while (o.groups < hp.P && o.ptr[o.groups] < o.ptr[hp.P]) ++o.groups;
   }
+  o.local = hp.by_rounds || (hp.by_greedy && o.longest_list > 1);
   return o;
 }
 
@@ -394,6 +396,7 @@ int upload(dbsp_plan* plan) {
   dv.groups = order.groups;
   dv.run_parts = order.parts;
   dv.run_log2 = order.run_log2;
+  dv.local = order.local;
   const std::vector<int32_t>& part_ptr = order.own ? order.ptr : hp.part_ptr;
   const std::vector<int32_t>& run = order.own ? order.run : hp.part_items;
   for (size_t r = 0; r < n_split; ++r) dv.max_chunks = std::max(dv.max_chunks, hp.split_rows[4 * r + 2]);
@@ -743,7 +746,7 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   // (the counters of in-place merges are sized for max_batch, and calls that share the static scratch leave
   // nothing behind in it: its split rows are merged by the second launch)
   p.in_place_ok = !static_scratch_wanted && (int64_t)B * hp.n_items() <= hp.P ? 1 : 0;
-  p.local = hp.by_rounds || hp.by_greedy ? 1 : 0;
+  p.local = dv.local ? 1 : 0;
   p.merge_later = 0;
   p.busy = dv.busy;
   p.hw_id = dv.hw_id;
@@ -968,7 +971,7 @@ int dbsp_plan_calibrate(const dbsp_plan* plan, int32_t* cost, void* stream) {
   return DBSP_OK;
 }
 
-int dbsp_plan_run_order(const dbsp_plan* plan, int32_t* partition_of, int32_t* items, int32_t* staged) {
+int dbsp_plan_run_order(const dbsp_plan* plan, int32_t* partition_of, int32_t* items, int32_t* local, int32_t* staged) {
   if (!plan) return fail(DBSP_EINVAL, "dbsp_plan_run_order: null plan");
   const dbsp_host_plan& hp = plan->host;
   try {
@@ -977,6 +980,7 @@ int dbsp_plan_run_order(const dbsp_plan* plan, int32_t* partition_of, int32_t* i
       for (int32_t b = 0; b < hp.P; ++b) partition_of[b] = dbsp_part_of(b, o.parts, o.run_log2);
     const std::vector<int32_t>& run = o.own ? o.run : hp.part_items;
     if (items) std::copy(run.begin(), run.end(), items);
+    if (local) *local = o.local ? 1 : 0;
   } catch (const std::bad_alloc&) {
     return fail(DBSP_ENOMEM, "dbsp_plan_run_order: out of host memory");
   }

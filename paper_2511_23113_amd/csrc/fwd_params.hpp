@@ -28,7 +28,8 @@ struct dbsp_fwd_params {
   int32_t n_placed;         // items the partitions' lists hold (all of them but the shared queue's)
   int32_t max_chunks;       // the most chunks a split row has; 0: no split rows
   int32_t in_place_ok;      // split_cnt may be used, and there are no more items than partitions, all batch entries counted
-  int32_t local;            // rows that share KV blocks run at a time behind one L2: the plan's placement is the round-based or the greedy one
+  int32_t local;            // a slice's barrier may leave two slices' copies under way, see dbsp_launch_fwd: the plan's placement is the
+                            // round-based one, or a greedy one that has more than an item for a workgroup
   int32_t merge_later;      // set by dbsp_launch_fwd: split rows are merged by a kernel of their own behind this one
   float scale;         // softmax scale
   float scale_log2;    // softmax scale * log2(e)

@@ -88,6 +88,7 @@ struct dbsp_device_plan {
   int32_t groups = 0;             // workgroups up to the last one that has items
   int32_t run_parts = 0, run_log2 = 0;                 // see dbsp_part_of
   int32_t part_of(int32_t b) const { return dbsp_part_of(b, run_parts, run_log2); }
+  bool local = false;             // see dbsp_fwd_params
   bool ran_staged = false;        // a launch has read the plan where it is staged
   uint64_t* busy = nullptr;       // [P]
   uint32_t* hw_id = nullptr;      // [P]

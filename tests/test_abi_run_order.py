@@ -46,7 +46,8 @@ def mask_of(rows, nK, seed):
 
 def lists(plan, items):
     """Items of every workgroup, in the order they run."""
-    of, run, _ = plan.run_order()
+    order = plan.run_order()
+    of, run = order["partition_of"], order["items"]
     ptr, n = plan.array(B.PART_PTR), np.diff(plan.array(B.PART_PTR))
     ends = np.cumsum(n[of])
     own = [run[e - c:e] for e, c in zip(ends, n[of])]
@@ -80,6 +81,7 @@ def test_every_partition_runs_once_longest_first(P, kind, block, pair):
         rows = 128 if pair else block
         worth = length.sum() * rows * rows >= 4 * 128 * 128 * len(length)
         assert np.array_equal(of, dealt(used, runs_of(load[:used]) if worth else 0, P))
+        assert plan.run_order()["local"] == (max(map(len, own)) > 1)       # an item each: nothing to put in an order
         for mine in own:
             assert list(mine) == (sorted(mine, key=lambda i: (-length[i], i)) if worth else sorted(mine))
 
@@ -89,8 +91,9 @@ def test_other_placements_run_as_they_stand():
     for kw in (dict(mode=B.MODE_NAIVE), dict(mode=B.MODE_ROUNDS, locality_groups=8), dict(mode=B.MODE_ROUNDS, dynamic_tail=40),
                dict(mode=B.MODE_REWARD, locality_groups=8, reward=1.0), dict(mode=B.MODE_ROUNDS, partition_cost=np.arange(1, 257))):
         plan = dbsp.plan_sparse_attn(mask, 128, num_partitions=256, host_only=True, **kw)
-        of, run, _ = plan.run_order()
-        assert np.array_equal(of, np.arange(256)) and np.array_equal(run, plan.array(B.PART_ITEMS))
+        order = plan.run_order()
+        assert np.array_equal(order["partition_of"], np.arange(256)) and np.array_equal(order["items"], plan.array(B.PART_ITEMS))
+        assert order["local"] == (kw["mode"] == B.MODE_ROUNDS)
 
 
 @pytest.mark.parametrize("P", [7, 64, 130, 256, 1024])
@@ -105,4 +108,4 @@ def test_with_costs_a_partitions_workgroup_is_settled_by_their_number(P):
             assert np.array_equal(of, dealt(P, longest_runs(P), P))
             # a placement carried over stays where it is
             kept, reused, _ = dbsp.plan_sparse_attn_reuse(plan, mask, 1e9, max_item_len=30, host_only=True)
-            assert reused and np.array_equal(kept.run_order()[0], of)
+            assert reused and np.array_equal(kept.run_order()["partition_of"], of)

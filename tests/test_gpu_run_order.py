@@ -85,7 +85,7 @@ def test_costs_stay_with_the_compute_unit(block, d, rows, P, kind):
     cost = plain.calibrate()
     by_partition = np.asarray(op.calibrate_cost(ticks.tolist(), plain.array(B.PART_LOAD).tolist()))
     tuned, ticks, hw_tuned = launched(partition_cost=cost)
-    here, there = plain.run_order()[0], tuned.run_order()[0]
+    here, there = plain.run_order()["partition_of"], tuned.run_order()["partition_of"]
     assert np.array_equal(cost[there], by_partition[here])
     # and that is where it runs: workgroup b on one die in every launch
     both = (plain.array(B.PART_LOAD)[here] > 0) & (tuned.array(B.PART_LOAD)[there] > 0)
