@@ -21,6 +21,7 @@ def test_first_launches_of_small_plans(block, d, length, mode):
     q, k, v = (torch.randn((1, H, n * block, d), generator=gen, device="cuda").to(torch.bfloat16) for n in (nQ, nK, nK))
     streams = [torch.cuda.current_stream(), torch.cuda.Stream()]
     torch.cuda.synchronize()
+    staged = 0
     for step in range(24):
         mask = (rng.random((H, nQ, nK)) < rng.choice([0.1, 0.4, 0.8])).astype(np.uint8)
         mask[0, 0, 0] = 1
@@ -39,9 +40,15 @@ def test_first_launches_of_small_plans(block, d, length, mode):
             # merged two chunks at a time here, four there: a rounding of O apart, a few of LSE (at most 8)
             torch.testing.assert_close(o, want_o, rtol=2.0 ** -7, atol=1e-4)
             torch.testing.assert_close(lse, want_lse, rtol=0, atol=8 * 2.0 ** -21)
+            # and the same bits from launch to launch, whichever way the plan was read
+            if launch == 0:
+                first_o, first_lse = o, lse
+            assert torch.equal(o, first_o) and torch.equal(lse, first_lse)
         ticks, _ = plan.busy()
         assert mode == 2 or np.array_equal(ticks > 0, plan.array(7) > 0)          # 7: blocks per partition
+        staged += plan.run_order()["staged"]
         del plan
+    assert staged > 0
 
 
 def test_a_batch_or_the_static_scratch_fetches():
@@ -99,6 +106,7 @@ def test_a_capture_right_behind_a_first_launch():
             graph.capture_begin()
             dbsp.sparse_attn_fwd(plan, q, k, v, o=out[0], lse=out[1])
             graph.capture_end()
+        assert plan.run_order()["staged"]
         ticks, _ = plan.busy(side)
         assert np.array_equal(ticks > 0, plan.array(7) > 0)        # 7: blocks per partition
         same(first, want)

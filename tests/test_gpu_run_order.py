@@ -22,9 +22,8 @@ def _run(plan, q, k, v):
     return o.float().cpu().numpy(), lse.cpu().numpy()
 
 
-# 60 rows of up to 13 blocks: equal rows (runs as long as they get, or cut short where the last partitions have an item
-# less), rows of all lengths, empty rows (workgroups behind the last partition that has items); with 64-token blocks the items
-# are too short for an order of their own
+# 60 rows of up to 13 blocks, too few for runs on the dies: equal rows, rows of all lengths, empty rows (workgroups behind the
+# last partition that has items); with 64-token blocks the items are too short for an order of their own
 @pytest.mark.parametrize("block, d", [(128, 128), (64, 64)])
 @pytest.mark.parametrize("kind", ["equal", "ragged", "empty_rows"])
 @pytest.mark.parametrize("P", [7, 8, 15, 16, 33, 60, 64, 130, 256])
@@ -55,6 +54,51 @@ def test_every_partition_runs_once(block, d, kind, P):
         some = ~np.isneginf(Lr)
         assert np.array_equal(~np.isneginf(lse), some)
         assert np.abs(o - Or).max() <= O_TOL * max(1.0, np.abs(Or).max()) and np.abs(lse[some] - Lr[some]).max() <= LSE_TOL
+
+
+# Partitions in runs on the dies, with and without some behind the last whole runs, lists sorted one by one (equal rows: two items
+# for the first partitions, one for the others) and by counting (rows of all lengths, ten a partition)
+@pytest.mark.parametrize("block, d, pair", [(128, 128, False), (128, 64, False), (64, 64, False), (64, 128, False), (64, 128, True)])
+@pytest.mark.parametrize("kind", ["equal", "ragged"])
+@pytest.mark.parametrize("P, twos", [(64, 32), (127, 64), (200, 96), (256, 128)])
+def test_partitions_in_runs(block, d, pair, kind, P, twos):
+    import torch
+    import paper_2511_23113_amd as dbsp
+    from paper_2511_23113_amd import binding as B
+    rows = P + twos if kind == "equal" else 10 * P
+    per, nK = (2, 80) if pair else (1, 40)
+    rng = np.random.default_rng(P)
+    keep = np.full(rows, 17) if kind == "equal" else rng.integers(17, 41, rows)
+    mask = np.zeros((1, rows * per, nK), np.uint8)
+    for i in range(rows):
+        mask[0, per * i:per * i + per, rng.permutation(nK)[:keep[i] * per]] = 1
+    q, k, v = (torch.randn((1, 1, n * block, d), device="cuda").to(torch.bfloat16) for n in (rows * per, nK, nK))
+
+    def launched(plan):
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full(q.shape[:3], float("nan"), device="cuda")
+        for _ in range(2):
+            dbsp.sparse_attn_fwd(plan, q, k, v, o=o, lse=lse)
+        torch.cuda.synchronize()
+        return o, lse
+
+    kw = dict(num_partitions=P, max_item_len=-1, pair_rows=pair)
+    greedy = dbsp.plan_sparse_attn(mask, block, **kw)
+    of = greedy.run_order()["partition_of"]
+    assert not np.array_equal(of, np.arange(P)) and sorted(of) == list(range(P))
+    want = launched(dbsp.plan_sparse_attn(mask, block, mode=dbsp.MODE_NAIVE, **kw))
+    assert bool(torch.isfinite(want[0]).all()) and bool(torch.isfinite(want[1]).all())
+    kept, reused, _ = dbsp.plan_sparse_attn_reuse(greedy, mask, 8.0, max_item_len=-1)
+    assert reused
+    for plan in (greedy, kept):
+        got = launched(plan)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        ticks, hw = plan.busy()
+        for die in range(8):                                  # times and places are their partitions' own
+            assert len(set(hw[of[die::8]] >> 16)) == 1
+        if kind == "equal":
+            two = np.diff(plan.array(B.PART_PTR)) == 2
+            assert two.sum() == twos and ticks[two].min() > 1.2 * np.median(ticks[~two])
 
 
 # 60 rows and a mask that leaves their partitions dealt one by one; 600 equal rows, dealt in runs as with costs; 600 of all lengths
