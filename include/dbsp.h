@@ -144,7 +144,8 @@ typedef struct dbsp_plan_opts {
  * process-wide pool): the call returns without waiting for it, and sparse_attn_fwd makes its
  * stream wait for the copy, so planning the next call overlaps with the device's work on the
  * current one.  A plan of up to 64 KiB is instead fetched by a kernel that the first
- * sparse_attn_fwd enqueues in front of its own.  Masks over 1 MB are counted on up to 8 host threads; the index lists are written
+ * sparse_attn_fwd enqueues in front of its own, or, with at most an item a partition, read in pinned memory by the first
+ * launch itself and fetched by the second.  Masks over 1 MB are counted on up to 8 host threads; the index lists are written
  * straight into pinned memory by helper threads while the calling thread builds items and
  * placement (the helpers belong to a process-wide pool and sleep between plans; all of them are
  * done before the call returns).
@@ -312,7 +313,10 @@ enum dbsp_plan_array {
                                chunks of split rows, in item order                                    */
   DBSP_SPLIT_ROWS = 4,      /* int32 [n_split*4] (row, first_slot, n_chunks, 0)                       */
   DBSP_PART_PTR = 5,        /* int32 [P + 1]     offsets into PART_ITEMS                              */
-  DBSP_PART_ITEMS = 6,      /* int32 [n_items]   item ids of each partition, in processing order      */
+  DBSP_PART_ITEMS = 6,      /* int32 [n_items]   item ids of each partition, in the placement's order: that
+                               of the rounds (DBSP_MODE_ROUNDS), else ascending.  The order in which they run, and the
+                               workgroup that runs a partition, may differ for DBSP_MODE_BALANCED, see
+                               dbsp_plan_run_order in dbsp_diag.h */
   DBSP_PART_LOAD = 7,       /* int64 [P]         active blocks per partition (pure block counts)      */
   DBSP_BLOCKS_PER_HEAD = 8, /* int64 [H]         active blocks per head                               */
   DBSP_ROW_CNT = 9,         /* int32 [H*nQ]      active blocks per row                                */

@@ -357,9 +357,12 @@ RunOrder run_order(const dbsp_host_plan& hp) {
     o.longest_list = std::max(o.longest_list, n);
     if (n) o.groups = g + 1;
   }
-  // (Not for short items, of fewer than four blocks of 128 tokens or sixteen of 64 in the mean: it takes the host longer than it
-  // gains.  11 heads, 212 x 212 blocks of 64 at d = 64, 13 blocks an item, planned on every call 87 us without and 94 with it; 3 heads, 217 x 108 blocks of 64 at d = 64, 6.2 blocks an item: the kernel 44.0 us without, 43.4 with it, planned on
-  // every call 86 and 90 a pass; 12 heads, 21 x 23 of 128, 5 an item: the kernel 59.5 and 55.2.)
+  // Not for short items, of fewer than four blocks of 128 tokens or sixteen of 64 in the mean.  us a pass listed / ordered of a kept plan,
+  // then planned on every call: 128 tokens at d = 128, 3.1 blocks an item 502 / 560, 511 / 568, 3.8 124 / 130, 128 / 136, 4.8
+  // 208 / 208, 213 / 214, 5.1 (12 heads, 21 x 23) 60 / 55; at d = 64 3.8 83 / 85, 111 / 118, 4.8 134 / 134, 141 / 143; pair rows, 2.9
+  // 129 / 123, 151 / 165, 4.1 196 / 186, 202 / 195.  With 64 tokens the kernel gains earlier, but the host, which has more
+  // items for the same work, loses it where it plans on every call: d = 64, 6.1 64 / 59, 117 / 129, 9.4 79 / 68, 113 / 122, 15.9
+  // 181 / 151, 190 / 172; at d = 128 8.4 100 / 91, 109 / 113, 12.7 137 / 118, 142 / 127.  A plan does not know how often it will be used.
   const bool worth = hp.by_greedy && hp.nnz * hp.tile_rows() * hp.tile_rows() >= 65536 * hp.n_items();
   o.parts = o.groups;
   if (hp.by_greedy && hp.by_cost) {
@@ -463,8 +466,8 @@ int upload(dbsp_plan* plan) {
     if (rc != DBSP_OK) return rc;
   }
 
-  // A launch of at most an item a workgroup, with nothing to count but what the front holds, see forward()
-  dv.direct = dv.front_zero && cnt_in_front && order.longest_list <= 1 && hp.tail_items.empty() && 4 * dv.max_chunks <= 14 &&
+  // A launch of at most an item a workgroup, with nothing to count but what the front holds, rows merged in place: see forward()
+  dv.direct = dv.front_zero && cnt_in_front && order.longest_list <= 1 && hp.tail_items.empty() && kMaxTilesPerWave * dv.max_chunks <= kTilesInPlace &&
               up_bytes + kv_bytes <= kInStreamBytes;
   for (int i = 0; i < NA; ++i) dv.array_off[i] = off[i];
   const int32_t* ints = reinterpret_cast<const int32_t*>(dv.blob);
@@ -769,8 +772,8 @@ static int forward(const dbsp_plan* plan, const void* q, const void* k, const vo
   // The first launch of a small plan, no more than an item a workgroup, reads it where it lies in pinned memory: a launch
   // less, which the host takes longer to make than the kernel runs.  What such a launch counts it counts in the device buffer's front,
   // which has to be zero: the plan that had the buffer before has sent zeros there, and every launch leaves them.  The
-  // second launch of the plan fetches it like any other's first.  512 tokens, two heads, planned on every call: 24.5 us a
-  // pass with the fetch, 21.4 so (the host's 19.3 and 17.7 for planning and launching).  A workgroup's way to its first
+  // second launch of the plan fetches it like any other's first.  512 tokens, two heads, planned on every call: 22 - 24 us a
+  // pass with the fetch, 20 - 21 so (runs of one side differ by up to 4; the host's 19.3 and 17.7 for planning and launching).  A workgroup's way to its first
   // blocks is three or four reads across the bus, one behind the other, as long as the fetch took; with more items a
   // workgroup they would come in between.
   const bool direct = dm.direct && !dm.sent && !capture && B == 1 && p.in_place_ok;

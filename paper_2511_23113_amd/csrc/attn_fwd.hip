@@ -113,6 +113,7 @@ struct Cfg {
   // the others to the waves of the other key groups.  Its outbox lies at the end of its group's ring, clear
   // of the first two K slices, which already belong to the next item by then.
   static constexpr int TPW = 2 * DT / NC, XCH = (NC - 1) * TPW * 4096;
+  static_assert(TPW <= kMaxTilesPerWave, "what plans go by that are read where they are staged");
   // Where the query groups share slices an item's Q comes by way of the LDS, tiles of 32 queries laid out like slices of K:
   // each wave copies QCP KiB of it.  It lies in the third and fourth K slice of the ring of key group wa, which neither the
   // next item's first slices nor the outboxes use, or behind the rings.
@@ -167,6 +168,11 @@ __device__ __forceinline__ const unsigned char* if_less(int a, int b, const unsi
   return z;
 }
 
+template <int N>
+__device__ __forceinline__ void wait_copies() {      // all but the N youngest copies of this wave have landed
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // The same, and all LDS reads have returned.  At d = 128 by the builtin, whose meaning the compiler knows: behind an asm
 // block it waits for these reads again, operand by operand, nine instructions of a slice's two hundred.  us by asm / by the
 // builtin: pair rows, 40 heads, 512 x 512 blocks 5338 / 5285, 24 heads, 301 x 301 blocks of 64 992 / 987, 40 heads,
@@ -181,11 +187,6 @@ __device__ __forceinline__ void wait_reads() {
     __builtin_amdgcn_s_waitcnt((N & 15) | 7 << 4 | 0 << 8 | (N >> 4) << 14);      // vmcnt, expcnt (not waited for), lgkmcnt
     asm volatile("" ::: "memory");
   }
-}
-
-template <int N>
-__device__ __forceinline__ void wait_copies() {      // all but the N youngest copies of this wave have landed
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // Partial results of split rows cross from one compute die's L2 to another's inside a launch: they are
@@ -486,8 +487,8 @@ void dbsp_fwd_kernel(const dbsp_fwd_params p, const int32_t* __restrict__ g_kv_i
   auto head_of = [&](const int4& d, int batch) { return (int64_t)batch * p.H + d.x; };
   // Copies of this wave's share of a slice: K or V of slice u of block J into position b of its ring,
   // KiB by KiB: begin() once (destination and base), then one() for x = 0 .. LOADS - 1.  Past the end of
-  // the list the last block is copied again, into positions nobody reads: that costs less than a branch
-  // in the step sequence.
+  // the list the last block is copied again (U == 2: the first one, or the next item's K and Q, see past),
+  // into positions nobody reads: that costs less than a branch in the step sequence.
   auto copy_begin = [&](const unsigned char* base, int J, int u, uint32_t b, int x) {
     from = base + (int64_t)(SHARED && U == 1 ? __builtin_amdgcn_readfirstlane(J) : J) * BLOCK_BYTES + u * C::SL + x * 1024;
     set_copy_dst(ring + b * C::SL + share + x * 1024);
@@ -1073,7 +1074,7 @@ hipError_t launch_fwd(dbsp_fwd_params p, int grid, hipStream_t stream) {
   // 128 at d = 128, 3 chunks 226 / 227, 4 chunks 162 / 158.  Where items queue up, who merges falls behind,
   // ends its next rows last and merges these as well: 12 heads, 21 x 23 blocks of 128, up to 4 chunks
   // 72 / 65; 10 heads, 128 x 256, up to 8 chunks 1068 / 771.
-  p.merge_later = p.max_chunks > 0 && (p.max_chunks * C::TPW > 14 || !p.in_place_ok);
+  p.merge_later = p.max_chunks > 0 && (p.max_chunks * C::TPW > kTilesInPlace || !p.in_place_ok);
   // the dynamic-LDS limit is a per-device function attribute: set it once per device
   static std::atomic<uint32_t> attr_set_mask{0};
   int dev = 0;

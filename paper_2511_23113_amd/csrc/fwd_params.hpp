@@ -5,6 +5,9 @@
 
 #include <cstdint>
 
+constexpr int kTilesInPlace = 14;       // a wave merges a split row in place up to so many tiles, see launch_fwd
+constexpr int kMaxTilesPerWave = 4;     // and has at most so many of every chunk (Cfg::TPW)
+
 struct dbsp_fwd_params {
   const uint16_t* q;   // bf16 [B,H,nQ*BLK,D]
   const uint16_t* k;   // bf16 [B,H,nK*BLK,D]
