@@ -342,8 +342,9 @@ int dbsp_plan_stats(const dbsp_plan* plan, double* rho_naive, double* rho_balanc
 /* dbsp_plan_calibrate: relative time per block of the compute units, measured by the LAST sparse_attn_fwd on this plan,
  * for dbsp_plan_opts.partition_cost of later plans with the same mode and partition count (compute units of one
  * chip differ by a few percent in speed, systematically).  cost: host, int32 [P], written: cost[g] belongs to the compute
- * unit that runs partition g of such a plan.  The partition h that it ran in this one is g, but for DBSP_MODE_BALANCED
- * plans made without partition_cost, whose masks may settle it otherwise:
+ * unit that runs partition g of such a plan (of more items than partitions: of others the costs settle nothing).  The
+ * partition h that it ran in this one is g, but for DBSP_MODE_BALANCED plans made without partition_cost or of fewer items,
+ * whose masks may settle it otherwise:
  * cost[g] = round(1024 * (busy[h] / load[h]) / (sum busy / sum load)) in exact integer arithmetic (round
  * half up), clamped to [512, 2048]; 1024 for a partition without work or measurement.  Synchronises
  * `stream` before reading.  Errors: DBSP_EINVAL (null pointer, host-only plan), DBSP_ENOMEM, DBSP_EHIP. */

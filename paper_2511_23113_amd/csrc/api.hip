@@ -365,12 +365,13 @@ RunOrder run_order(const dbsp_host_plan& hp) {
   // 181 / 151, 190 / 172; at d = 128 8.4 100 / 91, 109 / 113, 12.7 137 / 118, 142 / 127.  A plan does not know how often it will be used.
   const bool worth = hp.by_greedy && hp.nnz * hp.tile_rows() * hp.tile_rows() >= 65536 * hp.n_items();
   o.parts = o.groups;
-  if (hp.by_greedy && hp.by_cost) {
+  if (hp.by_greedy && hp.by_cost && o.longest_list > 1) {
     // costs are a compute unit's: which one runs a partition must not depend on the mask that they are used for (nor on the
     // one they were measured with, see dbsp_plan_calibrate), so the runs are those of the number of partitions.  us a pass
     // with a plan's own costs, by runs that go with the loads / these: 48 heads, 275 x 275 blocks of 64 at d = 64 1932 / 1640, 24 heads,
     // 301 x 301 at d = 128 2050 / 1833, 40 heads, 256 x 256 of 128 6265 / 6216, 12 heads, 21 x 23 57.6 / 52.9; in short items 48
-    // heads, 256 x 256 512 / 508, 11 heads, 212 x 212 blocks of 64 61.5 / 58.9
+    // heads, 256 x 256 512 / 508, 11 heads, 212 x 212 blocks of 64 61.5 / 58.9.  (Of an item at most a workgroup, costs settle
+    // nothing, and with fewer items than partitions these runs would keep to the first dies.)
     o.parts = hp.P;
     o.run_log2 = longest_runs_log2(hp.P);
   } else if (worth) {
