@@ -350,6 +350,7 @@ int die_run_log2(const dbsp_host_plan& hp, int32_t parts) {
   return lg;
 }
 
+constexpr int32_t kMostOfTheChip = 224;      // workgroups, see dbsp_launch_fwd
 RunOrder run_order(const dbsp_host_plan& hp) {
   RunOrder o;
   for (int32_t g = 0; g < hp.P; ++g) {
@@ -382,7 +383,7 @@ RunOrder run_order(const dbsp_host_plan& hp) {
     order_lists(hp, worth, o);
     while (o.groups < hp.P && o.ptr[o.groups] < o.ptr[hp.P]) ++o.groups;
   }
-  o.local = hp.by_rounds || (hp.by_greedy && o.longest_list > 1);
+  o.local = hp.by_rounds || (hp.by_greedy && (o.longest_list > 1 || o.groups < kMostOfTheChip));
   return o;
 }
 

@@ -1107,10 +1107,13 @@ hipError_t dbsp_launch_fwd(const dbsp_fwd_params& p, int block, int d, bool pair
   // slice's, with the greedy's items in the order of their heads and its partitions dealt to the dies one by one: 40 heads,
   // 256 x 256 blocks 7755 / 7175; pair rows, 40 heads, 512 x 512 7460 / 6860 (5, 6 or 8 copies in place of 4, or the short wait
   // at every second slice, keep part of the loss, 2 copies cost 1 - 10 % of other cases).  That is how the naive
-  // and the reward-biased placement run, and so does a greedy one of an item at most a workgroup, which has no order and rows
-  // of all lengths (ranges over five kinds of masks): 16 heads, 16 x 256 blocks 238 - 271 / 229 - 254, 8 heads, 32 x 900
-  // 819 - 883 / 772 - 832, 4 heads, 60 x 900 692 - 776 / 687 - 747, one head, 256 x 256 no difference, bands of 512 blocks, 16 heads,
-  // 16 rows each 556 / 571.  The rounds' and, longest items first and partitions in a row on a die
+  // and the reward-biased placement run, and so does a greedy one of an item at most a workgroup and at least seven eighths of the
+  // chip's workgroups, which has no order and rows of all lengths: 16 heads, 16 x 256 blocks 238 - 271 / 229 - 254 and 8 heads, 32 x 900
+  // 819 - 883 / 772 - 832 (ranges over five kinds of masks), 512 workgroups, 16 heads, 32 rows of 100 to 400 of 500 blocks
+  // 1125 / 1028, pair rows, 16 heads, 16 x 400 527 / 507, 4 heads, 64 x 400 317 / 318, 32 heads, 8 x 400 382 / 378; 224 workgroups, 8, 16
+  // and 32 heads 324 / 322, 344 / 338, 345 / 353.  With fewer nothing is short, and the longer wait is worth its copies: 192 workgroups,
+  // 4, 8, 16 and 32 heads 277 / 278, 299 / 299, 310 / 308, 309 / 326, 128 260 / 263, 269 / 275, 276 / 303, 281 / 325, 32 heads, 2 rows
+  // each 275 / 343.  The rounds' and, longest items first and partitions in a row on a die
   // (see run_order in api.hip), the greedy's run does better with two slices' copies: rounds, 40 heads, 256 x 256 5646 / 5666,
   // dense 97 x 97 up to 4 %; greedy, 40 heads, 256 x 256 5969 / 6187, 24 heads, 928 x 928 36.9 / 38.0 ms, pair rows, 40 heads, 512 x 512
   // 5816 / 5933, 16 heads, 513 x 513 1402 / 1410; 12 heads, 21 x 23, 5 blocks an item, 56.2 / 55.8.  So do the greedy's short items,

@@ -32,7 +32,7 @@ struct dbsp_fwd_params {
   int32_t max_chunks;       // the most chunks a split row has; 0: no split rows
   int32_t in_place_ok;      // split_cnt may be used, and there are no more items than partitions, all batch entries counted
   int32_t local;            // a slice's barrier may leave two slices' copies under way, see dbsp_launch_fwd: the plan's placement is the
-                            // round-based one, or a greedy one that has more than an item for a workgroup
+                            // round-based one, or a greedy one that has more than an item for a workgroup or leaves an eighth of the chip idle
   int32_t merge_later;      // set by dbsp_launch_fwd: split rows are merged by a kernel of their own behind this one
   float scale;         // softmax scale
   float scale_log2;    // softmax scale * log2(e)
